@@ -67,15 +67,17 @@
  *              la_causal_fwd_noalloc's built-in scratch array; calls from
  *              several host threads are safe as long as they do not share
  *              output or workspace buffers.
- *   Tuning     Five environment variables override the schedule (for tests and
+ *   Tuning     Six environment variables override the schedule (for tests and
  *              experiments): LA_TARGET_WAVES (default 2048: wavefronts wanted
  *              in flight), LA_MIN_SEG_CHUNKS (default 2: shortest segment, in
  *              16-token chunks), LA_FOLD_MAX_SEGS (default 8: up to this many
  *              segments per sequence the passes add up the segment totals
  *              themselves and no scan kernel runs), LA_BWD_SEG_GROUP (1 or 2:
  *              how many of the forward's segments a workgroup of the backward
- *              takes; default 1 for 32 x 32 heads, else 2) and LA_STREAM_LOADS
- *              (1: non-temporal instead of plain loads of the tensors).
+ *              takes; default 1 for 32 x 32 heads, else 2), LA_STREAM_LOADS
+ *              (1: non-temporal instead of plain loads of the tensors) and
+ *              LA_BLOCK_KERNELS (the causal calls' workgroup kernels on
+ *              32-token blocks: 0 never, 1 always, default by size).
  *              Sequences are not cut at all once B*H reaches half of
  *              LA_TARGET_WAVES.  The environment is read once per process, by
  *              the first workspace query or entry point, so a query and the

@@ -25,6 +25,9 @@ struct Plan {
     int nchunks, nseg, cps;
     bool fold;      // few segments per sequence: no scan launch, every pass adds up the
                     // segment totals before (after) its own segment itself
+    bool fwd_block; // the forward (and its segment sums) by the workgroup kernels of la_block.h
+    bool bwd_block; // the causal backward
+    int bwd_group;  // how many of the forward's segments a workgroup of the backward takes
 };
 
 int env_int(const char *name, int dflt) {
@@ -43,6 +46,7 @@ struct Tuning {
     int fold_max;       // LA_FOLD_MAX_SEGS
     int bwd_group;      // LA_BWD_SEG_GROUP, 0 = by head size
     int stream;         // LA_STREAM_LOADS: 0, 1, or -1 = by tensor size
+    int block;          // LA_BLOCK_KERNELS: 0 never, 1 wherever they exist, or -1 = by size
 };
 
 std::mutex g_tuning_mu;
@@ -57,6 +61,8 @@ Tuning read_tuning() {
     t.bwd_group = env_int("LA_BWD_SEG_GROUP", 0);
     const char *s = getenv("LA_STREAM_LOADS");
     t.stream = (s != nullptr && (s[0] == '0' || s[0] == '1') && s[1] == '\0') ? s[0] - '0' : -1;
+    s = getenv("LA_BLOCK_KERNELS");
+    t.block = (s != nullptr && (s[0] == '0' || s[0] == '1') && s[1] == '\0') ? s[0] - '0' : -1;
     return t;
 }
 
@@ -85,6 +91,8 @@ Plan make_plan(long BH, int N) {
     p.cps = (int)((p.nchunks + nseg - 1) / nseg);
     p.nseg = (p.nchunks + p.cps - 1) / p.cps;
     p.fold = p.nseg > 1 && p.nseg <= tn.fold_max;
+    p.fwd_block = p.bwd_block = false;
+    p.bwd_group = 0;      // see backward_group
     return p;
 }
 
@@ -115,6 +123,72 @@ size_t esize(la_dtype t) { return (t == LA_BF16 || t == LA_BF16_FEATURES) ? 2 : 
 
 size_t states_bytes(long BH, const Plan &p, int D, int M) {
     return align256((size_t)BH * p.nseg * la::state_stride(D, M) * sizeof(float));
+}
+
+// The plan of a causal call: which kernels, and the cut that suits them.  The workgroup kernels
+// (la_block.h) put four or eight waves on a segment, so a quarter as many segments fill the machine
+// (512 workgroups, two per CU), in whole 32-token blocks: fewer, longer segments, hence less state to
+// write, scan and read.  The wave kernels (la_passes.h) have the shorter chain per token and win
+// where segments are long.  Measured on MI355X, step times wave / workgroup kernels in us (B*H x N):
+//   fp32, D = M = 64   16 x 65536  1051/1099   16 x 16384  274/270   16 x 8192  165/150   16 x 2048  83/60
+//   bf16, D = M = 64   16 x 65536   672/637    16 x 16384  194/159   16 x 8192  122/96    16 x 2048  67/47
+//   fp32, D = M = 32   16 x 65536   460/489    16 x 16384  122/120   16 x 8192   77/71    16 x 2048  38/37
+//   bf16, D = M = 32   16 x 65536   302/332    16 x 16384   91/88    16 x 8192   61/55    16 x 2048  40/38
+//   fp32, 64 x 32      16 x 65536   734/800    16 x 16384  183/194   16 x 8192  111/110
+//   fp32, 32 x 64      16 x 65536   703/735    16 x 16384  174/178   16 x 8192  108/100
+// so the line lies at 512 tokens per segment (fp32 with D = M = 64, bf16 with a 64-wide head dimension) or
+// 256.  Above it bf16 tensors with a 64-wide head dimension keep the wave kernel in the forward only
+// (114/158 us at 16 x 65536, backward 476/396).
+// Sequences are left whole from 512 on (256 if they are short: 256 x 512 136 us, 128 x 1024 in
+// four pieces 135, 256 x 128 40, 128 x 256 53).  Whole sequences, each kernel by what fills the machine
+// (fp32 D = M = 64, forward / dQ / dV+dK in us):
+//   1024 x 1024  wave 334 / 285 / 317   workgroup 235 / 354 / 358
+//   2048 x 512   wave 208 / 348 / 402   workgroup 252 / 350 / 356
+//   2048 x 512, D = M = 32   wave 113 / 135 / 144   workgroup 110 / 162 / 158
+// It never has more segments than make_plan's, which size the workspaces.
+// (The polynomial map is cut like fp32 tensors of 64 features.)
+Plan causal_plan(long BH, int N, int C, int M, la_dtype t) {
+    const Tuning tn = tuning();
+    Plan wave = make_plan(BH, N);
+    wave.bwd_group = backward_group(C, M);
+    if (tn.block == 0) return wave;
+    const long target = tn.target_waves >= 4 ? tn.target_waves / 4 : 1;
+    const long min_chunks = tn.min_chunks > 2 ? tn.min_chunks : 2;
+    const bool bf16 = esize(t) == 2, narrow = C == 32 && M == 32;
+    const int longest = (bf16 ? !narrow : C == 64 && M == 64) ? 512 : 256;     // tokens per segment
+    Plan p = wave;
+    const long want = (target + BH - 1) / BH;
+    long maxseg = p.nchunks / min_chunks;
+    if (maxseg < 1) maxseg = 1;
+    long nseg = want > maxseg ? maxseg : want;
+    if (2 * BH >= target && N <= 512) nseg = 1;
+    p.cps = (int)((p.nchunks + nseg - 1) / nseg);
+    p.cps += p.cps & 1;
+    p.nseg = (p.nchunks + p.cps - 1) / p.cps;
+    p.fold = p.nseg > 1 && p.nseg <= tn.fold_max;
+    p.fwd_block = p.bwd_block = true;
+    p.bwd_group = tn.bwd_group == 2 ? 2 : 1;
+    if (tn.block == 1) return p;
+    if (p.nseg > 1) {
+        if (p.cps * la::kChunk <= longest) return p;
+        if (bf16 && !narrow) {
+            wave.bwd_block = true;
+            wave.bwd_group = tn.bwd_group != 0 ? 2 : 4;
+        }
+        return wave;
+    }
+    // whole sequences: one wave per sequence (forward) fills three quarters of the machine from 1536 on,
+    // two waves per sequence (backward) nearly all of it at 1024
+    p.fwd_block = 4 * BH < 3 * (long)tn.target_waves;
+    const bool one_round = 16 * BH >= 7 * (long)tn.target_waves && 2 * BH <= tn.target_waves;
+    p.bwd_block = bf16 || !(one_round || (C == 32 && 2 * BH > tn.target_waves));
+    return p;
+}
+
+// What a causal call asks its caller for: the states of make_plan's segments
+size_t causal_states_bytes(long BH, int N, int C, int M) {
+    const Plan p = make_plan(BH, N);
+    return p.nseg > 1 ? states_bytes(BH, p, C, M) : 0;
 }
 
 // Feature width C of Q and K inside the kernels: D itself, or D^2 for the degree-2 polynomial
@@ -268,7 +342,7 @@ int run_causal_fwd(const void *Q, const void *K, const void *V, void *O, float *
         sa.Y = K; sa.Z = V; sa.state = states;
         sa.N = N; sa.nseg = p.nseg; sa.chunks_per_seg = p.cps; sa.skip_seg = p.nseg - 1;
         sa.heads = heads; sa.tok_heads = tok_heads;
-        { ProfScope ps(LA_K_SEG_KV, s); LA_TRY(la::launch_segment_state(D, M, (int)t, sa, nblocks, s)); }
+        { ProfScope ps(LA_K_SEG_KV, s); LA_TRY(la::launch_segment_state(p.fwd_block, D, M, (int)t, sa, nblocks, s)); }
         if (!p.fold)
             { ProfScope ps(LA_K_SCAN, s); LA_TRY(la::launch_scan(states, (int)BH, p.nseg, la::state_stride(D, M), la::kScanForward, s, S0, z0, D * M)); }
     }
@@ -280,7 +354,7 @@ int run_causal_fwd(const void *Q, const void *K, const void *V, void *O, float *
     a.out = O; a.den = den; a.state = p.nseg > 1 ? states : nullptr; a.fold = p.fold;
     a.init_S = scanned ? nullptr : S0; a.init_z = scanned ? nullptr : z0; a.final_S = S1; a.final_z = z1;
     a.N = N; a.nseg = p.nseg; a.chunks_per_seg = p.cps; a.eps = eps;
-    { ProfScope ps(LA_K_FWD, s); LA_TRY(la::launch_pass_fwd(false, D, M, (int)t, a, nblocks, s)); }
+    { ProfScope ps(LA_K_FWD, s); LA_TRY(la::launch_pass_fwd(false, p.fwd_block, D, M, (int)t, a, nblocks, s)); }
     return LA_OK;
 }
 
@@ -295,7 +369,7 @@ int run_global_fwd(const void *Q, const void *K, const void *V, void *O, float *
     sa.heads = heads; sa.tok_heads = tok_heads;
     sa.Y = K; sa.Z = V; sa.state = states;
     sa.N = N; sa.nseg = p.nseg; sa.chunks_per_seg = p.cps; sa.skip_seg = -1;
-    { ProfScope ps(LA_K_SEG_KV, s); LA_TRY(la::launch_segment_state(D, M, (int)t, sa, nblocks, s)); }
+    { ProfScope ps(LA_K_SEG_KV, s); LA_TRY(la::launch_segment_state(p.fwd_block, D, M, (int)t, sa, nblocks, s)); }
     if (p.nseg > 1 && !p.fold)
         { ProfScope ps(LA_K_SCAN, s); LA_TRY(la::launch_scan(states, (int)BH, p.nseg, la::state_stride(D, M), la::kScanTotal, s)); }
     la::PassArgs a{};
@@ -303,7 +377,7 @@ int run_global_fwd(const void *Q, const void *K, const void *V, void *O, float *
     a.heads = heads; a.tok_heads = tok_heads;
     a.Q = Q; a.K = K; a.V = V; a.out = O; a.den = den; a.state = states; a.fold = p.fold;
     a.N = N; a.nseg = p.nseg; a.chunks_per_seg = p.cps; a.eps = eps;
-    { ProfScope ps(LA_K_GLOBAL, s); LA_TRY(la::launch_pass_fwd(true, D, M, (int)t, a, nblocks, s)); }
+    { ProfScope ps(LA_K_GLOBAL, s); LA_TRY(la::launch_pass_fwd(true, false, D, M, (int)t, a, nblocks, s)); }
     return LA_OK;
 }
 }  // namespace
@@ -338,8 +412,7 @@ size_t la_causal_fwd_workspace(int B, int H, int N, int D, int M, la_dtype t) {
     if (check_dims(B, H, N, D, M, 0.0f, t) != LA_OK) return 0;
     const int C = feat_width(D, t);
     const long BH = (long)B * H;
-    const Plan p = make_plan(BH, N);
-    return p.nseg > 1 ? states_bytes(BH, p, C, M) : 0;
+    return causal_states_bytes(BH, N, C, M);
 }
 
 size_t la_causal_bwd_workspace(int B, int H, int N, int D, int M, la_dtype t) {
@@ -383,8 +456,8 @@ static int causal_fwd_impl(const void *Q, const void *K, const void *V, void *O,
     if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(O) || misaligned(ws))
         return LA_ERR_ALIGN;
     const long BH = (long)B * H;
-    const Plan p = make_plan(BH, N);
-    const size_t need = p.nseg > 1 ? states_bytes(BH, p, C, M) : 0;
+    const Plan p = causal_plan(BH, N, C, M, t);
+    const size_t need = causal_states_bytes(BH, N, C, M);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return LA_ERR_WORKSPACE;
     const size_t rows = (size_t)BH * N, e = esize(t);
     const Span outs[] = {{O, rows * M * e}, {den, rows * 4}, {ws, need}};
@@ -416,8 +489,8 @@ int la_causal_fwd_noalloc(const void *Q, const void *K, const void *V, void *O, 
     const int C = feat_width(D, t);
     if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(O)) return LA_ERR_ALIGN;
     const long BH = (long)B * H;
-    const Plan p = make_plan(BH, N);
-    const size_t need = p.nseg > 1 ? states_bytes(BH, p, C, M) : 0;
+    const Plan p = causal_plan(BH, N, C, M, t);
+    const size_t need = causal_states_bytes(BH, N, C, M);
     if (need > kScratchBytes) return LA_ERR_SCRATCH;
     const size_t rows = (size_t)BH * N, e = esize(t);
     const Span outs[] = {{O, rows * M * e}, {den, rows * 4}};
@@ -447,8 +520,8 @@ static int causal_fwd_state_impl(const void *Q, const void *K, const void *V, co
         misaligned(S0) || misaligned(z0) || misaligned(S1) || misaligned(z1))
         return LA_ERR_ALIGN;
     const long BH = (long)B * H;
-    const Plan p = make_plan(BH, N);
-    const size_t need = p.nseg > 1 ? states_bytes(BH, p, C, M) : 0;
+    const Plan p = causal_plan(BH, N, C, M, t);
+    const size_t need = causal_states_bytes(BH, N, C, M);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return LA_ERR_WORKSPACE;
     const size_t rows = (size_t)BH * N, e = esize(t);
     const Span outs[] = {{O, rows * M * e}, {den, rows * 4}, {ws, need},
@@ -501,7 +574,7 @@ static int causal_bwd_impl(const void *Q, const void *K, const void *V, const fl
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const long BH = (long)B * H;
-    const Plan p = make_plan(BH, N);
+    const Plan p = causal_plan(BH, N, C, M, t);
     const size_t rows = (size_t)BH * N;
     {
         const size_t e = esize(t), sb = (size_t)BH * C * M * 4, zb = (size_t)BH * C * 4;
@@ -509,7 +582,7 @@ static int causal_bwd_impl(const void *Q, const void *K, const void *V, const fl
                              {ws, need}, {dS0, sb}, {dz0, zb}};
         const Span ins[] = {{Q, rows * D * e}, {K, rows * D * e}, {V, rows * M * e},
                             {dO, rows * M * e}, {den, rows * 4}, {S0, sb}, {z0, zb}, {dS1, sb},
-                            {dz1, zb}, {fwd_ws, p.nseg > 1 ? states_bytes(BH, p, C, M) : 0}};
+                            {dz1, zb}, {fwd_ws, causal_states_bytes(BH, N, C, M)}};
         if (aliased(outs, ins)) return LA_ERR_ALIAS;
     }
     const int nt_loads = stream_loads();
@@ -542,7 +615,7 @@ static int causal_bwd_impl(const void *Q, const void *K, const void *V, const fl
         sa.Y = K; sa.Z = V; sa.state = stS;
         sa.skip_seg = p.nseg - 1;
         sa.heads = H; sa.tok_heads = tok_heads;
-        { ProfScope ps(LA_K_SEG_KV, s); LA_TRY(la::launch_segment_state(C, M, (int)t, sa, nblocks, s)); }
+        { ProfScope ps(LA_K_SEG_KV, s); LA_TRY(la::launch_segment_state(p.fwd_block, C, M, (int)t, sa, nblocks, s)); }
         if (!p.fold)
             { ProfScope ps(LA_K_SCAN, s); LA_TRY(la::launch_scan(stS, (int)BH, p.nseg, la::state_stride(C, M), la::kScanForward, s, S0, z0, C * M)); }
     }
@@ -550,7 +623,7 @@ static int causal_bwd_impl(const void *Q, const void *K, const void *V, const fl
     // many workgroups fill the machine: they take the forward's segments in pairs, see
     // backward_group.  The prefix states (laid out for the forward's cut) are then read at every
     // second slot.
-    const int group = backward_group(C, M);
+    const int group = p.bwd_group;
     Plan pb = p;
     if (p.nseg > 1) {
         pb.cps = group * p.cps;
@@ -569,7 +642,7 @@ static int causal_bwd_impl(const void *Q, const void *K, const void *V, const fl
     // the caller's state: the scan has added it to the prefix states already, if there was one
     const bool scanned = p.nseg > 1 && !p.fold;
     a.init_S = scanned ? nullptr : S0; a.init_z = scanned ? nullptr : z0;
-    { ProfScope ps(LA_K_DQ, s); LA_TRY(la::launch_pass_dq(true, C, M, (int)t, a, nblocks_b, s)); }
+    { ProfScope ps(LA_K_DQ, s); LA_TRY(la::launch_pass_dq(true, p.bwd_block, C, M, (int)t, a, nblocks_b, s)); }
     const bool scanned_b = pb.nseg > 1 && !p.fold;
     if (scanned_b)
         { ProfScope ps(LA_K_SCAN, s); LA_TRY(la::launch_scan(stR, (int)BH, pb.nseg, la::state_stride(C, M), la::kScanReverse, s, dS1, dz1, C * M)); }
@@ -577,7 +650,7 @@ static int causal_bwd_impl(const void *Q, const void *K, const void *V, const fl
     a.state_nseg = 0; a.state_step = 0;      // stR is laid out for this very cut
     a.init_S = scanned_b ? nullptr : dS1; a.init_z = scanned_b ? nullptr : dz1;
     a.final_S = dS0; a.final_z = dz0;
-    { ProfScope ps(LA_K_REV, s); LA_TRY(la::launch_pass_reverse(C, M, (int)t, a, nblocks_b, s)); }
+    { ProfScope ps(LA_K_REV, s); LA_TRY(la::launch_pass_reverse(p.bwd_block, C, M, (int)t, a, nblocks_b, s)); }
     return LA_OK;
 }
 
@@ -698,7 +771,7 @@ static int global_bwd_impl(const void *Q, const void *K, const void *V, const vo
         sa.heads = H; sa.tok_heads = tok_heads;
         sa.N = N; sa.nseg = p.nseg; sa.chunks_per_seg = p.cps; sa.skip_seg = -1;
         sa.Y = K; sa.Z = V; sa.state = stS;
-        { ProfScope ps(LA_K_SEG_KV, s); LA_TRY(la::launch_segment_state(C, M, (int)t, sa, nblocks, s)); }
+        { ProfScope ps(LA_K_SEG_KV, s); LA_TRY(la::launch_segment_state(p.fwd_block, C, M, (int)t, sa, nblocks, s)); }
         if (p.nseg > 1 && !p.fold)
             { ProfScope ps(LA_K_SCAN, s); LA_TRY(la::launch_scan(stS, (int)BH, p.nseg, la::state_stride(C, M), la::kScanTotal, s)); }
     }
@@ -715,7 +788,7 @@ static int global_bwd_impl(const void *Q, const void *K, const void *V, const vo
     a.Q = Q; a.K = K; a.V = V; a.G = dO; a.den_in = den; a.totals = stR;
     a.N = N; a.nseg = pb.nseg; a.chunks_per_seg = pb.cps; a.eps = eps;
     a.out = dQ; a.state = stS; a.state_nseg = p.nseg; a.fold = p.fold;
-    { ProfScope ps(LA_K_DQ, s); LA_TRY(la::launch_pass_dq(false, C, M, (int)t, a, (int)(BH * pb.nseg), s)); }
+    { ProfScope ps(LA_K_DQ, s); LA_TRY(la::launch_pass_dq(false, false, C, M, (int)t, a, (int)(BH * pb.nseg), s)); }
     if (pb.nseg > 1 && !p.fold)
         { ProfScope ps(LA_K_SCAN, s); LA_TRY(la::launch_scan(stR, (int)BH, pb.nseg, la::state_stride(C, M), la::kScanTotal, s)); }
     // dV and dK against the Q, dO total: one kernel, two waves per workgroup over the same

@@ -1,0 +1,1277 @@
+// Causal passes by workgroups of eight (or four) waves on 32-token blocks.
+//
+// The products of la_passes.h (out_a = sum_{b <= a} (X_a . Y_b) Z_b with a carried state U, see
+// the table there) on the bf16 matrix pipe only: every operand is cut into its bf16 parts ONCE,
+// when its tile is parked in LDS, and the waves of the workgroup read it from there in whichever
+// of the two orders a product needs.  fp32 tensors take three parts (exact, see split3), bf16
+// tensors two (and V, exact in bf16, one).
+//
+// What bounds these kernels: a SIMD's bf16 MFMAs and vector instructions hardly overlap (24 MFMAs
+// 165 ns, 144 fp32 instructions 158 ns, both 295 ns, four waves), so their times add, and both
+// compete with the fetches.  Against one or two waves per segment on 16-token chunks an operand is
+// split once instead of once per product that reads it, the state once per 32 tokens instead of
+// 16, and a quarter as many segments fill the machine (512 workgroups): a state of 16.6 KB per
+// segment less to write, scan and read, and fewer starts of the chain state - first tile - products.
+// Measured (dQ / dV + dK in us): bf16 B*H = 16, N = 65536: 235 / 231 -> 198 / 190; fp32 B*H = 32,
+// N = 3072: 39.8 / 37.5 -> 38 / 35.6; fp32 B*H = 32, N = 1024: 24.9 / 23.5 -> 17.2 / 16.1.
+//
+// Four "out" roles form the outputs (one per half of the tokens and half of the columns, or dV and
+// dK), four "state" roles keep the carried state in fp32 accumulators, its tiles spread over them.
+// One block:
+//   barrier    tiles of the block and the carried state are in LDS, as bf16 parts
+//   products   out roles: scores, read-out against the state, in-chunk term; state roles: update
+//   barrier    nobody reads the tiles any more
+//   park       outputs leave, the next block (fetched a block ago into registers) is mapped, cut
+//              and parked, the state is cut and published, the block after that is fetched
+// Two such workgroups share a compute unit (LDS: 74 KB each at D = M = 64, fp32; one alone takes 1.3
+// to 1.4 times as long), so that one parks while the other multiplies.  Eight waves with one role each
+// where 128 registers suffice, four waves with two roles each in the fp32 backward with 64 columns (the
+// three-part operands spill at 128: dV + dK 0.58 instead of 0.34 ms).  A second block in flight per
+// thread changes nothing (bf16 0.606 -> 0.610 ms per step).
+#pragma once
+
+#include "la_passes.h"
+
+namespace la {
+
+constexpr int kBlk = 32;          // tokens per block
+// waves per workgroup of the forward and of the two backward kernels
+template <int D, int M, typename T> constexpr int kFwdWaves = 8;
+template <int D, int M, typename T> constexpr int kBwdWaves = is_bf16<T> || (D == 32 && M == 32) ? 8 : 4;     // (the polynomial map relies on its 4)
+
+// ---- tiles of bf16 parts in LDS ----------------------------------------------------------------
+// A plane holds one part of a tile, row-major, F bf16 per row, in 16-byte pieces that are permuted
+// within a row by swz(row).  Both ways an operand is read then spread over the banks: 16 rows of
+// one piece each (read_tok) and 4 or 8 rows of two neighbouring pieces (read_feat).
+template <int F>
+__device__ __forceinline__ constexpr int swz(int row) {
+    if constexpr (F == 64) return (row & 6) ^ (5 * ((row >> 3) & 1));
+    else return ((row >> 1) & 2) ^ (3 * ((row >> 3) & 1));
+}
+template <int F>
+__device__ __forceinline__ int part_at(int row, int piece) {     // in elements
+    return row * F + ((piece ^ swz<F>(row)) << 3);
+}
+
+// The operand of a 16x16x32 product: P parts of eight values per lane.
+template <int P> struct Op {
+    bf16x8_t p[P];
+};
+// acc[n] += a[n] b[n] over the 32 contraction slots, to the parts the operands have: the smallest part
+// products first, those below the last part of the finer operand left out (P = 3: 2^-26 of the
+// product).  The N products take turns, so that none waits for its own last result.
+template <int N, int PA, int PB>
+__device__ __forceinline__ void mma_n(const Op<PA> (&a)[N], const Op<PB> (&b)[N], f32x4 (&acc)[N]) {
+    constexpr int top = (PA > PB ? PA : PB) - 1;
+#pragma unroll
+    for (int s = top; s >= 0; --s)
+#pragma unroll
+        for (int x = 0; x <= s; ++x)
+            if (x < PA && s - x < PB) {
+#pragma unroll
+                for (int n = 0; n < N; ++n) acc[n] = mfma32_bf16(a[n].p[x], b[n].p[s - x], acc[n]);
+            }
+}
+
+// Token-lane operand: lane (c, g) holds features 8 * piece .. + 7 of row `row`; a contraction over
+// features takes pieces 4s + g for its step s.
+template <int F, int P>
+__device__ __forceinline__ Op<P> read_tok(const uint16_t *tile, int plane, int row, int piece) {
+    Op<P> o;
+    const uint16_t *p = tile + part_at<F>(row, piece);
+#pragma unroll
+    for (int k = 0; k < P; ++k) o.p[k] = *reinterpret_cast<const bf16x8_t *>(p + k * plane);
+    return o;
+}
+
+// Transposed reads (ds_read_b64_tr_b16): of each group of 16 lanes, lane q supplies the address of
+// four consecutive elements of row q / 4; lane i gets element i % 4 of the pieces of lanes i / 4,
+// 4 + i / 4, ...: four rows of one column.
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x2_t read_tr(const uint16_t *p) {
+    const auto v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t *)p);
+    return __builtin_bit_cast(u32x2_t, v);
+}
+// Which of the F columns a lane's operand row rho = 4g + r of tile t stands for.  Natural: 16t + rho.
+// Paired (bf16 outputs): two tiles of a pair give a lane eight consecutive columns, one 16-byte store.
+template <bool kPair>
+__device__ __forceinline__ int col_of(int t, int rho) {
+    if constexpr (kPair) return 32 * (t >> 1) + 8 * (rho >> 2) + 4 * (t & 1) + (rho & 3);
+    else return 16 * t + rho;
+}
+// Feature-lane operand: lane (c, g) holds column col_of(t, c) of eight rows.  kNatural = false: rows
+// 4g .. + 3 and 16 + 4g .. + 3 (the order in which a pair of score tiles comes out of the accumulators),
+// true: rows 8g .. + 7 (the order of read_tok).  `row0` = first of the 32 rows.
+template <int F, int P, bool kPair, bool kNatural = false>
+__device__ __forceinline__ Op<P> read_feat(const uint16_t *tile, int plane, int row0, int t, int lane) {
+    const int q = lane & 15, g = lane >> 4;
+    const int ra = row0 + (kNatural ? 8 * g : 4 * g) + (q >> 2), rb = ra + (kNatural ? 4 : 16);
+    const int piece = kPair ? 4 * (t >> 1) + (q & 3) : 2 * t + ((q >> 1) & 1);
+    const int half = kPair ? 4 * (t & 1) : 4 * (q & 1);
+    const uint16_t *pa = tile + part_at<F>(ra, piece) + half, *pb = tile + part_at<F>(rb, piece) + half;
+    Op<P> o;
+#pragma unroll
+    for (int k = 0; k < P; ++k) o.p[k] = cat_parts(read_tr(pa + k * plane), read_tr(pb + k * plane));
+    return o;
+}
+
+// N quads cut into P parts stage by stage (an instruction and the one that needs its result are
+// then several instructions apart; quad by quad the compiler fills the gaps with idle cycles)
+template <int P, int N>
+__device__ __forceinline__ void split_batch(const f32x4 (&q)[N], u32x2_t (&s)[N][P]) {
+    f32x4 r[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) r[n] = q[n];
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+#pragma unroll
+        for (int n = 0; n < N; ++n)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) s[n][k][j] = round_pair(r[n][2 * j], r[n][2 * j + 1]);
+        if (k + 1 < P) {
+#pragma unroll
+            for (int n = 0; n < N; ++n)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    r[n][2 * j] = minus_low(s[n][k][j], r[n][2 * j]);
+                    r[n][2 * j + 1] = minus_high(s[n][k][j], r[n][2 * j + 1]);
+                }
+        }
+    }
+}
+// the parts of four values, at four consecutive columns of a row (`p`: the first of them)
+template <int P>
+__device__ __forceinline__ void put_parts(uint16_t *p, int plane, const u32x2_t (&s)[P]) {
+#pragma unroll
+    for (int k = 0; k < P; ++k) *reinterpret_cast<u32x2_t *>(p + k * plane) = s[k];
+}
+template <int F> __device__ __forceinline__ int quad_at(int row, int col) {
+    return part_at<F>(row, col >> 3) + (col & 4);
+}
+// ... and back (three parts: exactly the value that was put)
+template <int F>
+__device__ __forceinline__ f32x4 get_parts3(const uint16_t *tile, int plane, int row, int col) {
+    const uint16_t *p = tile + quad_at<F>(row, col);
+    const f32x4 h = widen(*reinterpret_cast<const u32x2_t *>(p));
+    const f32x4 m = widen(*reinterpret_cast<const u32x2_t *>(p + plane));
+    const f32x4 l = widen(*reinterpret_cast<const u32x2_t *>(p + 2 * plane));
+    return (h + m) + l;
+}
+
+// a pair of accumulator tiles (rows 16 * blk + 4g + r of a contraction) as the operand of the next product
+template <int P>
+__device__ __forceinline__ Op<P> op_of(f32x4 a, f32x4 b) {
+    const f32x4 q[2] = {a, b};
+    u32x2_t s[2][P];
+    split_batch<P>(q, s);
+    Op<P> o;
+#pragma unroll
+    for (int k = 0; k < P; ++k) o.p[k] = cat_parts(s[0][k], s[1][k]);
+    return o;
+}
+
+// ---- fetch and park ------------------------------------------------------------------------------
+// The 32 tokens of a block are read and written through a buffer descriptor of exactly the tokens that
+// exist: the addresses are a scalar base and one 32-bit offset per lane, rows past the end read as
+// zero and are not written.
+typedef __amdgpu_buffer_rsrc_t Rows;
+template <typename T>
+__device__ __forceinline__ Rows rows_of(const T *first, int ts, int nv) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(first), 0, nv * ts * (int)sizeof(T), 0x00020000);
+}
+constexpr int kAuxNt = 2;         // the non-temporal bit of a buffer instruction
+template <int kAux> __device__ __forceinline__ f32x4 rows_load(Rows r, int at, int step, f32x4) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, at, step, kAux));
+}
+template <int kAux> __device__ __forceinline__ u32x2_t rows_load(Rows r, int at, int step, u32x2_t) {
+    return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(r, at, step, kAux));
+}
+__device__ __forceinline__ float rows_load1(Rows r, int at, int step) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, at, step, 0));
+}
+
+// Parts of the operands by element type: tile values and states; V, exact in bf16
+template <typename T> constexpr int kOpParts = is_bf16<T> ? 2 : 3;
+template <typename T> constexpr int kVParts = is_bf16<T> ? 1 : 3;
+
+// The tiles of a block in LDS and their way there.  kLead: the tensor whose feature values are also
+// needed in full and that therefore takes three parts, Q (dQ pass) or K (dV, dK), or, in the
+// forward (no dO there), both: den is formed from them.
+// A 32 x F block is fetched in quads of four elements, one or two per thread: quad k of thread t is
+// row row(t) + k * kStep, columns col(t) .. + 3 (a wave reads whole rows).  Where a block has fewer quads
+// than there are threads, the two blocks of a pair (Q and K, or dO and V) take half of them each.
+enum Lead { kLeadQ = 0, kLeadK = 1, kLeadQK = 2 };
+template <int kLead, int D, int M, typename T, bool kStrided>
+struct BlkTiles {
+    static constexpr int kWaves = kLead == kLeadQK ? kFwdWaves<D, M, T> : kBwdWaves<D, M, T>, kThreads = kWave * kWaves;
+    static constexpr int P = kOpParts<T>, PV = kVParts<T>, PQ = kLead != kLeadK ? 3 : P, PK = kLead != kLeadQ ? 3 : P;
+    static constexpr bool kG = kLead != kLeadQK;
+    static constexpr int kElems = (PQ + PK) * kBlk * D + (PV + (kG ? P : 0)) * kBlk * M;
+    template <int F> static constexpr int kQuads = 8 * F > kThreads ? 8 * F / kThreads : 1;
+    template <int F> static constexpr int kStep = 4 * kThreads / F;
+    template <int F> static constexpr bool kShared = 8 * F < kThreads;
+    template <int F> static __device__ __forceinline__ int row(int tid) { return (tid % (8 * F)) / (F / 4); }
+    template <int F> static __device__ __forceinline__ int col(int tid) { return 4 * (tid % (F / 4)); }
+
+    uint16_t *sq, *sk, *sv, *sg;            // phi(Q), phi(K), V, dO/den
+    const T *Qs, *Ks, *Vs, *Gs;
+    const float *scale;                     // of the rows of dO: den (kLeadQ, its reciprocal is taken) or 1/den
+    int N, tid, half, tsd, tsm;
+    bool nt;
+    int offd, offm;                         // bytes
+    int qd, qm;
+    staged_t<T> fq[kQuads<D>], fk[kQuads<D>], fv[kQuads<M>], fg[kQuads<M>];
+    float sc[kQuads<M>];
+    // polynomial map: feature 8i + j = x_i x_j; fq, fk hold x_j .. x_j+3 of a quad, xq, xk its x_i
+    static constexpr int W = qk_width<T>(D);
+    float xq[kQuads<D>], xk[kQuads<D>];
+    int offx;
+
+    __device__ __forceinline__ BlkTiles(const PassArgs &a, uint16_t *lds, int bh, int tid_, int wave)
+        : N(a.N), tid(tid_), half(wave >= kWaves / 2), tsd(tok_stride<kStrided>(a.tok_heads, qk_width<T>(D))),
+          tsm(tok_stride<kStrided>(a.tok_heads, M)), nt(a.stream != 0) {
+        sq = lds, sk = sq + PQ * kBlk * D, sv = sk + PK * kBlk * D, sg = sv + PV * kBlk * M;
+        Qs = static_cast<const T *>(a.Q) + seq_base<kStrided>(a.N, a.heads, bh, W);
+        Ks = static_cast<const T *>(a.K) + seq_base<kStrided>(a.N, a.heads, bh, W);
+        Vs = static_cast<const T *>(a.V) + seq_base<kStrided>(a.N, a.heads, bh, M);
+        if constexpr (kG) {
+            Gs = static_cast<const T *>(a.G) + seq_base<kStrided>(a.N, a.heads, bh, M);
+            scale = (kLead == kLeadQ ? a.den_in : a.rden) + (size_t)bh * a.N;
+        }
+        offd = (row<D>(tid) * tsd + (is_poly<T> ? col<D>(tid) & 4 : col<D>(tid))) * (int)sizeof(T), offm = (row<M>(tid) * tsm + col<M>(tid)) * (int)sizeof(T);
+        offx = (row<D>(tid) * tsd + (col<D>(tid) >> 3)) * (int)sizeof(T);
+        qd = quad_at<D>(row<D>(tid), col<D>(tid)), qm = quad_at<M>(row<M>(tid), col<M>(tid));
+    }
+    template <int F> __device__ __forceinline__ bool mine(int which) const { return !kShared<F> || half == which; }
+
+    template <int F, int kAux>
+    __device__ __forceinline__ void load(const T *first, int off, int ts, int nv, staged_t<T> (&st)[kQuads<F>]) const {
+        const Rows r = rows_of(first, ts, nv);
+#pragma unroll
+        for (int k = 0; k < kQuads<F>; ++k) st[k] = rows_load<kAux>(r, off, k * kStep<F> * ts * (int)sizeof(T), staged_t<T>{});
+    }
+    template <int kAux>
+    __device__ __forceinline__ void load_all(const int t0, const int nv) {
+        if (kG && mine<M>(0)) {
+            const Rows r = rows_of(scale + t0, 1, nv);
+#pragma unroll
+            for (int k = 0; k < kQuads<M>; ++k) sc[k] = rows_load1(r, 4 * row<M>(tid), 4 * k * kStep<M>);
+            load<M, kAux>(Gs + (size_t)t0 * tsm, offm, tsm, nv, fg);
+        }
+        if (mine<M>(1)) load<M, kAux>(Vs + (size_t)t0 * tsm, offm, tsm, nv, fv);
+        if (mine<D>(0)) load<D, kAux>(Qs + (size_t)t0 * tsd, offd, tsd, nv, fq);
+        if (mine<D>(1)) load<D, kAux>(Ks + (size_t)t0 * tsd, offd, tsd, nv, fk);
+        if constexpr (is_poly<T>) {
+            const Rows q = rows_of(Qs + (size_t)t0 * tsd, tsd, nv), k_ = rows_of(Ks + (size_t)t0 * tsd, tsd, nv);
+#pragma unroll
+            for (int k = 0; k < kQuads<D>; ++k) {
+                xq[k] = rows_load1(q, offx, k * kStep<D> * tsd * (int)sizeof(T));
+                xk[k] = rows_load1(k_, offx, k * kStep<D> * tsd * (int)sizeof(T));
+            }
+        }
+    }
+    __device__ __forceinline__ void fetch(const int blk) {
+        const int t0 = blk * kBlk, nv = min(kBlk, N - t0);
+        if (nt) load_all<kAuxNt>(t0, nv);     // uniform
+        else load_all<0>(t0, nv);
+    }
+
+    template <int F, int PT, int MAP_, bool kFull>
+    __device__ __forceinline__ void put(uint16_t *tile, int at, const staged_t<T> (&st)[kQuads<F>], const float *by, int nv) const {
+        constexpr int MAP = is_poly<T> && MAP_ == kMapPhi ? kMapScale : is_feat<T> && MAP_ == kMapPhi ? kMapId : MAP_;
+        if constexpr (PT == 1 && MAP == kMapId && is_bf16<T>) {         // as it is
+#pragma unroll
+            for (int k = 0; k < kQuads<F>; ++k)
+                *reinterpret_cast<u32x2_t *>(tile + at + k * kStep<F> * F) =
+                    kFull || row<F>(tid) + k * kStep<F> < nv ? st[k] : u32x2_t{0u, 0u};
+        } else {
+            f32x4 v[kQuads<F>];
+#pragma unroll
+            for (int k = 0; k < kQuads<F>; ++k) {
+                const f32x4 w = widen(st[k]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float m = map_value<MAP>(w[r], MAP == kMapScale ? by[k] : 1.0f);
+                    v[k][r] = kFull || row<F>(tid) + k * kStep<F> < nv ? m : 0.0f;
+                }
+            }
+            u32x2_t s[kQuads<F>][PT];
+            split_batch<PT>(v, s);
+#pragma unroll
+            for (int k = 0; k < kQuads<F>; ++k) put_parts<PT>(tile + at + k * kStep<F> * F, kBlk * F, s[k]);
+        }
+    }
+    template <bool kFull>
+    __device__ __forceinline__ void put_all(const int nv) {
+        if (kG && mine<M>(0)) {
+            if constexpr (kLead == kLeadQ) {
+#pragma unroll
+                for (int k = 0; k < kQuads<M>; ++k) sc[k] = __builtin_amdgcn_rcpf(sc[k]);
+            }
+            put<M, P, kMapScale, kFull>(sg, qm, fg, sc, nv);
+        }
+        if (mine<M>(1)) put<M, PV, kG ? kMapId : kMapFinite, kFull>(sv, qm, fv, nullptr, nv);
+        if (mine<D>(0)) put<D, PQ, kMapPhi, kFull>(sq, qd, fq, xq, nv);
+        if (mine<D>(1)) put<D, PK, kMapPhi, kFull>(sk, qd, fk, xk, nv);
+    }
+    __device__ __forceinline__ void park(const int blk) {
+        const int nv = min(kBlk, N - blk * kBlk);
+        if (nv == kBlk) put_all<true>(nv);
+        else put_all<false>(nv);
+    }
+};
+// accumulator tiles of a carried state, cut and published (rows = columns of the tiles)
+template <int F, int P, int NX, int NY>
+__device__ __forceinline__ void publish(uint16_t *tile, int plane, const f32x4 (&U)[NX][NY], int x0, int y0, int c, int g) {
+#pragma unroll
+    for (int y = 0; y < NY; ++y) {
+        f32x4 q[NX];
+        u32x2_t s[NX][P];
+#pragma unroll
+        for (int x = 0; x < NX; ++x) q[x] = U[x][y];
+        split_batch<P>(q, s);
+#pragma unroll
+        for (int x = 0; x < NX; ++x) put_parts<P>(tile + quad_at<F>(16 * (y0 + y) + c, 16 * (x0 + x) + 4 * g), plane, s[x]);
+    }
+}
+
+// ---- outputs -------------------------------------------------------------------------------------
+// A wave's output, 16 tokens x 16 NT columns (lane (c, g): token c, four columns per tile), goes to
+// memory through LDS scratch of the wave's own, 16 bytes per lane and whole rows of the wave's columns
+// per instruction: straight from the accumulators a store instruction would touch 64 bytes of 16 rows
+// each (measured at N = 65536, fp32: dV + dK 0.58 against 0.43 ms without its stores).
+// The scratch is cut into pieces of 512 bytes, `stride` bytes apart.  At D = M = 64 it is the memory of the
+// rows that the wave itself will park next (four rows of each plane), so it costs no LDS.
+template <int D, int M> constexpr bool kScratchInTiles = D == 64 && M == 64;
+template <typename T, int NT>
+struct OutRows {
+    static constexpr int kBytes = 16 * NT * (int)sizeof(T);       // of one row
+    static constexpr int kPieces = kBytes / 16;                   // 16-byte pieces per row
+    static constexpr bool kDirect = is_bf16<T> && NT == 1;        // half pieces: stored as they are
+    static constexpr int kScratch = 16 * kBytes;                  // bytes per wave
+    template <int stride> static __device__ __forceinline__ int at(int row, int piece) {
+        return (row / (512 / kBytes)) * stride + (row % (512 / kBytes)) * kBytes +
+               ((piece ^ (row * kBytes / 256)) << 4);
+    }
+    // `r`: the tokens of the block, `at0`: byte offset of the wave's first token and column, `ts`: token stride in elements
+    template <int kStride>
+    static __device__ __forceinline__ void store(char *scratch, Rows r, int at0, int ts, const f32x4 (&out)[NT], int lane) {
+        const int c = lane & 15, g = lane >> 4;
+        if constexpr (kDirect) {
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{round_pair(out[0][0], out[0][1]), round_pair(out[0][2], out[0][3])}, r,
+                                                  (c * ts + 4 * g) * (int)sizeof(T) + at0, 0, 0);
+        } else {
+            if constexpr (is_bf16<T>) {
+#pragma unroll
+                for (int t = 0; t < NT; t += 2)
+                    *reinterpret_cast<u32x4_t *>(scratch + at<kStride>(c, 2 * t + g)) =
+                        u32x4_t{round_pair(out[t][0], out[t][1]), round_pair(out[t][2], out[t][3]),
+                                round_pair(out[t + 1][0], out[t + 1][1]), round_pair(out[t + 1][2], out[t + 1][3])};
+            } else {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) *reinterpret_cast<f32x4 *>(scratch + at<kStride>(c, 4 * t + g)) = out[t];
+            }
+            __builtin_amdgcn_wave_barrier();
+            constexpr int kRows = kWave / kPieces;
+            const int row0 = lane / kPieces, piece = lane % kPieces;
+#pragma unroll
+            for (int k = 0; k < 16 / kRows; ++k) {
+                const u32x4_t v = *reinterpret_cast<const u32x4_t *>(scratch + at<kStride>(row0 + kRows * k, piece));
+                __builtin_amdgcn_raw_buffer_store_b128(v, r, row0 * ts * (int)sizeof(T) + 16 * piece + at0,
+                                                       kRows * k * ts * (int)sizeof(T), !is_bf16<T> && LA_NT_STORES != 0 ? kAuxNt : 0);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+};
+
+// the blocks [begin, begin + count) of a segment
+__device__ __forceinline__ void blk_range(const PassArgs &a, int seg, int &begin, int &count) {
+    const int nblk = (a.N + kBlk - 1) / kBlk, per = (a.chunks_per_seg + 1) / 2;
+    begin = seg * per;
+    count = min(begin + per, nblk) - begin;
+}
+
+// Chain rule of x -> vec(x x^T) (see poly2_chain) for a block: `rows` holds the gradients for the 64
+// features of its 32 tokens (stride 68 floats), 256 threads take one of the 32 x 8 raw gradients each.
+constexpr int kChainStride = 68;
+template <typename T>
+__device__ __forceinline__ void blk_chain(const float *rows, const T *raw, T *out, int ts, int nv, int tid) {
+    const int token = tid >> 3, k = tid & 7;
+    const Rows r = rows_of(raw, ts, nv);
+    const f32x4 x0 = rows_load<0>(r, token * ts * 4, 0, f32x4{}), x1 = rows_load<0>(r, token * ts * 4, 16, f32x4{});
+    const float *p = rows + token * kChainStride;
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(p + 8 * k), b = *reinterpret_cast<const f32x4 *>(p + 8 * k + 4);
+    float acc = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        acc = fmaf(a[j] + p[8 * j + k], x0[j], acc);
+        acc = fmaf(b[j] + p[8 * (j + 4) + k], x1[j], acc);
+    }
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, acc), rows_of(out, ts, nv), (token * ts + k) * 4, 0, 0);
+}
+
+// ---- the loop over the blocks --------------------------------------------------------------------
+// first, first + dir, ..: `count` of them.  A role: init (its part of the starting state, after the first
+// fetch is under way), publish (its state to LDS), fetch / parked (what it needs per token), products
+// (between the barriers), finish (after the second: outputs leave).
+template <typename Tiles, typename... Role>
+__device__ __forceinline__ void blk_loop(Tiles &tiles, const int first, const int dir, const int count, Role &...role) {
+    tiles.fetch(first);
+    (role.fetch(first), ...);
+    (role.init(), ...);
+    (role.publish(), ...);
+    tiles.park(first);
+    (role.parked(first), ...);
+    if (count > 1) {
+        tiles.fetch(first + dir);
+        (role.fetch(first + dir), ...);
+    }
+    for (int n = 0; n < count; ++n) {
+        const int blk = first + dir * n;
+        __syncthreads();
+        (role.products(), ...);
+        __syncthreads();
+        (role.finish(blk), ...);
+        if (n + 1 < count) {
+            (role.publish(), ...);
+            tiles.park(blk + dir);
+            (role.parked(blk + dir), ...);
+            if (n + 2 < count) {
+                tiles.fetch(blk + 2 * dir);
+                (role.fetch(blk + 2 * dir), ...);
+            }
+        }
+    }
+}
+struct BlkLane {
+    int lane, c, g, i, h;                // i, h: the wave's quarter
+    __device__ __forceinline__ BlkLane(int tid, int wave) : lane(tid & (kWave - 1)), c(lane & 15), g(lane >> 4), i(wave & 1), h((wave >> 1) & 1) {}
+};
+// acc + a b summed over the S contraction steps, a chain of products per step
+template <int S, int PA, int PB>
+__device__ __forceinline__ f32x4 dot(const Op<PA> (&a)[S], const Op<PB> (&b)[S], f32x4 acc) {
+    f32x4 w[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) w[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    w[0] = acc;
+    mma_n(a, b, w);
+    return S == 2 ? w[0] + w[S - 1] : w[0];
+}
+// the same in one chain, the smallest part products of all steps first: one rounding at the size of the
+// result per step (for den, whose own rounding counts; one chain throughout costs the forward 6 %)
+template <int S, int PA, int PB>
+__device__ __forceinline__ f32x4 dot_chain(const Op<PA> (&a)[S], const Op<PB> (&b)[S], f32x4 acc) {
+    constexpr int top = (PA > PB ? PA : PB) - 1;
+#pragma unroll
+    for (int k = top; k >= 0; --k)
+#pragma unroll
+        for (int x = 0; x <= k; ++x)
+            if (x < PA && k - x < PB) {
+#pragma unroll
+                for (int s = 0; s < S; ++s) acc = mfma32_bf16(a[s].p[x], b[s].p[k - x], acc);
+            }
+    return acc;
+}
+template <int F, int P, int S>
+__device__ __forceinline__ void read_toks(const uint16_t *tile, int plane, int row, int g, Op<P> (&o)[S]) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) o[s] = read_tok<F, P>(tile, plane, row, 4 * s + g);
+}
+
+// ---- causal forward (eq. 9-12) ---------------------------------------------------------------------
+// Out role (i, h): the 16 tokens of sub-block i, columns of half h of V; the scores and with them the
+// denominators of a sub-block are formed by both of its roles.  bf16 tensors: den comes from three-part
+// operands (it is an fp32 result), the numerator from plain bf16 products as everywhere in the forward.
+template <int D, int M, typename T, bool kStrided>
+struct FwdOut : BlkLane {
+    using Tiles = BlkTiles<kLeadQK, D, M, T, kStrided>;
+    static constexpr int PV = Tiles::PV, PS = is_bf16<T> ? 1 : 3, NT = M / 32, SD = D / 32;
+    static constexpr bool kPair = is_bf16<T> && NT == 2;
+    using OutTile = OutRows<T, NT>;
+    const Tiles &tl;
+    const uint16_t *ss, *sz;
+    char *scratch;
+    T *outs;
+    float *den_out, eps, den;
+    int N, row;
+    f32x4 out[NT];                       // columns col_of(h NT + y, 4g + r) of the token
+
+    __device__ __forceinline__ FwdOut(const PassArgs &a, const Tiles &t, int bh, int tid, int wave, const uint16_t *ss_,
+                                      const uint16_t *sz_, char *scratch_)
+        : BlkLane(tid, wave), tl(t), ss(ss_), sz(sz_), scratch(scratch_ + 512 * (wave & 3)) {
+        outs = a.out != nullptr ? static_cast<T *>(a.out) + seq_base<kStrided>(a.N, a.heads, bh, M) : nullptr;
+        den_out = a.den != nullptr ? a.den + (size_t)bh * a.N : nullptr;
+        eps = a.eps, N = a.N, row = 16 * i + c;
+    }
+    __device__ __forceinline__ void init() {}
+    __device__ __forceinline__ void publish() {}
+    __device__ __forceinline__ void fetch(int) {}
+    __device__ __forceinline__ void parked(int) {}
+    __device__ __forceinline__ void products() {
+        const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+        // scores phi(Q_a) . phi(K_b): rows b, lane (c = a)
+        Op<3> qt[SD];
+        read_toks<D, 3>(tl.sq, kBlk * D, row, g, qt);
+        f32x4 w0, w1 = zero4;
+        {
+            Op<3> kt[SD];
+            read_toks<D, 3>(tl.sk, kBlk * D, c, g, kt);
+            w0 = dot(kt, qt, zero4);
+        }
+        if (i != 0) {
+            Op<3> kt[SD];
+            read_toks<D, 3>(tl.sk, kBlk * D, 16 + c, g, kt);
+            w1 = dot(kt, qt, zero4);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {        // select, never multiply
+            w0[r] = (i != 0 || 4 * g + r <= c) ? w0[r] : 0.f;
+            w1[r] = 4 * g + r <= c ? w1[r] : 0.f;
+        }
+        // den: phi(Q) . z (the same operand row in every lane c) and the row sums of the scores
+        {
+            Op<3> zt[SD];
+#pragma unroll
+            for (int s = 0; s < SD; ++s)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) zt[s].p[k] = *reinterpret_cast<const bf16x8_t *>(sz + k * D + 32 * s + 8 * g);
+            const float p = ((w0[0] + w0[1]) + (w0[2] + w0[3])) + ((w1[0] + w1[1]) + (w1[2] + w1[3]));
+            den = dot_chain(zt, qt, mfma16(1.0f, p, f32x4{eps, eps, eps, eps}))[0];
+        }
+        Op<PS> qs[SD];
+#pragma unroll
+        for (int s = 0; s < SD; ++s)
+#pragma unroll
+            for (int k = 0; k < PS; ++k) qs[s].p[k] = qt[s].p[k];
+#pragma unroll
+        for (int y = 0; y < NT; ++y) {
+            Op<PS> st[SD];
+            read_toks<D, PS>(ss, M * D, col_of<kPair>(h * NT + y, c), g, st);
+            out[y] = dot(st, qs, zero4);
+        }
+        const Op<PS> wop[1] = {op_of<PS>(w0, w1)};
+#pragma unroll
+        for (int y = 0; y < NT; ++y) {
+            const Op<PV> vf[1] = {read_feat<M, PV, kPair>(tl.sv, kBlk * M, 0, h * NT + y, lane)};
+            f32x4 o[1] = {out[y]};
+            mma_n(vf, wop, o);
+            out[y] = o[0];
+        }
+    }
+    __device__ __forceinline__ void finish(int blk) {
+        const int t0 = blk * kBlk, nv = min(kBlk, N - t0);
+        const float ri = __builtin_amdgcn_rcpf(den);
+#pragma unroll
+        for (int y = 0; y < NT; ++y)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) out[y][r] *= ri;
+        if (outs != nullptr)             // (a forward that is run for its denominators only)
+            OutTile::template store<kScratchInTiles<D, M> ? 2 * kBlk * D : 4 * 512>(
+                scratch, rows_of(outs + (size_t)t0 * tl.tsm, tl.tsm, nv), (16 * i * tl.tsm + h * (M / 2)) * (int)sizeof(T), tl.tsm, out, lane);
+        if (den_out != nullptr && h == 0 && g == 0 && row < nv) den_out[t0 + row] = den;
+    }
+};
+
+// State role (i, h): S (D x M), D / 32 x M / 32 tiles, published as [m][d]; (i, 0) also z.
+template <int D, int M, typename T, bool kStrided>
+struct FwdState : BlkLane {
+    using Tiles = BlkTiles<kLeadQK, D, M, T, kStrided>;
+    static constexpr int PV = Tiles::PV, PS = is_bf16<T> ? 1 : 3, DT = D / 32, MT = M / 32;
+    static constexpr int PU = is_bf16<T> ? 2 : 3;      // phi(K) in the update: the state also leaves the call
+    const PassArgs &a;
+    const Tiles &tl;
+    uint16_t *ss, *sz;
+    int bh, seg;
+    f32x4 U[DT][MT];       // element (d = 16 (i DT + x) + 4g + r, m = 16 (h MT + y) + c)
+    f32x4 z[DT];           // z[16 (i DT + x) + 4g + r]
+
+    __device__ __forceinline__ FwdState(const PassArgs &a_, const Tiles &t, int bh_, int seg_, int tid, int wave, uint16_t *ss_, uint16_t *sz_)
+        : BlkLane(tid, wave), a(a_), tl(t), ss(ss_), sz(sz_), bh(bh_), seg(seg_) {}
+    __device__ __forceinline__ void add(const float *sm, const float *v) {
+#pragma unroll
+        for (int x = 0; x < DT; ++x) {
+#pragma unroll
+            for (int y = 0; y < MT; ++y)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) U[x][y][r] += sm[(16 * (i * DT + x) + 4 * g + r) * M + 16 * (h * MT + y) + c];
+            z[x] += load4_state(v + 16 * (i * DT + x) + 4 * g);
+        }
+    }
+    __device__ __forceinline__ void init() {
+#pragma unroll
+        for (int x = 0; x < DT; ++x) {
+            z[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int y = 0; y < MT; ++y) U[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        if (a.init_S != nullptr) add(a.init_S + (size_t)bh * D * M, a.init_z + (size_t)bh * D);
+        if (a.state != nullptr) {
+            int nslots, lo, hi;
+            state_slots(a, seg, kStatePrefix, nslots, lo, hi);
+            for (int j = lo; j < hi; ++j) {
+                const float *st = a.state + ((size_t)bh * nslots + j) * state_stride(D, M);
+                add(st, st + D * M);
+            }
+        }
+    }
+    __device__ __forceinline__ void publish() {
+        la::publish<D, PS>(ss, M * D, U, i * DT, h * MT, c, g);
+        if (h == 0) {
+            u32x2_t s[DT][3];
+            split_batch<3>(z, s);
+            if (c == 0) {
+#pragma unroll
+                for (int x = 0; x < DT; ++x) put_parts<3>(sz + 16 * (i * DT + x) + 4 * g, D, s[x]);
+            }
+        }
+    }
+    __device__ __forceinline__ void fetch(int) {}
+    __device__ __forceinline__ void parked(int) {}
+    __device__ __forceinline__ void products() {
+        const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+        Op<3> kn[DT];
+        Op<PU> kk[DT * MT];
+        Op<PV> vn[MT], vv[DT * MT];
+        f32x4 u[DT * MT];
+#pragma unroll
+        for (int y = 0; y < MT; ++y) vn[y] = read_feat<M, PV, false>(tl.sv, kBlk * M, 0, h * MT + y, lane);
+#pragma unroll
+        for (int x = 0; x < DT; ++x) {
+            kn[x] = read_feat<D, 3, false>(tl.sk, kBlk * D, 0, i * DT + x, lane);
+#pragma unroll
+            for (int y = 0; y < MT; ++y) {
+#pragma unroll
+                for (int k = 0; k < PU; ++k) kk[x * MT + y].p[k] = kn[x].p[k];
+                vv[x * MT + y] = vn[y], u[x * MT + y] = zero4;
+            }
+        }
+        mma_n(kk, vv, u);
+#pragma unroll
+        for (int x = 0; x < DT; ++x)
+#pragma unroll
+            for (int y = 0; y < MT; ++y) U[x][y] += u[x * MT + y];
+        if (h == 0) {
+            const unsigned one2 = 0x3f803f80u;
+            Op<1> ones[DT];
+            f32x4 zz[DT];
+#pragma unroll
+            for (int x = 0; x < DT; ++x) ones[x].p[0] = cat_parts(u32x2_t{one2, one2}, u32x2_t{one2, one2}), zz[x] = zero4;
+            mma_n(kn, ones, zz);
+#pragma unroll
+            for (int x = 0; x < DT; ++x) z[x] += zz[x];
+        }
+    }
+    __device__ __forceinline__ void finish(int) {}
+    __device__ __forceinline__ void end() {       // the last segment ends with the final state
+        if (a.final_S == nullptr || seg != a.nseg - 1) return;
+        float *s1 = a.final_S + (size_t)bh * D * M;
+#pragma unroll
+        for (int x = 0; x < DT; ++x) {
+#pragma unroll
+            for (int y = 0; y < MT; ++y)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    s1[(16 * (i * DT + x) + 4 * g + r) * M + 16 * (h * MT + y) + c] = U[x][y][r];
+            if (h == 0 && c == 0) *reinterpret_cast<f32x4 *>(a.final_z + (size_t)bh * D + 16 * (i * DT + x) + 4 * g) = z[x];
+        }
+    }
+};
+
+template <int D, int M, typename T, bool kStrided = false>
+__global__ __launch_bounds__((kWave * kFwdWaves<D, M, T>)) __attribute__((amdgpu_waves_per_eu((kFwdWaves<D, M, T> / 2)))) void fwd_block_kernel(
+    const PassArgs a) {
+    using Tiles = BlkTiles<kLeadQK, D, M, T, kStrided>;
+    using OutRole = FwdOut<D, M, T, kStrided>;
+    using StateRole = FwdState<D, M, T, kStrided>;
+    constexpr bool kOwn = kScratchInTiles<D, M>;
+    __shared__ __attribute__((aligned(16))) uint16_t tiles[Tiles::kElems + (kOwn ? 0 : 4 * OutRole::OutTile::kScratch / 2)];
+    __shared__ __attribute__((aligned(16))) uint16_t ss[OutRole::PS * M * D];     // S before the block, [m][d]
+    __shared__ __attribute__((aligned(16))) uint16_t sz[3 * D];                   // z before the block, in parts
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int seg = blockIdx.x % a.nseg, bh = blockIdx.x / a.nseg;
+    int blk0, count;
+    blk_range(a, seg, blk0, count);
+    char *const scratch = reinterpret_cast<char *>(kOwn ? tiles : tiles + Tiles::kElems);
+    Tiles tl(a, tiles, bh, tid, wave);
+    if constexpr (Tiles::kWaves == 8) {
+        if (wave < 4) {
+            OutRole out(a, tl, bh, tid, wave, ss, sz, scratch);
+            blk_loop(tl, blk0, 1, count, out);
+        } else {
+            StateRole st(a, tl, bh, seg, tid, wave, ss, sz);
+            blk_loop(tl, blk0, 1, count, st);
+            st.end();
+        }
+    } else {
+        OutRole out(a, tl, bh, tid, wave, ss, sz, scratch);
+        StateRole st(a, tl, bh, seg, tid, wave, ss, sz);
+        blk_loop(tl, blk0, 1, count, out, st);
+        st.end();
+    }
+}
+
+// ---- causal dQ (eq. 13) ----------------------------------------------------------------------------
+// Out role (i, h): dQ of the 16 tokens of sub-block i, columns of half h.  The scores of a sub-block
+// are formed by both of its roles (12 or 24 of 54 to 66 products per block, against a barrier and an
+// exchange).  As in dq_causal_kernel delta comes from the role's own results,
+// delta_a = -(phi(Q_a) . A_a) / den_a; each of the two has half of that sum.
+template <int D, int M, typename T, bool kStrided>
+struct DqOut : BlkLane {
+    using Tiles = BlkTiles<kLeadQ, D, M, T, kStrided>;
+    static constexpr int P = Tiles::P, PV = Tiles::PV, NT = D / 32, SM = M / 32;
+    static constexpr bool kPair = is_bf16<T> && NT == 2;
+    using OutTile = OutRows<T, NT>;
+    const Tiles &tl;
+    const uint16_t *ss;
+    const float *sz, *den;
+    float (*sdel)[2][16], (*srho)[D];
+    char *scratch;
+    T *outs;
+    float *delta_out, *rden_out;
+    int N, row;
+    float nden, rd;
+    Op<1> mask;                          // token b <= token 16i + c over the 32 tokens of the block
+    f32x4 out[NT], cz[NT], fq[NT];       // columns col_of(h NT + y, 4g + r) of the token
+    f32x4 rho[NT];                       // this segment's delta phi(Q), per token lane
+
+    __device__ __forceinline__ DqOut(const PassArgs &a, const Tiles &t, int bh, int tid, int wave, const uint16_t *ss_,
+                                     const float *sz_, float (*sdel_)[2][16], float (*srho_)[D], char *scratch_)
+        : BlkLane(tid, wave), tl(t), ss(ss_), sz(sz_), sdel(sdel_), srho(srho_), scratch(scratch_ + 512 * (wave & 3)) {
+        const size_t rowbase = (size_t)bh * a.N;
+        den = a.den_in + rowbase;
+        outs = static_cast<T *>(a.out) + seq_base<kStrided>(a.N, a.heads, bh, qk_width<T>(D));
+        delta_out = a.delta_out + rowbase, rden_out = a.rden_out + rowbase;
+        N = a.N, row = 16 * i + c, nden = 1.f, rd = 0.f;
+        auto bit = [&](int b) { return b <= row ? 0x3f80u : 0u; };
+        const int b0 = 4 * g, b1 = 16 + 4 * g;
+        mask.p[0] = cat_parts(u32x2_t{bit(b0) | (bit(b0 + 1) << 16), bit(b0 + 2) | (bit(b0 + 3) << 16)},
+                              u32x2_t{bit(b1) | (bit(b1 + 1) << 16), bit(b1 + 2) | (bit(b1 + 3) << 16)});
+#pragma unroll
+        for (int y = 0; y < NT; ++y) rho[y] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ __forceinline__ void init() {}
+    __device__ __forceinline__ void publish() {}
+    __device__ __forceinline__ void fetch(int blk) { nden = den[min(blk * kBlk + row, N - 1)]; }
+    __device__ __forceinline__ void parked(int blk) { rd = __builtin_amdgcn_rcpf(nden); }
+    __device__ __forceinline__ void products() {
+        const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+        // scores (dO_a/den_a) . V_b: rows b, lane (c = a)
+        Op<P> gt[SM];
+        read_toks<M, P>(tl.sg, kBlk * M, row, g, gt);
+        f32x4 w0, w1 = zero4;
+        {
+            Op<PV> vt[SM];
+            read_toks<M, PV>(tl.sv, kBlk * M, c, g, vt);
+            w0 = dot(vt, gt, zero4);
+        }
+        if (i != 0) {
+            Op<PV> vt[SM];
+            read_toks<M, PV>(tl.sv, kBlk * M, 16 + c, g, vt);
+            w1 = dot(vt, gt, zero4);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {        // select, never multiply
+            w0[r] = (i != 0 || 4 * g + r <= c) ? w0[r] : 0.f;
+            w1[r] = 4 * g + r <= c ? w1[r] : 0.f;
+        }
+        // read-out against the state, in-chunk term, z up to each token
+#pragma unroll
+        for (int y = 0; y < NT; ++y) {
+            Op<P> st[SM];
+            read_toks<M, P>(ss, D * M, col_of<kPair>(h * NT + y, c), g, st);
+            out[y] = dot(st, gt, zero4);
+        }
+        const Op<P> wop = op_of<P>(w0, w1);
+        float p = 0.f;
+#pragma unroll
+        for (int y = 0; y < NT; ++y) {
+            const Op<P> kf[1] = {read_feat<D, P, kPair>(tl.sk, kBlk * D, 0, h * NT + y, lane)};
+            const Op<P> wo[1] = {wop};
+            const Op<1> mo[1] = {mask};
+            f32x4 o[1] = {out[y]};
+            f32x4 cc[1] = {*reinterpret_cast<const f32x4 *>(sz + col_of<kPair>(h * NT + y, 4 * g))};
+            mma_n(kf, mo, cc);
+            mma_n(kf, wo, o);
+            out[y] = o[0];
+            cz[y] = cc[0];
+            fq[y] = get_parts3<D>(tl.sq, kBlk * D, row, col_of<kPair>(h * NT + y, 4 * g));
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p = fmaf(out[y][r], fq[y][r], p);
+        }
+        p = sum_over_groups(p);
+        if (g == 0) sdel[i][h][c] = p;
+    }
+    __device__ __forceinline__ void finish(int blk) {
+        const int t0 = blk * kBlk, nv = min(kBlk, N - t0);
+        const float d = row < nv ? -(sdel[i][0][c] + sdel[i][1][c]) * rd : 0.f;
+#pragma unroll
+        for (int y = 0; y < NT; ++y)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                rho[y][r] = fmaf(d, fq[y][r], rho[y][r]);
+                out[y][r] = fmaf(d, cz[y][r], out[y][r]) * feature_slope<T>(fq[y][r]);
+            }
+        if constexpr (is_poly<T>) {      // (four waves, each with an out role: all of them are here)
+            float *rows = reinterpret_cast<float *>(tl.sq);
+#pragma unroll
+            for (int y = 0; y < NT; ++y)
+                *reinterpret_cast<f32x4 *>(rows + row * kChainStride + 16 * (h * NT + y) + 4 * g) = out[y];
+            __syncthreads();
+            blk_chain(rows, tl.Qs + (size_t)t0 * tl.tsd, outs + (size_t)t0 * tl.tsd, tl.tsd, nv, tl.tid);
+            __syncthreads();
+        } else {
+            OutTile::template store<kScratchInTiles<D, M> ? 2 * kBlk * D : 4 * 512>(
+                scratch, rows_of(outs + (size_t)t0 * tl.tsd, tl.tsd, nv), (16 * i * tl.tsd + h * (D / 2)) * (int)sizeof(T), tl.tsd, out, lane);
+        }
+        if (h == 0 && g == 0 && row < nv) {
+            delta_out[t0 + row] = d;
+            rden_out[t0 + row] = rd;
+        }
+    }
+    __device__ __forceinline__ void end() {
+#pragma unroll
+        for (int y = 0; y < NT; ++y)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float e = row_sum16(rho[y][r]);
+                if (c == 0) srho[i][col_of<kPair>(h * NT + y, 4 * g + r)] = e;
+            }
+    }
+};
+
+// State role (i, h): S^T (M x D) and, when the sequences are cut, this segment's phi(Q)^T dO/den, D / 32 x
+// M / 32 tiles of each; (0, h) also z.  The products of a block are summed on their own and added to
+// the running sums in one fp32 addition per element and block.
+template <int D, int M, typename T, bool kStrided>
+struct DqState : BlkLane {
+    using Tiles = BlkTiles<kLeadQ, D, M, T, kStrided>;
+    static constexpr int P = Tiles::P, PV = Tiles::PV, NT = D / 32, MT = M / 32;
+    const PassArgs &a;
+    const Tiles &tl;
+    uint16_t *ss;
+    float *sz;
+    int bh, seg;
+    f32x4 U[MT][NT];       // S^T: element (m = 16 (i MT + x) + 4g + r, d = 16 (h NT + y) + c)
+    f32x4 R[NT][MT];       // element (d = 16 (h NT + y) + 4g + r, m = 16 (i MT + x) + c)
+    f32x4 z[NT];           // z[16 (h NT + y) + 4g + r]
+
+    __device__ __forceinline__ DqState(const PassArgs &a_, const Tiles &t, int bh_, int seg_, int tid, int wave, uint16_t *ss_, float *sz_)
+        : BlkLane(tid, wave), a(a_), tl(t), ss(ss_), sz(sz_), bh(bh_), seg(seg_) {}
+    __device__ __forceinline__ void add(const float *sm, const float *v) {     // sm: S as [D][M], v: z
+#pragma unroll
+        for (int y = 0; y < NT; ++y) {
+#pragma unroll
+            for (int x = 0; x < MT; ++x)
+                U[x][y] += load4_state(sm + (16 * (h * NT + y) + c) * M + 16 * (i * MT + x) + 4 * g);
+            z[y] += load4_state(v + 16 * (h * NT + y) + 4 * g);
+        }
+    }
+    __device__ __forceinline__ void init() {
+#pragma unroll
+        for (int y = 0; y < NT; ++y) {
+            z[y] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int x = 0; x < MT; ++x) U[x][y] = R[y][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        if (a.init_S != nullptr) add(a.init_S + (size_t)bh * D * M, a.init_z + (size_t)bh * D);
+        if (a.state != nullptr) {
+            int nslots, lo, hi;
+            state_slots(a, seg, kStatePrefix, nslots, lo, hi);
+            for (int j = lo; j < hi; ++j) {
+                const float *st = a.state + ((size_t)bh * nslots + j) * state_stride(D, M);
+                add(st, st + D * M);
+            }
+        }
+    }
+    __device__ __forceinline__ void publish() {
+        la::publish<M, P>(ss, D * M, U, i * MT, h * NT, c, g);
+        if (i == 0 && c == 0) {
+#pragma unroll
+            for (int y = 0; y < NT; ++y) *reinterpret_cast<f32x4 *>(sz + 16 * (h * NT + y) + 4 * g) = z[y];
+        }
+    }
+    __device__ __forceinline__ void fetch(int) {}
+    __device__ __forceinline__ void parked(int) {}
+    __device__ __forceinline__ void products() {
+        const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+        {
+            Op<P> kn[NT], kk[NT * MT];
+            Op<PV> vv[NT * MT];
+            f32x4 u[NT * MT];
+#pragma unroll
+            for (int y = 0; y < NT; ++y) kn[y] = read_feat<D, P, false>(tl.sk, kBlk * D, 0, h * NT + y, lane);
+#pragma unroll
+            for (int x = 0; x < MT; ++x) {
+                const Op<PV> vf = read_feat<M, PV, false>(tl.sv, kBlk * M, 0, i * MT + x, lane);
+#pragma unroll
+                for (int y = 0; y < NT; ++y) vv[x * NT + y] = vf, kk[x * NT + y] = kn[y], u[x * NT + y] = zero4;
+            }
+            mma_n(vv, kk, u);
+#pragma unroll
+            for (int x = 0; x < MT; ++x)
+#pragma unroll
+                for (int y = 0; y < NT; ++y) U[x][y] += u[x * NT + y];
+            if (i == 0) {
+                const unsigned one2 = 0x3f803f80u;
+                Op<1> ones[NT];
+                f32x4 zz[NT];
+#pragma unroll
+                for (int y = 0; y < NT; ++y) ones[y].p[0] = cat_parts(u32x2_t{one2, one2}, u32x2_t{one2, one2}), zz[y] = zero4;
+                mma_n(kn, ones, zz);
+#pragma unroll
+                for (int y = 0; y < NT; ++y) z[y] += zz[y];
+            }
+        }
+        if (a.totals != nullptr) {
+            Op<P> gn[MT], qq[NT * MT], gg[NT * MT];
+            f32x4 u[NT * MT];
+#pragma unroll
+            for (int x = 0; x < MT; ++x) gn[x] = read_feat<M, P, false>(tl.sg, kBlk * M, 0, i * MT + x, lane);
+#pragma unroll
+            for (int y = 0; y < NT; ++y) {
+                const Op<P> qf = read_feat<D, P, false>(tl.sq, kBlk * D, 0, h * NT + y, lane);
+#pragma unroll
+                for (int x = 0; x < MT; ++x) qq[y * MT + x] = qf, gg[y * MT + x] = gn[x], u[y * MT + x] = zero4;
+            }
+            mma_n(qq, gg, u);
+#pragma unroll
+            for (int y = 0; y < NT; ++y)
+#pragma unroll
+                for (int x = 0; x < MT; ++x) R[y][x] += u[y * MT + x];
+        }
+    }
+    __device__ __forceinline__ void finish(int) {}
+    __device__ __forceinline__ void end(float *tot) {
+#pragma unroll
+        for (int y = 0; y < NT; ++y)
+#pragma unroll
+            for (int x = 0; x < MT; ++x)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    tot[(16 * (h * NT + y) + 4 * g + r) * M + 16 * (i * MT + x) + c] = R[y][x][r];
+    }
+};
+
+template <int D, int M, typename T, bool kStrided = false>
+__global__ __launch_bounds__((kWave * kBwdWaves<D, M, T>)) __attribute__((amdgpu_waves_per_eu((kBwdWaves<D, M, T> / 2)))) void dq_block_kernel(
+    const PassArgs a) {
+    using Tiles = BlkTiles<kLeadQ, D, M, T, kStrided>;
+    using OutRole = DqOut<D, M, T, kStrided>;
+    using StateRole = DqState<D, M, T, kStrided>;
+    constexpr bool kOwn = kScratchInTiles<D, M>;
+    __shared__ __attribute__((aligned(16))) uint16_t tiles[Tiles::kElems + (kOwn ? 0 : 4 * OutRole::OutTile::kScratch / 2)];
+    __shared__ __attribute__((aligned(16))) uint16_t ss[Tiles::P * D * M];        // S before the block, [d][m]
+    __shared__ __attribute__((aligned(16))) float sz[D];                          // z before the block
+    __shared__ float sdel[2][2][16];
+    __shared__ float srho[2][D];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int seg = blockIdx.x % a.nseg, bh = blockIdx.x / a.nseg;
+    int blk0, count;
+    blk_range(a, seg, blk0, count);
+    char *const scratch = reinterpret_cast<char *>(kOwn ? tiles : tiles + Tiles::kElems);
+    float *const tot = a.totals != nullptr ? a.totals + ((size_t)bh * a.nseg + seg) * state_stride(D, M) : nullptr;
+    Tiles tl(a, tiles, bh, tid, wave);
+    if constexpr (Tiles::kWaves == 8) {
+        if (wave < 4) {
+            OutRole out(a, tl, bh, tid, wave, ss, sz, sdel, srho, scratch);
+            blk_loop(tl, blk0, 1, count, out);
+            if (tot != nullptr) out.end();
+        } else {
+            StateRole st(a, tl, bh, seg, tid, wave, ss, sz);
+            blk_loop(tl, blk0, 1, count, st);
+            if (tot != nullptr) st.end(tot);
+        }
+    } else {
+        OutRole out(a, tl, bh, tid, wave, ss, sz, sdel, srho, scratch);
+        StateRole st(a, tl, bh, seg, tid, wave, ss, sz);
+        blk_loop(tl, blk0, 1, count, out, st);
+        if (tot != nullptr) {
+            out.end();
+            st.end(tot);
+        }
+    }
+    if (tot != nullptr) {
+        __syncthreads();
+        if (tid < D) tot[D * M + tid] = srho[0][tid] + srho[1][tid];
+    }
+}
+
+// ---- dV and dK (eq. 14-15) -------------------------------------------------------------------------
+// Out role (i, j): the 16 tokens of sub-block i, dV (j = 0) or dK (j = 1).
+template <int D, int M, typename T, bool kStrided>
+struct RevOut : BlkLane {
+    using Tiles = BlkTiles<kLeadK, D, M, T, kStrided>;
+    static constexpr int P = Tiles::P, PV = Tiles::PV, TD = D / 16, TM = M / 16, SD = D / 32, SM = M / 32;
+    static constexpr int TX = TD > TM ? TD : TM;
+    static constexpr bool kPair = is_bf16<T>;
+    using RowsV = OutRows<T, TM>;
+    using RowsK = OutRows<T, TD>;
+    static constexpr int kScratch = RowsV::kScratch > RowsK::kScratch ? RowsV::kScratch : RowsK::kScratch;
+    const Tiles &tl;
+    const uint16_t *sr;
+    const float *srho, *sdel;
+    char *scratch;
+    T *outv, *outk;
+    int N, row;
+    f32x4 out[TX];           // dV: columns m, dK: columns d, col_of(t, 4g + r) of the token
+
+    __device__ __forceinline__ RevOut(const PassArgs &a, const Tiles &t, int bh, int tid, int wave, const uint16_t *sr_,
+                                      const float *srho_, const float *sdel_, char *scratch_)
+        : BlkLane(tid, wave), tl(t), sr(sr_), srho(srho_), sdel(sdel_), scratch(scratch_ + 512 * (wave & 3)) {
+        outv = static_cast<T *>(a.out) + seq_base<kStrided>(a.N, a.heads, bh, M);
+        outk = static_cast<T *>(a.out2) + seq_base<kStrided>(a.N, a.heads, bh, qk_width<T>(D));
+        N = a.N, row = 16 * i + c;
+    }
+    __device__ __forceinline__ void init() {}
+    __device__ __forceinline__ void publish() {}
+    __device__ __forceinline__ void fetch(int) {}
+    __device__ __forceinline__ void parked(int) {}
+    // rows a of the block against the role's tokens b (lane c), kept where a >= b
+    __device__ __forceinline__ void keep(f32x4 &w0, f32x4 &w1) const {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {        // select, never multiply
+            w0[r] = (i == 0 && 4 * g + r >= c) ? w0[r] : 0.f;
+            w1[r] = (i == 0 || 4 * g + r >= c) ? w1[r] : 0.f;
+        }
+    }
+    __device__ __forceinline__ void products() {
+        const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+        f32x4 w0 = zero4, w1;
+        if (h == 0) {
+            // scores phi(Q_a) . phi(K_b)
+            Op<P> kt[SD];
+            read_toks<D, P>(tl.sk, kBlk * D, row, g, kt);
+            if (i == 0) {
+                Op<P> qt[SD];
+                read_toks<D, P>(tl.sq, kBlk * D, c, g, qt);
+                w0 = dot(qt, kt, zero4);
+            }
+            {
+                Op<P> qt[SD];
+                read_toks<D, P>(tl.sq, kBlk * D, 16 + c, g, qt);
+                w1 = dot(qt, kt, zero4);
+            }
+            keep(w0, w1);
+#pragma unroll
+            for (int t = 0; t < TM; ++t) {
+                Op<P> rr[SD];
+                read_toks<D, P>(sr, M * D, col_of<kPair>(t, c), g, rr);
+                out[t] = dot(rr, kt, zero4);
+            }
+            const Op<P> wop = op_of<P>(w0, w1);
+#pragma unroll
+            for (int t = 0; t < TM; t += 2) {
+                const Op<P> gf[2] = {read_feat<M, P, kPair>(tl.sg, kBlk * M, 0, t, lane),
+                                     read_feat<M, P, kPair>(tl.sg, kBlk * M, 0, t + 1, lane)};
+                const Op<P> wo[2] = {wop, wop};
+                f32x4 o[2] = {out[t], out[t + 1]};
+                mma_n(gf, wo, o);
+                out[t] = o[0], out[t + 1] = o[1];
+            }
+        } else {
+            // scores V_b . dO_a/den_a + delta_a
+            Op<PV> vt[SM];
+            read_toks<M, PV>(tl.sv, kBlk * M, row, g, vt);
+            if (i == 0) {
+                Op<P> gt[SM];
+                read_toks<M, P>(tl.sg, kBlk * M, c, g, gt);
+                w0 = dot(gt, vt, *reinterpret_cast<const f32x4 *>(sdel + 4 * g));
+            }
+            {
+                Op<P> gt[SM];
+                read_toks<M, P>(tl.sg, kBlk * M, 16 + c, g, gt);
+                w1 = dot(gt, vt, *reinterpret_cast<const f32x4 *>(sdel + 16 + 4 * g));
+            }
+            keep(w0, w1);
+#pragma unroll
+            for (int t = 0; t < TD; ++t) {
+                Op<P> rr[SM];
+#pragma unroll
+                for (int s = 0; s < SM; ++s) rr[s] = read_feat<D, P, kPair, true>(sr, M * D, 32 * s, t, lane);
+                out[t] = dot(rr, vt, *reinterpret_cast<const f32x4 *>(srho + col_of<kPair>(t, 4 * g)));
+            }
+            const Op<P> wop = op_of<P>(w0, w1);
+#pragma unroll
+            for (int t = 0; t < TD; t += 2) {
+                const Op<P> qf[2] = {read_feat<D, P, kPair>(tl.sq, kBlk * D, 0, t, lane),
+                                     read_feat<D, P, kPair>(tl.sq, kBlk * D, 0, t + 1, lane)};
+                const Op<P> wo[2] = {wop, wop};
+                f32x4 o[2] = {out[t], out[t + 1]};
+                mma_n(qf, wo, o);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const f32x4 f = get_parts3<D>(tl.sk, kBlk * D, row, col_of<kPair>(t + u, 4 * g));
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) out[t + u][r] = o[u][r] * feature_slope<T>(f[r]);
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void finish(int blk) {
+        const int t0 = blk * kBlk, nv = min(kBlk, N - t0);
+        constexpr int kStride = kScratchInTiles<D, M> ? 2 * kBlk * D : 4 * 512;
+        if constexpr (is_poly<T>) {      // (four waves, as in the dQ pass)
+            if (h == 0)
+                RowsV::template store<kStride>(scratch, rows_of(outv + (size_t)t0 * tl.tsm, tl.tsm, nv), 16 * i * tl.tsm * (int)sizeof(T),
+                                               tl.tsm, reinterpret_cast<const f32x4 (&)[TM]>(out), lane);
+            __syncthreads();
+            float *rows = reinterpret_cast<float *>(tl.sk);
+            if (h != 0) {
+#pragma unroll
+                for (int t = 0; t < TD; ++t) *reinterpret_cast<f32x4 *>(rows + row * kChainStride + 16 * t + 4 * g) = out[t];
+            }
+            __syncthreads();
+            blk_chain(rows, tl.Ks + (size_t)t0 * tl.tsd, outk + (size_t)t0 * tl.tsd, tl.tsd, nv, tl.tid);
+            __syncthreads();
+        } else if (TD == TM || h == 0) {
+            T *o = TD == TM && h != 0 ? outk : outv;
+            RowsV::template store<kStride>(scratch, rows_of(o + (size_t)t0 * tl.tsm, tl.tsm, nv), 16 * i * tl.tsm * (int)sizeof(T), tl.tsm,
+                                           reinterpret_cast<const f32x4 (&)[TM]>(out), lane);
+        } else {
+            RowsK::template store<kStride>(scratch, rows_of(outk + (size_t)t0 * tl.tsd, tl.tsd, nv), 16 * i * tl.tsd * (int)sizeof(T), tl.tsd,
+                                           reinterpret_cast<const f32x4 (&)[TD]>(out), lane);
+        }
+    }
+};
+
+// State role (i, j): R (D x M), D / 32 x M / 32 tiles, published as [m][d]: dV reads its rows, dK reads them
+// transposed; and one tile of rho = sum delta phi(Q), the ones column.
+template <int D, int M, typename T, bool kStrided>
+struct RevState : BlkLane {
+    using Tiles = BlkTiles<kLeadK, D, M, T, kStrided>;
+    static constexpr int P = Tiles::P, DT = D / 32, MT = M / 32;
+    const PassArgs &a;
+    const Tiles &tl;
+    uint16_t *sr;
+    float *srho, *sdel;
+    const float *delta;
+    int bh, seg, rt, tid;
+    float ndel;
+    f32x4 U[DT][MT];       // element (d = 16 (i DT + x) + 4g + r, m = 16 (h MT + y) + c)
+    f32x4 rho;             // element d = 16 rt + 4g + r
+
+    __device__ __forceinline__ RevState(const PassArgs &a_, const Tiles &t, int bh_, int seg_, int tid_, int wave, uint16_t *sr_, float *srho_, float *sdel_)
+        : BlkLane(tid_, wave), a(a_), tl(t), sr(sr_), srho(srho_), sdel(sdel_), bh(bh_), seg(seg_), tid(tid_) {
+        delta = a.delta + (size_t)bh * a.N;
+        rt = DT == 2 ? 2 * i + h : i;
+        ndel = 0.f;
+    }
+    __device__ __forceinline__ void add(const float *sm, const float *v) {
+#pragma unroll
+        for (int x = 0; x < DT; ++x)
+#pragma unroll
+            for (int y = 0; y < MT; ++y)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) U[x][y][r] += sm[(16 * (i * DT + x) + 4 * g + r) * M + 16 * (h * MT + y) + c];
+        rho += load4_state(v + 16 * rt + 4 * g);
+    }
+    __device__ __forceinline__ void init() {
+        rho = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int x = 0; x < DT; ++x)
+#pragma unroll
+            for (int y = 0; y < MT; ++y) U[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (a.init_S != nullptr) add(a.init_S + (size_t)bh * D * M, a.init_z + (size_t)bh * D);
+        if (a.state != nullptr) {
+            int nslots, lo, hi;
+            state_slots(a, seg, kStateSuffix, nslots, lo, hi);
+            for (int j = lo; j < hi; ++j) {
+                const float *st = a.state + ((size_t)bh * nslots + j) * state_stride(D, M);
+                add(st, st + D * M);
+            }
+        }
+    }
+    __device__ __forceinline__ void publish() {
+        la::publish<D, P>(sr, M * D, U, i * DT, h * MT, c, g);
+        if (c == 0) *reinterpret_cast<f32x4 *>(srho + 16 * rt + 4 * g) = rho;
+    }
+    // one wave brings delta
+    __device__ __forceinline__ void fetch(int blk) {
+        if (i == 0 && h == 0) ndel = delta[min(blk * kBlk + (lane & 31), a.N - 1)];
+    }
+    __device__ __forceinline__ void parked(int blk) {
+        if (i == 0 && h == 0 && lane < kBlk) sdel[lane] = blk * kBlk + lane < a.N ? ndel : 0.f;
+    }
+    __device__ __forceinline__ void products() {
+        const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+        Op<P> gn[MT], qn[DT], qq[DT * MT], gg[DT * MT];
+        f32x4 u[DT * MT];
+#pragma unroll
+        for (int y = 0; y < MT; ++y) gn[y] = read_feat<M, P, false>(tl.sg, kBlk * M, 0, h * MT + y, lane);
+#pragma unroll
+        for (int x = 0; x < DT; ++x) {
+            qn[x] = read_feat<D, P, false>(tl.sq, kBlk * D, 0, i * DT + x, lane);
+#pragma unroll
+            for (int y = 0; y < MT; ++y) qq[x * MT + y] = qn[x], gg[x * MT + y] = gn[y], u[x * MT + y] = zero4;
+        }
+        mma_n(qq, gg, u);
+#pragma unroll
+        for (int x = 0; x < DT; ++x)
+#pragma unroll
+            for (int y = 0; y < MT; ++y) U[x][y] += u[x * MT + y];
+        const Op<P> dop[1] = {op_of<P>(*reinterpret_cast<const f32x4 *>(sdel + 4 * g),
+                                       *reinterpret_cast<const f32x4 *>(sdel + 16 + 4 * g))};
+        f32x4 rr[1] = {zero4};
+        if (DT == 1 || h == 0) {
+            const Op<P> q1[1] = {qn[0]};
+            mma_n(q1, dop, rr);
+        } else {
+            const Op<P> q1[1] = {qn[DT - 1]};
+            mma_n(q1, dop, rr);
+        }
+        rho += rr[0];
+    }
+    __device__ __forceinline__ void finish(int) {}
+    // what has piled up when the first segment is through is the gradient for the initial state
+    __device__ __forceinline__ void end() {
+        if (seg == 0 && a.final_S != nullptr) {
+            float *s1 = a.final_S + (size_t)bh * D * M;
+#pragma unroll
+            for (int x = 0; x < DT; ++x)
+#pragma unroll
+                for (int y = 0; y < MT; ++y)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        s1[(16 * (i * DT + x) + 4 * g + r) * M + 16 * (h * MT + y) + c] = U[x][y][r];
+        }
+        if (seg == 0 && a.final_z != nullptr && c == 0 && (DT == 2 || h == 0))
+            *reinterpret_cast<f32x4 *>(a.final_z + (size_t)bh * D + 16 * rt + 4 * g) = rho;
+    }
+};
+
+template <int D, int M, typename T, bool kStrided = false>
+__global__ __launch_bounds__((kWave * kBwdWaves<D, M, T>)) __attribute__((amdgpu_waves_per_eu((kBwdWaves<D, M, T> / 2)))) void reverse_block_kernel(
+    const PassArgs a) {
+    using Tiles = BlkTiles<kLeadK, D, M, T, kStrided>;
+    using OutRole = RevOut<D, M, T, kStrided>;
+    using StateRole = RevState<D, M, T, kStrided>;
+    constexpr bool kOwn = kScratchInTiles<D, M>;
+    __shared__ __attribute__((aligned(16))) uint16_t tiles[Tiles::kElems + (kOwn ? 0 : 4 * OutRole::kScratch / 2)];
+    __shared__ __attribute__((aligned(16))) uint16_t sr[Tiles::P * M * D];        // R after the block, [m][d]
+    __shared__ __attribute__((aligned(16))) float srho[D];
+    __shared__ __attribute__((aligned(16))) float sdel[kBlk];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int seg = blockIdx.x % a.nseg, bh = blockIdx.x / a.nseg;
+    int blk0, count;
+    blk_range(a, seg, blk0, count);
+    char *const scratch = reinterpret_cast<char *>(kOwn ? tiles : tiles + Tiles::kElems);
+    Tiles tl(a, tiles, bh, tid, wave);
+    if constexpr (Tiles::kWaves == 8) {
+        if (wave < 4) {
+            OutRole out(a, tl, bh, tid, wave, sr, srho, sdel, scratch);
+            blk_loop(tl, blk0 + count - 1, -1, count, out);
+        } else {
+            StateRole st(a, tl, bh, seg, tid, wave, sr, srho, sdel);
+            blk_loop(tl, blk0 + count - 1, -1, count, st);
+            st.end();
+        }
+    } else {
+        OutRole out(a, tl, bh, tid, wave, sr, srho, sdel, scratch);
+        StateRole st(a, tl, bh, seg, tid, wave, sr, srho, sdel);
+        blk_loop(tl, blk0 + count - 1, -1, count, out, st);
+        st.end();
+    }
+}
+
+}  // namespace la

@@ -11,17 +11,18 @@ namespace la {
 // dtype: the la_dtype of the public header (0 fp32, 1 bf16, 2 / 3 the same with Q, K holding
 // feature values already, 4 fp32 with the degree-2 polynomial map: D is then the FEATURE width
 // 64, Q and K hold 8 raw values per token)
-hipError_t launch_pass_fwd(bool global, int D, int M, int dtype, const PassArgs &a, int nblocks,
+// block: the workgroup kernels of la_block.h (causal passes); the plan that sized the segments says which
+hipError_t launch_pass_fwd(bool global, bool block, int D, int M, int dtype, const PassArgs &a, int nblocks,
                            hipStream_t s);
 // dQ, 1/den, delta and (a.totals) the per-segment Q, dO sums; causal or against the global sums
-hipError_t launch_pass_dq(bool causal, int D, int M, int dtype, const PassArgs &a, int nblocks,
+hipError_t launch_pass_dq(bool causal, bool block, int D, int M, int dtype, const PassArgs &a, int nblocks,
                           hipStream_t s);
 // both reverse passes (dV into a.out, dK into a.out2) on one fetch of the inputs
-hipError_t launch_pass_reverse(int D, int M, int dtype, const PassArgs &a, int nblocks,
+hipError_t launch_pass_reverse(bool block, int D, int M, int dtype, const PassArgs &a, int nblocks,
                                hipStream_t s);
 // read-out-only gradients of the non-causal form: dV into a.out, dK into a.out2
 hipError_t launch_global_dkdv(int D, int M, int dtype, const PassArgs &a, int nblocks, hipStream_t s);
-hipError_t launch_segment_state(int D, int M, int dtype, const SegArgs &a, int nblocks,
+hipError_t launch_segment_state(bool block, int D, int M, int dtype, const SegArgs &a, int nblocks,
                                 hipStream_t s);
 
 enum ScanMode { kScanForward = 0, kScanReverse = 1, kScanTotal = 2 };

@@ -1821,17 +1821,26 @@ struct SegArgs {
     int stream;           // as in PassArgs
 };
 
-template <int D, int M, typename T, bool kStrided = false>
-__global__ __launch_bounds__(kWave) void segment_state_kernel(const SegArgs a) {
+// LDS written and read by one wave only: its LDS instructions execute in order
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <int D, int M, typename T, bool kStrided = false, int kWaves = 1>
+__global__ __launch_bounds__(kWave * kWaves) void segment_state_kernel(const SegArgs a) {
     constexpr int XT = D / 16, ZT = M / 16;
     // bf16 tensors: 16-bit operands (two parts), not plain bf16 products.  These sums also
     // serve the backward passes (as the states at the segment borders, and as the grand total
     // of the non-causal gradient), which need S and z built from the same feature values
     // to better than 8 bits: their results are differences of nearly equal terms.
     constexpr int kParts = is_bf16<T> ? 2 : 3;
-    __shared__ float lds_y[tile_floats(D)];
-    __shared__ float lds_z[tile_floats(M)];
-    const int lane = threadIdx.x, c = lane & 15, g = lane >> 4;
+    // tiles private to each wave; several waves: afterwards the sums of two of them
+    constexpr int kTiles = tile_floats(D) + tile_floats(M), kSums = state_stride(D, M);
+    __shared__ __attribute__((aligned(16))) float lds[kWaves == 1 || kWaves * kTiles > 2 * kSums ? kWaves * kTiles : 2 * kSums];
+    const int lane = threadIdx.x & (kWave - 1), c = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float *const lds_y = lds + wave * kTiles, *const lds_z = lds_y + tile_floats(D);
     const bool nt = a.stream != 0;        // non-temporal fetches
     const int seg = blockIdx.x % a.nseg, bh = blockIdx.x / a.nseg;
     if (seg == a.skip_seg) return;
@@ -1875,10 +1884,10 @@ __global__ __launch_bounds__(kWave) void segment_state_kernel(const SegArgs a) {
         }
     };
 
-    if (ch_begin < ch_end) fetch(ch_begin);
-    for (int ch = ch_begin; ch < ch_end; ++ch) {
+    if (ch_begin + wave < ch_end) fetch(ch_begin + wave);
+    for (int ch = ch_begin + wave; ch < ch_end; ch += kWaves) {     // the waves take the chunks in turn
         const int nvalid = min(kChunk, a.N - ch * kChunk);
-        __syncthreads();
+        wave_sync();
         if (nvalid == kChunk) {
             park_tile<D, kMapPhi, true, is_feat<T>>(lds_y, sy, oney, nvalid, lane);
             park_tile<M, kMapId, true, is_feat<T>>(lds_z, sz, onez, nvalid, lane);
@@ -1886,10 +1895,10 @@ __global__ __launch_bounds__(kWave) void segment_state_kernel(const SegArgs a) {
             park_tile<D, kMapPhi, false, is_feat<T>>(lds_y, sy, oney, nvalid, lane);
             park_tile<M, kMapId, false, is_feat<T>>(lds_z, sz, onez, nvalid, lane);
         }
-        if (ch + 1 < ch_end) fetch(ch + 1);
+        if (ch + kWaves < ch_end) fetch(ch + kWaves);
         __builtin_amdgcn_s_sleep(LA_SLEEP_AFTER_FETCH);    // see run_pass
         __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
+        wave_sync();
 
         float yf[XT][4], zf[ZT][4];
         lds_feature_lane<D>(lds_y, c, g, yf);
@@ -1921,6 +1930,35 @@ __global__ __launch_bounds__(kWave) void segment_state_kernel(const SegArgs a) {
         }
 #pragma unroll
         for (int xt = 0; xt < XT; ++xt) ec[xt] += (yf[xt][0] + yf[xt][1]) + (yf[xt][2] + yf[xt][3]);
+    }
+    if constexpr (kWaves == 4) {
+        // (0 + 2) + (1 + 3), in this order; a lane finds its own elements where the other wave's lane put them
+        auto put = [&](float *p) {
+#pragma unroll
+            for (int xt = 0; xt < XT; ++xt) {
+#pragma unroll
+                for (int zt = 0; zt < ZT; ++zt) lds_store4(p + ((xt * ZT + zt) * kWave + lane) * 4, U[xt][zt]);
+                const float e = sum_over_groups(ec[xt]);
+                if (g == 0) p[D * M + 16 * xt + c] = e;
+            }
+        };
+        auto take = [&](const float *p) {
+#pragma unroll
+            for (int xt = 0; xt < XT; ++xt) {
+#pragma unroll
+                for (int zt = 0; zt < ZT; ++zt) U[xt][zt] += *reinterpret_cast<const f32x4 *>(p + ((xt * ZT + zt) * kWave + lane) * 4);
+                ec[xt] += g == 0 ? p[D * M + 16 * xt + c] : 0.f;
+            }
+        };
+        __syncthreads();
+        if (wave >= 2) put(lds + (wave - 2) * kSums);
+        __syncthreads();
+        if (wave < 2) take(lds + wave * kSums);
+        __syncthreads();
+        if (wave == 1) put(lds);
+        __syncthreads();
+        if (wave != 0) return;
+        take(lds);
     }
     float *st = a.state + ((size_t)bh * a.nseg + seg) * state_stride(D, M);
 #pragma unroll

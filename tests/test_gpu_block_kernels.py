@@ -1,0 +1,124 @@
+"""The workgroup kernels of the causal passes (32-token blocks, csrc/la_block.h): every kind of call
+at the edges of their blocks, forced on and off (LA_BLOCK_KERNELS), against the oracle.
+
+Tolerances, max-norm relative: outputs of fp32 tensors 1e-5 (every product is exact to 2^-23 and an
+element is the sum of a few dozen of them per block, each rounded at 2^-24; measured 5e-7 at most).
+Gradients of fp32 tensors 1e-4: grad_errs floors a tensor's scale at 1e-3 of the largest, and where dQ
+and dK vanish by cancellation (N = 1) a rounding of 2^-24 of the terms that cancel counts a
+thousandfold, 6e-5.  bf16 tensors: the gate of the oracle comparison everywhere else, 2e-2."""
+import contextlib
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from gpu_util import DEV, SCHEDULES, grad_errs, maybe_bf16, rel_err, schedule, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@contextlib.contextmanager
+def block_kernels(monkeypatch, on, sched):
+    """LA_BLOCK_KERNELS is read with the schedule's own knobs"""
+    import paper_2006_16236_amd as la
+    monkeypatch.setenv("LA_BLOCK_KERNELS", on)
+    try:
+        with schedule(**SCHEDULES[sched]):
+            yield la
+    finally:
+        monkeypatch.delenv("LA_BLOCK_KERNELS")
+        la.la_tuning_reload()
+
+
+def run(la, dev, eps, token_major=False, **kw):
+    """forward and backward: O, den, dQ, dK, dV as [B, H, N, .] host arrays"""
+    q, k, v, g = (x.transpose(1, 2).contiguous() for x in dev) if token_major else dev
+    B, H, N = dev[0].shape[:3]
+    O = torch.full_like(v, float("nan"))
+    den = torch.full((B, H, N), float("nan"), device=DEV)
+    fwd = la.la_causal_fwd_bnhd if token_major else la.la_causal_fwd
+    bwd = la.la_causal_bwd_bnhd if token_major else la.la_causal_bwd
+    ws = fwd(q, k, v, O, den, eps, **kw)
+    grads = [torch.full_like(x, float("nan")) for x in (q, k, v)]
+    bwd(q, k, v, None, den, g, *grads, eps, fwd_ws=ws, **kw)
+    torch.cuda.synchronize()
+    return [to_host(x.transpose(1, 2) if token_major else x) for x in (O, *grads)], den.cpu().numpy()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("D,M", [(64, 64), (32, 32), (64, 32), (32, 64)])
+@pytest.mark.parametrize("N,sched", [(1, "default"), (16, "default"), (31, "default"), (32, "default"), (33, "default"),
+                                     (65, "many_segments"), (255, "many_segments"), (700, "three_chunk_segments"),
+                                     (1027, "default")])
+def test_block_edges(oracle, monkeypatch, N, sched, D, M, bf16):
+    B, H = 1, 3
+    host = maybe_bf16(wl.random_case(8100 + N + D + 2 * M, B, H, N, D, M), bf16)
+    ref = oracle.causal_fwd_prefix(*host[:3], 1e-6)
+    gref = oracle.causal_bwd_linear(*host, 1e-6)
+    dev = [to_dev(x, bf16) for x in host]
+    tol = 2e-2 if bf16 else 1e-5
+    got = {}
+    for on in "01":
+        with block_kernels(monkeypatch, on, sched) as la:
+            (O, *grads), den = got[on] = run(la, dev, 1e-6)
+            (Ot, *gt), dent = run(la, dev, 1e-6, token_major=True)
+        assert rel_err(O, ref) <= tol
+        assert max(grad_errs(grads, gref)) <= (tol if bf16 else 1e-4)
+        for a, b in zip((O, *grads, den), (Ot, *gt, dent)):
+            assert np.array_equal(a, b)
+    # den is an fp32 result whatever the tensors are; for bf16 tensors the wave kernels form the part of it
+    # that comes from a token's own chunk from two-part operands, 2^-16
+    assert rel_err(got["1"][1], got["0"][1].astype(np.float64)) <= (1.6e-5 if bf16 else 1e-6)
+
+
+@pytest.mark.parametrize("sched", ["default", "many_segments"])
+@pytest.mark.parametrize("kind", ["f32", "bf16", "poly2"])
+def test_state_in_and_out(oracle, monkeypatch, kind, sched):
+    """forward and backward from a state and into one: both kinds of kernels give the same to
+    rounding, and the pieces the caller sees (final state, its gradient) are finite and equal"""
+    B, H, N, M, bf16 = 2, 2, 301, 64, kind == "bf16"
+    D = 8 if kind == "poly2" else 64
+    C, eps, kw = 64, 0.5 if kind == "poly2" else 1e-6, {"features": "poly2"} if kind == "poly2" else {}
+    dev = [to_dev(x, bf16) for x in maybe_bf16(wl.random_case(8300 + D, B, H, N, D, M), bf16)]
+    S0, z0 = (torch.rand(s, device=DEV, generator=torch.Generator(DEV).manual_seed(3)) * 8 for s in ((B, H, C, M), (B, H, C)))
+    dS1, dz1 = torch.randn(B, H, C, M, device=DEV), torch.randn(B, H, C, device=DEV)
+    res = []
+    for on in "01":
+        with block_kernels(monkeypatch, on, sched) as la:
+            q, k, v, g = dev
+            O, den = torch.full_like(v, float("nan")), torch.full((B, H, N), float("nan"), device=DEV)
+            S1, z1, dS0, dz0 = (torch.full_like(x, float("nan")) for x in (S0, z0, S0, z0))
+            ws = la.la_causal_fwd_state(q, k, v, O, den, S0, z0, S1, z1, eps, **kw)
+            grads = [torch.full_like(x, float("nan")) for x in (q, k, v)]
+            la.la_causal_bwd_state(q, k, v, None, den, g, *grads, S0, z0, dS1, dz1, dS0, dz0, eps, fwd_ws=ws, **kw)
+            torch.cuda.synchronize()
+            res.append([to_host(x) for x in (O, den, S1, z1, *grads, dS0, dz0)])
+    for i, (a, b) in enumerate(zip(*res)):
+        exact = i in (1, 2, 3)               # den, S1, z1: fp32 results for every element type
+        tol = (1e-2 if i == 2 else 1e-5) if exact and bf16 else 2e-2 if bf16 else 2e-5
+        assert np.isfinite(b).all() and rel_err(b, a.astype(np.float64)) <= tol, i
+
+
+def test_poly2_edges(oracle, monkeypatch):
+    for N, sched in ((1, "default"), (33, "default"), (130, "many_segments"), (515, "default")):
+        host = wl.random_case(8500 + N, 1, 2, N, 8, 64)
+        ref = oracle.causal_fwd_poly2(*host[:3], 0.5)
+        gref = oracle.causal_bwd_poly2(*host, 0.5)
+        with block_kernels(monkeypatch, "1", sched) as la:
+            for token_major in (False, True):
+                (O, *grads), _ = run(la, [to_dev(x) for x in host], 0.5, token_major, features="poly2")
+                assert rel_err(O, ref) <= 1e-5 and max(grad_errs(grads, gref)) <= 1e-4, N
+
+
+def test_non_temporal_loads_change_no_bit(monkeypatch):
+    dev = [to_dev(x) for x in wl.random_case(8600, 2, 2, 333, 64, 64)]
+    with block_kernels(monkeypatch, "1", "many_segments") as la:
+        a = run(la, dev, 1e-6)
+    monkeypatch.setenv("LA_BLOCK_KERNELS", "1")
+    with schedule(**SCHEDULES["many_segments"], stream_loads=1):
+        b = run(la, dev, 1e-6)
+    monkeypatch.delenv("LA_BLOCK_KERNELS")
+    la.la_tuning_reload()
+    for x, y in zip((*a[0], a[1]), (*b[0], b[1])):
+        assert np.array_equal(x, y)
