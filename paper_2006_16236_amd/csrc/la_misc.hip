@@ -165,96 +165,155 @@ __global__ __launch_bounds__(256) void recurrent_step_kernel(const T *q, const T
 }
 
 // T consecutive decode steps in one launch, for callers that already hold the q, k, v of
-// all T tokens (scoring, teacher forcing): the state stays in registers between steps, the
-// next token's q, k, v are fetched while the current one is processed.  The arithmetic of a
-// step, lane for lane, is that of recurrent_step_kernel: T steps here and T launches of
-// the single step give bit-identical outputs and states.
+// all T tokens (scoring, teacher forcing): the state stays in registers between steps.  The
+// additions of a step are those of recurrent_step_kernel in the same order: T steps here and T
+// launches of the single step give bit-identical outputs and states.
+//
+// Steps are taken kStepBatch at a time: every wave runs the rank-1 updates and its lanes' partial
+// read-outs of all steps without a barrier, leaving the partial sums in LDS; after one barrier all threads
+// add them up and store the batch's outputs.  The threads stage the next batch's k, q (each feature
+// mapped once) and v in LDS on the way, the one after that is in flight.  Bounded by instruction issue and LDS:
+// 16 state elements per lane (D = M = 64) take 40 vector instructions and four 16-byte LDS accesses
+// per step.  B*H = 512, T = 784: 742 us with the sums formed step by step (shuffles, one barrier
+// each), 208 us so; 253 us with the features passed between the lanes of a row by DPP (moves of their
+// own) instead of read from LDS.
+constexpr int kStepBatch = 8;
+// (x0 + x1) + (x2 + x3) ...: the order in which the single step's shuffles add
+template <int N> __device__ __forceinline__ float tree_sum(const float (&x)[N]) {
+    if constexpr (N == 1) return x[0];
+    else {
+        float y[N / 2];
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) y[i] = x[2 * i] + x[2 * i + 1];
+        return tree_sum<N / 2>(y);
+    }
+}
 template <int D, int M, typename T>
 __global__ __launch_bounds__(256) void recurrent_steps_kernel(const T *q, const T *k, const T *v,
                                                               float *S, float *z, T *out,
                                                               float eps, int steps, size_t BH) {
     constexpr int LPR = M / 4, RPW = kWave / LPR, RPI = 4 * RPW, NIT = D / RPI;
-    __shared__ float red[2][4][M];
-    __shared__ float dred[2][4];
+    constexpr int W = qk_width<T>(D);          // elements per token of q and k
+    constexpr int NF = kStepBatch * 2 * D / 256, NV = kStepBatch * M / 256;      // values a thread stages per batch
+    typedef float fN __attribute__((ext_vector_type(NIT)));
+    __shared__ __attribute__((aligned(16))) float feat[2][kStepBatch][2][D];          // k, q; row (wave, rsub, it) order
+    __shared__ __attribute__((aligned(16))) float vals[2][kStepBatch][M];
+    __shared__ __attribute__((aligned(16))) float part[2][kStepBatch][4][kWave][4];   // read-out partial sums
+    __shared__ __attribute__((aligned(16))) float dpart[2][4][RPW][kStepBatch];
 
     const int bh = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int col4 = (lane % LPR) * 4, rsub = lane / LPR;
+    const int col4 = (lane % LPR) * 4, rsub = lane / LPR, r0 = wave * RPW + rsub;
     float *Sh = S + (size_t)bh * D * M, *zh = z + (size_t)bh * D;
 
     f32x4 s4[NIT];
-    float zr[NIT];
+    float zr[NIT];                            // (the same in all lanes of a row)
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int d = it * RPI + wave * RPW + rsub;
-        s4[it] = *reinterpret_cast<const f32x4 *>(Sh + (size_t)d * M + col4);
-        zr[it] = zh[d];
+        s4[it] = *reinterpret_cast<const f32x4 *>(Sh + (size_t)(it * RPI + r0) * M + col4);
+        zr[it] = zh[it * RPI + r0];
     }
-    constexpr int W = qk_width<T>(D);          // elements per token of q and k
-    // The wave sweeps NR rows of S per step, and every lane of a row needs that row's feature of
-    // k and of q.  The feature map is evaluated once per row and wave, not once per lane: lane
-    // j < NR fetches and maps k's element of row j of the sweep, lane NR + j the same of q (the
-    // lanes above 2 NR repeat them, unused), and the lanes of a row pick the values up with a
-    // shuffle.  The values are those every lane computed for itself before, bit for bit.
-    constexpr int NR = NIT * RPW;
-    static_assert(2 * NR <= kWave, "one lane per row and operand");
-    const int j = lane % NR;
-    const bool mine_is_q = ((lane / NR) & 1) != 0;
-    const int dj = (j / RPW) * RPI + wave * RPW + (j % RPW);
-    auto fetch = [&](int t, float &x, f32x4 &v4) {
-        const T *row = (mine_is_q ? q : k) + ((size_t)t * BH + bh) * W;
-        if constexpr (is_poly<T>) x = feature_of<T>(row, dj);   // the feature itself (x_i x_j): nothing is left to map
-        else x = to_f32(row[dj]);
-        v4 = load4(v + ((size_t)t * BH + bh) * M + col4);
+    // value j of a thread: step tf + j * TF of the batch, of k or q, feature df; step tv + j * TV, column tid % M of v
+    constexpr int TF = 256 / (2 * D), TV = 256 / M;
+    const size_t hop_f = BH * W, hop_v = BH * M;             // from one step to the next
+    const int tf = tid / (2 * D), df = tid % D, tv = tid / M, fq = (tid / D) & 1;
+    const T *pf = (fq ? q : k) + (size_t)bh * W, *pv = v + (size_t)bh * M + tid % M;
+    float xf[NF], xv[NV];
+    const size_t of = (size_t)tf * hop_f, ov = (size_t)tv * hop_v;
+    auto one_f = [&](const T *row) {
+        if constexpr (is_poly<T>) return feature_of<T>(row, df);      // the feature itself (x_i x_j)
+        else return to_f32(row[df]);
     };
-    float x_next;
-    f32x4 v_next;
-    fetch(0, x_next, v_next);
-    for (int t = 0; t < steps; ++t) {
-        const float f = feature<T>(x_next);
-        const f32x4 v4 = v_next;
-        if (t + 1 < steps) fetch(t + 1, x_next, v_next);
-
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        float dpart = 0.f;
+    auto fetch = [&](const int t0) {
+        if (t0 + kStepBatch <= steps) {
 #pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            const float kd = __shfl(f, it * RPW + rsub);
-            const float qd = __shfl(f, NR + it * RPW + rsub);
+            for (int j = 0; j < NF; ++j) xf[j] = one_f(pf + (size_t)(t0 + j * TF) * hop_f + of);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                s4[it][e] = fmaf(kd, v4[e], s4[it][e]);
-                acc[e] = fmaf(qd, s4[it][e], acc[e]);
+            for (int j = 0; j < NV; ++j) xv[j] = to_f32(pv[(size_t)(t0 + j * TV) * hop_v + ov]);
+        } else {                              // steps past the end repeat the last one, unused
+#pragma unroll
+            for (int j = 0; j < NF; ++j) xf[j] = one_f(pf + min(t0 + tf + j * TF, steps - 1) * hop_f);
+#pragma unroll
+            for (int j = 0; j < NV; ++j) xv[j] = to_f32(pv[min(t0 + tv + j * TV, steps - 1) * hop_v]);
+        }
+    };
+    float *const fput = &feat[0][tf][fq][(df % RPI) * NIT + df / RPI];       // df = it * RPI + r
+    auto stage = [&](const int buf) {
+#pragma unroll
+        for (int j = 0; j < NF; ++j) fput[buf * kStepBatch * 2 * D + j * TF * 2 * D] = feature<T>(xf[j]);
+#pragma unroll
+        for (int j = 0; j < NV; ++j) (&vals[buf][0][0])[tid + 256 * j] = xv[j];
+    };
+    fetch(0);
+    stage(0);
+    if (kStepBatch < steps) fetch(kStepBatch);
+    __syncthreads();
+    int buf = 0;
+    for (int t0 = 0; t0 < steps; t0 += kStepBatch, buf ^= 1) {
+        const int n = min(kStepBatch, steps - t0);
+        float dp8[kStepBatch];
+        auto step = [&](const int t) {
+            const fN kd = *reinterpret_cast<const fN *>(&feat[buf][t][0][r0 * NIT]);
+            const fN qd = *reinterpret_cast<const fN *>(&feat[buf][t][1][r0 * NIT]);
+            const f32x4 v4 = *reinterpret_cast<const f32x4 *>(&vals[buf][t][col4]);
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            float dp = 0.f;
+#pragma unroll
+            for (int it = 0; it < NIT; ++it) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    s4[it][e] = fmaf(kd[it], v4[e], s4[it][e]);          // eq. 18
+                    acc[e] = fmaf(qd[it], s4[it][e], acc[e]);
+                }
+                zr[it] += kd[it];                                        // eq. 19
+                dp = fmaf(qd[it], zr[it], dp);
             }
-            if (col4 == 0) {
-                zr[it] += kd;
-                dpart = fmaf(qd, zr[it], dpart);
-            }
+            *reinterpret_cast<f32x4 *>(&part[buf][t][wave][lane][0]) = acc;
+            return dp;
+        };
+        if (n == kStepBatch) {
+#pragma unroll
+            for (int t = 0; t < kStepBatch; ++t) dp8[t] = step(t);
+        } else {
+#pragma unroll
+            for (int t = 0; t < kStepBatch; ++t) dp8[t] = t < n ? step(t) : 0.f;
         }
+        if (col4 == 0) {
 #pragma unroll
-        for (int off = LPR; off < kWave; off <<= 1) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], off);
+            for (int t = 0; t < kStepBatch; t += 4)
+                *reinterpret_cast<f32x4 *>(&dpart[buf][wave][rsub][t]) = f32x4{dp8[t], dp8[t + 1], dp8[t + 2], dp8[t + 3]};
         }
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) dpart += __shfl_xor(dpart, off);
-        const int buf = t & 1;            // two LDS buffers: one barrier per step suffices
-        if (rsub == 0) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) red[buf][wave][col4 + e] = acc[e];
+        if (t0 + kStepBatch < steps) {
+            stage(buf ^ 1);
+            if (t0 + 2 * kStepBatch < steps) fetch(t0 + 2 * kStepBatch);
         }
-        if (lane == 0) dred[buf][wave] = dpart;
+        // one barrier per batch: what is read behind it is written again two batches on, behind the next one
         __syncthreads();
-        if (tid < M) {
-            const float num = (red[buf][0][tid] + red[buf][1][tid]) + (red[buf][2][tid] + red[buf][3][tid]);
-            const float den = ((dred[buf][0] + dred[buf][1]) + (dred[buf][2] + dred[buf][3])) + eps;
-            store_elem(out + ((size_t)t * BH + bh) * M + tid, num / den);
+        // NV adjacent columns of one step per thread
+        const int t = tid / (M / NV), m = NV * (tid % (M / NV));
+        if (t < n) {
+            float num[NV][4], den[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                float x[NV][RPW], y[RPW];
+#pragma unroll
+                for (int r = 0; r < RPW; ++r) {
+#pragma unroll
+                    for (int i = 0; i < NV; ++i) x[i][r] = part[buf][t][w][r * LPR + m / 4][m % 4 + i];
+                    y[r] = dpart[buf][w][r][t];
+                }
+#pragma unroll
+                for (int i = 0; i < NV; ++i) num[i][w] = tree_sum<RPW>(x[i]);
+                den[w] = tree_sum<RPW>(y);
+            }
+            const float dn = tree_sum<4>(den) + eps;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) store_elem(out + ((size_t)(t0 + t) * BH + bh) * M + m + i, tree_sum<4>(num[i]) / dn);   // eq. 20
         }
     }
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int d = it * RPI + wave * RPW + rsub;
-        *reinterpret_cast<f32x4 *>(Sh + (size_t)d * M + col4) = s4[it];
-        if (col4 == 0) zh[d] = zr[it];
+        *reinterpret_cast<f32x4 *>(Sh + (size_t)(it * RPI + r0) * M + col4) = s4[it];
+        if (col4 == 0) zh[it * RPI + r0] = zr[it];
     }
 }
 

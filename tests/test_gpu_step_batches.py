@@ -1,0 +1,33 @@
+"""la_recurrent_steps takes its steps in batches of eight: every remainder of a batch, for every
+element type and head size, must leave the bits that single steps leave (exact: the additions are the
+same in the same order)."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("kind", ["f32", "bf16", "given", "poly2"])
+@pytest.mark.parametrize("D,M", [(64, 64), (32, 32), (64, 32), (32, 64)])
+def test_batches_equal_single_steps(kind, D, M):
+    import paper_2006_16236_amd as la
+    if kind == "poly2" and D != 64:
+        pytest.skip("the polynomial map has 64 features")
+    B, H, W = 2, 3, 8 if kind == "poly2" else D
+    kw = {"given": {"features": True}, "poly2": {"features": "poly2"}}.get(kind, {})
+    dt = torch.bfloat16 if kind == "bf16" else torch.float32
+    g = torch.Generator(DEV).manual_seed(D + 2 * M)
+    for T in (1, 2, 7, 8, 9, 16, 17, 31):
+        q, k = (torch.randn(T, B, H, W, device=DEV, generator=g).to(dt) for _ in range(2))
+        if kind == "given":
+            q, k = q.abs(), k.abs()
+        v = torch.randn(T, B, H, M, device=DEV, generator=g).to(dt)
+        S = torch.rand(B, H, D, M, device=DEV, generator=g)
+        z = torch.rand(B, H, D, device=DEV, generator=g)
+        S1, z1, out, out1 = S.clone(), z.clone(), torch.empty_like(v), torch.empty_like(v)
+        la.la_recurrent_steps(q, k, v, S, z, out, 0.5, **kw)
+        for t in range(T):
+            la.la_recurrent_step(q[t], k[t], v[t], S1, z1, out1[t], 0.5, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(out, out1) and torch.equal(S, S1) and torch.equal(z, z1), T
