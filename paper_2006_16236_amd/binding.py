@@ -102,6 +102,37 @@ def _load() -> ctypes.CDLL:
 _lib = _load()
 
 
+def _bind_call():
+    """The native accepting path of the calls below (csrc/la_call.cpp): each of its functions checks the
+    tensors of a call and makes it, or answers None, and the call then takes the path in this file, which
+    names what is wrong with it."""
+    from . import _call as c
+    names = ["la_recurrent_step"]
+    names += [f"la_{kind}_{way}{layout}" for way in ("fwd", "bwd") for kind in ("causal", "global") for layout in ("", "_bnhd")]
+    names += [f"la_{kind}_{way}_workspace" for way in ("fwd", "bwd") for kind in ("causal", "global")]
+    c.bind([ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in names])
+    return c
+
+
+_call = _bind_call()
+_CAUSAL, _CAUSAL_BNHD, _GLOBAL, _GLOBAL_BNHD = 0, 1, 2, 3
+
+
+def _fwd_call(kind, Q, K, V, O, den, ws, eps, stream, features, where):
+    """The workspace if the native path took the call, else None."""
+    r = _call.fwd(kind, Q, K, V, O, den, ws, float(eps), features) if stream is None else None
+    if type(r) is int:
+        _check(r, where)
+    return r
+
+
+def _bwd_call(kind, Q, K, V, O, den, dO, dQ, dK, dV, ws, fwd_ws, eps, stream, features, where):
+    r = _call.bwd(kind, Q, K, V, O, den, dO, dQ, dK, dV, ws, fwd_ws, float(eps), features) if stream is None else None
+    if type(r) is int:
+        _check(r, where)
+    return r
+
+
 def status_string(status: int) -> str:
     return _lib.la_status_string(int(status)).decode()
 
@@ -307,6 +338,9 @@ def _fwd_ws_bytes(fwd_ws, need, name):
 def la_causal_fwd(Q, K, V, O, den=None, eps=1e-6, ws=None, stream=None, features=False):
     """O [B,H,N,M] <- causal linear attention of Q, K [B,H,N,D], V [B,H,N,M]; den [B,H,N] fp32
     (optional) receives the denominators.  Enqueues on `stream` (default: torch's current)."""
+    r = _fwd_call(_CAUSAL, Q, K, V, O, den, ws, eps, stream, features, "la_causal_fwd")
+    if r is not None:
+        return r
     sz = _Sizes(Q, V, features=features)
     sz.forward(Q, K, V, O, den)
     _bytes("ws", ws, sz.dev)
@@ -346,6 +380,9 @@ def la_causal_bwd(Q, K, V, O, den, dO, dQ, dK, dV, eps=1e-6, ws=None, stream=Non
     """dQ, dK, dV <- gradients of causal linear attention for upstream dO; O and den are the
     forward results (den None: recomputed; O is not read and may be None).  fwd_ws (optional) is
     the workspace tensor la_causal_fwd returned for the same call: its segment states are reused."""
+    r = _bwd_call(_CAUSAL, Q, K, V, O, den, dO, dQ, dK, dV, ws, fwd_ws, eps, stream, features, "la_causal_bwd")
+    if r is not None:
+        return r
     sz = _Sizes(Q, V, features=features)
     sz.backward(Q, K, V, O, den, dO, dQ, dK, dV, fwd_ws)
     _fwd_ws_bytes(fwd_ws, la_causal_fwd_workspace(*sz.dims, sz.t), "la_causal_bwd")
@@ -359,6 +396,9 @@ def la_causal_bwd(Q, K, V, O, den, dO, dQ, dK, dV, eps=1e-6, ws=None, stream=Non
 
 def la_causal_fwd_bnhd(Q, K, V, O, den=None, eps=1e-6, ws=None, stream=None, features=False):
     """la_causal_fwd on token-major tensors: Q, K [B,N,H,D], V, O [B,N,H,M]; den stays [B,H,N]."""
+    r = _fwd_call(_CAUSAL_BNHD, Q, K, V, O, den, ws, eps, stream, features, "la_causal_fwd_bnhd")
+    if r is not None:
+        return r
     sz = _Sizes(Q, V, token_major=True, features=features)
     sz.forward(Q, K, V, O, den)
     _bytes("ws", ws, sz.dev)
@@ -372,6 +412,9 @@ def la_causal_bwd_bnhd(Q, K, V, O, den, dO, dQ, dK, dV, eps=1e-6, ws=None, strea
                        features=False):
     """la_causal_bwd on token-major tensors ([B,N,H,.]; den [B,H,N]); fwd_ws from
     la_causal_fwd_bnhd."""
+    r = _bwd_call(_CAUSAL_BNHD, Q, K, V, O, den, dO, dQ, dK, dV, ws, fwd_ws, eps, stream, features, "la_causal_bwd_bnhd")
+    if r is not None:
+        return r
     sz = _Sizes(Q, V, token_major=True, features=features)
     sz.backward(Q, K, V, O, den, dO, dQ, dK, dV, fwd_ws)
     _fwd_ws_bytes(fwd_ws, la_causal_fwd_workspace(*sz.dims, sz.t), "la_causal_bwd_bnhd")
@@ -406,6 +449,9 @@ def la_causal_bwd_state(Q, K, V, O, den, dO, dQ, dK, dV, S0=None, z0=None, dS1=N
 def la_global_fwd(Q, K, V, O, eps=1e-6, ws=None, stream=None, den=None, features=False):
     """O <- non-causal linear attention (every query sees every key); den [B,H,N] fp32
     (optional) receives the denominators."""
+    r = _fwd_call(_GLOBAL, Q, K, V, O, den, ws, eps, stream, features, "la_global_fwd")
+    if r is not None:
+        return r
     sz = _Sizes(Q, V, features=features)
     sz.forward(Q, K, V, O, den)
     _bytes("ws", ws, sz.dev)
@@ -420,6 +466,9 @@ def la_global_bwd(Q, K, V, O, den, dO, dQ, dK, dV, eps=1e-6, ws=None, stream=Non
     """dQ, dK, dV <- gradients of non-causal linear attention for upstream dO; O and den are the
     results of la_global_fwd (den None: recomputed; O is not read and may be None).  fwd_ws
     (optional) is the workspace tensor la_global_fwd returned for the same call."""
+    r = _bwd_call(_GLOBAL, Q, K, V, O, den, dO, dQ, dK, dV, ws, fwd_ws, eps, stream, features, "la_global_bwd")
+    if r is not None:
+        return r
     sz = _Sizes(Q, V, features=features)
     sz.backward(Q, K, V, O, den, dO, dQ, dK, dV, fwd_ws)
     _fwd_ws_bytes(fwd_ws, la_global_fwd_workspace(*sz.dims, sz.t), "la_global_bwd")
@@ -433,6 +482,9 @@ def la_global_bwd(Q, K, V, O, den, dO, dQ, dK, dV, eps=1e-6, ws=None, stream=Non
 
 def la_global_fwd_bnhd(Q, K, V, O, eps=1e-6, ws=None, stream=None, den=None, features=False):
     """la_global_fwd on token-major tensors: Q, K [B,N,H,D], V, O [B,N,H,M]; den stays [B,H,N]."""
+    r = _fwd_call(_GLOBAL_BNHD, Q, K, V, O, den, ws, eps, stream, features, "la_global_fwd_bnhd")
+    if r is not None:
+        return r
     sz = _Sizes(Q, V, token_major=True, features=features)
     sz.forward(Q, K, V, O, den)
     _bytes("ws", ws, sz.dev)
@@ -446,6 +498,9 @@ def la_global_bwd_bnhd(Q, K, V, O, den, dO, dQ, dK, dV, eps=1e-6, ws=None, strea
                        features=False):
     """la_global_bwd on token-major tensors ([B,N,H,.]; den [B,H,N]); fwd_ws from
     la_global_fwd_bnhd."""
+    r = _bwd_call(_GLOBAL_BNHD, Q, K, V, O, den, dO, dQ, dK, dV, ws, fwd_ws, eps, stream, features, "la_global_bwd_bnhd")
+    if r is not None:
+        return r
     sz = _Sizes(Q, V, token_major=True, features=features)
     sz.backward(Q, K, V, O, den, dO, dQ, dK, dV, fwd_ws)
     _fwd_ws_bytes(fwd_ws, la_global_fwd_workspace(*sz.dims, sz.t), "la_global_bwd_bnhd")
@@ -493,6 +548,11 @@ def _step_checks(q, k, v, S, z, out, lead, features):
 def la_recurrent_step(q, k, v, S, z, out, eps=1e-6, stream=None, features=False):
     """One decode step for q, k [B,H,D], v [B,H,M]: S [B,H,D,M], z [B,H,D] (fp32) are updated
     in place, out [B,H,M] receives the attention output of the new token."""
+    if stream is None:
+        st = _call.step(q, k, v, S, z, out, float(eps), features)
+        if st is not None:
+            _check(st, "la_recurrent_step")
+            return
     t, B, H, D, M = _step_checks(q, k, v, S, z, out, 0, features)
     _check(_lib.la_recurrent_step(_ptr(q), _ptr(k), _ptr(v), _ptr(S), _ptr(z), _ptr(out), B, H, D,
                                   M, float(eps), t, _stream(stream)),

@@ -1,4 +1,5 @@
-"""Builds the gfx950 shared library (csrc/*.hip -> libla_hip.so) with hipcc.
+"""Builds the gfx950 shared library (csrc/*.hip -> libla_hip.so) with hipcc, and the binding's
+native argument checks (csrc/la_call.cpp -> _call.so) with g++.
 
 hipcc cross-compiles without a GPU, so this runs anywhere the ROCm toolchain is
 installed.  The library is kept in-tree next to this file.
@@ -20,18 +21,36 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
+CALL = os.path.join(HERE, "_call.so")
+
+
+def _build_call() -> None:
+    """The native argument checks (csrc/la_call.cpp), a CPython module on torch's headers; host code."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                    "-I", os.path.join(root, "include"), "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                    "-I", "/opt/rocm/include", "-I", sysconfig.get_paths()["include"],
+                    os.path.join(CSRC, "la_call.cpp"), "-o", CALL, "-L", os.path.join(root, "lib"),
+                    "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", f"-Wl,-rpath,{os.path.join(root, 'lib')}"],
+                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+
+
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
 def _deps_mtime():
-    files = sources() + glob.glob(os.path.join(CSRC, "*.h")) + \
+    files = sources() + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(CSRC, "*.cpp")) + \
         glob.glob(os.path.join(HERE, "..", "include", "*.h"))
     return max(os.path.getmtime(f) for f in files)
 
 
 def is_current() -> bool:
-    return os.path.exists(LIB) and os.path.getmtime(LIB) >= _deps_mtime()
+    return all(os.path.exists(f) and os.path.getmtime(f) >= _deps_mtime() for f in (LIB, CALL))
 
 
 def _compile(src: str) -> str:
@@ -42,14 +61,16 @@ def _compile(src: str) -> str:
 
 
 def build_library(force: bool = True, jobs: int = 6) -> str:
-    """Compile every HIP source for gfx950 and link libla_hip.so.  With
+    """Compile every HIP source for gfx950, link libla_hip.so, and build _call.so.  With
     force=False an up-to-date library is left alone."""
     if not force and is_current():
         return LIB
     os.makedirs(OBJ, exist_ok=True)
     try:
         with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as ex:
+            call = ex.submit(_build_call)
             objs = list(ex.map(_compile, sources()))
+            call.result()
         subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs],
                        check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
     except subprocess.CalledProcessError as e:  # show the compiler's message
