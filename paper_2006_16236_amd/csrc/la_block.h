@@ -482,11 +482,13 @@ __device__ __forceinline__ void read_toks(const uint16_t *tile, int plane, int r
 // ---- causal forward (eq. 9-12) ---------------------------------------------------------------------
 // Out role (i, h): the 16 tokens of sub-block i, columns of half h of V; the scores and with them the
 // denominators of a sub-block are formed by both of its roles.  bf16 tensors: den comes from three-part
-// operands (it is an fp32 result), the numerator from plain bf16 products as everywhere in the forward.
+// operands (it is an fp32 result), the numerator from bf16 products, the scores in two parts.
 template <int D, int M, typename T, bool kStrided>
 struct FwdOut : BlkLane {
     using Tiles = BlkTiles<kLeadQK, D, M, T, kStrided>;
     static constexpr int PV = Tiles::PV, PS = is_bf16<T> ? 1 : 3, NT = M / 32, SD = D / 32;
+    static constexpr int PW = is_bf16<T> ? 2 : 3;      // scores: a block's own part of the output is twice as long as
+                                                       // a 16-token chunk's
     static constexpr bool kPair = is_bf16<T> && NT == 2;
     using OutTile = OutRows<T, NT>;
     const Tiles &tl;
@@ -550,7 +552,7 @@ struct FwdOut : BlkLane {
             read_toks<D, PS>(ss, M * D, col_of<kPair>(h * NT + y, c), g, st);
             out[y] = dot(st, qs, zero4);
         }
-        const Op<PS> wop[1] = {op_of<PS>(w0, w1)};
+        const Op<PW> wop[1] = {op_of<PW>(w0, w1)};
 #pragma unroll
         for (int y = 0; y < NT; ++y) {
             const Op<PV> vf[1] = {read_feat<M, PV, kPair>(tl.sv, kBlk * M, 0, h * NT + y, lane)};
