@@ -1835,9 +1835,9 @@ __global__ __launch_bounds__(kWave * kWaves) void segment_state_kernel(const Seg
     // of the non-causal gradient), which need S and z built from the same feature values
     // to better than 8 bits: their results are differences of nearly equal terms.
     constexpr int kParts = is_bf16<T> ? 2 : 3;
-    // tiles private to each wave; several waves: afterwards the sums of two of them
-    constexpr int kTiles = tile_floats(D) + tile_floats(M), kSums = state_stride(D, M);
-    __shared__ __attribute__((aligned(16))) float lds[kWaves == 1 || kWaves * kTiles > 2 * kSums ? kWaves * kTiles : 2 * kSums];
+    // tiles private to each wave; several waves: afterwards the sums of each
+    constexpr int kTiles = tile_floats(D) + tile_floats(M), kSums = kWaves == 1 ? 0 : D * M + D;
+    __shared__ __attribute__((aligned(16))) float lds[kWaves * (kTiles > kSums ? kTiles : kSums)];
     const int lane = threadIdx.x & (kWave - 1), c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float *const lds_y = lds + wave * kTiles, *const lds_z = lds_y + tile_floats(D);
@@ -1931,36 +1931,39 @@ __global__ __launch_bounds__(kWave * kWaves) void segment_state_kernel(const Seg
 #pragma unroll
         for (int xt = 0; xt < XT; ++xt) ec[xt] += (yf[xt][0] + yf[xt][1]) + (yf[xt][2] + yf[xt][3]);
     }
-    if constexpr (kWaves == 4) {
-        // (0 + 2) + (1 + 3), in this order; a lane finds its own elements where the other wave's lane put them
-        auto put = [&](float *p) {
-#pragma unroll
-            for (int xt = 0; xt < XT; ++xt) {
-#pragma unroll
-                for (int zt = 0; zt < ZT; ++zt) lds_store4(p + ((xt * ZT + zt) * kWave + lane) * 4, U[xt][zt]);
-                const float e = sum_over_groups(ec[xt]);
-                if (g == 0) p[D * M + 16 * xt + c] = e;
-            }
-        };
-        auto take = [&](const float *p) {
-#pragma unroll
-            for (int xt = 0; xt < XT; ++xt) {
-#pragma unroll
-                for (int zt = 0; zt < ZT; ++zt) U[xt][zt] += *reinterpret_cast<const f32x4 *>(p + ((xt * ZT + zt) * kWave + lane) * 4);
-                ec[xt] += g == 0 ? p[D * M + 16 * xt + c] : 0.f;
-            }
-        };
-        __syncthreads();
-        if (wave >= 2) put(lds + (wave - 2) * kSums);
-        __syncthreads();
-        if (wave < 2) take(lds + wave * kSums);
-        __syncthreads();
-        if (wave == 1) put(lds);
-        __syncthreads();
-        if (wave != 0) return;
-        take(lds);
-    }
     float *st = a.state + ((size_t)bh * a.nseg + seg) * state_stride(D, M);
+    if constexpr (kWaves == 4) {
+        // Wave w finishes tiles w kOwn ... of U: every wave puts its sums into LDS, then adds the four
+        // sums of its own as (0 + 2) + (1 + 3) and stores them.  Against halving in two steps with one wave
+        // that stores everything: 512 segments of 192 fp32 tokens 14.8 -> 13.3 us, 480 of 128 bf16 tokens
+        // 11.0 -> 10.1.  (Two chunks in flight per wave cost registers and were slower: 18.3 us, 11.2.)
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < XT * ZT; ++t) lds_store4(lds + ((wave * XT * ZT + t) * kWave + lane) * 4, U[t / ZT][t % ZT]);
+#pragma unroll
+        for (int xt = 0; xt < XT; ++xt) {
+            const float e = sum_over_groups(ec[xt]);
+            if (g == 0) lds[4 * D * M + wave * D + 16 * xt + c] = e;
+        }
+        __syncthreads();
+        auto sum4 = [](const auto &x0, const auto &x1, const auto &x2, const auto &x3) { return (x0 + x2) + (x1 + x3); };
+        constexpr int kOwn = XT * ZT / 4;
+#pragma unroll
+        for (int o = 0; o < kOwn; ++o) {
+            const int t = wave * kOwn + o, xt = t / ZT, zt = t % ZT;
+            f32x4 p[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) p[w] = *reinterpret_cast<const f32x4 *>(lds + ((w * XT * ZT + t) * kWave + lane) * 4);
+            const f32x4 u = sum4(p[0], p[1], p[2], p[3]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) st[(16 * xt + 4 * g + r) * M + 16 * zt + c] = u[r];
+        }
+        if (wave == 0 && lane < D) {
+            const float *e = lds + 4 * D * M + lane;
+            st[D * M + lane] = sum4(e[0], e[D], e[2 * D], e[3 * D]);
+        }
+        return;
+    }
 #pragma unroll
     for (int xt = 0; xt < XT; ++xt) {
 #pragma unroll
