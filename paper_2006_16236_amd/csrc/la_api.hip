@@ -139,8 +139,16 @@ size_t states_bytes(long BH, const Plan &p, int D, int M) {
 // so the line lies at 512 tokens per segment (fp32 with D = M = 64, bf16 with a 64-wide head dimension) or
 // 256.  Above it bf16 tensors with a 64-wide head dimension keep the wave kernel in the forward only
 // (114/158 us at 16 x 65536, backward 476/396).
+// Short segments: where one workgroup per CU does with at most eight chunks each (ten for one segment per
+// sequence, four where a sequence has more than four segments), two per CU gain nothing and double the
+// states.  Two / one per CU in us (B*H x N, D = M = 64):
+//   fp32 forward  40 x 256  20.7/13.1   64 x 512  27.5/19.3   step  160 x 128  52.0/38.2   64 x 480  64.6/52.4
+//   bf16 forward  40 x 256  18.7/11.5   110 x 128  15.0/10.5  step  160 x 128  43.6/25.3   64 x 480  54.4/38.1
+// (96 x 300 in ten chunks, 32-wide heads: step 27.1/30.1; 80 x 384, D = 64, M = 32: step 37.6/40.3.)  Up to 64
+// tokens one segment does (forward of one sequence, D = M = 32 6.3/3.9 us, bf16 7.6/4.9; the step of fp32 tensors
+// with D = 64, M = 32 17.2/17.8: those only when the batch fills a quarter of the CUs).
 // Sequences are left whole from 512 on (256 if they are short: 256 x 512 136 us, 128 x 1024 in
-// four pieces 135, 256 x 128 40, 128 x 256 53).  Whole sequences, each kernel by what fills the machine
+// four pieces 135).  Whole sequences, each kernel by what fills the machine
 // (fp32 D = M = 64, forward / dQ / dV+dK in us):
 //   1024 x 1024  wave 334 / 285 / 317   workgroup 235 / 354 / 358
 //   2048 x 512   wave 208 / 348 / 402   workgroup 252 / 350 / 356
@@ -157,12 +165,20 @@ Plan causal_plan(long BH, int N, int C, int M, la_dtype t) {
     const bool bf16 = esize(t) == 2, narrow = C == 32 && M == 32;
     const int longest = (bf16 ? !narrow : C == 64 && M == 64) ? 512 : 256;     // tokens per segment
     Plan p = wave;
+    // p.cps: at least make_plan's, so that there are never more segments than its
+    auto at_least = [&](long chunks) { if (p.cps < chunks) p.cps = (int)chunks; };
     const long want = (target + BH - 1) / BH;
-    long maxseg = p.nchunks / min_chunks;
-    if (maxseg < 1) maxseg = 1;
-    long nseg = want > maxseg ? maxseg : want;
-    if (2 * BH >= target && N <= 512) nseg = 1;
-    p.cps = (int)((p.nchunks + nseg - 1) / nseg);
+    at_least((p.nchunks + want - 1) / want);
+    at_least(min_chunks);
+    const long per_cu = target / (2 * BH);                  // segments a sequence may have at one per CU
+    if (per_cu > 0) {
+        const long chunks = (p.nchunks + per_cu - 1) / per_cu;
+        const bool fills = 8 * BH * per_cu > 3 * target;    // more than three quarters of the CUs
+        const int limit = per_cu > 4 ? 4 : per_cu == 1 && 8 * BH >= 3 * target ? 10 : bf16 || fills || per_cu == 1 ? 8 : 4;
+        if (chunks <= limit) at_least(chunks);
+    }
+    const bool shortest = N <= 64 && (bf16 || C == 32 || 8 * BH >= target);
+    if (shortest || (2 * BH >= target && N <= 512) || p.cps > p.nchunks) p.cps = p.nchunks;
     p.cps += p.cps & 1;
     p.nseg = (p.nchunks + p.cps - 1) / p.cps;
     p.fold = p.nseg > 1 && p.nseg <= tn.fold_max;
