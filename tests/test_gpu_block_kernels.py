@@ -122,3 +122,27 @@ def test_non_temporal_loads_change_no_bit(monkeypatch):
     la.la_tuning_reload()
     for x, y in zip((*a[0], a[1]), (*b[0], b[1])):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("BH,N,D,M", [(1, 64, 32, 32), (3, 64, 64, 64), (3, 65, 64, 64), (40, 250, 32, 32), (16, 784, 32, 64),
+                                      (96, 160, 64, 32), (128, 113, 32, 32), (200, 160, 32, 32), (200, 161, 32, 32)])
+def test_short_sequences_and_their_workspaces(oracle, BH, N, D, M, bf16):
+    """The default cut of short sequences at both sides of its lines; workspaces of exactly the size the
+    queries name, followed by a mark that has to stay."""
+    import paper_2006_16236_amd as la
+    host = maybe_bf16(wl.random_case(8300 + N + BH, 1, BH, N, D, M), bf16)
+    q, k, v, g = (to_dev(x, bf16) for x in host)
+    code = la.LA_BF16 if bf16 else la.LA_F32
+    sizes = [max(16, f(1, BH, N, D, M, code)) for f in (la.la_causal_fwd_workspace, la.la_causal_bwd_workspace)]
+    bufs = [torch.full((n + 4096,), 0xA5, dtype=torch.uint8, device=DEV) for n in sizes]
+    fws, bws = (b[:n] for b, n in zip(bufs, sizes))
+    O, den = torch.empty_like(v), torch.empty(1, BH, N, device=DEV)
+    grads = [torch.empty_like(x) for x in (q, k, v)]
+    la.la_causal_fwd(q, k, v, O, den, 1e-6, ws=fws)
+    la.la_causal_bwd(q, k, v, None, den, g, *grads, 1e-6, ws=bws, fwd_ws=fws)
+    torch.cuda.synchronize()
+    assert all(bool((b[n:] == 0xA5).all()) for b, n in zip(bufs, sizes))
+    assert rel_err(to_host(O), oracle.causal_fwd_prefix(*host[:3], 1e-6)) <= (2e-2 if bf16 else 1e-5)
+    errs = grad_errs([to_host(x) for x in grads], oracle.causal_bwd_linear(*host, 1e-6))
+    assert max(errs) <= (2e-2 if bf16 else 1e-4), errs
