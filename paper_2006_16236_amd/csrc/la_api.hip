@@ -11,24 +11,14 @@
 
 #include "../../include/la.h"
 #include "la_launch.h"
+#include "la_plan.h"
 
 namespace {
 
-constexpr int kVersion = 401;   // 0.4.1
+using namespace la_plan;
+static_assert(kChunk == la::kChunk && state_stride(32, 64) == la::state_stride(32, 64), "la_plan.h and the kernels");
 
-// ---- schedule ---------------------------------------------------------------------------------
-// One wavefront (forward) or one two-wave workgroup (backward) walks one segment of one
-// sequence.  MI355X holds 256 CUs x 4 SIMDs x 2 such waves; a sequence is cut into segments
-// only as far as needed to reach that many waves, never into segments shorter than a couple of
-// chunks, and not at all once the sequences alone fill half the machine.
-struct Plan {
-    int nchunks, nseg, cps;
-    bool fold;      // few segments per sequence: no scan launch, every pass adds up the
-                    // segment totals before (after) its own segment itself
-    bool fwd_block; // the forward (and its segment sums) by the workgroup kernels of la_block.h
-    bool bwd_block; // the causal backward
-    int bwd_group;  // how many of the forward's segments a workgroup of the backward takes
-};
+constexpr int kVersion = 401;   // 0.4.1
 
 int env_int(const char *name, int dflt) {
     const char *s = getenv(name);
@@ -36,18 +26,6 @@ int env_int(const char *name, int dflt) {
     const long v = strtol(s, nullptr, 10);
     return v > 0 && v < (1 << 24) ? (int)v : dflt;
 }
-
-// The schedule's knobs.  The environment is read once, at the first call that needs a value (and
-// again only on la_tuning_reload): a workspace query and the calls that use the workspace then see
-// the same values, and no entry point calls getenv while another thread changes the environment.
-struct Tuning {
-    int target_waves;   // LA_TARGET_WAVES
-    int min_chunks;     // LA_MIN_SEG_CHUNKS
-    int fold_max;       // LA_FOLD_MAX_SEGS
-    int bwd_group;      // LA_BWD_SEG_GROUP, 0 = by head size
-    int stream;         // LA_STREAM_LOADS: 0, 1, or -1 = by tensor size
-    int block;          // LA_BLOCK_KERNELS: 0 never, 1 wherever they exist, or -1 = by size
-};
 
 std::mutex g_tuning_mu;
 Tuning g_tuning;
@@ -66,6 +44,8 @@ Tuning read_tuning() {
     return t;
 }
 
+// Every entry point takes one snapshot: its plan, the workspace it asks for and where it carves it must agree
+// whatever la_tuning_reload does on another thread meanwhile.
 Tuning tuning() {
     std::lock_guard<std::mutex> lock(g_tuning_mu);
     if (!g_tuning_read) {
@@ -73,138 +53,6 @@ Tuning tuning() {
         g_tuning_read = true;
     }
     return g_tuning;
-}
-
-Plan make_plan(long BH, int N) {
-    const Tuning tn = tuning();
-    const int target_waves = tn.target_waves;
-    const int min_chunks = tn.min_chunks;
-    Plan p;
-    p.nchunks = (N + la::kChunk - 1) / la::kChunk;
-    long want = (target_waves + BH - 1) / BH;
-    long maxseg = p.nchunks / min_chunks;
-    if (maxseg < 1) maxseg = 1;
-    long nseg = want < 1 ? 1 : (want > maxseg ? maxseg : want);
-    // Cutting costs a second sweep over K, V (and Q, dO) plus the scan: measured on MI355X it
-    // pays from four segments per sequence on; with half the target already there, don't cut.
-    if (2 * BH >= target_waves) nseg = 1;
-    p.cps = (int)((p.nchunks + nseg - 1) / nseg);
-    p.nseg = (p.nchunks + p.cps - 1) / p.cps;
-    p.fold = p.nseg > 1 && p.nseg <= tn.fold_max;
-    p.fwd_block = p.bwd_block = false;
-    p.bwd_group = 0;      // see backward_group
-    return p;
-}
-
-// How many of the forward's segments one workgroup of the backward takes.  The backward's kernels
-// run two waves per workgroup; with a 64-wide head dimension they need so many registers that
-// two waves fill a SIMD, half as many workgroups fill the machine, and taking the segments in
-// pairs is 10 % faster.  At D = M = 32 four waves fit a SIMD and the finer cut wins.
-int backward_group(int C, int M) {
-    const int g = tuning().bwd_group;
-    if (g == 0) return (C == 32 && M == 32) ? 1 : 2;
-    return g == 1 ? 1 : 2;
-}
-
-// Whether a call fetches its tiles with non-temporal loads.  A step sweeps Q, K, V (and dO) several
-// times, one kernel after the other.  Where those tensors fit the last-level cache (256 MB) the
-// later sweeps find them there if the loads are plain (measured: MNIST / CIFAR shapes 2 % and 9 %
-// faster than with non-temporal loads); where they do not, the two kinds are equally fast for fp32
-// tensors and plain loads 1.5 % faster for bf16 ones (N = 65536).  So plain loads are the default
-// and LA_STREAM_LOADS=1 is there for measuring.  (The outputs are always stored non-temporally and
-// the segment states always loaded plain.)
-int stream_loads() {
-    return tuning().stream == 1 ? 1 : 0;
-}
-
-size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-
-size_t esize(la_dtype t) { return (t == LA_BF16 || t == LA_BF16_FEATURES) ? 2 : 4; }
-
-size_t states_bytes(long BH, const Plan &p, int D, int M) {
-    return align256((size_t)BH * p.nseg * la::state_stride(D, M) * sizeof(float));
-}
-
-// The plan of a causal call: which kernels, and the cut that suits them.  The workgroup kernels
-// (la_block.h) put four or eight waves on a segment, so a quarter as many segments fill the machine
-// (512 workgroups, two per CU), in whole 32-token blocks: fewer, longer segments, hence less state to
-// write, scan and read.  The wave kernels (la_passes.h) have the shorter chain per token and win
-// where segments are long.  Measured on MI355X, step times wave / workgroup kernels in us (B*H x N):
-//   fp32, D = M = 64   16 x 65536  1051/1099   16 x 16384  274/270   16 x 8192  165/150   16 x 2048  83/60
-//   bf16, D = M = 64   16 x 65536   672/637    16 x 16384  194/159   16 x 8192  122/96    16 x 2048  67/47
-//   fp32, D = M = 32   16 x 65536   460/489    16 x 16384  122/120   16 x 8192   77/71    16 x 2048  38/37
-//   bf16, D = M = 32   16 x 65536   302/332    16 x 16384   91/88    16 x 8192   61/55    16 x 2048  40/38
-//   fp32, 64 x 32      16 x 65536   734/800    16 x 16384  183/194   16 x 8192  111/110
-//   fp32, 32 x 64      16 x 65536   703/735    16 x 16384  174/178   16 x 8192  108/100
-// so the line lies at 512 tokens per segment (fp32 with D = M = 64, bf16 with a 64-wide head dimension) or
-// 256.  Above it bf16 tensors with a 64-wide head dimension keep the wave kernel in the forward only
-// (114/158 us at 16 x 65536, backward 476/396).
-// Short segments: where one workgroup per CU does with at most eight chunks each (ten for one segment per
-// sequence, four where a sequence has more than four segments), two per CU gain nothing and double the
-// states.  Two / one per CU in us (B*H x N, D = M = 64):
-//   fp32 forward  40 x 256  20.7/13.1   64 x 512  27.5/19.3   step  160 x 128  52.0/38.2   64 x 480  64.6/52.4
-//   bf16 forward  40 x 256  18.7/11.5   110 x 128  15.0/10.5  step  160 x 128  43.6/25.3   64 x 480  54.4/38.1
-// (96 x 300 in ten chunks, 32-wide heads: step 27.1/30.1; 80 x 384, D = 64, M = 32: step 37.6/40.3.)  Up to 64
-// tokens one segment does (forward of one sequence, D = M = 32 6.3/3.9 us, bf16 7.6/4.9; the step of fp32 tensors
-// with D = 64, M = 32 17.2/17.8: those only when the batch fills a quarter of the CUs).
-// Sequences are left whole from 512 on (256 if they are short: 256 x 512 136 us, 128 x 1024 in
-// four pieces 135).  Whole sequences, each kernel by what fills the machine
-// (fp32 D = M = 64, forward / dQ / dV+dK in us):
-//   1024 x 1024  wave 334 / 285 / 317   workgroup 235 / 354 / 358
-//   2048 x 512   wave 208 / 348 / 402   workgroup 252 / 350 / 356
-//   2048 x 512, D = M = 32   wave 113 / 135 / 144   workgroup 110 / 162 / 158
-// It never has more segments than make_plan's, which size the workspaces.
-// (The polynomial map is cut like fp32 tensors of 64 features.)
-Plan causal_plan(long BH, int N, int C, int M, la_dtype t) {
-    const Tuning tn = tuning();
-    Plan wave = make_plan(BH, N);
-    wave.bwd_group = backward_group(C, M);
-    if (tn.block == 0) return wave;
-    const long target = tn.target_waves >= 4 ? tn.target_waves / 4 : 1;
-    const long min_chunks = tn.min_chunks > 2 ? tn.min_chunks : 2;
-    const bool bf16 = esize(t) == 2, narrow = C == 32 && M == 32;
-    const int longest = (bf16 ? !narrow : C == 64 && M == 64) ? 512 : 256;     // tokens per segment
-    Plan p = wave;
-    // p.cps: at least make_plan's, so that there are never more segments than its
-    auto at_least = [&](long chunks) { if (p.cps < chunks) p.cps = (int)chunks; };
-    const long want = (target + BH - 1) / BH;
-    at_least((p.nchunks + want - 1) / want);
-    at_least(min_chunks);
-    const long per_cu = target / (2 * BH);                  // segments a sequence may have at one per CU
-    if (per_cu > 0) {
-        const long chunks = (p.nchunks + per_cu - 1) / per_cu;
-        const bool fills = 8 * BH * per_cu > 3 * target;    // more than three quarters of the CUs
-        const int limit = per_cu > 4 ? 4 : per_cu == 1 && 8 * BH >= 3 * target ? 10 : bf16 || fills || per_cu == 1 ? 8 : 4;
-        if (chunks <= limit) at_least(chunks);
-    }
-    const bool shortest = N <= 64 && (bf16 || C == 32 || 8 * BH >= target);
-    if (shortest || (2 * BH >= target && N <= 512) || p.cps > p.nchunks) p.cps = p.nchunks;
-    p.cps += p.cps & 1;
-    p.nseg = (p.nchunks + p.cps - 1) / p.cps;
-    p.fold = p.nseg > 1 && p.nseg <= tn.fold_max;
-    p.fwd_block = p.bwd_block = true;
-    p.bwd_group = tn.bwd_group == 2 ? 2 : 1;
-    if (tn.block == 1) return p;
-    if (p.nseg > 1) {
-        if (p.cps * la::kChunk <= longest) return p;
-        if (bf16 && !narrow) {
-            wave.bwd_block = true;
-            wave.bwd_group = tn.bwd_group != 0 ? 2 : 4;
-        }
-        return wave;
-    }
-    // whole sequences: one wave per sequence (forward) fills three quarters of the machine from 1536 on,
-    // two waves per sequence (backward) nearly all of it at 1024
-    p.fwd_block = 4 * BH < 3 * (long)tn.target_waves;
-    const bool one_round = 16 * BH >= 7 * (long)tn.target_waves && 2 * BH <= tn.target_waves;
-    p.bwd_block = bf16 || !(one_round || (C == 32 && 2 * BH > tn.target_waves));
-    return p;
-}
-
-// What a causal call asks its caller for: the states of make_plan's segments
-size_t causal_states_bytes(long BH, int N, int C, int M) {
-    const Plan p = make_plan(BH, N);
-    return p.nseg > 1 ? states_bytes(BH, p, C, M) : 0;
 }
 
 // Feature width C of Q and K inside the kernels: D itself, or D^2 for the degree-2 polynomial
@@ -351,10 +199,9 @@ int run_causal_fwd(const void *Q, const void *K, const void *V, void *O, float *
                    hipStream_t s, const float *S0 = nullptr, const float *z0 = nullptr,
                    float *S1 = nullptr, float *z1 = nullptr, int heads = 0, int tok_heads = 0) {
     const int nblocks = (int)(BH * p.nseg);
-    const int nt_loads = stream_loads();
     if (p.nseg > 1) {
         la::SegArgs sa{};
-        sa.stream = nt_loads;
+        sa.stream = p.nt_loads;
         sa.Y = K; sa.Z = V; sa.state = states;
         sa.N = N; sa.nseg = p.nseg; sa.chunks_per_seg = p.cps; sa.skip_seg = p.nseg - 1;
         sa.heads = heads; sa.tok_heads = tok_heads;
@@ -364,7 +211,7 @@ int run_causal_fwd(const void *Q, const void *K, const void *V, void *O, float *
     }
     const bool scanned = p.nseg > 1 && !p.fold;      // the scan has added the caller's state already
     la::PassArgs a{};
-    a.stream = nt_loads;
+    a.stream = p.nt_loads;
     a.heads = heads; a.tok_heads = tok_heads;
     a.Q = Q; a.K = K; a.V = V; a.G = nullptr; a.rden = nullptr; a.delta = nullptr;
     a.out = O; a.den = den; a.state = p.nseg > 1 ? states : nullptr; a.fold = p.fold;
@@ -379,9 +226,8 @@ int run_global_fwd(const void *Q, const void *K, const void *V, void *O, float *
                    int N, int D, int M, float eps, la_dtype t, const Plan &p, float *states,
                    hipStream_t s, int heads = 0, int tok_heads = 0) {
     const int nblocks = (int)(BH * p.nseg);
-    const int nt_loads = stream_loads();
     la::SegArgs sa{};
-    sa.stream = nt_loads;
+    sa.stream = p.nt_loads;
     sa.heads = heads; sa.tok_heads = tok_heads;
     sa.Y = K; sa.Z = V; sa.state = states;
     sa.N = N; sa.nseg = p.nseg; sa.chunks_per_seg = p.cps; sa.skip_seg = -1;
@@ -389,7 +235,7 @@ int run_global_fwd(const void *Q, const void *K, const void *V, void *O, float *
     if (p.nseg > 1 && !p.fold)
         { ProfScope ps(LA_K_SCAN, s); LA_TRY(la::launch_scan(states, (int)BH, p.nseg, la::state_stride(D, M), la::kScanTotal, s)); }
     la::PassArgs a{};
-    a.stream = nt_loads;
+    a.stream = p.nt_loads;
     a.heads = heads; a.tok_heads = tok_heads;
     a.Q = Q; a.K = K; a.V = V; a.out = O; a.den = den; a.state = states; a.fold = p.fold;
     a.N = N; a.nseg = p.nseg; a.chunks_per_seg = p.cps; a.eps = eps;
@@ -428,38 +274,24 @@ size_t la_causal_fwd_workspace(int B, int H, int N, int D, int M, la_dtype t) {
     if (check_dims(B, H, N, D, M, 0.0f, t) != LA_OK) return 0;
     const int C = feat_width(D, t);
     const long BH = (long)B * H;
-    return causal_states_bytes(BH, N, C, M);
+    return causal_states_bytes(tuning(), BH, N, C, M);
 }
 
 size_t la_causal_bwd_workspace(int B, int H, int N, int D, int M, la_dtype t) {
     if (check_dims(B, H, N, D, M, 0.0f, t) != LA_OK) return 0;
-    const int C = feat_width(D, t);
-    const long BH = (long)B * H;
-    const Plan p = make_plan(BH, N);
-    const size_t rows = (size_t)BH * N;
-    size_t bytes = 3 * align256(rows * sizeof(float));      // 1/den, delta, and den if it is recomputed
-    if (p.nseg > 1) bytes += 2 * states_bytes(BH, p, C, M); // S and R states
-    (void)t;
-    return bytes;
+    return causal_bwd_bytes(tuning(), (long)B * H, N, feat_width(D, t), M);
 }
 
 size_t la_global_fwd_workspace(int B, int H, int N, int D, int M, la_dtype t) {
     if (check_dims(B, H, N, D, M, 0.0f, t) != LA_OK) return 0;
     const int C = feat_width(D, t);
     const long BH = (long)B * H;
-    return states_bytes(BH, make_plan(BH, N), C, M);
+    return states_bytes(BH, make_plan(tuning(), BH, N), C, M);
 }
 
 size_t la_global_bwd_workspace(int B, int H, int N, int D, int M, la_dtype t) {
     if (check_dims(B, H, N, D, M, 0.0f, t) != LA_OK) return 0;
-    const int C = feat_width(D, t);
-    const long BH = (long)B * H;
-    const Plan p = make_plan(BH, N);
-    const size_t rows = (size_t)BH * N;
-    size_t bytes = 2 * states_bytes(BH, p, C, M);           // the two grand totals
-    bytes += align256(rows * sizeof(float));                // den if it is recomputed
-    (void)t;
-    return bytes;
+    return global_bwd_bytes(tuning(), (long)B * H, N, feat_width(D, t), M);
 }
 
 static int causal_fwd_impl(const void *Q, const void *K, const void *V, void *O, float *den,
@@ -472,8 +304,9 @@ static int causal_fwd_impl(const void *Q, const void *K, const void *V, void *O,
     if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(O) || misaligned(ws))
         return LA_ERR_ALIGN;
     const long BH = (long)B * H;
-    const Plan p = causal_plan(BH, N, C, M, t);
-    const size_t need = causal_states_bytes(BH, N, C, M);
+    const Tuning tn = tuning();
+    const Plan p = causal_plan(tn, BH, N, C, M, t);
+    const size_t need = causal_states_bytes(tn, BH, N, C, M);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return LA_ERR_WORKSPACE;
     const size_t rows = (size_t)BH * N, e = esize(t);
     const Span outs[] = {{O, rows * M * e}, {den, rows * 4}, {ws, need}};
@@ -505,8 +338,9 @@ int la_causal_fwd_noalloc(const void *Q, const void *K, const void *V, void *O, 
     const int C = feat_width(D, t);
     if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(O)) return LA_ERR_ALIGN;
     const long BH = (long)B * H;
-    const Plan p = causal_plan(BH, N, C, M, t);
-    const size_t need = causal_states_bytes(BH, N, C, M);
+    const Tuning tn = tuning();
+    const Plan p = causal_plan(tn, BH, N, C, M, t);
+    const size_t need = causal_states_bytes(tn, BH, N, C, M);
     if (need > kScratchBytes) return LA_ERR_SCRATCH;
     const size_t rows = (size_t)BH * N, e = esize(t);
     const Span outs[] = {{O, rows * M * e}, {den, rows * 4}};
@@ -536,8 +370,9 @@ static int causal_fwd_state_impl(const void *Q, const void *K, const void *V, co
         misaligned(S0) || misaligned(z0) || misaligned(S1) || misaligned(z1))
         return LA_ERR_ALIGN;
     const long BH = (long)B * H;
-    const Plan p = causal_plan(BH, N, C, M, t);
-    const size_t need = causal_states_bytes(BH, N, C, M);
+    const Tuning tn = tuning();
+    const Plan p = causal_plan(tn, BH, N, C, M, t);
+    const size_t need = causal_states_bytes(tn, BH, N, C, M);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return LA_ERR_WORKSPACE;
     const size_t rows = (size_t)BH * N, e = esize(t);
     const Span outs[] = {{O, rows * M * e}, {den, rows * 4}, {ws, need},
@@ -585,12 +420,13 @@ static int causal_bwd_impl(const void *Q, const void *K, const void *V, const fl
         misaligned(fwd_ws) || misaligned(S0) || misaligned(z0) || misaligned(dS1) ||
         misaligned(dz1) || misaligned(dS0) || misaligned(dz0))
         return LA_ERR_ALIGN;
-    const size_t need = la_causal_bwd_workspace(B, H, N, D, M, t);
+    const long BH = (long)B * H;
+    const Tuning tn = tuning();
+    const size_t need = causal_bwd_bytes(tn, BH, N, C, M);
     if (ws == nullptr || ws_bytes < need) return LA_ERR_WORKSPACE;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const long BH = (long)B * H;
-    const Plan p = causal_plan(BH, N, C, M, t);
+    const Plan p = causal_plan(tn, BH, N, C, M, t);
     const size_t rows = (size_t)BH * N;
     {
         const size_t e = esize(t), sb = (size_t)BH * C * M * 4, zb = (size_t)BH * C * 4;
@@ -598,10 +434,9 @@ static int causal_bwd_impl(const void *Q, const void *K, const void *V, const fl
                              {ws, need}, {dS0, sb}, {dz0, zb}};
         const Span ins[] = {{Q, rows * D * e}, {K, rows * D * e}, {V, rows * M * e},
                             {dO, rows * M * e}, {den, rows * 4}, {S0, sb}, {z0, zb}, {dS1, sb},
-                            {dz1, zb}, {fwd_ws, causal_states_bytes(BH, N, C, M)}};
+                            {dz1, zb}, {fwd_ws, causal_states_bytes(tn, BH, N, C, M)}};
         if (aliased(outs, ins)) return LA_ERR_ALIAS;
     }
-    const int nt_loads = stream_loads();
     Carver cv{static_cast<char *>(ws), 0};
     float *rden = static_cast<float *>(cv.take(rows * sizeof(float)));
     float *delta = static_cast<float *>(cv.take(rows * sizeof(float)));
@@ -626,7 +461,7 @@ static int causal_bwd_impl(const void *Q, const void *K, const void *V, const fl
     const int nblocks = (int)(BH * p.nseg);
     if (p.nseg > 1 && !have_states) {
         la::SegArgs sa{};
-        sa.stream = nt_loads;
+        sa.stream = p.nt_loads;
         sa.N = N; sa.nseg = p.nseg; sa.chunks_per_seg = p.cps;
         sa.Y = K; sa.Z = V; sa.state = stS;
         sa.skip_seg = p.nseg - 1;
@@ -649,7 +484,7 @@ static int causal_bwd_impl(const void *Q, const void *K, const void *V, const fl
     // forward direction: dQ; on the way 1/den and delta per token and, when the sequences
     // are cut, the per-segment sums that the reverse direction starts from
     la::PassArgs a{};
-    a.stream = nt_loads;
+    a.stream = p.nt_loads;
     a.heads = H; a.tok_heads = tok_heads;
     a.Q = Q; a.K = K; a.V = V; a.G = dO; a.rden = rden; a.delta = delta; a.den = nullptr;
     a.den_in = den; a.rden_out = rden; a.delta_out = delta; a.totals = pb.nseg > 1 ? stR : nullptr;
@@ -716,7 +551,7 @@ static int global_fwd_impl(const void *Q, const void *K, const void *V, void *O,
         misaligned(den))
         return LA_ERR_ALIGN;
     const long BH = (long)B * H;
-    const Plan p = make_plan(BH, N);
+    const Plan p = make_plan(tuning(), BH, N);
     if (ws == nullptr || ws_bytes < states_bytes(BH, p, C, M)) return LA_ERR_WORKSPACE;
     const size_t rows = (size_t)BH * N, e = esize(t);
     const Span outs[] = {{O, rows * M * e}, {den, rows * 4}, {ws, states_bytes(BH, p, C, M)}};
@@ -753,13 +588,14 @@ static int global_bwd_impl(const void *Q, const void *K, const void *V, const vo
         misaligned(dK) || misaligned(dV) || misaligned(O) || misaligned(den) || misaligned(ws) ||
         misaligned(fwd_ws))
         return LA_ERR_ALIGN;
-    const size_t need = la_global_bwd_workspace(B, H, N, D, M, t);
+    const long BH = (long)B * H;
+    const Tuning tn = tuning();
+    const size_t need = global_bwd_bytes(tn, BH, N, C, M);
     if (ws == nullptr || ws_bytes < need) return LA_ERR_WORKSPACE;
     (void)O;                                   // not read: delta is rebuilt from the read-out
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const long BH = (long)B * H;
-    const Plan p = make_plan(BH, N);
+    const Plan p = make_plan(tn, BH, N);
     const size_t rows = (size_t)BH * N;
     {
         const size_t e = esize(t);
@@ -768,7 +604,6 @@ static int global_bwd_impl(const void *Q, const void *K, const void *V, const vo
                             {dO, rows * M * e}, {den, rows * 4}, {fwd_ws, states_bytes(BH, p, C, M)}};
         if (aliased(outs, ins)) return LA_ERR_ALIAS;
     }
-    const int nt_loads = stream_loads();
     Carver cv{static_cast<char *>(ws), 0};
     float *stS = static_cast<float *>(cv.take(states_bytes(BH, p, C, M)));
     float *stR = static_cast<float *>(cv.take(states_bytes(BH, p, C, M)));
@@ -783,7 +618,7 @@ static int global_bwd_impl(const void *Q, const void *K, const void *V, const vo
         stS = const_cast<float *>(static_cast<const float *>(fwd_ws));
     } else {
         la::SegArgs sa{};
-        sa.stream = nt_loads;
+        sa.stream = p.nt_loads;
         sa.heads = H; sa.tok_heads = tok_heads;
         sa.N = N; sa.nseg = p.nseg; sa.chunks_per_seg = p.cps; sa.skip_seg = -1;
         sa.Y = K; sa.Z = V; sa.state = stS;
@@ -795,11 +630,11 @@ static int global_bwd_impl(const void *Q, const void *K, const void *V, const vo
     // waves per workgroup: it takes the segments in pairs (see the causal backward).
     Plan pb = p;
     if (p.nseg > 1) {
-        pb.cps = backward_group(C, M) * p.cps;
+        pb.cps = backward_group(tn, C, M) * p.cps;
         pb.nseg = (p.nchunks + pb.cps - 1) / pb.cps;
     }
     la::PassArgs a{};
-    a.stream = nt_loads;
+    a.stream = p.nt_loads;
     a.heads = H; a.tok_heads = tok_heads;
     a.Q = Q; a.K = K; a.V = V; a.G = dO; a.den_in = den; a.totals = stR;
     a.N = N; a.nseg = pb.nseg; a.chunks_per_seg = pb.cps; a.eps = eps;

@@ -1,0 +1,179 @@
+// Host side of the segment schedule: how a call cuts its sequences, which kernels take the pieces, and the
+// workspace that follows from it.  Plain C++ without a GPU header; every function takes the tuning values as an
+// argument, so that a call works from one snapshot of them.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include "../../include/la.h"
+
+namespace la_plan {
+
+constexpr int kChunk = 16;                                        // tokens per chunk (la_device.h)
+constexpr int state_stride(int D, int M) { return D * M + D; }    // floats per state (la_passes.h)
+
+// ---- schedule ---------------------------------------------------------------------------------
+// One wavefront (forward) or one two-wave workgroup (backward) walks one segment of one
+// sequence.  MI355X holds 256 CUs x 4 SIMDs x 2 such waves; a sequence is cut into segments
+// only as far as needed to reach that many waves, never into segments shorter than a couple of
+// chunks, and not at all once the sequences alone fill half the machine.
+struct Plan {
+    int nchunks, nseg, cps;
+    bool fold;      // few segments per sequence: no scan launch, every pass adds up the
+                    // segment totals before (after) its own segment itself
+    bool fwd_block; // the forward (and its segment sums) by the workgroup kernels of la_block.h
+    bool bwd_block; // the causal backward
+    int bwd_group;  // how many of the forward's segments a workgroup of the backward takes
+    // Whether the call fetches its tiles with non-temporal loads.  A step sweeps Q, K, V (and dO) several
+    // times, one kernel after the other.  Where those tensors fit the last-level cache (256 MB) the
+    // later sweeps find them there if the loads are plain (measured: MNIST / CIFAR shapes 2 % and 9 %
+    // faster than with non-temporal loads); where they do not, the two kinds are equally fast for fp32
+    // tensors and plain loads 1.5 % faster for bf16 ones (N = 65536).  So plain loads are the default
+    // and LA_STREAM_LOADS=1 is there for measuring.  (The outputs are always stored non-temporally and
+    // the segment states always loaded plain.)
+    int nt_loads;
+};
+
+// The schedule's knobs.  The environment is read once, at the first call that needs a value (and
+// again only on la_tuning_reload): a workspace query and the calls that use the workspace then see
+// the same values, and no entry point calls getenv while another thread changes the environment.
+struct Tuning {
+    int target_waves;   // LA_TARGET_WAVES
+    int min_chunks;     // LA_MIN_SEG_CHUNKS
+    int fold_max;       // LA_FOLD_MAX_SEGS
+    int bwd_group;      // LA_BWD_SEG_GROUP, 0 = by head size
+    int stream;         // LA_STREAM_LOADS: 0, 1, or -1 = by tensor size
+    int block;          // LA_BLOCK_KERNELS: 0 never, 1 wherever they exist, or -1 = by size
+};
+
+inline Plan make_plan(const Tuning &tn, long BH, int N) {
+    const int target_waves = tn.target_waves;
+    const int min_chunks = tn.min_chunks;
+    Plan p;
+    p.nchunks = (N + kChunk - 1) / kChunk;
+    long want = (target_waves + BH - 1) / BH;
+    long maxseg = p.nchunks / min_chunks;
+    if (maxseg < 1) maxseg = 1;
+    long nseg = want < 1 ? 1 : (want > maxseg ? maxseg : want);
+    // Cutting costs a second sweep over K, V (and Q, dO) plus the scan: measured on MI355X it
+    // pays from four segments per sequence on; with half the target already there, don't cut.
+    if (2 * BH >= target_waves) nseg = 1;
+    p.cps = (int)((p.nchunks + nseg - 1) / nseg);
+    p.nseg = (p.nchunks + p.cps - 1) / p.cps;
+    p.fold = p.nseg > 1 && p.nseg <= tn.fold_max;
+    p.nt_loads = tn.stream == 1 ? 1 : 0;
+    p.fwd_block = p.bwd_block = false;
+    p.bwd_group = 0;      // see backward_group
+    return p;
+}
+
+// How many of the forward's segments one workgroup of the backward takes.  The backward's kernels
+// run two waves per workgroup; with a 64-wide head dimension they need so many registers that
+// two waves fill a SIMD, half as many workgroups fill the machine, and taking the segments in
+// pairs is 10 % faster.  At D = M = 32 four waves fit a SIMD and the finer cut wins.
+inline int backward_group(const Tuning &tn, int C, int M) {
+    const int g = tn.bwd_group;
+    if (g == 0) return (C == 32 && M == 32) ? 1 : 2;
+    return g == 1 ? 1 : 2;
+}
+
+inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+inline size_t esize(la_dtype t) { return (t == LA_BF16 || t == LA_BF16_FEATURES) ? 2 : 4; }
+
+inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
+    return align256((size_t)BH * p.nseg * state_stride(D, M) * sizeof(float));
+}
+
+// The plan of a causal call: which kernels, and the cut that suits them.  The workgroup kernels
+// (la_block.h) put four or eight waves on a segment, so a quarter as many segments fill the machine
+// (512 workgroups, two per CU), in whole 32-token blocks: fewer, longer segments, hence less state to
+// write, scan and read.  The wave kernels (la_passes.h) have the shorter chain per token and win
+// where segments are long.  Measured on MI355X, step times wave / workgroup kernels in us (B*H x N):
+//   fp32, D = M = 64   16 x 65536  1051/1099   16 x 16384  274/270   16 x 8192  165/150   16 x 2048  83/60
+//   bf16, D = M = 64   16 x 65536   672/637    16 x 16384  194/159   16 x 8192  122/96    16 x 2048  67/47
+//   fp32, D = M = 32   16 x 65536   460/489    16 x 16384  122/120   16 x 8192   77/71    16 x 2048  38/37
+//   bf16, D = M = 32   16 x 65536   302/332    16 x 16384   91/88    16 x 8192   61/55    16 x 2048  40/38
+//   fp32, 64 x 32      16 x 65536   734/800    16 x 16384  183/194   16 x 8192  111/110
+//   fp32, 32 x 64      16 x 65536   703/735    16 x 16384  174/178   16 x 8192  108/100
+// so the line lies at 512 tokens per segment (fp32 with D = M = 64, bf16 with a 64-wide head dimension) or
+// 256.  Above it bf16 tensors with a 64-wide head dimension keep the wave kernel in the forward only
+// (114/158 us at 16 x 65536, backward 476/396).
+// Short segments: where one workgroup per CU does with at most eight chunks each (ten for one segment per
+// sequence, four where a sequence has more than four segments), two per CU gain nothing and double the
+// states.  Two / one per CU in us (B*H x N, D = M = 64):
+//   fp32 forward  40 x 256  20.7/13.1   64 x 512  27.5/19.3   step  160 x 128  52.0/38.2   64 x 480  64.6/52.4
+//   bf16 forward  40 x 256  18.7/11.5   110 x 128  15.0/10.5  step  160 x 128  43.6/25.3   64 x 480  54.4/38.1
+// (96 x 300 in ten chunks, 32-wide heads: step 27.1/30.1; 80 x 384, D = 64, M = 32: step 37.6/40.3.)  Up to 64
+// tokens one segment does (forward of one sequence, D = M = 32 6.3/3.9 us, bf16 7.6/4.9; the step of fp32 tensors
+// with D = 64, M = 32 17.2/17.8: those only when the batch fills a quarter of the CUs).
+// Sequences are left whole from 512 on (256 if they are short: 256 x 512 136 us, 128 x 1024 in
+// four pieces 135).  Whole sequences, each kernel by what fills the machine
+// (fp32 D = M = 64, forward / dQ / dV+dK in us):
+//   1024 x 1024  wave 334 / 285 / 317   workgroup 235 / 354 / 358
+//   2048 x 512   wave 208 / 348 / 402   workgroup 252 / 350 / 356
+//   2048 x 512, D = M = 32   wave 113 / 135 / 144   workgroup 110 / 162 / 158
+// It never has more segments than make_plan's, which size the workspaces.
+// (The polynomial map is cut like fp32 tensors of 64 features.)
+inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype t) {
+    Plan wave = make_plan(tn, BH, N);
+    wave.bwd_group = backward_group(tn, C, M);
+    if (tn.block == 0) return wave;
+    const long target = tn.target_waves >= 4 ? tn.target_waves / 4 : 1;
+    const long min_chunks = tn.min_chunks > 2 ? tn.min_chunks : 2;
+    const bool bf16 = esize(t) == 2, narrow = C == 32 && M == 32;
+    const int longest = (bf16 ? !narrow : C == 64 && M == 64) ? 512 : 256;     // tokens per segment
+    Plan p = wave;
+    // p.cps: at least make_plan's, so that there are never more segments than its
+    auto at_least = [&](long chunks) { if (p.cps < chunks) p.cps = (int)chunks; };
+    const long want = (target + BH - 1) / BH;
+    at_least((p.nchunks + want - 1) / want);
+    at_least(min_chunks);
+    const long per_cu = target / (2 * BH);                  // segments a sequence may have at one per CU
+    if (per_cu > 0) {
+        const long chunks = (p.nchunks + per_cu - 1) / per_cu;
+        const bool fills = 8 * BH * per_cu > 3 * target;    // more than three quarters of the CUs
+        const int limit = per_cu > 4 ? 4 : per_cu == 1 && 8 * BH >= 3 * target ? 10 : bf16 || fills || per_cu == 1 ? 8 : 4;
+        if (chunks <= limit) at_least(chunks);
+    }
+    const bool shortest = N <= 64 && (bf16 || C == 32 || 8 * BH >= target);
+    if (shortest || (2 * BH >= target && N <= 512) || p.cps > p.nchunks) p.cps = p.nchunks;
+    p.cps += p.cps & 1;
+    p.nseg = (p.nchunks + p.cps - 1) / p.cps;
+    p.fold = p.nseg > 1 && p.nseg <= tn.fold_max;
+    p.fwd_block = p.bwd_block = true;
+    p.bwd_group = tn.bwd_group == 2 ? 2 : 1;
+    if (tn.block == 1) return p;
+    if (p.nseg > 1) {
+        if (p.cps * kChunk <= longest) return p;
+        if (bf16 && !narrow) {
+            wave.bwd_block = true;
+            wave.bwd_group = tn.bwd_group != 0 ? 2 : 4;
+        }
+        return wave;
+    }
+    // whole sequences: one wave per sequence (forward) fills three quarters of the machine from 1536 on,
+    // two waves per sequence (backward) nearly all of it at 1024
+    p.fwd_block = 4 * BH < 3 * (long)tn.target_waves;
+    const bool one_round = 16 * BH >= 7 * (long)tn.target_waves && 2 * BH <= tn.target_waves;
+    p.bwd_block = bf16 || !(one_round || (C == 32 && 2 * BH > tn.target_waves));
+    return p;
+}
+
+// What a causal call asks its caller for: the states of make_plan's segments
+inline size_t causal_states_bytes(const Tuning &tn, long BH, int N, int C, int M) {
+    const Plan p = make_plan(tn, BH, N);
+    return p.nseg > 1 ? states_bytes(BH, p, C, M) : 0;
+}
+
+// ... and a backward: 1/den, delta, and den if it is recomputed; the S and R states
+inline size_t causal_bwd_bytes(const Tuning &tn, long BH, int N, int C, int M) {
+    return 3 * align256((size_t)BH * N * sizeof(float)) + 2 * causal_states_bytes(tn, BH, N, C, M);
+}
+// non-causal: the two grand totals; den if it is recomputed
+inline size_t global_bwd_bytes(const Tuning &tn, long BH, int N, int C, int M) {
+    return 2 * states_bytes(BH, make_plan(tn, BH, N), C, M) + align256((size_t)BH * N * sizeof(float));
+}
+
+}  // namespace la_plan

@@ -1,0 +1,63 @@
+"""The host side of the schedule (csrc/la_plan.h), without a GPU: plans, and the workspaces that have to
+hold what the plans write."""
+import os
+import random
+import re
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2006_16236_amd", "csrc")
+FIELDS = ("nchunks", "nseg", "cps", "fold", "fwd_block", "bwd_block", "bwd_group", "writes", "states", "bwd")
+DEFAULT = dict(target=2048, min_chunks=2, fold=8, group=0, block=-1)
+F32, BF16, POLY2 = 0, 1, 4
+
+
+@pytest.fixture(scope="session")
+def plans(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_probe")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", os.path.join(ROOT, "tests", "plan_probe.cpp"), "-o", exe], check=True)
+
+    def run(calls):
+        """calls: (BH, N, C, M, dtype, tuning overrides) -> one dict per call"""
+        lines = []
+        for BH, N, C, M, t, kw in calls:
+            k = {**DEFAULT, **kw}
+            lines.append(f"{k['target']} {k['min_chunks']} {k['fold']} {k['group']} {k['block']} {BH} {N} {C} {M} {t}")
+        out = subprocess.run([exe], input="\n".join(lines), capture_output=True, text=True, check=True).stdout.split("\n")
+        return [dict(zip(FIELDS, map(int, o.split()))) for o in out if o]
+
+    return run
+
+
+def test_one_snapshot_of_the_tuning_values_per_call():
+    """The plan of a call and the workspace it checks for come from the same values: la_plan.h is given them
+    and cannot read them, and no function of the C ABI reads them twice."""
+    text = open(os.path.join(CSRC, "la_api.hip")).read()
+    assert "tuning()" not in open(os.path.join(CSRC, "la_plan.h")).read()
+    bodies = re.findall(r"^(?:static )?(?:int|size_t|void|Plan|Tuning) (\w+)\([^;{]*\) \{\n(.*?)^\}", text, re.S | re.M)
+    reads = {name: len(re.findall(r"(?<!read_)\btuning\(\)", body)) for name, body in bodies}
+    entries = {"causal_fwd_impl", "la_causal_fwd_noalloc", "causal_fwd_state_impl", "causal_bwd_impl", "global_fwd_impl",
+               "global_bwd_impl", "la_causal_fwd_workspace", "la_causal_bwd_workspace", "la_global_fwd_workspace",
+               "la_global_bwd_workspace"}
+    assert {n for n, c in reads.items() if c} == entries
+    assert all(reads[n] == 1 for n in entries)
+    # ... nor calls another function that does
+    for name, body in bodies:
+        others = entries & set(re.findall(r"\b(\w+)\(", body))
+        assert not (others and name in entries), (name, others)
+
+
+def test_a_plan_never_has_more_segments_than_its_workspace_holds(plans):
+    rng, calls = random.Random(1), []
+    for _ in range(20000):
+        C, M = rng.choice(((64, 64), (32, 32), (64, 32), (32, 64)))
+        kw = dict(target=rng.choice((1, 3, 24, 256, 2047, 2048, 2048, 2048, 1 << 20)), min_chunks=rng.choice((1, 2, 2, 3, 8)),
+                  group=rng.choice((0, 1, 2)), block=rng.choice((-1, 0, 1)))
+        calls.append((int(2 ** rng.uniform(0, 13)), int(2 ** rng.uniform(0, 17)), C, M, rng.choice((F32, BF16)), kw))
+    for call, p in zip(calls, plans(calls)):
+        assert p["writes"] <= p["states"] and 2 * p["states"] < p["bwd"], (call, p)
+        assert (p["nseg"] - 1) * p["cps"] < p["nchunks"] <= p["nseg"] * p["cps"], (call, p)      # no segment is empty
+        if p["fwd_block"] or p["bwd_block"]:                # whole 32-token blocks
+            assert p["cps"] % 2 == 0 or p["nseg"] == 1 or (not p["fwd_block"] and p["cps"] * p["bwd_group"] % 2 == 0), (call, p)
