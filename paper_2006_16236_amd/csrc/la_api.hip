@@ -305,7 +305,7 @@ static int causal_fwd_impl(const void *Q, const void *K, const void *V, void *O,
         return LA_ERR_ALIGN;
     const long BH = (long)B * H;
     const Tuning tn = tuning();
-    const Plan p = causal_plan(tn, BH, N, C, M, t);
+    const Plan p = causal_plan(tn, BH, N, C, M, t, tok_heads);
     const size_t need = causal_states_bytes(tn, BH, N, C, M);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return LA_ERR_WORKSPACE;
     const size_t rows = (size_t)BH * N, e = esize(t);
@@ -339,7 +339,7 @@ int la_causal_fwd_noalloc(const void *Q, const void *K, const void *V, void *O, 
     if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(O)) return LA_ERR_ALIGN;
     const long BH = (long)B * H;
     const Tuning tn = tuning();
-    const Plan p = causal_plan(tn, BH, N, C, M, t);
+    const Plan p = causal_plan(tn, BH, N, C, M, t, 0);
     const size_t need = causal_states_bytes(tn, BH, N, C, M);
     if (need > kScratchBytes) return LA_ERR_SCRATCH;
     const size_t rows = (size_t)BH * N, e = esize(t);
@@ -371,7 +371,7 @@ static int causal_fwd_state_impl(const void *Q, const void *K, const void *V, co
         return LA_ERR_ALIGN;
     const long BH = (long)B * H;
     const Tuning tn = tuning();
-    const Plan p = causal_plan(tn, BH, N, C, M, t);
+    const Plan p = causal_plan(tn, BH, N, C, M, t, tok_heads);
     const size_t need = causal_states_bytes(tn, BH, N, C, M);
     if (need > 0 && (ws == nullptr || ws_bytes < need)) return LA_ERR_WORKSPACE;
     const size_t rows = (size_t)BH * N, e = esize(t);
@@ -426,7 +426,7 @@ static int causal_bwd_impl(const void *Q, const void *K, const void *V, const fl
     if (ws == nullptr || ws_bytes < need) return LA_ERR_WORKSPACE;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const Plan p = causal_plan(tn, BH, N, C, M, t);
+    const Plan p = causal_plan(tn, BH, N, C, M, t, tok_heads);
     const size_t rows = (size_t)BH * N;
     {
         const size_t e = esize(t), sb = (size_t)BH * C * M * 4, zb = (size_t)BH * C * 4;

@@ -31,10 +31,11 @@
 #pragma once
 
 #include "la_passes.h"
+#include "la_plan.h"
 
 namespace la {
 
-constexpr int kBlk = 32;          // tokens per block
+using la_plan::kBlk;              // tokens per block
 // waves per workgroup of the forward and of the two backward kernels
 template <int D, int M, typename T> constexpr int kFwdWaves = 8;
 template <int D, int M, typename T> constexpr int kBwdWaves = is_bf16<T> || (D == 32 && M == 32) ? 8 : 4;     // (the polynomial map relies on its 4)

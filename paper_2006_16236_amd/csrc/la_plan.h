@@ -11,6 +11,7 @@
 namespace la_plan {
 
 constexpr int kChunk = 16;                                        // tokens per chunk (la_device.h)
+constexpr int kBlk = 32;                                          // tokens per block (la_block.h)
 constexpr int state_stride(int D, int M) { return D * M + D; }    // floats per state (la_passes.h)
 
 // ---- schedule ---------------------------------------------------------------------------------
@@ -116,10 +117,13 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 //   2048 x 512, D = M = 32   wave 113 / 135 / 144   workgroup 110 / 162 / 158
 // It never has more segments than make_plan's, which size the workspaces.
 // (The polynomial map is cut like fp32 tensors of 64 features.)
-inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype t) {
+// tok_heads: H of token-major tensors, else 0.  The workgroup kernels address the 32 tokens of a block with
+// 32-bit byte offsets, which token-major tensors of a few hundred thousand heads exceed; the wave kernels do not.
+inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype t, int tok_heads) {
     Plan wave = make_plan(tn, BH, N);
     wave.bwd_group = backward_group(tn, C, M);
-    if (tn.block == 0) return wave;
+    const int64_t block_bytes = (int64_t)kBlk * (tok_heads > 1 ? tok_heads : 1) * (C > M ? C : M) * (int64_t)esize(t);
+    if (tn.block == 0 || block_bytes > INT32_MAX) return wave;
     const long target = tn.target_waves >= 4 ? tn.target_waves / 4 : 1;
     const long min_chunks = tn.min_chunks > 2 ? tn.min_chunks : 2;
     const bool bf16 = esize(t) == 2, narrow = C == 32 && M == 32;

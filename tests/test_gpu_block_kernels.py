@@ -146,3 +146,26 @@ def test_short_sequences_and_their_workspaces(oracle, BH, N, D, M, bf16):
     assert rel_err(to_host(O), oracle.causal_fwd_prefix(*host[:3], 1e-6)) <= (2e-2 if bf16 else 1e-5)
     errs = grad_errs([to_host(x) for x in grads], oracle.causal_bwd_linear(*host, 1e-6))
     assert max(errs) <= (2e-2 if bf16 else 1e-4), errs
+
+
+def test_very_many_token_major_heads():
+    """[B, N, H, .] tensors with so many heads that a block of 32 tokens spans more than 4 GB, beyond what the
+    workgroup kernels address: a few heads of the call against the same heads on their own."""
+    import paper_2006_16236_amd as la
+    H, N, D = 1 << 19, 33, 64
+    g = torch.Generator(DEV).manual_seed(8700)
+    q, k, v, dO = (torch.randn(1, N, H, D, device=DEV, generator=g) for _ in range(4))
+    O, dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(4))
+    den = torch.empty(1, H, N, device=DEV)
+    ws = la.la_causal_fwd_bnhd(q, k, v, O, den, 1e-6)
+    la.la_causal_bwd_bnhd(q, k, v, None, den, dO, dq, dk, dv, 1e-6, fwd_ws=ws)
+    some = torch.tensor([0, 1, H // 2 - 1, H // 2, H - 1], device=DEV)
+    sq, sk, sv, sg = (x[:, :, some].transpose(1, 2).contiguous() for x in (q, k, v, dO))
+    got = [to_host(x[:, :, some].transpose(1, 2)) for x in (O, dq, dk, dv)]
+    sO, sden, *sgrads = (torch.empty_like(sv), torch.empty(1, len(some), N, device=DEV), *(torch.empty_like(x) for x in (sq, sk, sv)))
+    sws = la.la_causal_fwd(sq, sk, sv, sO, sden, 1e-6)
+    la.la_causal_bwd(sq, sk, sv, None, sden, sg, *sgrads, 1e-6, fwd_ws=sws)
+    assert rel_err(got[0], to_host(sO).astype(np.float64)) <= 1e-5
+    assert max(grad_errs(got[1:], [to_host(x).astype(np.float64) for x in sgrads])) <= 1e-4
+    del q, k, v, dO, O, dq, dk, dv, ws
+    torch.cuda.empty_cache()

@@ -10,7 +10,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2006_16236_amd", "csrc")
 FIELDS = ("nchunks", "nseg", "cps", "fold", "fwd_block", "bwd_block", "bwd_group", "writes", "states", "bwd")
-DEFAULT = dict(target=2048, min_chunks=2, fold=8, group=0, block=-1)
+DEFAULT = dict(target=2048, min_chunks=2, fold=8, group=0, block=-1, heads=0)
 F32, BF16, POLY2 = 0, 1, 4
 
 
@@ -24,7 +24,7 @@ def plans(tmp_path_factory):
         lines = []
         for BH, N, C, M, t, kw in calls:
             k = {**DEFAULT, **kw}
-            lines.append(f"{k['target']} {k['min_chunks']} {k['fold']} {k['group']} {k['block']} {BH} {N} {C} {M} {t}")
+            lines.append(f"{k['target']} {k['min_chunks']} {k['fold']} {k['group']} {k['block']} {BH} {N} {C} {M} {t} {k['heads']}")
         out = subprocess.run([exe], input="\n".join(lines), capture_output=True, text=True, check=True).stdout.split("\n")
         return [dict(zip(FIELDS, map(int, o.split()))) for o in out if o]
 
@@ -61,3 +61,24 @@ def test_a_plan_never_has_more_segments_than_its_workspace_holds(plans):
         assert (p["nseg"] - 1) * p["cps"] < p["nchunks"] <= p["nseg"] * p["cps"], (call, p)      # no segment is empty
         if p["fwd_block"] or p["bwd_block"]:                # whole 32-token blocks
             assert p["cps"] % 2 == 0 or p["nseg"] == 1 or (not p["fwd_block"] and p["cps"] * p["bwd_group"] % 2 == 0), (call, p)
+
+
+def test_very_many_heads_keep_the_wave_kernels(plans):
+    """Token-major tensors whose 32 tokens span more bytes than a 32-bit offset holds are not for the workgroup
+    kernels, whatever the tuning values; head-major tensors of the same sizes are."""
+    for t, e in ((F32, 4), (BF16, 2), (POLY2, 4)):
+        for C, M in ((64, 64), (32, 32), (64, 32), (32, 64)):
+            if t == POLY2 and C != 64:
+                continue
+            last = (2 ** 31 - 1) // (32 * max(C, M) * e)         # the most heads that fit
+            for block in (-1, 1):
+                for N in (1, 33, 512):
+                    calls = [(H, N, C, M, t, dict(block=block, heads=heads)) for H in (last, last + 1, 2 * last + 2, (1 << 20) - 1)
+                             if H < 1 << 20 for heads in (H, 0)]
+                    for (H, *_, kw), p in zip(calls, plans(calls)):
+                        if kw["heads"] > last:
+                            assert not (p["fwd_block"] or p["bwd_block"]), (H, kw, p)
+                        elif block == 1:
+                            assert p["fwd_block"] and p["bwd_block"], (H, kw, p)
+    # fp32 64 x 64 beyond one round of sequences is the workgroup kernels' by default: the case that overflowed
+    assert plans([(4096, 33, 64, 64, F32, dict(heads=4096))])[0]["bwd_block"] == 1
