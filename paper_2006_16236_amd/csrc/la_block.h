@@ -174,21 +174,22 @@ __device__ __forceinline__ Op<P> op_of(f32x4 a, f32x4 b) {
 // ---- fetch and park ------------------------------------------------------------------------------
 // The 32 tokens of a block are read and written through a buffer descriptor of exactly the tokens that
 // exist: the addresses are a scalar base and one 32-bit offset per lane, rows past the end read as
-// zero and are not written.
+// zero and are not written.  The whole offset goes into the lane's own, which is what the descriptor's
+// size is compared with; of the instruction's scalar offset the compiler's documentation says that it is not.
 typedef __amdgpu_buffer_rsrc_t Rows;
 template <typename T>
 __device__ __forceinline__ Rows rows_of(const T *first, int ts, int nv) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(first), 0, nv * ts * (int)sizeof(T), 0x00020000);
 }
 constexpr int kAuxNt = 2;         // the non-temporal bit of a buffer instruction
-template <int kAux> __device__ __forceinline__ f32x4 rows_load(Rows r, int at, int step, f32x4) {
-    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, at, step, kAux));
+template <int kAux> __device__ __forceinline__ f32x4 rows_load(Rows r, int at, f32x4) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, at, 0, kAux));
 }
-template <int kAux> __device__ __forceinline__ u32x2_t rows_load(Rows r, int at, int step, u32x2_t) {
-    return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(r, at, step, kAux));
+template <int kAux> __device__ __forceinline__ u32x2_t rows_load(Rows r, int at, u32x2_t) {
+    return __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, kAux));
 }
-__device__ __forceinline__ float rows_load1(Rows r, int at, int step) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, at, step, 0));
+__device__ __forceinline__ float rows_load1(Rows r, int at) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, at, 0, 0));
 }
 
 // Parts of the operands by element type: tile values and states; V, exact in bf16
@@ -249,14 +250,14 @@ struct BlkTiles {
     __device__ __forceinline__ void load(const T *first, int off, int ts, int nv, staged_t<T> (&st)[kQuads<F>]) const {
         const Rows r = rows_of(first, ts, nv);
 #pragma unroll
-        for (int k = 0; k < kQuads<F>; ++k) st[k] = rows_load<kAux>(r, off, k * kStep<F> * ts * (int)sizeof(T), staged_t<T>{});
+        for (int k = 0; k < kQuads<F>; ++k) st[k] = rows_load<kAux>(r, off + k * kStep<F> * ts * (int)sizeof(T), staged_t<T>{});
     }
     template <int kAux>
     __device__ __forceinline__ void load_all(const int t0, const int nv) {
         if (kG && mine<M>(0)) {
             const Rows r = rows_of(scale + t0, 1, nv);
 #pragma unroll
-            for (int k = 0; k < kQuads<M>; ++k) sc[k] = rows_load1(r, 4 * row<M>(tid), 4 * k * kStep<M>);
+            for (int k = 0; k < kQuads<M>; ++k) sc[k] = rows_load1(r, 4 * (row<M>(tid) + k * kStep<M>));
             load<M, kAux>(Gs + (size_t)t0 * tsm, offm, tsm, nv, fg);
         }
         if (mine<M>(1)) load<M, kAux>(Vs + (size_t)t0 * tsm, offm, tsm, nv, fv);
@@ -266,8 +267,8 @@ struct BlkTiles {
             const Rows q = rows_of(Qs + (size_t)t0 * tsd, tsd, nv), k_ = rows_of(Ks + (size_t)t0 * tsd, tsd, nv);
 #pragma unroll
             for (int k = 0; k < kQuads<D>; ++k) {
-                xq[k] = rows_load1(q, offx, k * kStep<D> * tsd * (int)sizeof(T));
-                xk[k] = rows_load1(k_, offx, k * kStep<D> * tsd * (int)sizeof(T));
+                xq[k] = rows_load1(q, offx + k * kStep<D> * tsd * (int)sizeof(T));
+                xk[k] = rows_load1(k_, offx + k * kStep<D> * tsd * (int)sizeof(T));
             }
         }
     }
@@ -378,8 +379,8 @@ struct OutRows {
 #pragma unroll
             for (int k = 0; k < 16 / kRows; ++k) {
                 const u32x4_t v = *reinterpret_cast<const u32x4_t *>(scratch + at<kStride>(row0 + kRows * k, piece));
-                __builtin_amdgcn_raw_buffer_store_b128(v, r, row0 * ts * (int)sizeof(T) + 16 * piece + at0,
-                                                       kRows * k * ts * (int)sizeof(T), !is_bf16<T> && LA_NT_STORES != 0 ? kAuxNt : 0);
+                __builtin_amdgcn_raw_buffer_store_b128(v, r, (row0 + kRows * k) * ts * (int)sizeof(T) + 16 * piece + at0, 0,
+                                                       !is_bf16<T> && LA_NT_STORES != 0 ? kAuxNt : 0);
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -400,7 +401,7 @@ template <typename T>
 __device__ __forceinline__ void blk_chain(const float *rows, const T *raw, T *out, int ts, int nv, int tid) {
     const int token = tid >> 3, k = tid & 7;
     const Rows r = rows_of(raw, ts, nv);
-    const f32x4 x0 = rows_load<0>(r, token * ts * 4, 0, f32x4{}), x1 = rows_load<0>(r, token * ts * 4, 16, f32x4{});
+    const f32x4 x0 = rows_load<0>(r, token * ts * 4, f32x4{}), x1 = rows_load<0>(r, token * ts * 4 + 16, f32x4{});
     const float *p = rows + token * kChainStride;
     const f32x4 a = *reinterpret_cast<const f32x4 *>(p + 8 * k), b = *reinterpret_cast<const f32x4 *>(p + 8 * k + 4);
     float acc = 0.f;

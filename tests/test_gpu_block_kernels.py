@@ -169,3 +169,48 @@ def test_very_many_token_major_heads():
     assert max(grad_errs(got[1:], [to_host(x).astype(np.float64) for x in sgrads])) <= 1e-4
     del q, k, v, dO, O, dq, dk, dv, ws
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("kind", ["f32", "bf16", "poly2"])
+@pytest.mark.parametrize("D,M", [(64, 64), (32, 32), (64, 32), (32, 64)])
+def test_nothing_is_touched_past_the_last_token(oracle, monkeypatch, kind, D, M):
+    """Last blocks of 1, 2, 15, 17 and 31 tokens, both layouts: every tensor of the call ends where a guard
+    begins, NaN behind the inputs (a value read there would show) and a mark that has to stay behind the
+    outputs.  One sequence, so that a row past its end is past the tensor's; three token-major heads."""
+    if kind == "poly2" and D != 64:
+        pytest.skip("the polynomial map has 64 features")
+    bf16, W, eps = kind == "bf16", 8 if kind == "poly2" else D, 0.5 if kind == "poly2" else 1e-6
+    kw = {"features": "poly2"} if kind == "poly2" else {}
+    dt, guard = torch.bfloat16 if bf16 else torch.float32, 64 * 64 * 3
+
+    def guarded(t, fill):
+        """a copy of t (or its uninitialised like) at the front of a longer buffer"""
+        buf = torch.full((t.numel() + guard,), fill, dtype=t.dtype, device=DEV)
+        view = buf[:t.numel()].view(t.shape)
+        return buf, view
+
+    with block_kernels(monkeypatch, "1", "default") as la:
+        for N in (1, 2, 15, 17, 33, 47, 49, 63, 65, 79):
+            for token_major in (False, True):
+                B, H = 1, 3 if token_major else 1
+                host = maybe_bf16(wl.random_case(8800 + N + D + 2 * M, B, H, N, W, M), bf16)
+                ins = []
+                for x in host:
+                    t = to_dev(x, bf16)
+                    t = t.transpose(1, 2).contiguous() if token_major else t
+                    _, view = guarded(t, float("nan"))
+                    view.copy_(t)
+                    ins.append(view)
+                q, k, v, g = ins
+                outs = [guarded(t, -7.0) for t in (v, q, k, v, torch.empty(B, H, N, device=DEV))]
+                (O, dq, dk, dv, den) = (view for _, view in outs)
+                fwd, bwd = (la.la_causal_fwd_bnhd, la.la_causal_bwd_bnhd) if token_major else (la.la_causal_fwd, la.la_causal_bwd)
+                ws = fwd(q, k, v, O, den, eps, **kw)
+                bwd(q, k, v, None, den, g, dq, dk, dv, eps, fwd_ws=ws, **kw)
+                torch.cuda.synchronize()
+                assert all(bool((buf[view.numel():] == -7.0).all()) for buf, view in outs), (N, token_major)
+                ref = (oracle.causal_fwd_poly2 if kw else oracle.causal_fwd_prefix)(*host[:3], eps)
+                gref = (oracle.causal_bwd_poly2 if kw else oracle.causal_bwd_linear)(*host, eps)
+                got = [to_host(x.transpose(1, 2) if token_major else x) for x in (O, dq, dk, dv)]
+                assert rel_err(got[0], ref) <= (2e-2 if bf16 else 1e-5), (N, token_major)
+                assert max(grad_errs(got[1:], gref)) <= (2e-2 if bf16 else 1e-4), (N, token_major)
