@@ -320,10 +320,119 @@ __global__ __launch_bounds__(256) void recurrent_steps_kernel(const T *q, const 
     }
 }
 
+// The same a step at a time, for launches of a few steps: the next token's q, k, v are fetched while the
+// current one is processed, one barrier per step.  What bounds such a launch is the state's way in and out, and
+// that wants many workgroups in flight: 2 KB of LDS instead of 77, and no fetch of eight steps for one.
+template <int D, int M, typename T>
+__global__ __launch_bounds__(256) void recurrent_steps_few_kernel(const T *q, const T *k, const T *v,
+                                                              float *S, float *z, T *out,
+                                                              float eps, int steps, size_t BH) {
+    constexpr int LPR = M / 4, RPW = kWave / LPR, RPI = 4 * RPW, NIT = D / RPI;
+    __shared__ float red[2][4][M];
+    __shared__ float dred[2][4];
+
+    const int bh = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int col4 = (lane % LPR) * 4, rsub = lane / LPR;
+    float *Sh = S + (size_t)bh * D * M, *zh = z + (size_t)bh * D;
+
+    f32x4 s4[NIT];
+    float zr[NIT];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int d = it * RPI + wave * RPW + rsub;
+        s4[it] = *reinterpret_cast<const f32x4 *>(Sh + (size_t)d * M + col4);
+        zr[it] = zh[d];
+    }
+    constexpr int W = qk_width<T>(D);          // elements per token of q and k
+    // The wave sweeps NR rows of S per step, and every lane of a row needs that row's feature of
+    // k and of q.  The feature map is evaluated once per row and wave, not once per lane: lane
+    // j < NR fetches and maps k's element of row j of the sweep, lane NR + j the same of q (the
+    // lanes above 2 NR repeat them, unused), and the lanes of a row pick the values up with a
+    // shuffle.
+    constexpr int NR = NIT * RPW;
+    static_assert(2 * NR <= kWave, "one lane per row and operand");
+    const int j = lane % NR;
+    const bool mine_is_q = ((lane / NR) & 1) != 0;
+    const int dj = (j / RPW) * RPI + wave * RPW + (j % RPW);
+    auto fetch = [&](int t, float &x, f32x4 &v4) {
+        const T *row = (mine_is_q ? q : k) + ((size_t)t * BH + bh) * W;
+        if constexpr (is_poly<T>) x = feature_of<T>(row, dj);   // the feature itself (x_i x_j): nothing is left to map
+        else x = to_f32(row[dj]);
+        v4 = load4(v + ((size_t)t * BH + bh) * M + col4);
+    };
+    float x_next;
+    f32x4 v_next;
+    fetch(0, x_next, v_next);
+    for (int t = 0; t < steps; ++t) {
+        const float f = feature<T>(x_next);
+        const f32x4 v4 = v_next;
+        if (t + 1 < steps) fetch(t + 1, x_next, v_next);
+
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        float dpart = 0.f;
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const float kd = __shfl(f, it * RPW + rsub);
+            const float qd = __shfl(f, NR + it * RPW + rsub);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                s4[it][e] = fmaf(kd, v4[e], s4[it][e]);
+                acc[e] = fmaf(qd, s4[it][e], acc[e]);
+            }
+            if (col4 == 0) {
+                zr[it] += kd;
+                dpart = fmaf(qd, zr[it], dpart);
+            }
+        }
+#pragma unroll
+        for (int off = LPR; off < kWave; off <<= 1) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], off);
+        }
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) dpart += __shfl_xor(dpart, off);
+        const int buf = t & 1;            // two LDS buffers: one barrier per step suffices
+        if (rsub == 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[buf][wave][col4 + e] = acc[e];
+        }
+        if (lane == 0) dred[buf][wave] = dpart;
+        __syncthreads();
+        if (tid < M) {
+            const float num = (red[buf][0][tid] + red[buf][1][tid]) + (red[buf][2][tid] + red[buf][3][tid]);
+            const float den = ((dred[buf][0] + dred[buf][1]) + (dred[buf][2] + dred[buf][3])) + eps;
+            store_elem(out + ((size_t)t * BH + bh) * M + tid, num / den);
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int d = it * RPI + wave * RPW + rsub;
+        *reinterpret_cast<f32x4 *>(Sh + (size_t)d * M + col4) = s4[it];
+        if (col4 == 0) zh[d] = zr[it];
+    }
+}
+
+// Which of the two.  Few / batched steps in us on the device (B*H sequences, fp32 unless noted):
+//   T = 1   64 x 64  64: 2.9/3.3  1024: 6.3/7.5  2048: 11.8/14.2  bf16 4096: 22.0/27.5   32 x 32  8192: 15.6/29.0
+//   T = 2   64 x 64  1024: 7.4/7.7  4096: 26.6/27.6  8192: 49.4/46.2   32 x 32  1024: 4.9/5.1  8192: 21.9/31.0
+//   T = 3   64 x 64  1024: 8.6/8.0  2048: 15.9/17.2  8192: 53.6/46.7   32 x 32  1024: 6.1/5.4  8192: 29.4/32.4
+//   T = 4   64 x 64  2048: 17.9/17.6  bf16 2048: 16.9/17.6  8192: 46.7/50.3   32 x 32  8192: 36.8/33.6
+inline bool few_steps(int steps, int BH, int D, int M, bool bf16) {
+    if (steps == 1) return true;
+    const bool widest = D == 64 && M == 64;
+    if (widest && !bf16 && BH > 4096) return false;
+    return BH >= (steps == 2 ? 1024 : 2048) && steps <= (widest && bf16 ? 4 : 3);
+}
+
 hipError_t launch_recurrent_steps(const void *q, const void *k, const void *v, float *S, float *z,
                                   void *out, int steps, int BH, int D, int M, float eps, int dtype,
                                   hipStream_t s) {
     LA_DISPATCH(D, M, dtype, {
+        if (few_steps(steps, BH, D, M, is_bf16<TT>)) {
+            recurrent_steps_few_kernel<kD, kM, TT><<<BH, 256, 0, s>>>((const TT *)q, (const TT *)k, (const TT *)v, S, z, (TT *)out,
+                                                                      eps, steps, (size_t)BH);
+            return hipGetLastError();
+        }
         recurrent_steps_kernel<kD, kM, TT><<<BH, 256, 0, s>>>((const TT *)q, (const TT *)k,
                                                              (const TT *)v, S, z, (TT *)out, eps,
                                                              steps, (size_t)BH);

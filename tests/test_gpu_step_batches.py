@@ -1,6 +1,7 @@
-"""la_recurrent_steps takes its steps in batches of eight: every remainder of a batch, for every
-element type and head size, must leave the bits that single steps leave (exact: the additions are the
-same in the same order)."""
+"""la_recurrent_steps takes its steps in batches of eight, or one at a time where a launch has few for many
+sequences: every remainder of a batch and both sides of the line between the two, for every element type
+and head size, must leave the bits that single steps leave (exact: the additions are the same in the same
+order)."""
 import pytest
 import torch
 
@@ -11,14 +12,27 @@ DEV = "cuda:0"
 @pytest.mark.parametrize("kind", ["f32", "bf16", "given", "poly2"])
 @pytest.mark.parametrize("D,M", [(64, 64), (32, 32), (64, 32), (32, 64)])
 def test_batches_equal_single_steps(kind, D, M):
-    import paper_2006_16236_amd as la
     if kind == "poly2" and D != 64:
         pytest.skip("the polynomial map has 64 features")
-    B, H, W = 2, 3, 8 if kind == "poly2" else D
+    check(kind, 2, 3, D, M, (1, 2, 7, 8, 9, 16, 17, 31))
+
+
+@pytest.mark.parametrize("kind", ["f32", "bf16", "poly2"])
+@pytest.mark.parametrize("D,M", [(64, 64), (32, 32), (64, 32), (32, 64)])
+def test_few_steps_of_many_sequences(kind, D, M):
+    if kind == "poly2" and D != 64:
+        pytest.skip("the polynomial map has 64 features")
+    for BH, steps in ((1023, (2,)), (1024, (1, 2, 3)), (2047, (3,)), (2048, (2, 3, 4, 5)), (4096, (2, 3)), (4097, (2, 3, 4))):
+        check(kind, BH, 1, D, M, steps)
+
+
+def check(kind, B, H, D, M, lengths):
+    import paper_2006_16236_amd as la
+    W = 8 if kind == "poly2" else D
     kw = {"given": {"features": True}, "poly2": {"features": "poly2"}}.get(kind, {})
     dt = torch.bfloat16 if kind == "bf16" else torch.float32
     g = torch.Generator(DEV).manual_seed(D + 2 * M)
-    for T in (1, 2, 7, 8, 9, 16, 17, 31):
+    for T in lengths:
         q, k = (torch.randn(T, B, H, W, device=DEV, generator=g).to(dt) for _ in range(2))
         if kind == "given":
             q, k = q.abs(), k.abs()
@@ -30,4 +44,4 @@ def test_batches_equal_single_steps(kind, D, M):
         for t in range(T):
             la.la_recurrent_step(q[t], k[t], v[t], S1, z1, out1[t], 0.5, **kw)
         torch.cuda.synchronize()
-        assert torch.equal(out, out1) and torch.equal(S, S1) and torch.equal(z, z1), T
+        assert torch.equal(out, out1) and torch.equal(S, S1) and torch.equal(z, z1), (B * H, T)
