@@ -103,16 +103,28 @@ __device__ __forceinline__ int col_of(int t, int rho) {
 // Feature-lane operand: lane (c, g) holds column col_of(t, c) of eight rows.  kNatural = false: rows
 // 4g .. + 3 and 16 + 4g .. + 3 (the order in which a pair of score tiles comes out of the accumulators),
 // true: rows 8g .. + 7 (the order of read_tok).  `row0` = first of the 32 rows.
-template <int F, int P, bool kPair, bool kNatural = false>
-__device__ __forceinline__ Op<P> read_feat(const uint16_t *tile, int plane, int row0, int t, int lane) {
+template <int F, bool kPair, bool kNatural = false>
+__device__ __forceinline__ bf16x8_t read_feat_part(const uint16_t *tile, int row0, int t, int lane) {      // of the plane at `tile`
     const int q = lane & 15, g = lane >> 4;
     const int ra = row0 + (kNatural ? 8 * g : 4 * g) + (q >> 2), rb = ra + (kNatural ? 4 : 16);
     const int piece = kPair ? 4 * (t >> 1) + (q & 3) : 2 * t + ((q >> 1) & 1);
     const int half = kPair ? 4 * (t & 1) : 4 * (q & 1);
-    const uint16_t *pa = tile + part_at<F>(ra, piece) + half, *pb = tile + part_at<F>(rb, piece) + half;
+    return cat_parts(read_tr(tile + part_at<F>(ra, piece) + half), read_tr(tile + part_at<F>(rb, piece) + half));
+}
+template <int F, int P, bool kPair, bool kNatural = false>
+__device__ __forceinline__ Op<P> read_feat(const uint16_t *tile, int plane, int row0, int t, int lane) {
     Op<P> o;
 #pragma unroll
-    for (int k = 0; k < P; ++k) o.p[k] = cat_parts(read_tr(pa + k * plane), read_tr(pb + k * plane));
+    for (int k = 0; k < P; ++k) o.p[k] = read_feat_part<F, kPair, kNatural>(tile + k * plane, row0, t, lane);
+    return o;
+}
+// three parts of such an operand of which P are there already
+template <int F, int P>
+__device__ __forceinline__ Op<3> full_feat(const Op<P> &have, const uint16_t *tile, int plane, int t, int lane) {
+    Op<3> o;
+#pragma unroll
+    for (int k = 0; k < P; ++k) o.p[k] = have.p[k];
+    if constexpr (P == 2) o.p[2] = read_feat_part<F, false>(tile + 2 * plane, 0, t, lane);
     return o;
 }
 
@@ -196,9 +208,10 @@ __device__ __forceinline__ float rows_load1(Rows r, int at) {
 template <typename T> constexpr int kOpParts = is_bf16<T> ? 2 : 3;
 template <typename T> constexpr int kVParts = is_bf16<T> ? 1 : 3;
 
-// The tiles of a block in LDS and their way there.  kLead: the tensor whose feature values are also
-// needed in full and that therefore takes three parts, Q (dQ pass) or K (dV, dK), or, in the
-// forward (no dO there), both: den is formed from them.
+// The tiles of a block in LDS and their way there.  Q and K take three parts for every element type:
+// besides the products of P parts their feature values are needed in full, for phi' and for the sums that
+// stay fp32, den in the forward, z and delta in the dQ pass, rho in the reverse pass.
+// kLead: the pass, by the tensor whose gradient it ends in (kLeadQK: the forward, no dO there).
 // A 32 x F block is fetched in quads of four elements, one or two per thread: quad k of thread t is
 // row row(t) + k * kStep, columns col(t) .. + 3 (a wave reads whole rows).  Where a block has fewer quads
 // than there are threads, the two blocks of a pair (Q and K, or dO and V) take half of them each.
@@ -206,7 +219,7 @@ enum Lead { kLeadQ = 0, kLeadK = 1, kLeadQK = 2 };
 template <int kLead, int D, int M, typename T, bool kStrided>
 struct BlkTiles {
     static constexpr int kWaves = kLead == kLeadQK ? kFwdWaves<D, M, T> : kBwdWaves<D, M, T>, kThreads = kWave * kWaves;
-    static constexpr int P = kOpParts<T>, PV = kVParts<T>, PQ = kLead != kLeadK ? 3 : P, PK = kLead != kLeadQ ? 3 : P;
+    static constexpr int P = kOpParts<T>, PV = kVParts<T>, PQ = 3, PK = 3;
     static constexpr bool kG = kLead != kLeadQK;
     static constexpr int kElems = (PQ + PK) * kBlk * D + (PV + (kG ? P : 0)) * kBlk * M;
     template <int F> static constexpr int kQuads = 8 * F > kThreads ? 8 * F / kThreads : 1;
@@ -919,10 +932,14 @@ struct DqState : BlkLane {
             if (i == 0) {
                 const unsigned one2 = 0x3f803f80u;
                 Op<1> ones[NT];
+                Op<3> kf[NT];             // z is an fp32 sum: three parts whatever P is
                 f32x4 zz[NT];
 #pragma unroll
-                for (int y = 0; y < NT; ++y) ones[y].p[0] = cat_parts(u32x2_t{one2, one2}, u32x2_t{one2, one2}), zz[y] = zero4;
-                mma_n(kn, ones, zz);
+                for (int y = 0; y < NT; ++y) {
+                    kf[y] = full_feat<D>(kn[y], tl.sk, kBlk * D, h * NT + y, lane);
+                    ones[y].p[0] = cat_parts(u32x2_t{one2, one2}, u32x2_t{one2, one2}), zz[y] = zero4;
+                }
+                mma_n(kf, ones, zz);
 #pragma unroll
                 for (int y = 0; y < NT; ++y) z[y] += zz[y];
             }
@@ -1214,14 +1231,15 @@ struct RevState : BlkLane {
         for (int x = 0; x < DT; ++x)
 #pragma unroll
             for (int y = 0; y < MT; ++y) U[x][y] += u[x * MT + y];
-        const Op<P> dop[1] = {op_of<P>(*reinterpret_cast<const f32x4 *>(sdel + 4 * g),
+        // rho, an fp32 sum: three parts on both sides whatever P is
+        const Op<3> dop[1] = {op_of<3>(*reinterpret_cast<const f32x4 *>(sdel + 4 * g),
                                        *reinterpret_cast<const f32x4 *>(sdel + 16 + 4 * g))};
         f32x4 rr[1] = {zero4};
         if (DT == 1 || h == 0) {
-            const Op<P> q1[1] = {qn[0]};
+            const Op<3> q1[1] = {full_feat<D>(qn[0], tl.sq, kBlk * D, rt, lane)};
             mma_n(q1, dop, rr);
         } else {
-            const Op<P> q1[1] = {qn[DT - 1]};
+            const Op<3> q1[1] = {full_feat<D>(qn[DT - 1], tl.sq, kBlk * D, rt, lane)};
             mma_n(q1, dop, rr);
         }
         rho += rr[0];

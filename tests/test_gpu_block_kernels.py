@@ -214,3 +214,35 @@ def test_nothing_is_touched_past_the_last_token(oracle, monkeypatch, kind, D, M)
                 got = [to_host(x.transpose(1, 2) if token_major else x) for x in (O, dq, dk, dv)]
                 assert rel_err(got[0], ref) <= (2e-2 if bf16 else 1e-5), (N, token_major)
                 assert max(grad_errs(got[1:], gref)) <= (2e-2 if bf16 else 1e-4), (N, token_major)
+
+
+@pytest.mark.parametrize("on", ["0", "1"])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("D,M", [(64, 64), (32, 32), (64, 32), (32, 64)])
+def test_gradient_for_z0_is_an_fp32_sum(monkeypatch, D, M, bf16, on):
+    """dz0 = dz1 + sum over the tokens of delta phi(Q), in fp32 for every element type: against that sum in
+    fp64 from the very deltas the backward has left in its workspace (second array, after 1/den).  Bound:
+    every product exact to 2^-23, sums of N terms in runs of at most 32 rounded at 2^-24 of their running
+    size; the terms change sign, so the measure is the sum of their sizes: 2^-20 of it is ample, and half
+    of what a factor cut to 16 bits (2^-17 of each term, with N = 40 hardly averaged) would do to single terms."""
+    B, H, N = 2, 2, 40
+    dev = [to_dev(x, bf16) for x in maybe_bf16(wl.random_case(8900 + D + 2 * M, B, H, N, D, M), bf16)]
+    q, k, v, g = dev
+    gen = torch.Generator(DEV).manual_seed(4)
+    S0, z0 = (torch.rand(s, device=DEV, generator=gen) for s in ((B, H, D, M), (B, H, D)))
+    dS1, dz1 = torch.zeros_like(S0), torch.zeros_like(z0)
+    with block_kernels(monkeypatch, on, "default") as la:
+        code = la.LA_BF16 if bf16 else la.LA_F32
+        O, den, dS0, dz0 = torch.empty_like(v), torch.empty(B, H, N, device=DEV), torch.empty_like(S0), torch.empty_like(z0)
+        ws = la.la_causal_fwd_state(q, k, v, O, den, S0, z0)
+        grads = [torch.empty_like(x) for x in (q, k, v)]
+        bws = torch.zeros(la.la_causal_bwd_workspace(B, H, N, D, M, code), dtype=torch.uint8, device=DEV)
+        la.la_causal_bwd_state(q, k, v, None, den, g, *grads, S0, z0, dS1, dz1, dS0, dz0, ws=bws, fwd_ws=ws)
+        torch.cuda.synchronize()
+    rows = (B * H * N * 4 + 255) // 256 * 256
+    delta = bws[rows:rows + B * H * N * 4].view(torch.float32).view(B, H, N).double()
+    x = q.float()
+    phi = torch.where(x > 0, x + 1.0, torch.exp(x)).double()
+    terms = delta[..., None] * phi
+    err = (dz0.double() - terms.sum(2)).abs() / terms.abs().sum(2)
+    assert float(err.max()) <= 2.0 ** -20
