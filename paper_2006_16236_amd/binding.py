@@ -105,7 +105,11 @@ _lib = _load()
 def _bind_call():
     """The native accepting path of the calls below (csrc/la_call.cpp): each of its functions checks the
     tensors of a call and makes it, or answers None, and the call then takes the path in this file, which
-    names what is wrong with it."""
+    names what is wrong with it.  A build without torch's headers has no _call.so: all calls go that way."""
+    if not os.path.exists(os.path.join(os.path.dirname(os.path.abspath(__file__)), "_call.so")):
+        class c:
+            fwd = bwd = step = staticmethod(lambda *args: None)
+        return c
     from . import _call as c
     names = ["la_recurrent_step"]
     names += [f"la_{kind}_{way}{layout}" for way in ("fwd", "bwd") for kind in ("causal", "global") for layout in ("", "_bnhd")]

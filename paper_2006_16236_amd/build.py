@@ -2,14 +2,18 @@
 native argument checks (csrc/la_call.cpp -> _call.so) with g++.
 
 hipcc cross-compiles without a GPU, so this runs anywhere the ROCm toolchain is
-installed.  The library is kept in-tree next to this file.
+installed.  The library is kept in-tree next to this file.  It needs neither torch nor Python;
+_call.so needs the headers of both and is left out where they, or g++, are missing: the binding
+then makes the same calls through its Python checks.
 """
 from __future__ import annotations
 
 import concurrent.futures
 import glob
 import os
+import shutil
 import subprocess
+import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -24,19 +28,35 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 CALL = os.path.join(HERE, "_call.so")
 
 
+def _call_command():
+    """The command that builds _call.so, or None where its headers or its compiler are missing."""
+    import sysconfig
+    try:
+        import torch
+    except ImportError:
+        return None
+    root, python = os.path.dirname(torch.__file__), sysconfig.get_paths()["include"]
+    needed = (os.path.join(root, "include", "torch", "csrc", "autograd", "python_variable.h"),
+              os.path.join(root, "include", "c10", "hip", "HIPStream.h"), os.path.join(python, "Python.h"))
+    if shutil.which("g++") is None or not all(os.path.exists(f) for f in needed):
+        return None
+    return ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+            "-isystem", "/opt/rocm/include", "-isystem", python, os.path.join(CSRC, "la_call.cpp"), "-o", CALL,
+            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+            f"-Wl,-rpath,{os.path.join(root, 'lib')}"]
+
+
 def _build_call() -> None:
     """The native argument checks (csrc/la_call.cpp), a CPython module on torch's headers; host code."""
-    import sysconfig
-
-    import torch
-    root = os.path.dirname(torch.__file__)
-    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-                    "-I", os.path.join(root, "include"), "-I", os.path.join(root, "include", "torch", "csrc", "api", "include"),
-                    "-I", "/opt/rocm/include", "-I", sysconfig.get_paths()["include"],
-                    os.path.join(CSRC, "la_call.cpp"), "-o", CALL, "-L", os.path.join(root, "lib"),
-                    "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", f"-Wl,-rpath,{os.path.join(root, 'lib')}"],
-                   check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    command = _call_command()
+    if command is None:
+        if os.path.exists(CALL):             # of older sources
+            os.remove(CALL)
+        print("_call.so left out: torch's or Python's headers or g++ not found", file=sys.stderr)
+        return
+    subprocess.run(command, check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
 
 
 def sources():
@@ -50,7 +70,8 @@ def _deps_mtime():
 
 
 def is_current() -> bool:
-    return all(os.path.exists(f) and os.path.getmtime(f) >= _deps_mtime() for f in (LIB, CALL))
+    files = (LIB, CALL) if _call_command() is not None else (LIB,)
+    return all(os.path.exists(f) and os.path.getmtime(f) >= _deps_mtime() for f in files)
 
 
 def _compile(src: str) -> str:
@@ -61,7 +82,7 @@ def _compile(src: str) -> str:
 
 
 def build_library(force: bool = True, jobs: int = 6) -> str:
-    """Compile every HIP source for gfx950, link libla_hip.so, and build _call.so.  With
+    """Compile every HIP source for gfx950, link libla_hip.so, and build _call.so where that can be.  With
     force=False an up-to-date library is left alone."""
     if not force and is_current():
         return LIB
@@ -74,7 +95,7 @@ def build_library(force: bool = True, jobs: int = 6) -> str:
         subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs],
                        check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
     except subprocess.CalledProcessError as e:  # show the compiler's message
-        raise RuntimeError(f"hipcc failed:\n{e.stdout.decode(errors='replace')}") from e
+        raise RuntimeError(f"{e.cmd[0]} failed:\n{e.stdout.decode(errors='replace')}") from e
     return LIB
 
 
