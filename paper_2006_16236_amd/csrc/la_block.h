@@ -37,7 +37,7 @@ namespace la {
 
 using la_plan::kBlk;              // tokens per block
 // waves per workgroup of the forward and of the two backward kernels
-template <int D, int M, typename T> constexpr int kFwdWaves = 8;
+constexpr int kFwdWaves = 8;
 template <int D, int M, typename T> constexpr int kBwdWaves = is_bf16<T> || (D == 32 && M == 32) ? 8 : 4;     // (the polynomial map relies on its 4)
 
 // ---- tiles of bf16 parts in LDS ----------------------------------------------------------------
@@ -218,7 +218,7 @@ template <typename T> constexpr int kVParts = is_bf16<T> ? 1 : 3;
 enum Lead { kLeadQ = 0, kLeadK = 1, kLeadQK = 2 };
 template <int kLead, int D, int M, typename T, bool kStrided>
 struct BlkTiles {
-    static constexpr int kWaves = kLead == kLeadQK ? kFwdWaves<D, M, T> : kBwdWaves<D, M, T>, kThreads = kWave * kWaves;
+    static constexpr int kWaves = kLead == kLeadQK ? kFwdWaves : kBwdWaves<D, M, T>, kThreads = kWave * kWaves;
     static constexpr int P = kOpParts<T>, PV = kVParts<T>, PQ = 3, PK = 3;
     static constexpr bool kG = kLead != kLeadQK;
     static constexpr int kElems = (PQ + PK) * kBlk * D + (PV + (kG ? P : 0)) * kBlk * M;
@@ -363,7 +363,7 @@ struct OutRows {
     static constexpr int kBytes = 16 * NT * (int)sizeof(T);       // of one row
     static constexpr int kPieces = kBytes / 16;                   // 16-byte pieces per row
     static constexpr bool kDirect = is_bf16<T> && NT == 1;        // half pieces: stored as they are
-    static constexpr int kScratch = 16 * kBytes;                  // bytes per wave
+    static constexpr int kScratch = kDirect ? 0 : 16 * kBytes;    // bytes per wave
     template <int stride> static __device__ __forceinline__ int at(int row, int piece) {
         return (row / (512 / kBytes)) * stride + (row % (512 / kBytes)) * kBytes +
                ((piece ^ (row * kBytes / 256)) << 4);
@@ -696,7 +696,7 @@ struct FwdState : BlkLane {
 };
 
 template <int D, int M, typename T, bool kStrided = false>
-__global__ __launch_bounds__((kWave * kFwdWaves<D, M, T>)) __attribute__((amdgpu_waves_per_eu((kFwdWaves<D, M, T> / 2)))) void fwd_block_kernel(
+__global__ __launch_bounds__((kWave * kFwdWaves)) __attribute__((amdgpu_waves_per_eu((kFwdWaves / 2)))) void fwd_block_kernel(
     const PassArgs a) {
     using Tiles = BlkTiles<kLeadQK, D, M, T, kStrided>;
     using OutRole = FwdOut<D, M, T, kStrided>;
@@ -711,19 +711,12 @@ __global__ __launch_bounds__((kWave * kFwdWaves<D, M, T>)) __attribute__((amdgpu
     blk_range(a, seg, blk0, count);
     char *const scratch = reinterpret_cast<char *>(kOwn ? tiles : tiles + Tiles::kElems);
     Tiles tl(a, tiles, bh, tid, wave);
-    if constexpr (Tiles::kWaves == 8) {
-        if (wave < 4) {
-            OutRole out(a, tl, bh, tid, wave, ss, sz, scratch);
-            blk_loop(tl, blk0, 1, count, out);
-        } else {
-            StateRole st(a, tl, bh, seg, tid, wave, ss, sz);
-            blk_loop(tl, blk0, 1, count, st);
-            st.end();
-        }
-    } else {
+    if (wave < 4) {
         OutRole out(a, tl, bh, tid, wave, ss, sz, scratch);
+        blk_loop(tl, blk0, 1, count, out);
+    } else {
         StateRole st(a, tl, bh, seg, tid, wave, ss, sz);
-        blk_loop(tl, blk0, 1, count, out, st);
+        blk_loop(tl, blk0, 1, count, st);
         st.end();
     }
 }

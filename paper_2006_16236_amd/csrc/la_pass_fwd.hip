@@ -8,8 +8,8 @@ hipError_t launch_pass_fwd(bool global, bool block, int D, int M, int dtype, con
                            hipStream_t s) {
     LA_DISPATCH(D, M, dtype, {
         if (block && !global) {
-            if (a.tok_heads > 1) fwd_block_kernel<kD, kM, TT, true><<<nblocks, kWave * kFwdWaves<kD, kM, TT>, 0, s>>>(a);
-            else fwd_block_kernel<kD, kM, TT><<<nblocks, kWave * kFwdWaves<kD, kM, TT>, 0, s>>>(a);
+            if (a.tok_heads > 1) fwd_block_kernel<kD, kM, TT, true><<<nblocks, kWave * kFwdWaves, 0, s>>>(a);
+            else fwd_block_kernel<kD, kM, TT><<<nblocks, kWave * kFwdWaves, 0, s>>>(a);
             return hipGetLastError();
         }
         if (a.tok_heads > 1) {
