@@ -101,6 +101,11 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 // so the line lies at 512 tokens per segment (fp32 with D = M = 64, bf16 with a 64-wide head dimension) or
 // 256.  Above it bf16 tensors with a 64-wide head dimension keep the wave kernel in the forward only
 // (114/158 us at 16 x 65536, backward 476/396).
+// As many segments as fill the machine, not one more: 52 sequences of 3524 tokens in 10 pieces are 520 workgroups
+// for 512 places, and the step took 289 us (wave kernels 222, 9 pieces 218).  One piece more only where the
+// shorter segments are within the lines above and the second round is not nearly empty, or three pieces in all
+// (two / three pieces: 200 x 1340 fp32 430/333, 175 x 1248 324/287); 257 to 383 sequences, which alone leave a third of the places empty, in
+// three or two pieces (fp32 D = M = 64, 257 .. 320: whole 0.92 of the wave kernels' time, two 0.87, three 0.76).
 // Short segments: where one workgroup per CU does with at most eight chunks each (ten for one segment per
 // sequence, four where a sequence has more than four segments), two per CU gain nothing and double the
 // states.  Two / one per CU in us (B*H x N, D = M = 64):
@@ -109,12 +114,25 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 // (96 x 300 in ten chunks, 32-wide heads: step 27.1/30.1; 80 x 384, D = 64, M = 32: step 37.6/40.3.)  Up to 64
 // tokens one segment does (forward of one sequence, D = M = 32 6.3/3.9 us, bf16 7.6/4.9; the step of fp32 tensors
 // with D = 64, M = 32 17.2/17.8: those only when the batch fills a quarter of the CUs).
-// Sequences are left whole from 512 on (256 if they are short: 256 x 512 136 us, 128 x 1024 in
-// four pieces 135).  Whole sequences, each kernel by what fills the machine
+// Sequences are left whole from 384 on (from 256 if they are short: 256 x 512 136 us, 128 x 1024 in
+// four pieces 135), narrow heads of more than 1024 tokens from 512 (bf16 406 x 1711 whole 1.08 of the wave
+// kernels' time).  Whole sequences, each kernel by what fills the machine
 // (fp32 D = M = 64, forward / dQ / dV+dK in us):
 //   1024 x 1024  wave 334 / 285 / 317   workgroup 235 / 354 / 358
 //   2048 x 512   wave 208 / 348 / 402   workgroup 252 / 350 / 356
 //   2048 x 512, D = M = 32   wave 113 / 135 / 144   workgroup 110 / 162 / 158
+// Workgroup / wave kernels of whole sequences, geometric mean over drawn lengths:
+//   bf16 forward from 1024 on     D = M = 64  1.09 .. 1.31   64 x 32  1.15 .. 1.52   32 x 32  1.03 .. 1.22   32 x 64  0.88
+//   backward with M = 32, fp32, from 1434 on  1.04 .. 1.24
+//   bf16 64 x 32, 513 .. 640 of more than 512 tokens (wave kernels in several pieces)  step 1.06, forward 1.08
+// A block is 32 tokens: of one chunk, or three, half a block is padding, and from 256 or 512 sequences on that
+// is not hidden (fp32 979 x 16 forward 5.5/9.7, bf16 1260 x 40 9.7/13.8; three chunks of bf16 D = M = 64 keep
+// the backward, 0.78 of the wave kernels' time at 1100 .. 1400 x 33 .. 48); one whole block loses its pipeline
+// of the next, and if it is not full (17 .. 31 tokens, from 768 sequences on) the wave kernels are ahead (forward
+// 1.06 .. 1.14, step 1.00 .. 1.07; not fp32 D = M = 64, 0.8 .. 1.01).
+// Left as they are: 257 .. 383 sequences of 257 .. 512 narrow tokens (step 0.81 .. 1.16 of the wave kernels' time,
+// forward 0.67 .. 0.95) and fp32 32-wide D, 513 .. 700 sequences of more than 512 tokens (step 1.01 .. 1.10,
+// forward 0.70 .. 0.88): every plan that helps the one harms the other.
 // It never has more segments than make_plan's, which size the workspaces.
 // (The polynomial map is cut like fp32 tensors of 64 features.)
 // tok_heads: H of token-major tensors, else 0.  The workgroup kernels address the 32 tokens of a block with
@@ -126,13 +144,25 @@ inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype
     if (tn.block == 0 || block_bytes > INT32_MAX) return wave;
     const long target = tn.target_waves >= 4 ? tn.target_waves / 4 : 1;
     const long min_chunks = tn.min_chunks > 2 ? tn.min_chunks : 2;
-    const bool bf16 = esize(t) == 2, narrow = C == 32 && M == 32;
-    const int longest = (bf16 ? !narrow : C == 64 && M == 64) ? 512 : 256;     // tokens per segment
+    const long waves = tn.target_waves;
+    const bool bf16 = esize(t) == 2, narrow = C == 32 && M == 32, widest = C == 64 && M == 64;
+    const int longest = (bf16 ? !narrow : widest) ? 512 : 256;     // tokens per segment
     Plan p = wave;
     // p.cps: at least make_plan's, so that there are never more segments than its
     auto at_least = [&](long chunks) { if (p.cps < chunks) p.cps = (int)chunks; };
-    const long want = (target + BH - 1) / BH;
-    at_least((p.nchunks + want - 1) / want);
+    // tokens per segment if a sequence is cut into `pieces`
+    auto tokens = [&](long pieces) {
+        long chunks = (p.nchunks + pieces - 1) / pieces;
+        if (chunks < wave.cps) chunks = wave.cps;
+        return kChunk * (chunks + (chunks & 1));
+    };
+    long pieces = BH < target ? target / BH : 1;
+    if (N > 512) {
+        const long up = (target + BH - 1) / BH;
+        if (2 * BH > target && 4 * BH < 3 * target) pieces = 2 * target / BH;
+        else if (pieces * BH < target && (up <= 3 || 10 * up * BH >= 11 * target) && tokens(pieces) > longest && tokens(up) <= longest) pieces = up;
+    }
+    at_least((p.nchunks + pieces - 1) / pieces);
     at_least(min_chunks);
     const long per_cu = target / (2 * BH);                  // segments a sequence may have at one per CU
     if (per_cu > 0) {
@@ -153,15 +183,27 @@ inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype
         if (p.cps * kChunk <= longest) return p;
         if (bf16 && !narrow) {
             wave.bwd_block = true;
-            wave.bwd_group = tn.bwd_group != 0 ? 2 : 4;
+            // four of the forward's segments each where that is within the places, else two (bf16 64 x 32,
+            // 150 x 4096: four make 600 workgroups, 1.06 of the wave kernels' step, two 0.90)
+            wave.bwd_group = tn.bwd_group != 0 || BH * ((wave.nseg + 3) / 4) > target ? 2 : 4;
         }
         return wave;
     }
-    // whole sequences: one wave per sequence (forward) fills three quarters of the machine from 1536 on,
-    // two waves per sequence (backward) nearly all of it at 1024
-    p.fwd_block = 4 * BH < 3 * (long)tn.target_waves;
-    const bool one_round = 16 * BH >= 7 * (long)tn.target_waves && 2 * BH <= tn.target_waves;
-    p.bwd_block = bf16 || !(one_round || (C == 32 && 2 * BH > tn.target_waves));
+    // whole sequences
+    if (narrow && BH < target && N > 1024) return wave;
+    if (bf16 && C == 64 && M == 32 && N > 512 && BH > target && 4 * BH <= 5 * target) return wave;
+    const bool one = p.nchunks == 1, three = p.nchunks == 3;
+    const bool one_block = N < 32 && 2 * BH >= 3 * target && (bf16 || !widest);
+    if ((one && 2 * BH >= target) || (three && BH >= target) || one_block) {
+        p.fwd_block = false;
+        p.bwd_block = bf16 && widest && (p.nchunks == 2 || (three && 2 * BH >= waves));
+        return p;
+    }
+    // one wave per sequence (forward) fills three quarters of the machine from 1536 on, two waves per sequence
+    // (backward) nearly all of it at 1024
+    p.fwd_block = bf16 && (C == 64 || narrow) ? 2 * BH < waves : 4 * BH < 3 * waves;
+    const bool one_round = 16 * BH >= 7 * waves && 2 * BH <= waves;
+    p.bwd_block = bf16 || !(one || one_round || (C == 32 && 2 * BH > waves) || (M == 32 && 10 * BH > 7 * waves));
     return p;
 }
 

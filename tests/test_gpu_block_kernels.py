@@ -148,10 +148,14 @@ def test_short_sequences_and_their_workspaces(oracle, BH, N, D, M, bf16):
     assert max(errs) <= (2e-2 if bf16 else 1e-4), errs
 
 
-def test_very_many_token_major_heads():
+def test_very_many_token_major_heads(monkeypatch):
     """[B, N, H, .] tensors with so many heads that a block of 32 tokens spans more than 4 GB, beyond what the
     workgroup kernels address: a few heads of the call against the same heads on their own."""
-    import paper_2006_16236_amd as la
+    with block_kernels(monkeypatch, "1", "default") as la:
+        very_many_token_major_heads(la)
+
+
+def very_many_token_major_heads(la):
     H, N, D = 1 << 19, 33, 64
     g = torch.Generator(DEV).manual_seed(8700)
     q, k, v, dO = (torch.randn(1, N, H, D, device=DEV, generator=g) for _ in range(4))

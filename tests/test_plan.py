@@ -81,4 +81,25 @@ def test_very_many_heads_keep_the_wave_kernels(plans):
                         elif block == 1:
                             assert p["fwd_block"] and p["bwd_block"], (H, kw, p)
     # fp32 64 x 64 beyond one round of sequences is the workgroup kernels' by default: the case that overflowed
-    assert plans([(4096, 33, 64, 64, F32, dict(heads=4096))])[0]["bwd_block"] == 1
+    assert plans([(4096, 64, 64, 64, F32, dict(heads=4096))])[0]["bwd_block"] == 1
+
+
+def test_no_nearly_empty_second_round(plans):
+    """Two workgroups per CU have a place, 512 in all: sequences long enough to be cut are not cut into a few
+    workgroups more than that."""
+    calls = [(BH, N, C, M, t, {}) for BH in range(1, 512) for N in (520, 1100, 2048, 3524, 7942, 20000)
+             for C, M, t in ((64, 64, F32), (64, 64, BF16), (32, 32, F32), (64, 32, BF16))]
+    for call, p in zip(calls, plans(calls)):
+        BH, N, C, M, t, _ = call
+        if p["fwd_block"]:
+            assert p["nseg"] <= 3 or not 512 < BH * p["nseg"] < 563, (call, p)
+        elif p["bwd_block"] and p["bwd_group"] == 4:         # the forward's segments four at a time
+            assert BH * -(-p["nseg"] // 4) <= 512, (call, p)
+
+
+def test_half_empty_blocks_of_many_sequences(plans):
+    """One chunk or three fill half of their last 32-token block: the wave kernels' forward takes them."""
+    calls = [(BH, N, C, M, t, {}) for BH in (512, 700, 1023, 1024, 2000) for N in (1, 16, 33, 48)
+             for C, M in ((64, 64), (32, 32), (64, 32), (32, 64)) for t in (F32, BF16)]
+    assert not any(p["fwd_block"] for p in plans(calls))
+    assert all(p["fwd_block"] for p in plans([(BH, N, 64, 64, F32, {}) for BH in (1, 8, 255) for N in (1, 16, 33, 48, 64)]))
