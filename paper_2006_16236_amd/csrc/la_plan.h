@@ -104,7 +104,9 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 // As many segments as fill the machine, not one more: 52 sequences of 3524 tokens in 10 pieces are 520 workgroups
 // for 512 places, and the step took 289 us (wave kernels 222, 9 pieces 218).  One piece more only where the
 // shorter segments are within the lines above and the second round is not nearly empty, or three pieces in all
-// (two / three pieces: 200 x 1340 fp32 430/333, 175 x 1248 324/287); 257 to 383 sequences, which alone leave a third of the places empty, in
+// (two / three pieces: 200 x 1340 fp32 430/333, 175 x 1248 324/287; six of 96 x 2944, 576 workgroups, bf16
+// forward 46 -> 64); bf16 32 x 32 heads, of which a CU holds four workgroups, may always have it
+// (211 x 480 step 46/41).  257 to 383 sequences, which alone leave a third of the places empty, in
 // three or two pieces (fp32 D = M = 64, 257 .. 320: whole 0.92 of the wave kernels' time, two 0.87, three 0.76).
 // Short segments: where one workgroup per CU does with at most eight chunks each (ten for one segment per
 // sequence, four where a sequence has more than four segments), two per CU gain nothing and double the
@@ -129,7 +131,7 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 // is not hidden (fp32 979 x 16 forward 5.5/9.7, bf16 1260 x 40 9.7/13.8; three chunks of bf16 D = M = 64 keep
 // the backward, 0.78 of the wave kernels' time at 1100 .. 1400 x 33 .. 48); one whole block loses its pipeline
 // of the next, and if it is not full (17 .. 31 tokens, from 768 sequences on) the wave kernels are ahead (forward
-// 1.06 .. 1.14, step 1.00 .. 1.07; not fp32 D = M = 64, 0.8 .. 1.01).
+// 1.06 .. 1.14, step 1.00 .. 1.07; fp32 D = M = 64 beyond 1024 not, 0.8).
 // Left as they are: 257 .. 383 sequences of 257 .. 512 narrow tokens (step 0.81 .. 1.16 of the wave kernels' time,
 // forward 0.67 .. 0.95) and fp32 32-wide D, 513 .. 700 sequences of more than 512 tokens (step 1.01 .. 1.10,
 // forward 0.70 .. 0.88): every plan that helps the one harms the other.
@@ -156,11 +158,11 @@ inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype
         if (chunks < wave.cps) chunks = wave.cps;
         return kChunk * (chunks + (chunks & 1));
     };
-    long pieces = BH < target ? target / BH : 1;
+    const long up = (target + BH - 1) / BH;
+    long pieces = bf16 && narrow ? up : BH < target ? target / BH : 1;
     if (N > 512) {
-        const long up = (target + BH - 1) / BH;
         if (2 * BH > target && 4 * BH < 3 * target) pieces = 2 * target / BH;
-        else if (pieces * BH < target && (up <= 3 || 10 * up * BH >= 11 * target) && tokens(pieces) > longest && tokens(up) <= longest) pieces = up;
+        else if ((up <= 3 || 7 * up * BH >= 8 * target) && tokens(pieces) > longest && tokens(up) <= longest) pieces = up;
     }
     at_least((p.nchunks + pieces - 1) / pieces);
     at_least(min_chunks);
@@ -193,7 +195,7 @@ inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype
     if (narrow && BH < target && N > 1024) return wave;
     if (bf16 && C == 64 && M == 32 && N > 512 && BH > target && 4 * BH <= 5 * target) return wave;
     const bool one = p.nchunks == 1, three = p.nchunks == 3;
-    const bool one_block = N < 32 && 2 * BH >= 3 * target && (bf16 || !widest);
+    const bool one_block = N < 32 && 2 * BH >= 3 * target && (bf16 || !widest || 2 * BH <= waves);
     if ((one && 2 * BH >= target) || (three && BH >= target) || one_block) {
         p.fwd_block = false;
         p.bwd_block = bf16 && widest && (p.nchunks == 2 || (three && 2 * BH >= waves));

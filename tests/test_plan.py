@@ -88,11 +88,11 @@ def test_no_nearly_empty_second_round(plans):
     """Two workgroups per CU have a place, 512 in all: sequences long enough to be cut are not cut into a few
     workgroups more than that."""
     calls = [(BH, N, C, M, t, {}) for BH in range(1, 512) for N in (520, 1100, 2048, 3524, 7942, 20000)
-             for C, M, t in ((64, 64, F32), (64, 64, BF16), (32, 32, F32), (64, 32, BF16))]
+             for C, M, t in ((64, 64, F32), (64, 64, BF16), (32, 64, F32), (64, 32, BF16))]
     for call, p in zip(calls, plans(calls)):
         BH, N, C, M, t, _ = call
         if p["fwd_block"]:
-            assert p["nseg"] <= 3 or not 512 < BH * p["nseg"] < 563, (call, p)
+            assert p["nseg"] <= 3 or not 512 < BH * p["nseg"] < 585, (call, p)
         elif p["bwd_block"] and p["bwd_group"] == 4:         # the forward's segments four at a time
             assert BH * -(-p["nseg"] // 4) <= 512, (call, p)
 
