@@ -74,12 +74,16 @@
  *              segments per sequence the passes add up the segment totals
  *              themselves and no scan kernel runs), LA_BWD_SEG_GROUP (1 or 2:
  *              how many of the forward's segments a workgroup of the backward
- *              takes; default 1 for 32 x 32 heads, else 2), LA_STREAM_LOADS
- *              (1: non-temporal instead of plain loads of the tensors) and
- *              LA_BLOCK_KERNELS (the causal calls' workgroup kernels on
- *              32-token blocks: 0 never, 1 always, default by size).
+ *              takes; default with the wave kernels 1 for 32 x 32 heads, else
+ *              2, with the workgroup kernels 1, and for long bf16 sequences, whose
+ *              forward keeps the wave kernels, 4 or 2 by how many workgroups
+ *              that makes), LA_STREAM_LOADS (1: non-temporal instead of plain
+ *              loads of the tensors) and LA_BLOCK_KERNELS (the causal calls'
+ *              workgroup kernels on 32-token blocks: 0 never, 1 wherever they
+ *              can address the tensors, default by size).
  *              Sequences are not cut at all once B*H reaches half of
- *              LA_TARGET_WAVES.  The environment is read once per process, by
+ *              LA_TARGET_WAVES; the workgroup kernels also leave them whole up
+ *              to 64 tokens, and up to 512 once B*H reaches an eighth of it.  The environment is read once per process, by
  *              the first workspace query or entry point, so a query and the
  *              calls that use its workspace see the same values;
  *              la_tuning_reload() reads it again.

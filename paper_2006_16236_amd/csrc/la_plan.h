@@ -187,7 +187,12 @@ inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype
             wave.bwd_block = true;
             // four of the forward's segments each where that is within the places, else two (bf16 64 x 32,
             // 150 x 4096: four make 600 workgroups, 1.06 of the wave kernels' step, two 0.90)
-            wave.bwd_group = tn.bwd_group != 0 || BH * ((wave.nseg + 3) / 4) > target ? 2 : 4;
+            wave.bwd_group = tn.bwd_group != 0 ? (tn.bwd_group == 1 ? 1 : 2) : BH * ((wave.nseg + 3) / 4) > target ? 2 : 4;
+            if (wave.bwd_group == 1) {       // its workgroups take whole blocks
+                wave.cps += wave.cps & 1;
+                wave.nseg = (wave.nchunks + wave.cps - 1) / wave.cps;
+                wave.fold = wave.nseg > 1 && wave.nseg <= tn.fold_max;
+            }
         }
         return wave;
     }

@@ -250,3 +250,16 @@ def test_gradient_for_z0_is_an_fp32_sum(monkeypatch, D, M, bf16, on):
     terms = delta[..., None] * phi
     err = (dz0.double() - terms.sum(2)).abs() / terms.abs().sum(2)
     assert float(err.max()) <= 2.0 ** -20
+
+
+@pytest.mark.parametrize("group", [None, 1, 2])
+@pytest.mark.parametrize("D,M,N", [(64, 64, 5000), (64, 32, 5009), (32, 64, 4991)])
+def test_workgroup_backward_on_the_wave_kernels_cut(oracle, D, M, N, group):
+    """bf16 sequences in segments of more than 512 tokens: the wave kernels' forward, the workgroup kernels'
+    backward on one, two or four of its segments (odd numbers of chunks among them)"""
+    import paper_2006_16236_amd as la
+    host = maybe_bf16(wl.random_case(9000 + N, 1, 3, N, D, M), True)
+    with schedule(target_waves=24, bwd_seg_group=group):
+        (O, *grads), _ = run(la, [to_dev(x, True) for x in host], 1e-6)
+    assert rel_err(O, oracle.causal_fwd_prefix(*host[:3], 1e-6)) <= 2e-2
+    assert max(grad_errs(grads, oracle.causal_bwd_linear(*host, 1e-6))) <= 2e-2

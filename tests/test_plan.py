@@ -103,3 +103,19 @@ def test_half_empty_blocks_of_many_sequences(plans):
              for C, M in ((64, 64), (32, 32), (64, 32), (32, 64)) for t in (F32, BF16)]
     assert not any(p["fwd_block"] for p in plans(calls))
     assert all(p["fwd_block"] for p in plans([(BH, N, 64, 64, F32, {}) for BH in (1, 8, 255) for N in (1, 16, 33, 48, 64)]))
+
+
+def test_a_requested_segment_group_is_honoured(plans):
+    """LA_BWD_SEG_GROUP = 1 or 2 holds for every plan that cuts its sequences, the wave kernels' forward with the
+    workgroup kernels' backward (long bf16 sequences) among them."""
+    rng = random.Random(2)
+    for group in (1, 2):
+        calls = [(int(2 ** rng.uniform(0, 9)), int(2 ** rng.uniform(9, 17)), *rng.choice(((64, 64), (32, 32), (64, 32), (32, 64))),
+                  rng.choice((F32, BF16)), dict(group=group, block=rng.choice((-1, 0, 1)))) for _ in range(3000)]
+        mixed = 0
+        for call, p in zip(calls, plans(calls)):
+            if p["nseg"] > 1:
+                assert p["bwd_group"] == group, (call, p)
+                mixed += p["bwd_block"] and not p["fwd_block"]
+                assert not p["bwd_block"] or p["cps"] * group % 2 == 0, (call, p)
+        assert mixed > 100
