@@ -263,3 +263,47 @@ def test_workgroup_backward_on_the_wave_kernels_cut(oracle, D, M, N, group):
         (O, *grads), _ = run(la, [to_dev(x, True) for x in host], 1e-6)
     assert rel_err(O, oracle.causal_fwd_prefix(*host[:3], 1e-6)) <= 2e-2
     assert max(grad_errs(grads, oracle.causal_bwd_linear(*host, 1e-6))) <= 2e-2
+
+
+@pytest.mark.parametrize("sched", ["default", "many_segments"])
+@pytest.mark.parametrize("kind", ["f32", "bf16"])
+@pytest.mark.parametrize("D,M", [(64, 64), (32, 32), (64, 32), (32, 64)])
+def test_states_against_fp64(monkeypatch, kind, D, M, sched):
+    """The states a call returns and the gradients for the ones it took, from the workgroup kernels, against
+    fp64 from the same (rounded) inputs; every error measured against the sum of the sizes of the terms.
+    fp32: products exact to 2^-23, sums of 301 terms in runs of 32 and over segments: 2^-20; twice that behind
+    delta.  bf16: phi(K) in two parts in S1 (2^-17 per term, V exact): 2^-16; phi(Q) and dO / den in two parts,
+    their smallest product dropped, in dS0: 2^-15; behind delta in dz0 another four such cuts (dO / den, S, the
+    scores, phi(K)): 2^-14.  A part lost anywhere (2^-9) is far outside."""
+    B, H, N, bf16 = 1, 2, 301, kind == "bf16"
+    dev = [to_dev(x, bf16) for x in maybe_bf16(wl.random_case(9100 + D + 2 * M, B, H, N, D, M), bf16)]
+    q, k, v, g = dev
+    gen = torch.Generator(DEV).manual_seed(6)
+    S0, z0 = (torch.rand(s, device=DEV, generator=gen) * 8 for s in ((B, H, D, M), (B, H, D)))
+    dS1, dz1 = (torch.randn(s, device=DEV, generator=gen) for s in ((B, H, D, M), (B, H, D)))
+    with block_kernels(monkeypatch, "1", sched) as la:
+        O, den = torch.empty_like(v), torch.empty(B, H, N, device=DEV)
+        S1, z1, dS0, dz0 = (torch.full_like(x, float("nan")) for x in (S0, z0, S0, z0))
+        ws = la.la_causal_fwd_state(q, k, v, O, den, S0, z0, S1, z1, 1e-6)
+        grads = [torch.empty_like(x) for x in (q, k, v)]
+        la.la_causal_bwd_state(q, k, v, None, den, g, *grads, S0, z0, dS1, dz1, dS0, dz0, 1e-6, fwd_ws=ws)
+        torch.cuda.synchronize()
+    x = [t.cpu().double() for t in (*dev, S0, z0, dS1, dz1)]
+    q, k, v, g, s0, zz0, ds1, dzz1 = x
+    fq, fk = (torch.where(t > 0, t + 1, torch.exp(t)) for t in (q, k))
+
+    def states(a, b, start):                      # running sums of a b^T behind `start`, after every token
+        return start[:, :, None] + torch.cumsum(a[..., :, None] * b[..., None, :], 2)
+
+    z = zz0[:, :, None] + torch.cumsum(fk, 2)
+    dn = (fq * z).sum(-1, keepdim=True) + 1e-6
+    gd = g / dn
+    S, Sabs = states(fk, v, s0), states(fk, v.abs(), s0)
+    delta = -(fq * (S @ gd[..., None])[..., 0]).sum(-1, keepdim=True) / dn
+    dabs = (fq * (Sabs @ gd.abs()[..., None])[..., 0]).sum(-1, keepdim=True) / dn
+    want = {"S1": (S1, S[:, :, -1], Sabs[:, :, -1], 20, 16), "z1": (z1, z[:, :, -1], z[:, :, -1], 20, 20),
+            "dS0": (dS0, ds1 + fq.transpose(2, 3) @ gd, ds1.abs() + fq.transpose(2, 3) @ gd.abs(), 20, 15),
+            "dz0": (dz0, dzz1 + (delta * fq).sum(2), dzz1.abs() + (dabs * fq).sum(2), 19, 14)}
+    for name, (got, ref, size, bits, bits16) in want.items():
+        err = float(((got.cpu().double() - ref).abs() / size).max())
+        assert err <= 2.0 ** -(bits16 if bf16 else bits), (name, err)
