@@ -12,7 +12,7 @@
 // split once instead of once per product that reads it, the state once per 32 tokens instead of
 // 16, and a quarter as many segments fill the machine (512 workgroups): a state of 16.6 KB per
 // segment less to write, scan and read, and fewer starts of the chain state - first tile - products.
-// Measured (dQ / dV + dK in us): bf16 B*H = 16, N = 65536: 235 / 231 -> 198 / 190; fp32 B*H = 32,
+// Measured (dQ / dV + dK in us): bf16 B*H = 16, N = 65536: 235 / 231 -> 200 / 197; fp32 B*H = 32,
 // N = 3072: 39.8 / 37.5 -> 38 / 35.6; fp32 B*H = 32, N = 1024: 24.9 / 23.5 -> 17.2 / 16.1.
 //
 // Four "out" roles form the outputs (one per half of the tokens and half of the columns, or dV and

@@ -99,13 +99,15 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 //   fp32, 64 x 32      16 x 65536   734/800    16 x 16384  183/194   16 x 8192  111/110
 //   fp32, 32 x 64      16 x 65536   703/735    16 x 16384  174/178   16 x 8192  108/100
 // so the line lies at 512 tokens per segment (fp32 with D = M = 64, bf16 with a 64-wide head dimension) or
-// 256.  Above it bf16 tensors with a 64-wide head dimension keep the wave kernel in the forward only
-// (114/158 us at 16 x 65536, backward 476/396).
+// 256.  (Those figures are of cuts that rounded up, see below.  Of cuts that do not, drawn sizes of 257 .. 512
+// tokens per segment with a 32-wide D or M take 0.87 .. 0.94 of the wave kernels' step and 0.85 .. 1.02 of their
+// forward: the line of these heads could lie higher.)  Above it bf16 tensors with a 64-wide head dimension keep the wave kernel in the forward only
+// (114/158 us at 16 x 65536, backward 476/400).
 // As many segments as fill the machine, not one more: 52 sequences of 3524 tokens in 10 pieces are 520 workgroups
 // for 512 places, and the step took 289 us (wave kernels 222, 9 pieces 218).  One piece more only where the
 // shorter segments are within the lines above and the second round is not nearly empty, or three pieces in all
 // (two / three pieces: 200 x 1340 fp32 430/333, 175 x 1248 324/287; six of 96 x 2944, 576 workgroups, bf16
-// forward 46 -> 64); bf16 32 x 32 heads, of which a CU holds four workgroups, may always have it
+// forward 46 -> 64); bf16 32 x 32 heads, of which a CU holds three or four workgroups, may always have it
 // (211 x 480 step 46/41).  257 to 383 sequences, which alone leave a third of the places empty, in
 // three or two pieces (fp32 D = M = 64, 257 .. 320: whole 0.92 of the wave kernels' time, two 0.87, three 0.76).
 // Short segments: where one workgroup per CU does with at most eight chunks each (ten for one segment per
