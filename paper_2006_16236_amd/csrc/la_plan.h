@@ -131,9 +131,13 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 //   bf16 64 x 32, 513 .. 640 of more than 512 tokens (wave kernels in several pieces)  step 1.06, forward 1.08
 // A block is 32 tokens: of one chunk, or three, half a block is padding, and from 256 or 512 sequences on that
 // is not hidden (fp32 979 x 16 forward 5.5/9.7, bf16 1260 x 40 9.7/13.8; three chunks of bf16 D = M = 64 keep
-// the backward, 0.78 of the wave kernels' time at 1100 .. 1400 x 33 .. 48); one whole block loses its pipeline
-// of the next, and if it is not full (17 .. 31 tokens, from 768 sequences on) the wave kernels are ahead (forward
-// 1.06 .. 1.14, step 1.00 .. 1.07; fp32 D = M = 64 beyond 1024 not, 0.8).
+// the backward, 0.78 of the wave kernels' time at 1100 .. 1400 x 33 .. 48).  One block in all has no next one to
+// fetch meanwhile: from 769 sequences on (a fourth per CU) workgroup / wave kernels, 24 tokens
+//   bf16 D = M = 64  forward 1.21, step with only the backward by workgroups 0.98, beyond 1024 0.81;  other heads 1.12 .. 1.27,
+//   0.98 .. 1.06, from 1536 on 0.91 .. 1.05
+//   fp32 D = M = 64  forward 1.07, step with the wave backward 0.92, beyond 1024 with either 0.83;  other heads 1.06 .. 1.20,
+//   0.95 .. 1.06, beyond 1024 forward 0.91 .. 1.00
+// (768 sequences: all 0.83 .. 0.97 but the bf16 forward, 0.99 .. 1.08).
 // Left as they are: 257 .. 383 sequences of 257 .. 512 narrow tokens (step 0.81 .. 1.16 of the wave kernels' time,
 // forward 0.67 .. 0.95) and fp32 32-wide D, 513 .. 700 sequences of more than 512 tokens (step 1.01 .. 1.10,
 // forward 0.70 .. 0.88): every plan that helps the one harms the other.
@@ -202,10 +206,14 @@ inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype
     if (narrow && BH < target && N > 1024) return wave;
     if (bf16 && C == 64 && M == 32 && N > 512 && BH > target && 4 * BH <= 5 * target) return wave;
     const bool one = p.nchunks == 1, three = p.nchunks == 3;
-    const bool one_block = N < 32 && 2 * BH >= 3 * target && (bf16 || !widest || 2 * BH <= waves);
-    if ((one && 2 * BH >= target) || (three && BH >= target) || one_block) {
+    if ((one && 2 * BH >= target) || (three && BH >= target)) {
         p.fwd_block = false;
-        p.bwd_block = bf16 && widest && (p.nchunks == 2 || (three && 2 * BH >= waves));
+        p.bwd_block = bf16 && widest && three && 2 * BH >= waves;
+        return p;
+    }
+    if (p.nchunks == 2 && 2 * BH > 3 * target && (bf16 ? 4 * BH < 3 * waves : 2 * BH <= waves)) {
+        p.fwd_block = !bf16 && widest;
+        p.bwd_block = bf16 && widest;
         return p;
     }
     // one wave per sequence (forward) fills three quarters of the machine from 1536 on, two waves per sequence
