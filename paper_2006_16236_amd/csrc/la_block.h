@@ -432,6 +432,10 @@ __device__ __forceinline__ void blk_chain(const float *rows, const T *raw, T *ou
 // (between the barriers), finish (after the second: outputs leave).
 template <typename Tiles, typename... Role>
 __device__ __forceinline__ void blk_loop(Tiles &tiles, const int first, const int dir, const int count, Role &...role) {
+    // Nothing is in flight here, but the compiler's count of it does not know which role's code a wave has come
+    // through: without this the out roles' products of the bf16 forward and dV + dK pass wait, block after block, for
+    // registers of the state roles' fetch, that is for their own.
+    __builtin_amdgcn_s_waitcnt(0x0f70);           // vmcnt(0)
     tiles.fetch(first);
     (role.fetch(first), ...);
     (role.init(), ...);
@@ -763,7 +767,13 @@ struct DqOut : BlkLane {
     __device__ __forceinline__ void init() {}
     __device__ __forceinline__ void publish() {}
     __device__ __forceinline__ void fetch(int blk) { nden = den[min(blk * kBlk + row, N - 1)]; }
-    __device__ __forceinline__ void parked(int blk) { rd = __builtin_amdgcn_rcpf(nden); }
+    // Kept ahead of the next fetch: sunk behind it, the old and the new denominator take two registers, and the copy
+    // from one to the other waits for the fetch that has just been sent, a trip to memory per block (dQ pass, fp32
+    // B*H = 16, N = 65536: 381 -> 334 us; bf16 206 -> 190)
+    __device__ __forceinline__ void parked(int blk) {
+        rd = __builtin_amdgcn_rcpf(nden);
+        asm volatile("" : "+v"(rd));
+    }
     __device__ __forceinline__ void products() {
         const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
         // scores (dO_a/den_a) . V_b: rows b, lane (c = a)
