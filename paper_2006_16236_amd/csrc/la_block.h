@@ -4,7 +4,7 @@
 // the table there) on the bf16 matrix pipe only: every operand is cut into its bf16 parts ONCE,
 // when its tile is parked in LDS, and the waves of the workgroup read it from there in whichever
 // of the two orders a product needs.  fp32 tensors take three parts (exact, see split3), bf16
-// tensors two (and V, exact in bf16, one).
+// tensors two (V and dO, exact in bf16, one).
 //
 // What bounds these kernels: a SIMD's bf16 MFMAs and vector instructions hardly overlap (24 MFMAs
 // 165 ns, 144 fp32 instructions 158 ns, both 295 ns, four waves), so their times add, and both
@@ -212,6 +212,12 @@ template <typename T> constexpr int kVParts = is_bf16<T> ? 1 : 3;
 // besides the products of P parts their feature values are needed in full, for phi' and for the sums that
 // stay fp32, den in the forward, z and delta in the dQ pass, rho in the reverse pass.
 // kLead: the pass, by the tensor whose gradient it ends in (kLeadQK: the forward, no dO there).
+// bf16 backward (kRaw): dO stays as it is, one exact part, and 1/den goes with phi(Q) where a product needs it
+// (every sum over tokens a takes dO_a and phi(Q_a) together) or to the finished row.  And the pass that needs a
+// tensor's feature values in full per token (phi(Q) in the dQ pass, phi(K) in the other) reads them from an fp32
+// plane, not from three parts.  Against dO/den in two parts and three parts throughout: 44 instead of 56 products
+// per SIMD and block in the dQ pass and 3/4 of the vector instructions, of which either kind costs its own issue
+// time (bf16 step, B*H = 16, N = 65536: 608 -> 570 us; B*H = 32, N = 3072, through autograd: 79 -> 74).
 // A 32 x F block is fetched in quads of four elements, one or two per thread: quad k of thread t is
 // row row(t) + k * kStep, columns col(t) .. + 3 (a wave reads whole rows).  Where a block has fewer quads
 // than there are threads, the two blocks of a pair (Q and K, or dO and V) take half of them each.
@@ -219,24 +225,28 @@ enum Lead { kLeadQ = 0, kLeadK = 1, kLeadQK = 2 };
 template <int kLead, int D, int M, typename T, bool kStrided>
 struct BlkTiles {
     static constexpr int kWaves = kLead == kLeadQK ? kFwdWaves : kBwdWaves<D, M, T>, kThreads = kWave * kWaves;
-    static constexpr int P = kOpParts<T>, PV = kVParts<T>, PQ = 3, PK = 3;
-    static constexpr bool kG = kLead != kLeadQK;
-    static constexpr int kElems = (PQ + PK) * kBlk * D + (PV + (kG ? P : 0)) * kBlk * M;
+    static constexpr bool kG = kLead != kLeadQK, kRaw = kG && is_bf16<T>;
+    static constexpr int P = kOpParts<T>, PV = kVParts<T>, PG = kRaw ? 1 : P;
+    static constexpr int PQ = kRaw && kLead == kLeadQ ? 2 : 3, PK = kRaw && kLead == kLeadK ? 2 : 3;
+    static constexpr int kPlaneElems = kRaw ? 2 * kBlk * D : 0;
+    static constexpr int kElems = (PQ + PK) * kBlk * D + (PV + (kG ? PG : 0)) * kBlk * M + kPlaneElems;
+    static constexpr int S = kRaw ? D : M;  // width of the tensor whose rows are scaled
     template <int F> static constexpr int kQuads = 8 * F > kThreads ? 8 * F / kThreads : 1;
     template <int F> static constexpr int kStep = 4 * kThreads / F;
     template <int F> static constexpr bool kShared = 8 * F < kThreads;
     template <int F> static __device__ __forceinline__ int row(int tid) { return (tid % (8 * F)) / (F / 4); }
     template <int F> static __device__ __forceinline__ int col(int tid) { return 4 * (tid % (F / 4)); }
 
-    uint16_t *sq, *sk, *sv, *sg;            // phi(Q), phi(K), V, dO/den
+    uint16_t *sq, *sk, *sv, *sg;            // phi(Q), phi(K), V, dO/den; kRaw: phi(Q)/den, phi(K), V, dO
+    float *sf;                              // kRaw: phi(Q) (kLeadQ) or phi(K), fp32
     const T *Qs, *Ks, *Vs, *Gs;
-    const float *scale;                     // of the rows of dO: den (kLeadQ, its reciprocal is taken) or 1/den
+    const float *scale;                     // of the rows of dO or Q: den (kLeadQ, its reciprocal is taken) or 1/den
     int N, tid, half, tsd, tsm;
     bool nt;
     int offd, offm;                         // bytes
     int qd, qm;
     staged_t<T> fq[kQuads<D>], fk[kQuads<D>], fv[kQuads<M>], fg[kQuads<M>];
-    float sc[kQuads<M>];
+    float sc[kQuads<S>];
     // polynomial map: feature 8i + j = x_i x_j; fq, fk hold x_j .. x_j+3 of a quad, xq, xk its x_i
     static constexpr int W = qk_width<T>(D);
     float xq[kQuads<D>], xk[kQuads<D>];
@@ -246,6 +256,7 @@ struct BlkTiles {
         : N(a.N), tid(tid_), half(wave >= kWaves / 2), tsd(tok_stride<kStrided>(a.tok_heads, qk_width<T>(D))),
           tsm(tok_stride<kStrided>(a.tok_heads, M)), nt(a.stream != 0) {
         sq = lds, sk = sq + PQ * kBlk * D, sv = sk + PK * kBlk * D, sg = sv + PV * kBlk * M;
+        if constexpr (kRaw) sf = reinterpret_cast<float *>(sg + PG * kBlk * M);
         Qs = static_cast<const T *>(a.Q) + seq_base<kStrided>(a.N, a.heads, bh, W);
         Ks = static_cast<const T *>(a.K) + seq_base<kStrided>(a.N, a.heads, bh, W);
         Vs = static_cast<const T *>(a.V) + seq_base<kStrided>(a.N, a.heads, bh, M);
@@ -267,12 +278,12 @@ struct BlkTiles {
     }
     template <int kAux>
     __device__ __forceinline__ void load_all(const int t0, const int nv) {
-        if (kG && mine<M>(0)) {
+        if (kG && mine<S>(0)) {
             const Rows r = rows_of(scale + t0, 1, nv);
 #pragma unroll
-            for (int k = 0; k < kQuads<M>; ++k) sc[k] = rows_load1(r, 4 * (row<M>(tid) + k * kStep<M>));
-            load<M, kAux>(Gs + (size_t)t0 * tsm, offm, tsm, nv, fg);
+            for (int k = 0; k < kQuads<S>; ++k) sc[k] = rows_load1(r, 4 * (row<S>(tid) + k * kStep<S>));
         }
+        if (kG && mine<M>(0)) load<M, kAux>(Gs + (size_t)t0 * tsm, offm, tsm, nv, fg);
         if (mine<M>(1)) load<M, kAux>(Vs + (size_t)t0 * tsm, offm, tsm, nv, fv);
         if (mine<D>(0)) load<D, kAux>(Qs + (size_t)t0 * tsd, offd, tsd, nv, fq);
         if (mine<D>(1)) load<D, kAux>(Ks + (size_t)t0 * tsd, offd, tsd, nv, fk);
@@ -291,7 +302,12 @@ struct BlkTiles {
         else load_all<0>(t0, nv);
     }
 
-    template <int F, int PT, int MAP_, bool kFull>
+    // where the fp32 plane holds columns 4 * piece .. + 3 of a row: the pieces of sixteen rows spread over all banks
+    static __device__ __forceinline__ int plane_at(int row, int piece) {
+        return row * D + ((piece ^ (D == 64 ? row & 15 : (row >> 1) & 7)) << 2);
+    }
+    // kKeep: the mapped values go to the fp32 plane too; kBy: their rows are scaled by `by` before they are cut
+    template <int F, int PT, int MAP_, bool kFull, bool kKeep = false, bool kBy = false>
     __device__ __forceinline__ void put(uint16_t *tile, int at, const staged_t<T> (&st)[kQuads<F>], const float *by, int nv) const {
         constexpr int MAP = is_poly<T> && MAP_ == kMapPhi ? kMapScale : is_feat<T> && MAP_ == kMapPhi ? kMapId : MAP_;
         if constexpr (PT == 1 && MAP == kMapId && is_bf16<T>) {         // as it is
@@ -304,11 +320,15 @@ struct BlkTiles {
 #pragma unroll
             for (int k = 0; k < kQuads<F>; ++k) {
                 const f32x4 w = widen(st[k]);
+                const int at_row = row<F>(tid) + k * kStep<F>;
+                f32x4 kept;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float m = map_value<MAP>(w[r], MAP == kMapScale ? by[k] : 1.0f);
-                    v[k][r] = kFull || row<F>(tid) + k * kStep<F> < nv ? m : 0.0f;
+                    kept[r] = kFull || at_row < nv ? m : 0.0f;
+                    v[k][r] = !kBy ? kept[r] : kFull || at_row < nv ? m * by[k] : 0.0f;
                 }
+                if constexpr (kKeep) *reinterpret_cast<f32x4 *>(sf + plane_at(at_row, col<F>(tid) >> 2)) = kept;
             }
             u32x2_t s[kQuads<F>][PT];
             split_batch<PT>(v, s);
@@ -318,21 +338,24 @@ struct BlkTiles {
     }
     template <bool kFull>
     __device__ __forceinline__ void put_all(const int nv) {
-        if (kG && mine<M>(0)) {
-            if constexpr (kLead == kLeadQ) {
+        if (kLead == kLeadQ && mine<S>(0)) {
 #pragma unroll
-                for (int k = 0; k < kQuads<M>; ++k) sc[k] = __builtin_amdgcn_rcpf(sc[k]);
-            }
-            put<M, P, kMapScale, kFull>(sg, qm, fg, sc, nv);
+            for (int k = 0; k < kQuads<S>; ++k) sc[k] = __builtin_amdgcn_rcpf(sc[k]);
         }
+        if (kG && mine<M>(0)) put<M, PG, kRaw ? kMapId : kMapScale, kFull>(sg, qm, fg, sc, nv);
         if (mine<M>(1)) put<M, PV, kG ? kMapId : kMapFinite, kFull>(sv, qm, fv, nullptr, nv);
-        if (mine<D>(0)) put<D, PQ, kMapPhi, kFull>(sq, qd, fq, xq, nv);
-        if (mine<D>(1)) put<D, PK, kMapPhi, kFull>(sk, qd, fk, xk, nv);
+        if (mine<D>(0)) put<D, PQ, kMapPhi, kFull, kRaw && kLead == kLeadQ, kRaw>(sq, qd, fq, kRaw ? sc : xq, nv);
+        if (mine<D>(1)) put<D, PK, kMapPhi, kFull, kRaw && kLead == kLeadK>(sk, qd, fk, xk, nv);
     }
     __device__ __forceinline__ void park(const int blk) {
         const int nv = min(kBlk, N - blk * kBlk);
         if (nv == kBlk) put_all<true>(nv);
         else put_all<false>(nv);
+    }
+    // feature values of the pass's tensor in full, columns 4 * piece .. + 3 of a row
+    __device__ __forceinline__ f32x4 full_values(int row, int piece) const {
+        if constexpr (kRaw) return *reinterpret_cast<const f32x4 *>(sf + plane_at(row, piece));
+        else return get_parts3<D>(kLead == kLeadQ ? sq : sk, kBlk * D, row, 4 * piece);
     }
 };
 // accumulator tiles of a carried state, cut and published (rows = columns of the tiles)
@@ -733,7 +756,7 @@ __global__ __launch_bounds__((kWave * kFwdWaves)) __attribute__((amdgpu_waves_pe
 template <int D, int M, typename T, bool kStrided>
 struct DqOut : BlkLane {
     using Tiles = BlkTiles<kLeadQ, D, M, T, kStrided>;
-    static constexpr int P = Tiles::P, PV = Tiles::PV, NT = D / 32, SM = M / 32;
+    static constexpr int P = Tiles::P, PV = Tiles::PV, PG = Tiles::PG, NT = D / 32, SM = M / 32;
     static constexpr bool kPair = is_bf16<T> && NT == 2;
     using OutTile = OutRows<T, NT>;
     const Tiles &tl;
@@ -776,9 +799,9 @@ struct DqOut : BlkLane {
     }
     __device__ __forceinline__ void products() {
         const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-        // scores (dO_a/den_a) . V_b: rows b, lane (c = a)
-        Op<P> gt[SM];
-        read_toks<M, P>(tl.sg, kBlk * M, row, g, gt);
+        // scores (dO_a/den_a) . V_b (kRaw: dO_a . V_b, and the whole row waits for its 1/den): rows b, lane (c = a)
+        Op<PG> gt[SM];
+        read_toks<M, PG>(tl.sg, kBlk * M, row, g, gt);
         f32x4 w0, w1 = zero4;
         {
             Op<PV> vt[SM];
@@ -815,7 +838,7 @@ struct DqOut : BlkLane {
             mma_n(kf, wo, o);
             out[y] = o[0];
             cz[y] = cc[0];
-            fq[y] = get_parts3<D>(tl.sq, kBlk * D, row, col_of<kPair>(h * NT + y, 4 * g));
+            fq[y] = tl.full_values(row, col_of<kPair>(h * NT + y, 4 * g) >> 2);
 #pragma unroll
             for (int r = 0; r < 4; ++r) p = fmaf(out[y][r], fq[y][r], p);
         }
@@ -824,13 +847,15 @@ struct DqOut : BlkLane {
     }
     __device__ __forceinline__ void finish(int blk) {
         const int t0 = blk * kBlk, nv = min(kBlk, N - t0);
-        const float d = row < nv ? -(sdel[i][0][c] + sdel[i][1][c]) * rd : 0.f;
+        const float dr = row < nv ? -(sdel[i][0][c] + sdel[i][1][c]) * rd : 0.f;     // kRaw: delta den
+        const float d = Tiles::kRaw ? (row < nv ? dr * rd : 0.f) : dr;
 #pragma unroll
         for (int y = 0; y < NT; ++y)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 rho[y][r] = fmaf(d, fq[y][r], rho[y][r]);
-                out[y][r] = fmaf(d, cz[y][r], out[y][r]) * feature_slope<T>(fq[y][r]);
+                out[y][r] = fmaf(dr, cz[y][r], out[y][r]) * feature_slope<T>(fq[y][r]);
+                if constexpr (Tiles::kRaw) out[y][r] *= rd;
             }
         if constexpr (is_poly<T>) {      // (four waves, each with an out role: all of them are here)
             float *rows = reinterpret_cast<float *>(tl.sq);
@@ -866,7 +891,7 @@ struct DqOut : BlkLane {
 template <int D, int M, typename T, bool kStrided>
 struct DqState : BlkLane {
     using Tiles = BlkTiles<kLeadQ, D, M, T, kStrided>;
-    static constexpr int P = Tiles::P, PV = Tiles::PV, NT = D / 32, MT = M / 32;
+    static constexpr int P = Tiles::P, PV = Tiles::PV, PG = Tiles::PG, NT = D / 32, MT = M / 32;
     const PassArgs &a;
     const Tiles &tl;
     uint16_t *ss;
@@ -948,10 +973,11 @@ struct DqState : BlkLane {
             }
         }
         if (a.totals != nullptr) {
-            Op<P> gn[MT], qq[NT * MT], gg[NT * MT];
+            Op<P> qq[NT * MT];
+            Op<PG> gn[MT], gg[NT * MT];
             f32x4 u[NT * MT];
 #pragma unroll
-            for (int x = 0; x < MT; ++x) gn[x] = read_feat<M, P, false>(tl.sg, kBlk * M, 0, i * MT + x, lane);
+            for (int x = 0; x < MT; ++x) gn[x] = read_feat<M, PG, false>(tl.sg, kBlk * M, 0, i * MT + x, lane);
 #pragma unroll
             for (int y = 0; y < NT; ++y) {
                 const Op<P> qf = read_feat<D, P, false>(tl.sq, kBlk * D, 0, h * NT + y, lane);
@@ -1026,7 +1052,7 @@ __global__ __launch_bounds__((kWave * kBwdWaves<D, M, T>)) __attribute__((amdgpu
 template <int D, int M, typename T, bool kStrided>
 struct RevOut : BlkLane {
     using Tiles = BlkTiles<kLeadK, D, M, T, kStrided>;
-    static constexpr int P = Tiles::P, PV = Tiles::PV, TD = D / 16, TM = M / 16, SD = D / 32, SM = M / 32;
+    static constexpr int P = Tiles::P, PV = Tiles::PV, PG = Tiles::PG, TD = D / 16, TM = M / 16, SD = D / 32, SM = M / 32;
     static constexpr int TX = TD > TM ? TD : TM;
     static constexpr bool kPair = is_bf16<T>;
     using RowsV = OutRows<T, TM>;
@@ -1063,7 +1089,7 @@ struct RevOut : BlkLane {
         const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
         f32x4 w0 = zero4, w1;
         if (h == 0) {
-            // scores phi(Q_a) . phi(K_b)
+            // scores phi(Q_a) . phi(K_b) (kRaw: over den_a)
             Op<P> kt[SD];
             read_toks<D, P>(tl.sk, kBlk * D, row, g, kt);
             if (i == 0) {
@@ -1086,25 +1112,25 @@ struct RevOut : BlkLane {
             const Op<P> wop = op_of<P>(w0, w1);
 #pragma unroll
             for (int t = 0; t < TM; t += 2) {
-                const Op<P> gf[2] = {read_feat<M, P, kPair>(tl.sg, kBlk * M, 0, t, lane),
-                                     read_feat<M, P, kPair>(tl.sg, kBlk * M, 0, t + 1, lane)};
+                const Op<PG> gf[2] = {read_feat<M, PG, kPair>(tl.sg, kBlk * M, 0, t, lane),
+                                      read_feat<M, PG, kPair>(tl.sg, kBlk * M, 0, t + 1, lane)};
                 const Op<P> wo[2] = {wop, wop};
                 f32x4 o[2] = {out[t], out[t + 1]};
                 mma_n(gf, wo, o);
                 out[t] = o[0], out[t + 1] = o[1];
             }
         } else {
-            // scores V_b . dO_a/den_a + delta_a
+            // scores V_b . dO_a/den_a + delta_a (kRaw: times den_a, which phi(Q_a)/den_a takes out again)
             Op<PV> vt[SM];
             read_toks<M, PV>(tl.sv, kBlk * M, row, g, vt);
             if (i == 0) {
-                Op<P> gt[SM];
-                read_toks<M, P>(tl.sg, kBlk * M, c, g, gt);
+                Op<PG> gt[SM];
+                read_toks<M, PG>(tl.sg, kBlk * M, c, g, gt);
                 w0 = dot(gt, vt, *reinterpret_cast<const f32x4 *>(sdel + 4 * g));
             }
             {
-                Op<P> gt[SM];
-                read_toks<M, P>(tl.sg, kBlk * M, 16 + c, g, gt);
+                Op<PG> gt[SM];
+                read_toks<M, PG>(tl.sg, kBlk * M, 16 + c, g, gt);
                 w1 = dot(gt, vt, *reinterpret_cast<const f32x4 *>(sdel + 16 + 4 * g));
             }
             keep(w0, w1);
@@ -1125,7 +1151,7 @@ struct RevOut : BlkLane {
                 mma_n(qf, wo, o);
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    const f32x4 f = get_parts3<D>(tl.sk, kBlk * D, row, col_of<kPair>(t + u, 4 * g));
+                    const f32x4 f = tl.full_values(row, col_of<kPair>(t + u, 4 * g) >> 2);
 #pragma unroll
                     for (int r = 0; r < 4; ++r) out[t + u][r] = o[u][r] * feature_slope<T>(f[r]);
                 }
@@ -1164,22 +1190,22 @@ struct RevOut : BlkLane {
 template <int D, int M, typename T, bool kStrided>
 struct RevState : BlkLane {
     using Tiles = BlkTiles<kLeadK, D, M, T, kStrided>;
-    static constexpr int P = Tiles::P, DT = D / 32, MT = M / 32;
+    static constexpr int P = Tiles::P, PG = Tiles::PG, DT = D / 32, MT = M / 32;
     const PassArgs &a;
     const Tiles &tl;
     uint16_t *sr;
     float *srho, *sdel;
-    const float *delta;
+    const float *delta, *den;
     int bh, seg, rt, tid;
-    float ndel;
+    float ndel, nden;
     f32x4 U[DT][MT];       // element (d = 16 (i DT + x) + 4g + r, m = 16 (h MT + y) + c)
     f32x4 rho;             // element d = 16 rt + 4g + r
 
     __device__ __forceinline__ RevState(const PassArgs &a_, const Tiles &t, int bh_, int seg_, int tid_, int wave, uint16_t *sr_, float *srho_, float *sdel_)
         : BlkLane(tid_, wave), a(a_), tl(t), sr(sr_), srho(srho_), sdel(sdel_), bh(bh_), seg(seg_), tid(tid_) {
-        delta = a.delta + (size_t)bh * a.N;
+        delta = a.delta + (size_t)bh * a.N, den = a.den_in + (size_t)bh * a.N;
         rt = DT == 2 ? 2 * i + h : i;
-        ndel = 0.f;
+        ndel = nden = 0.f;
     }
     __device__ __forceinline__ void add(const float *sm, const float *v) {
 #pragma unroll
@@ -1210,19 +1236,24 @@ struct RevState : BlkLane {
         la::publish<D, P>(sr, M * D, U, i * DT, h * MT, c, g);
         if (c == 0) *reinterpret_cast<f32x4 *>(srho + 16 * rt + 4 * g) = rho;
     }
-    // one wave brings delta
+    // one wave brings delta (kRaw: times den, as the scores of dK are)
     __device__ __forceinline__ void fetch(int blk) {
-        if (i == 0 && h == 0) ndel = delta[min(blk * kBlk + (lane & 31), a.N - 1)];
+        if (i == 0 && h == 0) {
+            const int token = min(blk * kBlk + (lane & 31), a.N - 1);
+            ndel = delta[token];
+            if constexpr (Tiles::kRaw) nden = den[token];
+        }
     }
     __device__ __forceinline__ void parked(int blk) {
-        if (i == 0 && h == 0 && lane < kBlk) sdel[lane] = blk * kBlk + lane < a.N ? ndel : 0.f;
+        if (i == 0 && h == 0 && lane < kBlk) sdel[lane] = blk * kBlk + lane < a.N ? (Tiles::kRaw ? ndel * nden : ndel) : 0.f;
     }
     __device__ __forceinline__ void products() {
         const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-        Op<P> gn[MT], qn[DT], qq[DT * MT], gg[DT * MT];
+        Op<PG> gn[MT], gg[DT * MT];
+        Op<P> qn[DT], qq[DT * MT];
         f32x4 u[DT * MT];
 #pragma unroll
-        for (int y = 0; y < MT; ++y) gn[y] = read_feat<M, P, false>(tl.sg, kBlk * M, 0, h * MT + y, lane);
+        for (int y = 0; y < MT; ++y) gn[y] = read_feat<M, PG, false>(tl.sg, kBlk * M, 0, h * MT + y, lane);
 #pragma unroll
         for (int x = 0; x < DT; ++x) {
             qn[x] = read_feat<D, P, false>(tl.sq, kBlk * D, 0, i * DT + x, lane);
