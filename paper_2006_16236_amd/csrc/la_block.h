@@ -128,9 +128,25 @@ __device__ __forceinline__ Op<3> full_feat(const Op<P> &have, const uint16_t *ti
     return o;
 }
 
+// The remainders of four values against their roundings, leaving the values as they are: the two-address form that
+// the compiler picks for minus_low and minus_high has them copied first (16 copies beside 48 vector instructions of a
+// state role's publishing).  The compiler does not see dot products in an asm block, so the three cycles that one
+// needs before another kind of instruction may read its result are part of it.
+__device__ __forceinline__ void remainders(const u32x2_t pair, const f32x4 x, f32x4 &r) {
+    float a, b, c, d;
+    asm("v_dot2_f32_bf16 %0, %4, %10, %6\n\t"
+        "v_dot2_f32_bf16 %1, %4, %11, %7\n\t"
+        "v_dot2_f32_bf16 %2, %5, %10, %8\n\t"
+        "v_dot2_f32_bf16 %3, %5, %11, %9\n\t"
+        "s_nop 2"
+        : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
+        : "v"(pair[0]), "v"(pair[1]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "s"(0x8000bf80u), "s"(0xbf808000u));
+    r = f32x4{a, b, c, d};
+}
+
 // N quads cut into P parts stage by stage (an instruction and the one that needs its result are
 // then several instructions apart; quad by quad the compiler fills the gaps with idle cycles)
-template <int P, int N>
+template <int P, int N, bool kLive = false>      // kLive: the quads are needed afterwards
 __device__ __forceinline__ void split_batch(const f32x4 (&q)[N], u32x2_t (&s)[N][P]) {
     f32x4 r[N];
 #pragma unroll
@@ -143,12 +159,17 @@ __device__ __forceinline__ void split_batch(const f32x4 (&q)[N], u32x2_t (&s)[N]
             for (int j = 0; j < 2; ++j) s[n][k][j] = round_pair(r[n][2 * j], r[n][2 * j + 1]);
         if (k + 1 < P) {
 #pragma unroll
-            for (int n = 0; n < N; ++n)
+            for (int n = 0; n < N; ++n) {
+                if (kLive && k == 0) {
+                    remainders(s[n][k], q[n], r[n]);
+                    continue;
+                }
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     r[n][2 * j] = minus_low(s[n][k][j], r[n][2 * j]);
                     r[n][2 * j + 1] = minus_high(s[n][k][j], r[n][2 * j + 1]);
                 }
+            }
         }
     }
 }
@@ -306,29 +327,27 @@ struct BlkTiles {
     static __device__ __forceinline__ int plane_at(int row, int piece) {
         return row * D + ((piece ^ (D == 64 ? row & 15 : (row >> 1) & 7)) << 2);
     }
-    // kKeep: the mapped values go to the fp32 plane too; kBy: their rows are scaled by `by` before they are cut
-    template <int F, int PT, int MAP_, bool kFull, bool kKeep = false, bool kBy = false>
-    __device__ __forceinline__ void put(uint16_t *tile, int at, const staged_t<T> (&st)[kQuads<F>], const float *by, int nv) const {
+    // kKeep: the mapped values go to the fp32 plane too; kBy: their rows are scaled by `by` before they are cut;
+    // kZero: rows past the end are zero
+    template <int F, int PT, int MAP_, bool kKeep = false, bool kBy = false, bool kZero = false>
+    __device__ __forceinline__ void put(uint16_t *tile, int at, const staged_t<T> (&st)[kQuads<F>], const float *by, int nv = kBlk) const {
         constexpr int MAP = is_poly<T> && MAP_ == kMapPhi ? kMapScale : is_feat<T> && MAP_ == kMapPhi ? kMapId : MAP_;
         if constexpr (PT == 1 && MAP == kMapId && is_bf16<T>) {         // as it is
 #pragma unroll
-            for (int k = 0; k < kQuads<F>; ++k)
-                *reinterpret_cast<u32x2_t *>(tile + at + k * kStep<F> * F) =
-                    kFull || row<F>(tid) + k * kStep<F> < nv ? st[k] : u32x2_t{0u, 0u};
+            for (int k = 0; k < kQuads<F>; ++k) *reinterpret_cast<u32x2_t *>(tile + at + k * kStep<F> * F) = st[k];
         } else {
             f32x4 v[kQuads<F>];
 #pragma unroll
             for (int k = 0; k < kQuads<F>; ++k) {
                 const f32x4 w = widen(st[k]);
                 const int at_row = row<F>(tid) + k * kStep<F>;
-                f32x4 kept;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float m = map_value<MAP>(w[r], MAP == kMapScale ? by[k] : 1.0f);
-                    kept[r] = kFull || at_row < nv ? m : 0.0f;
-                    v[k][r] = !kBy ? kept[r] : kFull || at_row < nv ? m * by[k] : 0.0f;
+                    v[k][r] = !kZero || at_row < nv ? m : 0.0f;
                 }
-                if constexpr (kKeep) *reinterpret_cast<f32x4 *>(sf + plane_at(at_row, col<F>(tid) >> 2)) = kept;
+                if constexpr (kKeep) *reinterpret_cast<f32x4 *>(sf + plane_at(at_row, col<F>(tid) >> 2)) = v[k];
+                if constexpr (kBy) v[k] *= by[k];
             }
             u32x2_t s[kQuads<F>][PT];
             split_batch<PT>(v, s);
@@ -336,21 +355,24 @@ struct BlkTiles {
             for (int k = 0; k < kQuads<F>; ++k) put_parts<PT>(tile + at + k * kStep<F> * F, kBlk * F, s[k]);
         }
     }
-    template <bool kFull>
-    __device__ __forceinline__ void put_all(const int nv) {
-        if (kLead == kLeadQ && mine<S>(0)) {
-#pragma unroll
-            for (int k = 0; k < kQuads<S>; ++k) sc[k] = __builtin_amdgcn_rcpf(sc[k]);
-        }
-        if (kG && mine<M>(0)) put<M, PG, kRaw ? kMapId : kMapScale, kFull>(sg, qm, fg, sc, nv);
-        if (mine<M>(1)) put<M, PV, kG ? kMapId : kMapFinite, kFull>(sv, qm, fv, nullptr, nv);
-        if (mine<D>(0)) put<D, PQ, kMapPhi, kFull, kRaw && kLead == kLeadQ, kRaw>(sq, qd, fq, kRaw ? sc : xq, nv);
-        if (mine<D>(1)) put<D, PK, kMapPhi, kFull, kRaw && kLead == kLeadK>(sk, qd, fk, xk, nv);
-    }
+    // Rows past the end were fetched as zeros, so V and dO are zero there and phi(0) = 1 of Q and K meets only those
+    // zeros, a delta that is set to zero, or rows of an output that are not stored.  It must be finite, hence
+    // no reciprocal of a denominator that is not there; and the forward's z counts keys: those are zeroed,
+    // in code of their own for the one block that has such rows.  (With all tiles in two versions the
+    // compiler copied what both share.)
     __device__ __forceinline__ void park(const int blk) {
         const int nv = min(kBlk, N - blk * kBlk);
-        if (nv == kBlk) put_all<true>(nv);
-        else put_all<false>(nv);
+        if (kLead == kLeadQ && mine<S>(0)) {
+#pragma unroll
+            for (int k = 0; k < kQuads<S>; ++k) sc[k] = row<S>(tid) + k * kStep<S> < nv ? __builtin_amdgcn_rcpf(sc[k]) : 0.0f;
+        }
+        if (kG && mine<M>(0)) put<M, PG, kRaw ? kMapId : kMapScale>(sg, qm, fg, sc);
+        if (mine<M>(1)) put<M, PV, kG ? kMapId : kMapFinite>(sv, qm, fv, nullptr);
+        if (mine<D>(0)) put<D, PQ, kMapPhi, kRaw && kLead == kLeadQ, kRaw>(sq, qd, fq, kRaw ? sc : xq);
+        if (mine<D>(1)) {
+            if (kG || nv == kBlk) put<D, PK, kMapPhi, kRaw && kLead == kLeadK>(sk, qd, fk, xk);
+            else put<D, PK, kMapPhi, false, false, true>(sk, qd, fk, xk, nv);
+        }
     }
     // feature values of the pass's tensor in full, columns 4 * piece .. + 3 of a row
     __device__ __forceinline__ f32x4 full_values(int row, int piece) const {
@@ -367,7 +389,7 @@ __device__ __forceinline__ void publish(uint16_t *tile, int plane, const f32x4 (
         u32x2_t s[NX][P];
 #pragma unroll
         for (int x = 0; x < NX; ++x) q[x] = U[x][y];
-        split_batch<P>(q, s);
+        split_batch<P, NX, true>(q, s);
 #pragma unroll
         for (int x = 0; x < NX; ++x) put_parts<P>(tile + quad_at<F>(16 * (y0 + y) + c, 16 * (x0 + x) + 4 * g), plane, s[x]);
     }
@@ -662,12 +684,13 @@ struct FwdState : BlkLane {
     __device__ __forceinline__ void publish() {
         la::publish<D, PS>(ss, M * D, U, i * DT, h * MT, c, g);
         if (h == 0) {
-            u32x2_t s[DT][3];
-            split_batch<3>(z, s);
-            if (c == 0) {
+            // every lane c has all of z: lane x cuts and stores quad x
+            f32x4 q[1];
+            u32x2_t s[1][3];
 #pragma unroll
-                for (int x = 0; x < DT; ++x) put_parts<3>(sz + 16 * (i * DT + x) + 4 * g, D, s[x]);
-            }
+            for (int r = 0; r < 4; ++r) q[0][r] = DT == 2 && c != 0 ? z[DT - 1][r] : z[0][r];
+            split_batch<3>(q, s);
+            if (c < DT) put_parts<3>(sz + 16 * (i * DT + c) + 4 * g, D, s[0]);
         }
     }
     __device__ __forceinline__ void fetch(int) {}
