@@ -235,7 +235,7 @@ template <typename T> constexpr int kVParts = is_bf16<T> ? 1 : 3;
 // kLead: the pass, by the tensor whose gradient it ends in (kLeadQK: the forward, no dO there).
 // bf16 backward (kRaw): dO stays as it is, one exact part, and 1/den goes with phi(Q) where a product needs it
 // (every sum over tokens a takes dO_a and phi(Q_a) together) or to the finished row.  And the pass that needs a
-// tensor's values in full per token (phi(Q) in the dQ pass, phi'(K) in the other) reads them from an fp32
+// tensor's feature values in full per token (phi(Q) in the dQ pass, phi(K) in the other) reads them from an fp32
 // plane, not from three parts.  Against dO/den in two parts and three parts throughout: 44 instead of 56 products
 // per SIMD and block in the dQ pass and 3/4 of the vector instructions, of which either kind costs its own issue
 // time (bf16 step, B*H = 16, N = 65536: 608 -> 570 us; B*H = 32, N = 3072, through autograd: 79 -> 74).
@@ -249,7 +249,7 @@ struct BlkTiles {
     static constexpr bool kG = kLead != kLeadQK, kRaw = kG && is_bf16<T>;
     static constexpr int P = kOpParts<T>, PV = kVParts<T>, PG = kRaw ? 1 : P;
     static constexpr int PQ = kRaw && kLead == kLeadQ ? 2 : 3, PK = kRaw && kLead == kLeadK ? 2 : 3;
-    static constexpr int kPlaneElems = kRaw && (kLead == kLeadQ || !is_feat<T>) ? 2 * kBlk * D : 0;
+    static constexpr int kPlaneElems = kRaw ? 2 * kBlk * D : 0;
     static constexpr int kElems = (PQ + PK) * kBlk * D + (PV + (kG ? PG : 0)) * kBlk * M + kPlaneElems;
     static constexpr int S = kRaw ? D : M;  // width of the tensor whose rows are scaled
     template <int F> static constexpr int kQuads = 8 * F > kThreads ? 8 * F / kThreads : 1;
@@ -259,7 +259,7 @@ struct BlkTiles {
     template <int F> static __device__ __forceinline__ int col(int tid) { return 4 * (tid % (F / 4)); }
 
     uint16_t *sq, *sk, *sv, *sg;            // phi(Q), phi(K), V, dO/den; kRaw: phi(Q)/den, phi(K), V, dO
-    float *sf;                              // kRaw: phi(Q) (kLeadQ) or phi'(K), fp32
+    float *sf;                              // kRaw: phi(Q) (kLeadQ) or phi(K), fp32
     const T *Qs, *Ks, *Vs, *Gs;
     const float *scale;                     // of the rows of dO or Q: den (kLeadQ, its reciprocal is taken) or 1/den
     int N, tid, half, tsd, tsm;
@@ -346,14 +346,7 @@ struct BlkTiles {
                     const float m = map_value<MAP>(w[r], MAP == kMapScale ? by[k] : 1.0f);
                     v[k][r] = !kZero || at_row < nv ? m : 0.0f;
                 }
-                if constexpr (kKeep) {
-                    f32x4 kept = v[k];
-                    if constexpr (kLead == kLeadK) {         // the slope, which phi is formed from
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) kept[r] = dphi(w[r]);
-                    }
-                    *reinterpret_cast<f32x4 *>(sf + plane_at(at_row, col<F>(tid) >> 2)) = kept;
-                }
+                if constexpr (kKeep) *reinterpret_cast<f32x4 *>(sf + plane_at(at_row, col<F>(tid) >> 2)) = v[k];
                 if constexpr (kBy) v[k] *= by[k];
             }
             u32x2_t s[kQuads<F>][PT];
@@ -377,25 +370,14 @@ struct BlkTiles {
         if (mine<M>(1)) put<M, PV, kG ? kMapId : kMapFinite>(sv, qm, fv, nullptr);
         if (mine<D>(0)) put<D, PQ, kMapPhi, kRaw && kLead == kLeadQ, kRaw>(sq, qd, fq, kRaw ? sc : xq);
         if (mine<D>(1)) {
-            if (kG || nv == kBlk) put<D, PK, kMapPhi, kRaw && kLead == kLeadK && !is_feat<T>>(sk, qd, fk, xk);
+            if (kG || nv == kBlk) put<D, PK, kMapPhi, kRaw && kLead == kLeadK>(sk, qd, fk, xk);
             else put<D, PK, kMapPhi, false, false, true>(sk, qd, fk, xk, nv);
         }
     }
-    // phi(Q) (kLeadQ) in full, columns 4 * piece .. + 3 of a row
+    // feature values of the pass's tensor in full, columns 4 * piece .. + 3 of a row
     __device__ __forceinline__ f32x4 full_values(int row, int piece) const {
         if constexpr (kRaw) return *reinterpret_cast<const f32x4 *>(sf + plane_at(row, piece));
-        else return get_parts3<D>(sq, kBlk * D, row, 4 * piece);
-    }
-    // the slope of the map at K (kLeadK)
-    __device__ __forceinline__ f32x4 slopes(int row, int piece) const {
-        if constexpr (is_feat<T>) return f32x4{1.0f, 1.0f, 1.0f, 1.0f};
-        else if constexpr (kRaw) return *reinterpret_cast<const f32x4 *>(sf + plane_at(row, piece));
-        else {
-            f32x4 f = get_parts3<D>(sk, kBlk * D, row, 4 * piece);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) f[r] = feature_slope<T>(f[r]);
-            return f;
-        }
+        else return get_parts3<D>(kLead == kLeadQ ? sq : sk, kBlk * D, row, 4 * piece);
     }
 };
 // accumulator tiles of a carried state, cut and published (rows = columns of the tiles)
@@ -1192,9 +1174,9 @@ struct RevOut : BlkLane {
                 mma_n(qf, wo, o);
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    const f32x4 f = tl.slopes(row, col_of<kPair>(t + u, 4 * g) >> 2);
+                    const f32x4 f = tl.full_values(row, col_of<kPair>(t + u, 4 * g) >> 2);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) out[t + u][r] = o[u][r] * f[r];
+                    for (int r = 0; r < 4; ++r) out[t + u][r] = o[u][r] * feature_slope<T>(f[r]);
                 }
             }
         }
