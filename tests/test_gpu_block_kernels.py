@@ -307,3 +307,18 @@ def test_states_against_fp64(monkeypatch, kind, D, M, sched):
     for name, (got, ref, size, bits, bits16) in want.items():
         err = float(((got.cpu().double() - ref).abs() / size).max())
         assert err <= 2.0 ** -(bits16 if bf16 else bits), (name, err)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("D,M", [(64, 64), (32, 32), (64, 32), (32, 64)])
+@pytest.mark.parametrize("N,sched", [(33, "default"), (70, "many_segments")])
+def test_gradients_scale_with_the_upstream_gradient(monkeypatch, N, sched, D, M, bf16):
+    """dO times a power of two scales every product and sum of the backward exactly, wherever the kernel brings
+    1/den in (to dO, to phi(Q) or to the finished row): the gradients scale bit for bit."""
+    q, k, v, g = (to_dev(x, bf16) for x in maybe_bf16(wl.random_case(9200 + N + D + 2 * M, 1, 3, N, D, M), bf16))
+    with block_kernels(monkeypatch, "1", sched) as la:
+        (_, *want), _ = run(la, (q, k, v, g), 1e-6)
+        for scale in (2.0 ** 40, 2.0 ** -40):
+            (_, *got), _ = run(la, (q, k, v, g * scale), 1e-6)
+            for a, b in zip(got, want):
+                assert np.array_equal(a / scale, b)
