@@ -233,17 +233,24 @@ template <typename T> constexpr int kVParts = is_bf16<T> ? 1 : 3;
 // besides the products of P parts their feature values are needed in full, for phi' and for the sums that
 // stay fp32, den in the forward, z and delta in the dQ pass, rho in the reverse pass.
 // kLead: the pass, by the tensor whose gradient it ends in (kLeadQK: the forward, no dO there).
-// bf16 backward (kRaw): dO stays as it is, one exact part, and 1/den goes with phi(Q) where a product needs it
-// (every sum over tokens a takes dO_a and phi(Q_a) together) or to the finished row.  And the pass that needs a
+// bf16 backward (kRaw): dO takes the power of two of 1/den only, which leaves it one exact part, and the rest, 1 to 2
+// in size, goes with phi(Q) where a product needs it (every sum over tokens a takes dO_a and phi(Q_a) together) or to
+// the finished row.  (dO as it is and all of 1/den with phi(Q) saves 1 % of the step, 576 -> 570 us at B*H = 16,
+// N = 65536, but its sums are den times as large: they overflow for gradients for which dO/den is nowhere near it.)  And the pass that needs a
 // tensor's feature values in full per token (phi(Q) in the dQ pass, phi(K) in the other) reads them from an fp32
 // plane, not from three parts.  Against dO/den in two parts and three parts throughout: 44 instead of 56 products
 // per SIMD and block in the dQ pass and 3/4 of the vector instructions, of which either kind costs its own issue
 // time (bf16 step, B*H = 16, N = 65536: 608 -> 570 us; B*H = 32, N = 3072, through autograd: 79 -> 74).
-// What it asks for: |dO| times the state, a sum over up to N keys, within fp32's range (|dO| |V| N below 1e38), where
-// dO/den needed |dO| |V| below that; in return a tiny den no longer overflows dO/den.
 // A 32 x F block is fetched in quads of four elements, one or two per thread: quad k of thread t is
 // row row(t) + k * kStep, columns col(t) .. + 3 (a wave reads whole rows).  Where a block has fewer quads
 // than there are threads, the two blocks of a pair (Q and K, or dO and V) take half of them each.
+// r = pow2_of(r) rest_of(r): a power of two not above |r|, and 1 <= |rest| < 2 (r = 0: 0 and 1; infinite: itself and 1)
+__device__ __forceinline__ float pow2_of(float r) {
+    return r == r ? __builtin_bit_cast(float, __builtin_bit_cast(unsigned, r) & 0x7f800000u) : r;
+}
+__device__ __forceinline__ float rest_of(float r) {
+    return __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, r) & 0x807fffffu) | 0x3f800000u);
+}
 enum Lead { kLeadQ = 0, kLeadK = 1, kLeadQK = 2 };
 template <int kLead, int D, int M, typename T, bool kStrided>
 struct BlkTiles {
@@ -253,23 +260,22 @@ struct BlkTiles {
     static constexpr int PQ = kRaw && kLead == kLeadQ ? 2 : 3, PK = kRaw && kLead == kLeadK ? 2 : 3;
     static constexpr int kPlaneElems = kRaw ? 2 * kBlk * D : 0;
     static constexpr int kElems = (PQ + PK) * kBlk * D + (PV + (kG ? PG : 0)) * kBlk * M + kPlaneElems;
-    static constexpr int S = kRaw ? D : M;  // width of the tensor whose rows are scaled
     template <int F> static constexpr int kQuads = 8 * F > kThreads ? 8 * F / kThreads : 1;
     template <int F> static constexpr int kStep = 4 * kThreads / F;
     template <int F> static constexpr bool kShared = 8 * F < kThreads;
     template <int F> static __device__ __forceinline__ int row(int tid) { return (tid % (8 * F)) / (F / 4); }
     template <int F> static __device__ __forceinline__ int col(int tid) { return 4 * (tid % (F / 4)); }
 
-    uint16_t *sq, *sk, *sv, *sg;            // phi(Q), phi(K), V, dO/den; kRaw: phi(Q)/den, phi(K), V, dO
+    uint16_t *sq, *sk, *sv, *sg;            // phi(Q), phi(K), V, dO/den; kRaw: the rest of 1/den with phi(Q)
     float *sf;                              // kRaw: phi(Q) (kLeadQ) or phi(K), fp32
     const T *Qs, *Ks, *Vs, *Gs;
-    const float *scale;                     // of the rows of dO or Q: den (kLeadQ, its reciprocal is taken) or 1/den
+    const float *scale;                     // of the rows of dO: den (kLeadQ, its reciprocal is taken) or 1/den
     int N, tid, half, tsd, tsm;
     bool nt;
     int offd, offm;                         // bytes
     int qd, qm;
     staged_t<T> fq[kQuads<D>], fk[kQuads<D>], fv[kQuads<M>], fg[kQuads<M>];
-    float sc[kQuads<S>];
+    float sc[kQuads<M>], rest[kQuads<D>];   // of the rows of dO; kRaw: of Q
     // polynomial map: feature 8i + j = x_i x_j; fq, fk hold x_j .. x_j+3 of a quad, xq, xk its x_i
     static constexpr int W = qk_width<T>(D);
     float xq[kQuads<D>], xk[kQuads<D>];
@@ -301,10 +307,16 @@ struct BlkTiles {
     }
     template <int kAux>
     __device__ __forceinline__ void load_all(const int t0, const int nv) {
-        if (kG && mine<S>(0)) {
+        if constexpr (kG) {
             const Rows r = rows_of(scale + t0, 1, nv);
+            if (mine<M>(0)) {
 #pragma unroll
-            for (int k = 0; k < kQuads<S>; ++k) sc[k] = rows_load1(r, 4 * (row<S>(tid) + k * kStep<S>));
+                for (int k = 0; k < kQuads<M>; ++k) sc[k] = rows_load1(r, 4 * (row<M>(tid) + k * kStep<M>));
+            }
+            if (kRaw && D != M && mine<D>(0)) {
+#pragma unroll
+                for (int k = 0; k < kQuads<D>; ++k) rest[k] = rows_load1(r, 4 * (row<D>(tid) + k * kStep<D>));
+            }
         }
         if (kG && mine<M>(0)) load<M, kAux>(Gs + (size_t)t0 * tsm, offm, tsm, nv, fg);
         if (mine<M>(1)) load<M, kAux>(Vs + (size_t)t0 * tsm, offm, tsm, nv, fv);
@@ -357,6 +369,10 @@ struct BlkTiles {
             for (int k = 0; k < kQuads<F>; ++k) put_parts<PT>(tile + at + k * kStep<F> * F, kBlk * F, s[k]);
         }
     }
+    // 1/den of a row from what was fetched for it (rows past the end: 0)
+    static __device__ __forceinline__ float rden_of(float fetched, int at_row, int nv) {
+        return kLead != kLeadQ ? fetched : at_row < nv ? __builtin_amdgcn_rcpf(fetched) : 0.0f;
+    }
     // Rows past the end were fetched as zeros, so V and dO are zero there and phi(0) = 1 of Q and K meets only those
     // zeros, a delta that is set to zero, or rows of an output that are not stored.  It must be finite, hence
     // no reciprocal of a denominator that is not there; and the forward's z counts keys: those are zeroed,
@@ -365,13 +381,21 @@ struct BlkTiles {
     // 570 -> 560 us; fp32 B*H = 32, N = 3072, forward 28.0 -> 27.1, dQ 37.9 -> 36.5, dV + dK 37.5 -> 36.8).
     __device__ __forceinline__ void park(const int blk) {
         const int nv = min(kBlk, N - blk * kBlk);
-        if (kLead == kLeadQ && mine<S>(0)) {
+        if (kG && mine<M>(0)) {
 #pragma unroll
-            for (int k = 0; k < kQuads<S>; ++k) sc[k] = row<S>(tid) + k * kStep<S> < nv ? __builtin_amdgcn_rcpf(sc[k]) : 0.0f;
+            for (int k = 0; k < kQuads<M>; ++k) {
+                const float r = rden_of(sc[k], row<M>(tid) + k * kStep<M>, nv);
+                if constexpr (kRaw && D == M) rest[k] = rest_of(r);
+                sc[k] = kRaw ? pow2_of(r) : r;
+            }
+            put<M, PG, kMapScale>(sg, qm, fg, sc);
         }
-        if (kG && mine<M>(0)) put<M, PG, kRaw ? kMapId : kMapScale>(sg, qm, fg, sc);
+        if (kRaw && D != M && mine<D>(0)) {
+#pragma unroll
+            for (int k = 0; k < kQuads<D>; ++k) rest[k] = rest_of(rden_of(rest[k], row<D>(tid) + k * kStep<D>, nv));
+        }
         if (mine<M>(1)) put<M, PV, kG ? kMapId : kMapFinite>(sv, qm, fv, nullptr);
-        if (mine<D>(0)) put<D, PQ, kMapPhi, kRaw && kLead == kLeadQ, kRaw>(sq, qd, fq, kRaw ? sc : xq);
+        if (mine<D>(0)) put<D, PQ, kMapPhi, kRaw && kLead == kLeadQ, kRaw>(sq, qd, fq, kRaw ? rest : xq);
         if (mine<D>(1)) {
             if (kG || nv == kBlk) put<D, PK, kMapPhi, kRaw && kLead == kLeadK>(sk, qd, fk, xk);
             else put<D, PK, kMapPhi, false, false, true>(sk, qd, fk, xk, nv);
@@ -825,7 +849,7 @@ struct DqOut : BlkLane {
     }
     __device__ __forceinline__ void products() {
         const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-        // scores (dO_a/den_a) . V_b (kRaw: dO_a . V_b, and the whole row waits for its 1/den): rows b, lane (c = a)
+        // scores (dO_a/den_a) . V_b (kRaw: the whole row waits for the rest of its 1/den): rows b, lane (c = a)
         Op<PG> gt[SM];
         read_toks<M, PG>(tl.sg, kBlk * M, row, g, gt);
         f32x4 w0, w1 = zero4;
@@ -873,15 +897,16 @@ struct DqOut : BlkLane {
     }
     __device__ __forceinline__ void finish(int blk) {
         const int t0 = blk * kBlk, nv = min(kBlk, N - t0);
-        const float dr = row < nv ? -(sdel[i][0][c] + sdel[i][1][c]) * rd : 0.f;     // kRaw: delta den
-        const float d = Tiles::kRaw ? (row < nv ? dr * rd : 0.f) : dr;
+        const float rest = Tiles::kRaw ? rest_of(rd) : 1.f;
+        const float dr = row < nv ? -(sdel[i][0][c] + sdel[i][1][c]) * rd : 0.f;     // delta / rest, as the row is
+        const float d = Tiles::kRaw ? (row < nv ? dr * rest : 0.f) : dr;
 #pragma unroll
         for (int y = 0; y < NT; ++y)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 rho[y][r] = fmaf(d, fq[y][r], rho[y][r]);
                 out[y][r] = fmaf(dr, cz[y][r], out[y][r]) * feature_slope<T>(fq[y][r]);
-                if constexpr (Tiles::kRaw) out[y][r] *= rd;
+                if constexpr (Tiles::kRaw) out[y][r] *= rest;
             }
         if constexpr (is_poly<T>) {      // (four waves, each with an out role: all of them are here)
             float *rows = reinterpret_cast<float *>(tl.sq);
@@ -1115,7 +1140,7 @@ struct RevOut : BlkLane {
         const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
         f32x4 w0 = zero4, w1;
         if (h == 0) {
-            // scores phi(Q_a) . phi(K_b) (kRaw: over den_a)
+            // scores phi(Q_a) . phi(K_b) (kRaw: times the rest of 1/den_a)
             Op<P> kt[SD];
             read_toks<D, P>(tl.sk, kBlk * D, row, g, kt);
             if (i == 0) {
@@ -1146,7 +1171,7 @@ struct RevOut : BlkLane {
                 out[t] = o[0], out[t + 1] = o[1];
             }
         } else {
-            // scores V_b . dO_a/den_a + delta_a (kRaw: times den_a, which phi(Q_a)/den_a takes out again)
+            // scores V_b . dO_a/den_a + delta_a (kRaw: over the rest of 1/den_a, which phi(Q_a) brings)
             Op<PV> vt[SM];
             read_toks<M, PV>(tl.sv, kBlk * M, row, g, vt);
             if (i == 0) {
@@ -1221,17 +1246,17 @@ struct RevState : BlkLane {
     const Tiles &tl;
     uint16_t *sr;
     float *srho, *sdel;
-    const float *delta, *den;
+    const float *delta, *rden;
     int bh, seg, rt, tid;
-    float ndel, nden;
+    float ndel, nrden;
     f32x4 U[DT][MT];       // element (d = 16 (i DT + x) + 4g + r, m = 16 (h MT + y) + c)
     f32x4 rho;             // element d = 16 rt + 4g + r
 
     __device__ __forceinline__ RevState(const PassArgs &a_, const Tiles &t, int bh_, int seg_, int tid_, int wave, uint16_t *sr_, float *srho_, float *sdel_)
         : BlkLane(tid_, wave), a(a_), tl(t), sr(sr_), srho(srho_), sdel(sdel_), bh(bh_), seg(seg_), tid(tid_) {
-        delta = a.delta + (size_t)bh * a.N, den = a.den_in + (size_t)bh * a.N;
+        delta = a.delta + (size_t)bh * a.N, rden = a.rden + (size_t)bh * a.N;
         rt = DT == 2 ? 2 * i + h : i;
-        ndel = nden = 0.f;
+        ndel = 0.f, nrden = 1.f;
     }
     __device__ __forceinline__ void add(const float *sm, const float *v) {
 #pragma unroll
@@ -1262,16 +1287,19 @@ struct RevState : BlkLane {
         la::publish<D, P>(sr, M * D, U, i * DT, h * MT, c, g);
         if (c == 0) *reinterpret_cast<f32x4 *>(srho + 16 * rt + 4 * g) = rho;
     }
-    // one wave brings delta (kRaw: times den, as the scores of dK are)
+    // one wave brings delta (kRaw: over the rest of 1/den, as the scores of dK are)
     __device__ __forceinline__ void fetch(int blk) {
         if (i == 0 && h == 0) {
             const int token = min(blk * kBlk + (lane & 31), a.N - 1);
             ndel = delta[token];
-            if constexpr (Tiles::kRaw) nden = den[token];
+            if constexpr (Tiles::kRaw) nrden = rden[token];
         }
     }
     __device__ __forceinline__ void parked(int blk) {
-        if (i == 0 && h == 0 && lane < kBlk) sdel[lane] = blk * kBlk + lane < a.N ? (Tiles::kRaw ? ndel * nden : ndel) : 0.f;
+        if (i == 0 && h == 0 && lane < kBlk) {
+            const float d = Tiles::kRaw ? ndel * __builtin_amdgcn_rcpf(rest_of(nrden)) : ndel;
+            sdel[lane] = blk * kBlk + lane < a.N ? d : 0.f;
+        }
     }
     __device__ __forceinline__ void products() {
         const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};

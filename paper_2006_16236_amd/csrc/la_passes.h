@@ -102,7 +102,7 @@ struct PassArgs {
                                  // the pass then only writes the denominators)
     void *out2;                  // reverse_pass_kernel only: dK [BH, N, D]
     float *den;                  // [BH, N] or null             (kFwd, kGlobal)
-    const float *den_in;         // kDq, reverse_block_kernel: the forward's denominators [BH, N]
+    const float *den_in;         // kDq: the forward's denominators [BH, N]
     float *rden_out, *delta_out; // kDq: [BH, N] 1/den_i and delta_i for the reverse passes (or both null)
     float *totals;               // kDq: [BH, nseg, state_stride] per-segment sums of
                                  // phi(Q)^T dO/den and delta phi(Q), or null

@@ -322,3 +322,44 @@ def test_gradients_scale_with_the_upstream_gradient(monkeypatch, N, sched, D, M,
             (_, *got), _ = run(la, (q, k, v, g * scale), 1e-6)
             for a, b in zip(got, want):
                 assert np.array_equal(a / scale, b)
+
+
+@pytest.mark.parametrize("on", ["0", "1"])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("D,M", [(64, 64), (32, 32), (64, 32), (32, 64)])
+@pytest.mark.parametrize("N,sched", [(33, "default"), (300, "many_segments"), (1027, "default")])
+def test_range_of_the_backward(monkeypatch, N, sched, D, M, bf16, on):
+    """The backward's sums hold dO/den, not dO: gradients are finite wherever |dO| |V| M and dO/den are, however
+    large den is.  Features phi(Q) 2^a, phi(K) 2^b and dO 2^c (eps = 0) scale den by 2^(a + b), and dQ, dK, dV by
+    2^(c - a), 2^(c - b), 2^c, bit for bit while nothing leaves the range of fp32; sums of dO itself would reach
+    2^(c + a + b + 20).  With the elu map den is up to 2^18 here."""
+    host = wl.random_case(9300 + N + D + 2 * M, 1, 3, N, D, M)
+    q, k, v, g = (to_dev(x, bf16) for x in maybe_bf16(host, bf16))
+    fq, fk = (to_dev(x, bf16) for x in maybe_bf16([np.abs(x) + np.float32(0.125) for x in host[:2]], bf16))
+    with block_kernels(monkeypatch, on, sched) as la:
+        for dev, eps, kw, exponents in (((q, k, v, g), 1e-6, {}, [(0, 0, 110), (0, 0, -60)]),
+                                        ((fq, fk, v, g), 0.0, {"features": True},
+                                         [(27, 27, 85), (45, 20, 100), (-30, -30, 40), (-70, 70, 0), (60, -60, 40)])):
+            (O, *want), den = run(la, dev, eps, **kw)
+            for a, b, c in exponents:
+                x = [t * 2.0 ** e for t, e in zip(dev, (a, b, 0, c))]
+                (Ox, *got), denx = run(la, x, eps, **kw)
+                assert np.array_equal(Ox, O) and np.array_equal(denx.astype(np.float64), den * 2.0 ** (a + b)), (a, b, c)
+                for name, have, ref, e in zip(("dQ", "dK", "dV"), got, want, (c - a, c - b, c)):
+                    assert np.isfinite(have).all() and np.array_equal(have.astype(np.float64), ref * 2.0 ** e), (name, a, b, c)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("D,M", [(64, 64), (32, 32), (64, 32), (32, 64)])
+@pytest.mark.parametrize("N,sched", [(33, "default"), (300, "many_segments")])
+def test_small_denominators(oracle, monkeypatch, N, sched, D, M, bf16):
+    """Keys around -60, phi(K) = e^-60: den is near 1e-23 and eps = 0.  A reciprocal applied twice, left out, or
+    taken out of delta again by mistake is 20 decades off.  fp32: of exp(x) comes 2^-24 |x log2 e| <= 2^-17, of
+    every key alike in den, S and the gradients' sums: 1e-4 is ample (grad_errs' floor included)."""
+    host = wl.random_case(9400 + N + D + 2 * M, 1, 3, N, D, M)
+    host = maybe_bf16([host[0], host[1] - np.float32(60.0), *host[2:]], bf16)
+    with block_kernels(monkeypatch, "1", sched) as la:
+        (O, dq, dk, dv), _ = run(la, [to_dev(x, bf16) for x in host], 0.0)
+    assert rel_err(O, oracle.causal_fwd_prefix(*host[:3], 0.0)) <= (2e-2 if bf16 else 1e-4)
+    for got, ref in zip((dq, dk, dv), oracle.causal_bwd_linear(*host, 0.0)):
+        assert rel_err(got, ref) <= (2e-2 if bf16 else 1e-4)
