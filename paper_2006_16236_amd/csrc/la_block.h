@@ -128,20 +128,33 @@ __device__ __forceinline__ Op<3> full_feat(const Op<P> &have, const uint16_t *ti
     return o;
 }
 
-// The remainders of four values against their roundings, leaving the values as they are: the two-address form that
+// The first parts of N quads and what is left of them, leaving the quads as they are: the two-address form that
 // the compiler picks for minus_low and minus_high has them copied first (16 copies beside 48 vector instructions of a
-// state role's publishing).  The compiler does not see dot products in an asm block, so the three cycles that one
-// needs before another kind of instruction may read its result are part of it.
-__device__ __forceinline__ void remainders(const u32x2_t pair, const f32x4 x, f32x4 &r) {
-    float a, b, c, d;
-    asm("v_dot2_f32_bf16 %0, %4, %10, %6\n\t"
-        "v_dot2_f32_bf16 %1, %4, %11, %7\n\t"
-        "v_dot2_f32_bf16 %2, %5, %10, %8\n\t"
-        "v_dot2_f32_bf16 %3, %5, %11, %9\n\t"
-        "s_nop 2"
-        : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
-        : "v"(pair[0]), "v"(pair[1]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "s"(0x8000bf80u), "s"(0xbf808000u));
-    r = f32x4{a, b, c, d};
+// state role's publishing).  The compiler sees no vector instruction in an asm block and inserts no wait states for
+// it.  Behind it: the three cycles a dot product needs before another kind of instruction may read its result are
+// part of the block.  Ahead of it: a quad may come straight from a matrix product, so the block takes roundings that
+// are made here, of the same quad; the compiler has the rounding wait for the product, and the block needs the
+// rounding.  (The registers it writes: in the code built here no product within 15 instructions ahead of a block has
+// one of them as its result or its addend, and a product takes 8 passes.)
+template <int N>
+__device__ __forceinline__ void first_parts(const f32x4 (&q)[N], u32x2_t (&pair)[N], f32x4 (&r)[N]) {
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) pair[n][j] = round_pair(q[n][2 * j], q[n][2 * j + 1]);
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        float a, b, c, d;
+        asm("v_dot2_f32_bf16 %0, %4, %10, %6\n\t"
+            "v_dot2_f32_bf16 %1, %4, %11, %7\n\t"
+            "v_dot2_f32_bf16 %2, %5, %10, %8\n\t"
+            "v_dot2_f32_bf16 %3, %5, %11, %9\n\t"
+            "s_nop 2"
+            : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
+            : "v"(pair[n][0]), "v"(pair[n][1]), "v"(q[n][0]), "v"(q[n][1]), "v"(q[n][2]), "v"(q[n][3]), "s"(0x8000bf80u),
+              "s"(0xbf808000u));
+        r[n] = f32x4{a, b, c, d};
+    }
 }
 
 // N quads cut into P parts stage by stage (an instruction and the one that needs its result are
@@ -153,23 +166,25 @@ __device__ __forceinline__ void split_batch(const f32x4 (&q)[N], u32x2_t (&s)[N]
     for (int n = 0; n < N; ++n) r[n] = q[n];
 #pragma unroll
     for (int k = 0; k < P; ++k) {
+        if (kLive && k == 0 && P > 1) {
+            u32x2_t pair[N];
+            first_parts(q, pair, r);
+#pragma unroll
+            for (int n = 0; n < N; ++n) s[n][0] = pair[n];
+            continue;
+        }
 #pragma unroll
         for (int n = 0; n < N; ++n)
 #pragma unroll
             for (int j = 0; j < 2; ++j) s[n][k][j] = round_pair(r[n][2 * j], r[n][2 * j + 1]);
         if (k + 1 < P) {
 #pragma unroll
-            for (int n = 0; n < N; ++n) {
-                if (kLive && k == 0) {
-                    remainders(s[n][k], q[n], r[n]);
-                    continue;
-                }
+            for (int n = 0; n < N; ++n)
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
                     r[n][2 * j] = minus_low(s[n][k][j], r[n][2 * j]);
                     r[n][2 * j + 1] = minus_high(s[n][k][j], r[n][2 * j + 1]);
                 }
-            }
         }
     }
 }
@@ -377,7 +392,7 @@ struct BlkTiles {
     // zeros, a delta that is set to zero, or rows of an output that are not stored.  It must be finite, hence
     // no reciprocal of a denominator that is not there; and the forward's z counts keys: those are zeroed,
     // in code of their own for the one block that has such rows.  With all tiles in two versions the
-    // compiler copied what both share (that and the state's copies, see remainders: bf16 step, B*H = 16, N = 65536,
+    // compiler copied what both share (that and the state's copies, see first_parts: bf16 step, B*H = 16, N = 65536,
     // 570 -> 560 us; fp32 B*H = 32, N = 3072, forward 28.0 -> 27.1, dQ 37.9 -> 36.5, dV + dK 37.5 -> 36.8).
     __device__ __forceinline__ void park(const int blk) {
         const int nv = min(kBlk, N - blk * kBlk);
