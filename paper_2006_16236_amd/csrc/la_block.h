@@ -12,8 +12,9 @@
 // split once instead of once per product that reads it, the state once per 32 tokens instead of
 // 16, and a quarter as many segments fill the machine (512 workgroups): a state of 16.6 KB per
 // segment less to write, scan and read, and fewer starts of the chain state - first tile - products.
-// Measured (dQ / dV + dK in us): bf16 B*H = 16, N = 65536: 235 / 231 -> 200 / 197; fp32 B*H = 32,
-// N = 3072: 39.8 / 37.5 -> 38 / 35.6; fp32 B*H = 32, N = 1024: 24.9 / 23.5 -> 17.2 / 16.1.
+// Measured (dQ / dV + dK in us, kernel trace, wave -> workgroup kernels): bf16 B*H = 16, N = 65536: 256 / 260 -> 174 / 186;
+// fp32 B*H = 32, N = 1024: 24.4 / 21.3 -> 16.4 / 15.0; fp32 B*H = 32, N = 3072: 43.3 / 40.8 -> 40.9 / 40.9, and the
+// scans 19 -> 12.
 //
 // Four "out" roles form the outputs (one per half of the tokens and half of the columns, or dV and
 // dK), four "state" roles keep the carried state in fp32 accumulators, its tiles spread over them.
@@ -135,7 +136,7 @@ __device__ __forceinline__ Op<3> full_feat(const Op<P> &have, const uint16_t *ti
 // part of the block.  Ahead of it: a quad may come straight from a matrix product, so the block takes roundings that
 // are made here, of the same quad; the compiler has the rounding wait for the product, and the block needs the
 // rounding.  (The registers it writes: in the code built here no product within 15 instructions ahead of a block has
-// one of them as its result or its addend, and a product takes 8 passes.)
+// one of them as its result or its addend.)
 template <int N>
 __device__ __forceinline__ void first_parts(const f32x4 (&q)[N], u32x2_t (&pair)[N], f32x4 (&r)[N]) {
 #pragma unroll
@@ -244,18 +245,20 @@ __device__ __forceinline__ float rows_load1(Rows r, int at) {
 template <typename T> constexpr int kOpParts = is_bf16<T> ? 2 : 3;
 template <typename T> constexpr int kVParts = is_bf16<T> ? 1 : 3;
 
-// The tiles of a block in LDS and their way there.  Q and K take three parts for every element type:
-// besides the products of P parts their feature values are needed in full, for phi' and for the sums that
-// stay fp32, den in the forward, z and delta in the dQ pass, rho in the reverse pass.
+// The tiles of a block in LDS and their way there.  Besides the products of P parts the feature values of Q and K
+// are needed in full, for phi' and for the sums that stay fp32, den in the forward, z and delta in the dQ pass, rho in
+// the reverse pass: three parts for every element type, but for one tensor of the bf16 backward (kRaw, below).
 // kLead: the pass, by the tensor whose gradient it ends in (kLeadQK: the forward, no dO there).
 // bf16 backward (kRaw): dO takes the power of two of 1/den only, which leaves it one exact part, and the rest, 1 to 2
 // in size, goes with phi(Q) where a product needs it (every sum over tokens a takes dO_a and phi(Q_a) together) or to
 // the finished row.  (dO as it is and all of 1/den with phi(Q) saves 1 % of the step, 576 -> 570 us at B*H = 16,
-// N = 65536, but its sums are den times as large: they overflow for gradients for which dO/den is nowhere near it.)  And the pass that needs a
-// tensor's feature values in full per token (phi(Q) in the dQ pass, phi(K) in the other) reads them from an fp32
-// plane, not from three parts.  Against dO/den in two parts and three parts throughout: 44 instead of 56 products
-// per SIMD and block in the dQ pass and 3/4 of the vector instructions, of which either kind costs its own issue
-// time (bf16 step, B*H = 16, N = 65536: 608 -> 570 us; B*H = 32, N = 3072, through autograd: 79 -> 74).
+// N = 65536, but its sums are den times as large: they overflow for gradients for which dO/den is nowhere near it.)
+// And the pass that needs a tensor's feature values in full per token, phi(Q) in the dQ pass, phi(K) in the other,
+// reads them from an fp32 plane and has two parts of that tensor; of the other tensor sums over tokens (z, rho) take
+// three.  Against dO/den in two parts and three parts of Q and K throughout: 40 instead of 51 products per SIMD and
+// block in the dQ pass, 50 instead of 58 in the other, 13 to 14 % fewer vector instructions, of which either kind costs
+// its own issue time (bf16 step, B*H = 16, N = 65536, with the parking in one version: 617 -> 570 us; dQ / dV + dK at
+// B*H = 32, N = 3072 21.6 / 21.9 -> 19.3 / 19.9, kernel traces on two boxes).
 // A 32 x F block is fetched in quads of four elements, one or two per thread: quad k of thread t is
 // row row(t) + k * kStep, columns col(t) .. + 3 (a wave reads whole rows).  Where a block has fewer quads
 // than there are threads, the two blocks of a pair (Q and K, or dO and V) take half of them each.
@@ -856,8 +859,9 @@ struct DqOut : BlkLane {
     __device__ __forceinline__ void publish() {}
     __device__ __forceinline__ void fetch(int blk) { nden = den[min(blk * kBlk + row, N - 1)]; }
     // Kept ahead of the next fetch: sunk behind it, the old and the new denominator take two registers, and the copy
-    // from one to the other waits for the fetch that has just been sent, a trip to memory per block (dQ pass, fp32
-    // B*H = 16, N = 65536: 381 -> 334 us; bf16 206 -> 190)
+    // from one to the other waits for the fetch that has just been sent, a trip to memory per block (dQ pass,
+    // B*H = 16, N = 65536: bf16 206 -> 190 us, fp32, for which the plan takes the wave kernel there, forced 381 -> 334;
+    // step, fp32 B*H = 32, N = 3072, with the wait ahead of the loop: 117.4 -> 113.9)
     __device__ __forceinline__ void parked(int blk) {
         rd = __builtin_amdgcn_rcpf(nden);
         asm volatile("" : "+v"(rd));

@@ -92,17 +92,20 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 // (512 workgroups, two per CU), in whole 32-token blocks: fewer, longer segments, hence less state to
 // write, scan and read.  The wave kernels (la_passes.h) have the shorter chain per token and win
 // where segments are long.  Measured on MI355X, step times wave / workgroup kernels in us (B*H x N):
-//   fp32, D = M = 64   16 x 65536  1051/1099   16 x 16384  274/270   16 x 8192  165/150   16 x 2048  83/60
-//   bf16, D = M = 64   16 x 65536   672/637    16 x 16384  194/159   16 x 8192  122/96    16 x 2048  67/47
-//   fp32, D = M = 32   16 x 65536   460/489    16 x 16384  122/120   16 x 8192   77/71    16 x 2048  38/37
-//   bf16, D = M = 32   16 x 65536   302/332    16 x 16384   91/88    16 x 8192   61/55    16 x 2048  40/38
-//   fp32, 64 x 32      16 x 65536   734/800    16 x 16384  183/194   16 x 8192  111/110
-//   fp32, 32 x 64      16 x 65536   703/735    16 x 16384  174/178   16 x 8192  108/100
+//   fp32, D = M = 64   16 x 65536  1028/1047   16 x 16384  284/271   16 x 8192  164/146   16 x 2048  81/58
+//   bf16, D = M = 64   16 x 65536   689/587    16 x 16384  203/160   16 x 8192  123/90    16 x 2048  65/45
+//   fp32, D = M = 32   16 x 65536   461/469    16 x 16384  127/122   16 x 8192   78/68    16 x 2048  35/32
+//   bf16, D = M = 32   16 x 65536   303/302    16 x 16384   93/86    16 x 8192   61/52    16 x 2048  35/29
+//   fp32, 64 x 32      16 x 65536   736/767    16 x 16384  191/193   16 x 8192  112/106   16 x 2048  57/44
+//   bf16, 64 x 32      16 x 65536   521/476    16 x 16384  151/128   16 x 8192   91/73    16 x 2048  50/37
+//   fp32, 32 x 64      16 x 65536   702/710    16 x 16384  182/179   16 x 8192  106/99    16 x 2048  53/41
+//   bf16, 32 x 64      16 x 65536   473/397    16 x 16384  138/107   16 x 8192   85/63    16 x 2048  45/35
 // so the line lies at 512 tokens per segment (fp32 with D = M = 64, bf16 with a 64-wide head dimension) or
-// 256.  (Those figures are of cuts that rounded up, see below.  Of cuts that do not, drawn sizes of 257 .. 512
-// tokens per segment with a 32-wide D or M take 0.87 .. 0.94 of the wave kernels' step and 0.85 .. 1.02 of their
-// forward: the line of these heads could lie higher.)  Above it bf16 tensors with a 64-wide head dimension keep the wave kernel in the forward only
-// (114/158 us at 16 x 65536, backward 476/400).
+// 256 (fp32 with a 32-wide D or M, where the two are within 2 to 4 % at 512, and bf16 32 x 32).  The line of bf16
+// 32 x 32 heads could lie higher: at 512 tokens per segment they take 0.92 of the wave kernels' step, 100 x 2000
+// 83/71 us, and only the forward is slower (31/34 us at 16 x 16384); it was drawn when the backward took 0.97.
+// Above it bf16 tensors with a 64-wide head dimension keep the wave kernel in the forward only (16 x 65536,
+// D = M = 64: forward 198/218 us, backward 470/372; 64 x 32 132/178, 349/298; 32 x 64 128/145, 303/251).
 // As many segments as fill the machine, not one more: 52 sequences of 3524 tokens in 10 pieces are 520 workgroups
 // for 512 places, and the step took 289 us (wave kernels 222, 9 pieces 218).  One piece more only where the
 // shorter segments are within the lines above and the second round is not nearly empty, or three pieces in all
@@ -114,13 +117,13 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 // sequence, four where a sequence has more than four segments), two per CU gain nothing and double the
 // states.  Two / one per CU in us (B*H x N, D = M = 64):
 //   fp32 forward  40 x 256  20.7/13.1   64 x 512  27.5/19.3   step  160 x 128  52.0/38.2   64 x 480  64.6/52.4
-//   bf16 forward  40 x 256  18.7/11.5   110 x 128  15.0/10.5  step  160 x 128  43.6/25.3   64 x 480  54.4/38.1
+//   bf16 forward  40 x 256  18.7/11.5   110 x 128  15.0/10.5  step  160 x 128  31.2/24.0   64 x 480  53.9/36.6
 // (96 x 300 in ten chunks, 32-wide heads: step 27.1/30.1; 80 x 384, D = 64, M = 32: step 37.6/40.3.)  Up to 64
 // tokens one segment does (forward of one sequence, D = M = 32 6.3/3.9 us, bf16 7.6/4.9; the step of fp32 tensors
 // with D = 64, M = 32 17.2/17.8: those only when the batch fills a quarter of the CUs).
 // Sequences are left whole from 384 on (from 256 if they are short: 256 x 512 136 us, 128 x 1024 in
-// four pieces 135), narrow heads of more than 1024 tokens from 512 (bf16 406 x 1711 whole 1.08 of the wave
-// kernels' time).  Whole sequences, each kernel by what fills the machine
+// four pieces 135), narrow heads of more than 1024 tokens from 512 (bf16 406 x 1711 whole took 1.08 of the
+// wave kernels' step when that line was drawn, 0.92 with the present backward, forward 1.25).  Whole sequences, each kernel by what fills the machine
 // (fp32 D = M = 64, forward / dQ / dV+dK in us):
 //   1024 x 1024  wave 334 / 285 / 317   workgroup 235 / 354 / 358
 //   2048 x 512   wave 208 / 348 / 402   workgroup 252 / 350 / 356
@@ -128,13 +131,15 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 // Workgroup / wave kernels of whole sequences, geometric mean over drawn lengths:
 //   bf16 forward from 1024 on     D = M = 64  1.09 .. 1.31   64 x 32  1.15 .. 1.52   32 x 32  1.03 .. 1.22   32 x 64  0.88
 //   backward with M = 32, fp32, from 1434 on  1.04 .. 1.24
-//   bf16 64 x 32, 513 .. 640 of more than 512 tokens (wave kernels in several pieces)  step 1.06, forward 1.08
+//   bf16 64 x 32, 513 .. 640 of more than 512 tokens (wave kernels in several pieces)  step 1.06, forward 1.08; with
+//   the present backward 550 x 700 has 0.87 and 0.94: the rule that keeps the wave kernels there could go
 // A block is 32 tokens: of one chunk, or three, half a block is padding, and from 256 or 512 sequences on that
 // is not hidden (fp32 979 x 16 forward 5.5/9.7, bf16 1260 x 40 9.7/13.8; three chunks of bf16 D = M = 64 keep
-// the backward, 0.78 of the wave kernels' time at 1100 .. 1400 x 33 .. 48).  One block in all has no next one to
+// the backward, 0.73 .. 0.77 of the wave kernels' time at 1100 .. 1400 x 40).  One block in all has no next one to
 // fetch meanwhile: from 769 sequences on (a fourth per CU) workgroup / wave kernels, 24 tokens
-//   bf16 D = M = 64  forward 1.21, step with only the backward by workgroups 0.98, beyond 1024 0.81;  other heads 1.12 .. 1.27,
-//   0.98 .. 1.06, from 1536 on 0.91 .. 1.05
+//   bf16 D = M = 64  forward 1.13 .. 1.19, step with only the backward by workgroups 0.90, beyond 1024 0.75 .. 0.86;  other
+//   heads forward 1.01 .. 1.17, step 0.91 .. 1.03, from 1536 on with only the backward 0.93 .. 1.02 (the line was drawn when
+//   they took 1.12 .. 1.27, 0.98 .. 1.06, 0.91 .. 1.05)
 //   fp32 D = M = 64  forward 1.07, step with the wave backward 0.92, beyond 1024 with either 0.83;  other heads 1.06 .. 1.20,
 //   0.95 .. 1.06, beyond 1024 forward 0.91 .. 1.00
 // (768 sequences: all 0.83 .. 0.97 but the bf16 forward, 0.99 .. 1.08).
@@ -192,7 +197,8 @@ inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype
         if (bf16 && !narrow) {
             wave.bwd_block = true;
             // four of the forward's segments each where that is within the places, else two (bf16 64 x 32,
-            // 150 x 4096: four make 600 workgroups, 1.06 of the wave kernels' step, two 0.90)
+            // 150 x 4096: four make 600 workgroups and took 1.06 of the wave kernels' step where two took 0.90; two now
+            // take 0.80, 300/373 us)
             wave.bwd_group = tn.bwd_group != 0 ? (tn.bwd_group == 1 ? 1 : 2) : BH * ((wave.nseg + 3) / 4) > target ? 2 : 4;
             if (wave.bwd_group == 1) {       // its workgroups take whole blocks
                 wave.cps += wave.cps & 1;
