@@ -98,7 +98,9 @@ hipError_t launch_scan(float *state, int BH, int nseg, int stride, int mode, hip
 
 // feature d of one token's q or k: eq. 7 of element d, the element itself when the caller has
 // applied the map, or x_i x_j with 8i + j = d for the degree-2 polynomial map (section 3.2)
+// (rounded by itself: not to be folded into the addition to z, which the kernels of several steps add it to from LDS)
 template <typename T> __device__ __forceinline__ float feature_of(const T *row, int d) {
+#pragma clang fp contract(off)
     if constexpr (is_poly<T>) return to_f32(row[d >> 3]) * to_f32(row[d & 7]);
     else return feature<T>(to_f32(row[d]));
 }
@@ -109,55 +111,70 @@ template <typename T> __device__ __forceinline__ float feature_of(const T *row, 
 // update, the z update and the read-out run in one sweep over S (read once,
 // written once); the column sums are combined by wave shuffles, then across the
 // four waves through LDS.  Fixed order everywhere: bit-identical run to run.
-template <int D, int M, typename T>
+//
+// A step of a serving batch is one trip to memory and back, so everything it reads is on its way before anything
+// is computed or stored: with loads and stores in turn the compiler cannot move a load ahead of a store that might
+// alias it, and a workgroup makes up to eight trips one after the other (B*H = 512, D = M = 64, back to back 4.4 -> 3.9 us;
+// 32768: 208.6 -> 200.7).  kStream: S passes the caches by, see launch_recurrent_step.
+template <int D, int M, typename T, bool kStream>
 __global__ __launch_bounds__(256) void recurrent_step_kernel(const T *q, const T *k, const T *v,
                                                              float *S, float *z, T *out,
                                                              float eps) {
     constexpr int LPR = M / 4;            // lanes per row of S
     constexpr int RPW = kWave / LPR;      // rows per wave per iteration
     constexpr int RPI = 4 * RPW;          // rows per workgroup per iteration
+    constexpr int NIT = D / RPI;
     static_assert(D % RPI == 0, "D must be a multiple of the rows swept per iteration");
-    __shared__ float red[4][M];
+    __shared__ __attribute__((aligned(16))) float red[4][M];
     __shared__ float dred[4];
 
     const int bh = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int col4 = (lane % LPR) * 4, rsub = lane / LPR;
+    const int col4 = (lane % LPR) * 4, rsub = lane / LPR, r0 = wave * RPW + rsub;
     constexpr int W = qk_width<T>(D);          // elements per token of q and k
     const T *qh = q + (size_t)bh * W, *kh = k + (size_t)bh * W;
-    float *Sh = S + (size_t)bh * D * M, *zh = z + (size_t)bh * D;
+    float *Sh = S + (size_t)bh * D * M + r0 * M + col4, *zh = z + (size_t)bh * D + r0;
 
+    f32x4 s4[NIT];
+    float zr[NIT], kd[NIT], qd[NIT];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const f32x4 *p = reinterpret_cast<const f32x4 *>(Sh + it * RPI * M);
+        if constexpr (kStream) s4[it] = __builtin_nontemporal_load(p);
+        else s4[it] = *p;
+    }
     const f32x4 v4 = load4(v + (size_t)bh * M + col4);
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        zr[it] = zh[it * RPI];                 // (the same in all lanes of a row)
+        kd[it] = feature_of<T>(kh, it * RPI + r0);
+        qd[it] = feature_of<T>(qh, it * RPI + r0);
+    }
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     float dpart = 0.f;
 #pragma unroll
-    for (int it = 0; it < D / RPI; ++it) {
-        const int d = it * RPI + wave * RPW + rsub;
-        const float kd = feature_of<T>(kh, d);
-        const float qd = feature_of<T>(qh, d);
-        f32x4 s4 = *reinterpret_cast<f32x4 *>(Sh + (size_t)d * M + col4);
+    for (int it = 0; it < NIT; ++it) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            s4[e] = fmaf(kd, v4[e], s4[e]);          // eq. 18
-            acc[e] = fmaf(qd, s4[e], acc[e]);
+            s4[it][e] = fmaf(kd[it], v4[e], s4[it][e]);          // eq. 18
+            acc[e] = fmaf(qd[it], s4[it][e], acc[e]);
         }
-        *reinterpret_cast<f32x4 *>(Sh + (size_t)d * M + col4) = s4;
-        if (col4 == 0) {
-            const float zn = zh[d] + kd;             // eq. 19
-            zh[d] = zn;
-            dpart = fmaf(qd, zn, dpart);
-        }
+        zr[it] += kd[it];                                        // eq. 19
+        dpart = fmaf(qd[it], zr[it], dpart);
+        f32x4 *p = reinterpret_cast<f32x4 *>(Sh + it * RPI * M);
+        if constexpr (kStream) __builtin_nontemporal_store(s4[it], p);
+        else *p = s4[it];
+    }
+    if (col4 == 0) {
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) zh[it * RPI] = zr[it];
     }
 #pragma unroll
     for (int off = LPR; off < kWave; off <<= 1) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], off);
+        dpart += __shfl_xor(dpart, off);
     }
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) dpart += __shfl_xor(dpart, off);
-    if (rsub == 0) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) red[wave][col4 + e] = acc[e];
-    }
+    if (rsub == 0) *reinterpret_cast<f32x4 *>(&red[wave][col4]) = acc;
     if (lane == 0) dred[wave] = dpart;
     __syncthreads();
     if (tid < M) {
@@ -443,9 +460,14 @@ hipError_t launch_recurrent_steps(const void *q, const void *k, const void *v, f
 hipError_t launch_recurrent_step(const void *q, const void *k, const void *v, float *S, float *z,
                                  void *out, int BH, int D, int M, float eps, int dtype,
                                  hipStream_t s) {
+    // What is left of the states in the last-level cache (256 MB) when a step has gone through them serves the next
+    // step; where they are so much larger that little of it does, non-temporal loads and stores are faster (one
+    // without the other is not).  Plain / non-temporal in us, D = M = 64, by MB of S: 134 42.9/42.5, 268 75.7/84.7,
+    // 282 84.0/89.3, 295 92.9/93.5, 308 101/98, 341 120/108, 537 201/173, 786 296/255.
+    const bool stream = (size_t)BH * D * M * sizeof(float) > ((size_t)288 << 20);
     LA_DISPATCH(D, M, dtype, {
-        recurrent_step_kernel<kD, kM, TT><<<BH, 256, 0, s>>>((const TT *)q, (const TT *)k,
-                                                            (const TT *)v, S, z, (TT *)out, eps);
+        if (stream) recurrent_step_kernel<kD, kM, TT, true><<<BH, 256, 0, s>>>((const TT *)q, (const TT *)k, (const TT *)v, S, z, (TT *)out, eps);
+        else recurrent_step_kernel<kD, kM, TT, false><<<BH, 256, 0, s>>>((const TT *)q, (const TT *)k, (const TT *)v, S, z, (TT *)out, eps);
     });
     return hipGetLastError();
 }
