@@ -105,6 +105,20 @@ template <typename T> __device__ __forceinline__ float feature_of(const T *row, 
     else return feature<T>(to_f32(row[d]));
 }
 
+// a b, rounded by itself: the denominators of the three decode kernels are sums of these products over the rows in one order
+__device__ __forceinline__ float product(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
+// (x0 + x1) + (x2 + x3) ... over each 2^LEVELS neighbouring lanes (up to 16), result in all of them
+template <int LEVELS> __device__ __forceinline__ float tree_sum_lanes(float v) {
+    if constexpr (LEVELS > 0) v += dpp_move<0xb1>(v);       // quad_perm: lane ^ 1
+    if constexpr (LEVELS > 1) v += dpp_move<0x4e>(v);       // lane ^ 2
+    if constexpr (LEVELS > 2) v += dpp_move<0x141>(v);      // row_half_mirror: the other four of eight
+    if constexpr (LEVELS > 3) v += dpp_move<0x140>(v);      // row_mirror: the other eight of sixteen
+    return v;
+}
+
 // ---- recurrent decode step (eq. 16-20) -------------------------------------------------------
 // One workgroup of four waves per head.  Every lane owns four adjacent columns of
 // S; M/4 lanes cover a row, a wave covers 256/M rows per iteration.  The rank-1
@@ -132,10 +146,13 @@ __global__ __launch_bounds__(256) void recurrent_step_kernel(const T *q, const T
     const int col4 = (lane % LPR) * 4, rsub = lane / LPR, r0 = wave * RPW + rsub;
     constexpr int W = qk_width<T>(D);          // elements per token of q and k
     const T *qh = q + (size_t)bh * W, *kh = k + (size_t)bh * W;
-    float *Sh = S + (size_t)bh * D * M + r0 * M + col4, *zh = z + (size_t)bh * D + r0;
+    // lane `own` of a row's lanes keeps z of row `own` of its rows
+    const int own = (lane % LPR) % NIT;
+    const bool keeps = lane % LPR < NIT;
+    float *Sh = S + (size_t)bh * D * M + r0 * M + col4, *zh = z + (size_t)bh * D + own * RPI + r0;
 
     f32x4 s4[NIT];
-    float zr[NIT], kd[NIT], qd[NIT];
+    float kd[NIT], qd[NIT];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
         const f32x4 *p = reinterpret_cast<const f32x4 *>(Sh + it * RPI * M);
@@ -143,14 +160,14 @@ __global__ __launch_bounds__(256) void recurrent_step_kernel(const T *q, const T
         else s4[it] = *p;
     }
     const f32x4 v4 = load4(v + (size_t)bh * M + col4);
+    float zr = *zh;
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        zr[it] = zh[it * RPI];                 // (the same in all lanes of a row)
         kd[it] = feature_of<T>(kh, it * RPI + r0);
         qd[it] = feature_of<T>(qh, it * RPI + r0);
     }
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    float dpart = 0.f;
+    float kz = kd[0], qz = qd[0];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
 #pragma unroll
@@ -158,16 +175,14 @@ __global__ __launch_bounds__(256) void recurrent_step_kernel(const T *q, const T
             s4[it][e] = fmaf(kd[it], v4[e], s4[it][e]);          // eq. 18
             acc[e] = fmaf(qd[it], s4[it][e], acc[e]);
         }
-        zr[it] += kd[it];                                        // eq. 19
-        dpart = fmaf(qd[it], zr[it], dpart);
+        if (own == it) kz = kd[it], qz = qd[it];
         f32x4 *p = reinterpret_cast<f32x4 *>(Sh + it * RPI * M);
         if constexpr (kStream) __builtin_nontemporal_store(s4[it], p);
         else *p = s4[it];
     }
-    if (col4 == 0) {
-#pragma unroll
-        for (int it = 0; it < NIT; ++it) zh[it * RPI] = zr[it];
-    }
+    zr += kz;                                                    // eq. 19
+    if (keeps) *zh = zr;
+    float dpart = tree_sum_lanes<NIT == 4 ? 2 : NIT - 1>(product(qz, zr));
 #pragma unroll
     for (int off = LPR; off < kWave; off <<= 1) {
 #pragma unroll
@@ -189,14 +204,16 @@ __global__ __launch_bounds__(256) void recurrent_step_kernel(const T *q, const T
 // additions of a step are those of recurrent_step_kernel in the same order: T steps here and T
 // launches of the single step give bit-identical outputs and states.
 //
-// Steps are taken kStepBatch at a time: every wave runs the rank-1 updates and its lanes' partial
-// read-outs of all steps without a barrier, leaving the partial sums in LDS; after one barrier all threads
-// add them up and store the batch's outputs.  The threads stage the next batch's k, q (each feature
-// mapped once) and v in LDS on the way, the one after that is in flight.  Bounded by instruction issue and LDS:
-// 16 state elements per lane (D = M = 64) take 40 vector instructions and four 16-byte LDS accesses
-// per step.  B*H = 512, T = 784: 742 us with the sums formed step by step (shuffles, one barrier
-// each), 208 us so; 253 us with the features passed between the lanes of a row by DPP (moves of their
-// own) instead of read from LDS.
+// Steps are taken kStepBatch at a time by two groups of four waves.  The first runs the rank-1 updates and its lanes'
+// partial read-outs of a batch and leaves the partial sums in LDS, neighbouring rows added where a row takes 16 lanes
+// (D = M = 64: 36 vector instructions and five LDS accesses per step, no barrier inside a batch).  The second meanwhile
+// adds up and stores the batch before, stages k, q (each feature mapped once) and v of the one to come, and has the one
+// after that in flight: chains of LDS reads, additions and divisions that leave a SIMD idle half of the time where
+// the first group has to walk them itself.  One barrier per batch.
+// B*H = 512, T = 784, D = M = 64: 742 us with the sums formed step by step, 185 with four waves that do everything, 158
+// with eight, 152 with the pairs added, 149 with the first group ahead in the SIMDs' choice.  Bounded by LDS (half of the time
+// without stalls is its) and instruction issue: the features taken from a neighbouring lane by the instruction itself
+// (`v_fmac_f32_dpp`) instead of from LDS cost more than they save (187 -> 199 with four waves).
 constexpr int kStepBatch = 8;
 // (x0 + x1) + (x2 + x3) ...: the order in which the single step's shuffles add
 template <int N> __device__ __forceinline__ float tree_sum(const float (&x)[N]) {
@@ -208,8 +225,14 @@ template <int N> __device__ __forceinline__ float tree_sum(const float (&x)[N]) 
         return tree_sum<N / 2>(y);
     }
 }
+// x0 and x1, columns of four rows in 16 lanes each: the sums of rows 0, 1 and of rows 2, 3; even rows get x0's, odd ones x1's
+__device__ __forceinline__ float add_row_pairs(float x0, float x1) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
 template <int D, int M, typename T>
-__global__ __launch_bounds__(256) void recurrent_steps_kernel(const T *q, const T *k, const T *v,
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void recurrent_steps_kernel(const T *q, const T *k, const T *v,
                                                               float *S, float *z, T *out,
                                                               float eps, int steps, size_t BH) {
     constexpr int LPR = M / 4, RPW = kWave / LPR, RPI = 4 * RPW, NIT = D / RPI;
@@ -218,21 +241,70 @@ __global__ __launch_bounds__(256) void recurrent_steps_kernel(const T *q, const 
     typedef float fN __attribute__((ext_vector_type(NIT)));
     __shared__ __attribute__((aligned(16))) float feat[2][kStepBatch][2][D];          // k, q; row (wave, rsub, it) order
     __shared__ __attribute__((aligned(16))) float vals[2][kStepBatch][M];
-    __shared__ __attribute__((aligned(16))) float part[2][kStepBatch][4][kWave][4];   // read-out partial sums
-    __shared__ __attribute__((aligned(16))) float dpart[2][4][RPW][kStepBatch];
+    constexpr bool kPairs = LPR == 16;         // the sums of neighbouring rows are added before they go to LDS
+    constexpr int kSums = kPairs ? RPW / 2 : RPW;
+    __shared__ __attribute__((aligned(16))) float part[2][kStepBatch][4][kWave][kPairs ? 2 : 4];   // read-out partial sums
+    __shared__ __attribute__((aligned(16))) float dprod[2][kStepBatch][D];            // q z of a row; row order as in feat
 
-    const int bh = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int col4 = (lane % LPR) * 4, rsub = lane / LPR, r0 = wave * RPW + rsub;
-    float *Sh = S + (size_t)bh * D * M, *zh = z + (size_t)bh * D;
+    const int bh = blockIdx.x, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int batches = (steps + kStepBatch - 1) / kStepBatch;
+    if (wave < 4) {
+        __builtin_amdgcn_s_setprio(2);            // every batch waits for these
+        const int lane = threadIdx.x & 63, col4 = (lane % LPR) * 4, rsub = lane / LPR, r0 = wave * RPW + rsub;
+        const int own = (lane % LPR) % NIT;       // z: as in recurrent_step_kernel
+        const bool keeps = lane % LPR < NIT;
+        float *Sh = S + (size_t)bh * D * M, *zh = z + (size_t)bh * D + own * RPI + r0;
 
-    f32x4 s4[NIT];
-    float zr[NIT];                            // (the same in all lanes of a row)
+        f32x4 s4[NIT];
+        float zr = *zh;
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        s4[it] = *reinterpret_cast<const f32x4 *>(Sh + (size_t)(it * RPI + r0) * M + col4);
-        zr[it] = zh[it * RPI + r0];
+        for (int it = 0; it < NIT; ++it) s4[it] = *reinterpret_cast<const f32x4 *>(Sh + (size_t)(it * RPI + r0) * M + col4);
+        __syncthreads();
+        for (int b = 0; b < batches; ++b) {
+            const int n = min(kStepBatch, steps - b * kStepBatch), buf = b & 1;
+            float dp8[kStepBatch];
+            auto step = [&](const int t) {
+                const fN kd = *reinterpret_cast<const fN *>(&feat[buf][t][0][r0 * NIT]);
+                const fN qd = *reinterpret_cast<const fN *>(&feat[buf][t][1][r0 * NIT]);
+                const f32x4 v4 = *reinterpret_cast<const f32x4 *>(&vals[buf][t][col4]);
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int it = 0; it < NIT; ++it) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        s4[it][e] = fmaf(kd[it], v4[e], s4[it][e]);          // eq. 18
+                        acc[e] = fmaf(qd[it], s4[it][e], acc[e]);
+                    }
+                }
+                if constexpr (kPairs) {
+                    const float p0 = add_row_pairs(acc[0], acc[1]), p1 = add_row_pairs(acc[2], acc[3]);
+                    *reinterpret_cast<f32x2_t *>(&part[buf][t][wave][lane][0]) = f32x2_t{p0, p1};
+                } else {
+                    *reinterpret_cast<f32x4 *>(&part[buf][t][wave][lane][0]) = acc;
+                }
+                zr += feat[buf][t][0][r0 * NIT + own];                       // eq. 19
+                return product(feat[buf][t][1][r0 * NIT + own], zr);
+            };
+            if (n == kStepBatch) {
+#pragma unroll
+                for (int t = 0; t < kStepBatch; ++t) dp8[t] = step(t);
+            } else {
+#pragma unroll
+                for (int t = 0; t < kStepBatch; ++t) dp8[t] = t < n ? step(t) : 0.f;
+            }
+            if (keeps) {
+#pragma unroll
+                for (int t = 0; t < kStepBatch; ++t) dprod[buf][t][r0 * NIT + own] = dp8[t];
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) *reinterpret_cast<f32x4 *>(Sh + (size_t)(it * RPI + r0) * M + col4) = s4[it];
+        if (keeps) *zh = zr;
+        return;
     }
     // value j of a thread: step tf + j * TF of the batch, of k or q, feature df; step tv + j * TV, column tid % M of v
+    const int tid = threadIdx.x - 256;
     constexpr int TF = 256 / (2 * D), TV = 256 / M;
     const size_t hop_f = BH * W, hop_v = BH * M;             // from one step to the next
     const int tf = tid / (2 * D), df = tid % D, tv = tid / M, fq = (tid / D) & 1;
@@ -263,78 +335,47 @@ __global__ __launch_bounds__(256) void recurrent_steps_kernel(const T *q, const 
 #pragma unroll
         for (int j = 0; j < NV; ++j) (&vals[buf][0][0])[tid + 256 * j] = xv[j];
     };
+    // NV adjacent columns of one step per thread, 32 threads per step; the denominator's D products are
+    // added up between those threads
+    static_assert(M / NV == 32 && D % 32 == 0, "32 threads per step");
+    const int t = tid / 32, m = NV * (tid % 32);
+    auto outputs = [&](const int b) {
+        const int buf = b & 1;
+        const float *y = &dprod[buf][t][D / 32 * (tid % 32)];
+        float dn = tree_sum_lanes<4>(D == 64 ? y[0] + y[D / 32 - 1] : y[0]);
+        dn = dn + __shfl_xor(dn, 16) + eps;
+        if (b * kStepBatch + t < steps) {
+            float num[NV][4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                float x[NV][kSums];
+#pragma unroll
+                for (int r = 0; r < kSums; ++r) {
+#pragma unroll
+                    for (int i = 0; i < NV; ++i)
+                        x[i][r] = kPairs ? part[buf][t][w][(2 * r + i) * LPR + m / 4][m % 4 / 2] : part[buf][t][w][r * LPR + m / 4][m % 4 + i];
+                }
+#pragma unroll
+                for (int i = 0; i < NV; ++i) num[i][w] = tree_sum<kSums>(x[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < NV; ++i)
+                store_elem(out + ((size_t)(b * kStepBatch + t) * BH + bh) * M + m + i, tree_sum<4>(num[i]) / dn);   // eq. 20
+        }
+    };
     fetch(0);
     stage(0);
     if (kStepBatch < steps) fetch(kStepBatch);
     __syncthreads();
-    int buf = 0;
-    for (int t0 = 0; t0 < steps; t0 += kStepBatch, buf ^= 1) {
-        const int n = min(kStepBatch, steps - t0);
-        float dp8[kStepBatch];
-        auto step = [&](const int t) {
-            const fN kd = *reinterpret_cast<const fN *>(&feat[buf][t][0][r0 * NIT]);
-            const fN qd = *reinterpret_cast<const fN *>(&feat[buf][t][1][r0 * NIT]);
-            const f32x4 v4 = *reinterpret_cast<const f32x4 *>(&vals[buf][t][col4]);
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-            float dp = 0.f;
-#pragma unroll
-            for (int it = 0; it < NIT; ++it) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    s4[it][e] = fmaf(kd[it], v4[e], s4[it][e]);          // eq. 18
-                    acc[e] = fmaf(qd[it], s4[it][e], acc[e]);
-                }
-                zr[it] += kd[it];                                        // eq. 19
-                dp = fmaf(qd[it], zr[it], dp);
-            }
-            *reinterpret_cast<f32x4 *>(&part[buf][t][wave][lane][0]) = acc;
-            return dp;
-        };
-        if (n == kStepBatch) {
-#pragma unroll
-            for (int t = 0; t < kStepBatch; ++t) dp8[t] = step(t);
-        } else {
-#pragma unroll
-            for (int t = 0; t < kStepBatch; ++t) dp8[t] = t < n ? step(t) : 0.f;
+    for (int b = 0; b < batches; ++b) {
+        if (b > 0) outputs(b - 1);
+        if (b + 1 < batches) {
+            stage((b + 1) & 1);
+            if (b + 2 < batches) fetch((b + 2) * kStepBatch);
         }
-        if (col4 == 0) {
-#pragma unroll
-            for (int t = 0; t < kStepBatch; t += 4)
-                *reinterpret_cast<f32x4 *>(&dpart[buf][wave][rsub][t]) = f32x4{dp8[t], dp8[t + 1], dp8[t + 2], dp8[t + 3]};
-        }
-        if (t0 + kStepBatch < steps) {
-            stage(buf ^ 1);
-            if (t0 + 2 * kStepBatch < steps) fetch(t0 + 2 * kStepBatch);
-        }
-        // one barrier per batch: what is read behind it is written again two batches on, behind the next one
         __syncthreads();
-        // NV adjacent columns of one step per thread
-        const int t = tid / (M / NV), m = NV * (tid % (M / NV));
-        if (t < n) {
-            float num[NV][4], den[4];
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                float x[NV][RPW], y[RPW];
-#pragma unroll
-                for (int r = 0; r < RPW; ++r) {
-#pragma unroll
-                    for (int i = 0; i < NV; ++i) x[i][r] = part[buf][t][w][r * LPR + m / 4][m % 4 + i];
-                    y[r] = dpart[buf][w][r][t];
-                }
-#pragma unroll
-                for (int i = 0; i < NV; ++i) num[i][w] = tree_sum<RPW>(x[i]);
-                den[w] = tree_sum<RPW>(y);
-            }
-            const float dn = tree_sum<4>(den) + eps;
-#pragma unroll
-            for (int i = 0; i < NV; ++i) store_elem(out + ((size_t)(t0 + t) * BH + bh) * M + m + i, tree_sum<4>(num[i]) / dn);   // eq. 20
-        }
     }
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        *reinterpret_cast<f32x4 *>(Sh + (size_t)(it * RPI + r0) * M + col4) = s4[it];
-        if (col4 == 0) zh[it * RPI + r0] = zr[it];
-    }
+    outputs(batches - 1);
 }
 
 // The same a step at a time, for launches of a few steps: the next token's q, k, v are fetched while the
@@ -350,15 +391,16 @@ __global__ __launch_bounds__(256) void recurrent_steps_few_kernel(const T *q, co
 
     const int bh = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int col4 = (lane % LPR) * 4, rsub = lane / LPR;
-    float *Sh = S + (size_t)bh * D * M, *zh = z + (size_t)bh * D;
+    const int own = (lane % LPR) % NIT;       // z: as in recurrent_step_kernel
+    const bool keeps = lane % LPR < NIT;
+    float *Sh = S + (size_t)bh * D * M, *zh = z + (size_t)bh * D + own * RPI + wave * RPW + rsub;
 
     f32x4 s4[NIT];
-    float zr[NIT];
+    float zr = *zh;
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
         const int d = it * RPI + wave * RPW + rsub;
         s4[it] = *reinterpret_cast<const f32x4 *>(Sh + (size_t)d * M + col4);
-        zr[it] = zh[d];
     }
     constexpr int W = qk_width<T>(D);          // elements per token of q and k
     // The wave sweeps NR rows of S per step, and every lane of a row needs that row's feature of
@@ -386,7 +428,6 @@ __global__ __launch_bounds__(256) void recurrent_steps_few_kernel(const T *q, co
         if (t + 1 < steps) fetch(t + 1, x_next, v_next);
 
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        float dpart = 0.f;
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const float kd = __shfl(f, it * RPW + rsub);
@@ -396,18 +437,15 @@ __global__ __launch_bounds__(256) void recurrent_steps_few_kernel(const T *q, co
                 s4[it][e] = fmaf(kd, v4[e], s4[it][e]);
                 acc[e] = fmaf(qd, s4[it][e], acc[e]);
             }
-            if (col4 == 0) {
-                zr[it] += kd;
-                dpart = fmaf(qd, zr[it], dpart);
-            }
         }
+        zr += __shfl(f, own * RPW + rsub);
+        float dpart = tree_sum_lanes<NIT == 4 ? 2 : NIT - 1>(product(__shfl(f, NR + own * RPW + rsub), zr));
 #pragma unroll
         for (int off = LPR; off < kWave; off <<= 1) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], off);
+            dpart += __shfl_xor(dpart, off);
         }
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) dpart += __shfl_xor(dpart, off);
         const int buf = t & 1;            // two LDS buffers: one barrier per step suffices
         if (rsub == 0) {
 #pragma unroll
@@ -425,20 +463,20 @@ __global__ __launch_bounds__(256) void recurrent_steps_few_kernel(const T *q, co
     for (int it = 0; it < NIT; ++it) {
         const int d = it * RPI + wave * RPW + rsub;
         *reinterpret_cast<f32x4 *>(Sh + (size_t)d * M + col4) = s4[it];
-        if (col4 == 0) zh[d] = zr[it];
     }
+    if (keeps) *zh = zr;
 }
 
 // Which of the two.  Few / batched steps in us on the device (B*H sequences, fp32 unless noted):
-//   T = 1   64 x 64  64: 2.9/3.3  1024: 6.3/7.5  2048: 11.8/14.2  bf16 4096: 22.0/27.5   32 x 32  8192: 15.6/29.0
-//   T = 2   64 x 64  1024: 7.4/7.7  4096: 26.6/27.6  8192: 49.4/46.2   32 x 32  1024: 4.9/5.1  8192: 21.9/31.0
-//   T = 3   64 x 64  1024: 8.6/8.0  2048: 15.9/17.2  8192: 53.6/46.7   32 x 32  1024: 6.1/5.4  8192: 29.4/32.4
-//   T = 4   64 x 64  2048: 17.9/17.6  bf16 2048: 16.9/17.6  8192: 46.7/50.3   32 x 32  8192: 36.8/33.6
+//   T = 1   64 x 64  64: 2.5/2.8  1024: 5.4/7.1  2048: 10.5/11.5  4096: 22.6/21.5  8192: 42/37  bf16 8192: 33.8/36.9
+//           32 x 32  1024: 3.3/4.5  8192: 13.9/27.6   64 x 32  8192: 23.3/34.0   32 x 64  8192: 23.5/26.1
+//   T = 2   64 x 64  512: 4.5/4.2  1024: 6.4/7.4  2048: 10.8/11.9  4096: 24.6/22.2  bf16 8192: 34.7/37.4   32 x 32  512: 3.4/3.1  8192: 19.4/29.3
+//   T = 3   64 x 64  1024: 7.6/7.7  2048: 13.6/12.7  bf16 2048: 12.8/12.8  4096: 21.4/22.1   32 x 32  2048: 8.1/8.3  4096: 13.6/14.8
+//           64 x 32  2048: 10.1/9.9  4096: 18.0/21.1   32 x 64  4096: 17.2/16.8  8192: 31.0/27.8  bf16 4096: 15.1/17.1
+//   T = 4   64 x 64  2048: 15.7/12.8  bf16 8192: 39.5/37.9   32 x 32  8192: 31.8/32.0
 inline bool few_steps(int steps, int BH, int D, int M, bool bf16) {
-    if (steps == 1) return true;
-    const bool widest = D == 64 && M == 64;
-    if (widest && !bf16 && BH > 4096) return false;
-    return BH >= (steps == 2 ? 1024 : 2048) && steps <= (widest && bf16 ? 4 : 3);
+    if (D == 64 && M == 64 && !bf16 && BH >= 4096) return false;
+    return steps == 1 || (steps == 2 && BH >= 1024) || (steps == 3 && BH >= 4096 && (bf16 || M == 32));
 }
 
 hipError_t launch_recurrent_steps(const void *q, const void *k, const void *v, float *S, float *z,
@@ -450,7 +488,7 @@ hipError_t launch_recurrent_steps(const void *q, const void *k, const void *v, f
                                                                       eps, steps, (size_t)BH);
             return hipGetLastError();
         }
-        recurrent_steps_kernel<kD, kM, TT><<<BH, 256, 0, s>>>((const TT *)q, (const TT *)k,
+        recurrent_steps_kernel<kD, kM, TT><<<BH, 512, 0, s>>>((const TT *)q, (const TT *)k,
                                                              (const TT *)v, S, z, (TT *)out, eps,
                                                              steps, (size_t)BH);
     });
