@@ -25,9 +25,12 @@
 //   park       outputs leave, the next block (fetched a block ago into registers) is mapped, cut
 //              and parked, the state is cut and published, the block after that is fetched
 // Two such workgroups share a compute unit (LDS: 74 KB each at D = M = 64, fp32; one alone takes 1.3
-// to 1.4 times as long), so that one parks while the other multiplies.  Eight waves with one role each
-// where 128 registers suffice, four waves with two roles each in the fp32 backward with 64 columns (the
-// three-part operands spill at 128: dV + dK 0.58 instead of 0.34 ms).  A second block in flight per
+// to 1.4 times as long), so that one parks while the other multiplies.  Eight waves with one role each in 128
+// registers; four waves with two roles each only for the polynomial map.  (The fp32 backward with a 64-wide D or M had
+// four while its state roles took all of their products at once and its two out roles shared their code, and with it
+// the registers of both: at 128 they went to scratch memory, whose loads wait for the fetch that is under way.
+// dQ + dV + dK, four -> eight waves, D = M = 64, N = 1024: B*H = 64 188 -> 161 us, 256 200 -> 189, 512 333 -> 323,
+// 1024 673 -> 652; 64 x 32 145 -> 117, 152 -> 137, 254 -> 237, 500 -> 468.)  A second block in flight per
 // thread changes nothing (bf16 0.606 -> 0.610 ms per step).
 #pragma once
 
@@ -39,7 +42,7 @@ namespace la {
 using la_plan::kBlk;              // tokens per block
 // waves per workgroup of the forward and of the two backward kernels
 constexpr int kFwdWaves = 8;
-template <int D, int M, typename T> constexpr int kBwdWaves = is_bf16<T> || (D == 32 && M == 32) ? 8 : 4;     // (the polynomial map relies on its 4)
+template <int D, int M, typename T> constexpr int kBwdWaves = is_poly<T> ? 4 : 8;     // (blk_chain is written for 4)
 
 // ---- tiles of bf16 parts in LDS ----------------------------------------------------------------
 // A plane holds one part of a tile, row-major, F bf16 per row, in 16-byte pieces that are permuted
@@ -1011,22 +1014,20 @@ struct DqState : BlkLane {
     __device__ __forceinline__ void products() {
         const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
         {
-            Op<P> kn[NT], kk[NT * MT];
-            Op<PV> vv[NT * MT];
-            f32x4 u[NT * MT];
+            Op<P> kn[NT];
 #pragma unroll
             for (int y = 0; y < NT; ++y) kn[y] = read_feat<D, P, false>(tl.sk, kBlk * D, 0, h * NT + y, lane);
 #pragma unroll
             for (int x = 0; x < MT; ++x) {
                 const Op<PV> vf = read_feat<M, PV, false>(tl.sv, kBlk * M, 0, i * MT + x, lane);
+                Op<PV> vv[NT];
+                f32x4 u[NT];
 #pragma unroll
-                for (int y = 0; y < NT; ++y) vv[x * NT + y] = vf, kk[x * NT + y] = kn[y], u[x * NT + y] = zero4;
+                for (int y = 0; y < NT; ++y) vv[y] = vf, u[y] = zero4;
+                mma_n(vv, kn, u);
+#pragma unroll
+                for (int y = 0; y < NT; ++y) U[x][y] += u[y];
             }
-            mma_n(vv, kk, u);
-#pragma unroll
-            for (int x = 0; x < MT; ++x)
-#pragma unroll
-                for (int y = 0; y < NT; ++y) U[x][y] += u[x * NT + y];
             if (i == 0) {
                 const unsigned one2 = 0x3f803f80u;
                 Op<1> ones[NT];
@@ -1043,22 +1044,20 @@ struct DqState : BlkLane {
             }
         }
         if (a.totals != nullptr) {
-            Op<P> qq[NT * MT];
-            Op<PG> gn[MT], gg[NT * MT];
-            f32x4 u[NT * MT];
+            Op<PG> gn[MT];
 #pragma unroll
             for (int x = 0; x < MT; ++x) gn[x] = read_feat<M, PG, false>(tl.sg, kBlk * M, 0, i * MT + x, lane);
 #pragma unroll
             for (int y = 0; y < NT; ++y) {
                 const Op<P> qf = read_feat<D, P, false>(tl.sq, kBlk * D, 0, h * NT + y, lane);
+                Op<P> qq[MT];
+                f32x4 u[MT];
 #pragma unroll
-                for (int x = 0; x < MT; ++x) qq[y * MT + x] = qf, gg[y * MT + x] = gn[x], u[y * MT + x] = zero4;
+                for (int x = 0; x < MT; ++x) qq[x] = qf, u[x] = zero4;
+                mma_n(qq, gn, u);
+#pragma unroll
+                for (int x = 0; x < MT; ++x) R[y][x] += u[x];
             }
-            mma_n(qq, gg, u);
-#pragma unroll
-            for (int y = 0; y < NT; ++y)
-#pragma unroll
-                for (int x = 0; x < MT; ++x) R[y][x] += u[y * MT + x];
         }
     }
     __device__ __forceinline__ void finish(int) {}
@@ -1118,8 +1117,9 @@ __global__ __launch_bounds__((kWave * kBwdWaves<D, M, T>)) __attribute__((amdgpu
 }
 
 // ---- dV and dK (eq. 14-15) -------------------------------------------------------------------------
-// Out role (i, j): the 16 tokens of sub-block i, dV (j = 0) or dK (j = 1).
-template <int D, int M, typename T, bool kStrided>
+// Out role (i, j): the 16 tokens of sub-block i, dV (j = 0) or dK (j = 1).  kJ: j where the waves of either have code
+// of their own, and registers for what that code keeps over the blocks; -1 where a wave may have both.
+template <int D, int M, typename T, bool kStrided, int kJ>
 struct RevOut : BlkLane {
     using Tiles = BlkTiles<kLeadK, D, M, T, kStrided>;
     static constexpr int P = Tiles::P, PV = Tiles::PV, PG = Tiles::PG, TD = D / 16, TM = M / 16, SD = D / 32, SM = M / 32;
@@ -1143,6 +1143,7 @@ struct RevOut : BlkLane {
         outk = static_cast<T *>(a.out2) + seq_base<kStrided>(a.N, a.heads, bh, qk_width<T>(D));
         N = a.N, row = 16 * i + c;
     }
+    __device__ __forceinline__ int j() const { return kJ < 0 ? h : kJ; }
     __device__ __forceinline__ void init() {}
     __device__ __forceinline__ void publish() {}
     __device__ __forceinline__ void fetch(int) {}
@@ -1158,7 +1159,7 @@ struct RevOut : BlkLane {
     __device__ __forceinline__ void products() {
         const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
         f32x4 w0 = zero4, w1;
-        if (h == 0) {
+        if (j() == 0) {
             // scores phi(Q_a) . phi(K_b) (kRaw: times the rest of 1/den_a)
             Op<P> kt[SD];
             read_toks<D, P>(tl.sk, kBlk * D, row, g, kt);
@@ -1212,16 +1213,18 @@ struct RevOut : BlkLane {
                 out[t] = dot(rr, vt, *reinterpret_cast<const f32x4 *>(srho + col_of<kPair>(t, 4 * g)));
             }
             const Op<P> wop = op_of<P>(w0, w1);
+            int rowk = row, lk = lane;       // the addresses are formed again per block, not kept: 128 registers
+            asm volatile("" : "+v"(rowk), "+v"(lk));
 #pragma unroll
             for (int t = 0; t < TD; t += 2) {
-                const Op<P> qf[2] = {read_feat<D, P, kPair>(tl.sq, kBlk * D, 0, t, lane),
-                                     read_feat<D, P, kPair>(tl.sq, kBlk * D, 0, t + 1, lane)};
+                const Op<P> qf[2] = {read_feat<D, P, kPair>(tl.sq, kBlk * D, 0, t, lk),
+                                     read_feat<D, P, kPair>(tl.sq, kBlk * D, 0, t + 1, lk)};
                 const Op<P> wo[2] = {wop, wop};
                 f32x4 o[2] = {out[t], out[t + 1]};
                 mma_n(qf, wo, o);
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    const f32x4 f = tl.full_values(row, col_of<kPair>(t + u, 4 * g) >> 2);
+                    const f32x4 f = tl.full_values(rowk, col_of<kPair>(t + u, 4 * g) >> 2);
 #pragma unroll
                     for (int r = 0; r < 4; ++r) out[t + u][r] = o[u][r] * feature_slope<T>(f[r]);
                 }
@@ -1232,20 +1235,20 @@ struct RevOut : BlkLane {
         const int t0 = blk * kBlk, nv = min(kBlk, N - t0);
         constexpr int kStride = kScratchInTiles<D, M> ? 2 * kBlk * D : 4 * 512;
         if constexpr (is_poly<T>) {      // (four waves, as in the dQ pass)
-            if (h == 0)
+            if (j() == 0)
                 RowsV::template store<kStride>(scratch, rows_of(outv + (size_t)t0 * tl.tsm, tl.tsm, nv), 16 * i * tl.tsm * (int)sizeof(T),
                                                tl.tsm, reinterpret_cast<const f32x4 (&)[TM]>(out), lane);
             __syncthreads();
             float *rows = reinterpret_cast<float *>(tl.sk);
-            if (h != 0) {
+            if (j() != 0) {
 #pragma unroll
                 for (int t = 0; t < TD; ++t) *reinterpret_cast<f32x4 *>(rows + row * kChainStride + 16 * t + 4 * g) = out[t];
             }
             __syncthreads();
             blk_chain(rows, tl.Ks + (size_t)t0 * tl.tsd, outk + (size_t)t0 * tl.tsd, tl.tsd, nv, tl.tid);
             __syncthreads();
-        } else if (TD == TM || h == 0) {
-            T *o = TD == TM && h != 0 ? outk : outv;
+        } else if (TD == TM || j() == 0) {
+            T *o = TD == TM && j() != 0 ? outk : outv;
             RowsV::template store<kStride>(scratch, rows_of(o + (size_t)t0 * tl.tsm, tl.tsm, nv), 16 * i * tl.tsm * (int)sizeof(T), tl.tsm,
                                            reinterpret_cast<const f32x4 (&)[TM]>(out), lane);
         } else {
@@ -1322,22 +1325,20 @@ struct RevState : BlkLane {
     }
     __device__ __forceinline__ void products() {
         const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-        Op<PG> gn[MT], gg[DT * MT];
-        Op<P> qn[DT], qq[DT * MT];
-        f32x4 u[DT * MT];
+        Op<P> qn[DT];
 #pragma unroll
-        for (int y = 0; y < MT; ++y) gn[y] = read_feat<M, PG, false>(tl.sg, kBlk * M, 0, h * MT + y, lane);
+        for (int x = 0; x < DT; ++x) qn[x] = read_feat<D, P, false>(tl.sq, kBlk * D, 0, i * DT + x, lane);
 #pragma unroll
-        for (int x = 0; x < DT; ++x) {
-            qn[x] = read_feat<D, P, false>(tl.sq, kBlk * D, 0, i * DT + x, lane);
+        for (int y = 0; y < MT; ++y) {
+            const Op<PG> gf = read_feat<M, PG, false>(tl.sg, kBlk * M, 0, h * MT + y, lane);
+            Op<PG> gg[DT];
+            f32x4 u[DT];
 #pragma unroll
-            for (int y = 0; y < MT; ++y) qq[x * MT + y] = qn[x], gg[x * MT + y] = gn[y], u[x * MT + y] = zero4;
+            for (int x = 0; x < DT; ++x) gg[x] = gf, u[x] = zero4;
+            mma_n(qn, gg, u);
+#pragma unroll
+            for (int x = 0; x < DT; ++x) U[x][y] += u[x];
         }
-        mma_n(qq, gg, u);
-#pragma unroll
-        for (int x = 0; x < DT; ++x)
-#pragma unroll
-            for (int y = 0; y < MT; ++y) U[x][y] += u[x * MT + y];
         // rho, an fp32 sum: three parts on both sides whatever P is
         const Op<3> dop[1] = {op_of<3>(*reinterpret_cast<const f32x4 *>(sdel + 4 * g),
                                        *reinterpret_cast<const f32x4 *>(sdel + 16 + 4 * g))};
@@ -1373,7 +1374,7 @@ template <int D, int M, typename T, bool kStrided = false>
 __global__ __launch_bounds__((kWave * kBwdWaves<D, M, T>)) __attribute__((amdgpu_waves_per_eu((kBwdWaves<D, M, T> / 2)))) void reverse_block_kernel(
     const PassArgs a) {
     using Tiles = BlkTiles<kLeadK, D, M, T, kStrided>;
-    using OutRole = RevOut<D, M, T, kStrided>;
+    using OutRole = RevOut<D, M, T, kStrided, -1>;
     using StateRole = RevState<D, M, T, kStrided>;
     constexpr bool kOwn = kScratchInTiles<D, M>;
     __shared__ __attribute__((aligned(16))) uint16_t tiles[Tiles::kElems + (kOwn ? 0 : 4 * OutRole::kScratch / 2)];
@@ -1387,8 +1388,11 @@ __global__ __launch_bounds__((kWave * kBwdWaves<D, M, T>)) __attribute__((amdgpu
     char *const scratch = reinterpret_cast<char *>(kOwn ? tiles : tiles + Tiles::kElems);
     Tiles tl(a, tiles, bh, tid, wave);
     if constexpr (Tiles::kWaves == 8) {
-        if (wave < 4) {
-            OutRole out(a, tl, bh, tid, wave, sr, srho, sdel, scratch);
+        if (wave < 2) {
+            RevOut<D, M, T, kStrided, 0> out(a, tl, bh, tid, wave, sr, srho, sdel, scratch);
+            blk_loop(tl, blk0 + count - 1, -1, count, out);
+        } else if (wave < 4) {
+            RevOut<D, M, T, kStrided, 1> out(a, tl, bh, tid, wave, sr, srho, sdel, scratch);
             blk_loop(tl, blk0 + count - 1, -1, count, out);
         } else {
             StateRole st(a, tl, bh, seg, tid, wave, sr, srho, sdel);
