@@ -486,7 +486,7 @@ struct OutRows {
             for (int k = 0; k < 16 / kRows; ++k) {
                 const u32x4_t v = *reinterpret_cast<const u32x4_t *>(scratch + at<kStride>(row0 + kRows * k, piece));
                 __builtin_amdgcn_raw_buffer_store_b128(v, r, (row0 + kRows * k) * ts * (int)sizeof(T) + 16 * piece + at0, 0,
-                                                       !is_bf16<T> && LA_NT_STORES != 0 ? kAuxNt : 0);
+                                                       LA_NT_STORES != 0 ? kAuxNt : 0);
             }
             __builtin_amdgcn_wave_barrier();
         }

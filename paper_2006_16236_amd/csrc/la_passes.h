@@ -245,7 +245,11 @@ __device__ __forceinline__ void store_tile(float *lds_o, const f32x4 (&out)[F / 
             const f32x4 hi = *reinterpret_cast<const f32x4 *>(lds_o + row * tile_stride(F) + col + 4);
             const u32x4_t packed = {round_pair(lo[0], lo[1]), round_pair(lo[2], lo[3]),
                                     round_pair(hi[0], hi[1]), round_pair(hi[2], hi[3])};
-            if (row < nvalid) *reinterpret_cast<u32x4_t *>(tile_out + (size_t)row * tso + col) = packed;
+            u32x4_t *p = reinterpret_cast<u32x4_t *>(tile_out + (size_t)row * tso + col);
+            if (row < nvalid) {
+                if constexpr (LA_NT_STORES != 0) __builtin_nontemporal_store(packed, p);
+                else *p = packed;
+            }
         } else {
             static_assert(sizeof(T) == 4, "fp32 element types");
             f32x4 *p = reinterpret_cast<f32x4 *>(tile_out + (size_t)row * tso + col);
