@@ -199,15 +199,24 @@ int run_causal_fwd(const void *Q, const void *K, const void *V, void *O, float *
                    hipStream_t s, const float *S0 = nullptr, const float *z0 = nullptr,
                    float *S1 = nullptr, float *z1 = nullptr, int heads = 0, int tok_heads = 0) {
     const int nblocks = (int)(BH * p.nseg);
-    if (p.nseg > 1) {
-        la::SegArgs sa{};
-        sa.stream = p.nt_loads;
-        sa.Y = K; sa.Z = V; sa.state = states;
-        sa.N = N; sa.nseg = p.nseg; sa.chunks_per_seg = p.cps; sa.skip_seg = p.nseg - 1;
-        sa.heads = heads; sa.tok_heads = tok_heads;
+    la::SegArgs sa{};
+    sa.stream = p.nt_loads;
+    sa.Y = K; sa.Z = V; sa.state = states;
+    sa.N = N; sa.nseg = p.nseg; sa.chunks_per_seg = p.cps; sa.skip_seg = p.nseg - 1;
+    sa.heads = heads; sa.tok_heads = tok_heads;
+    // (calls with a state in or out carry it through the segments)
+    const bool direct = p.fwd_direct && S0 == nullptr && z0 == nullptr && S1 == nullptr && z1 == nullptr;
+    auto scan = [&]() -> int {
+        ProfScope ps(LA_K_SCAN, s);
+        LA_TRY(la::launch_scan(states, (int)BH, p.nseg, la::state_stride(D, M), la::kScanForward, s, S0, z0, D * M));
+        return LA_OK;
+    };
+    if (p.nseg > 1 && !direct) {
         { ProfScope ps(LA_K_SEG_KV, s); LA_TRY(la::launch_segment_state(p.fwd_block, D, M, (int)t, sa, nblocks, s)); }
-        if (!p.fold)
-            { ProfScope ps(LA_K_SCAN, s); LA_TRY(la::launch_scan(states, (int)BH, p.nseg, la::state_stride(D, M), la::kScanForward, s, S0, z0, D * M)); }
+        if (!p.fold) {
+            const int st = scan();
+            if (st != LA_OK) return st;
+        }
     }
     const bool scanned = p.nseg > 1 && !p.fold;      // the scan has added the caller's state already
     la::PassArgs a{};
@@ -217,6 +226,11 @@ int run_causal_fwd(const void *Q, const void *K, const void *V, void *O, float *
     a.out = O; a.den = den; a.state = p.nseg > 1 ? states : nullptr; a.fold = p.fold;
     a.init_S = scanned ? nullptr : S0; a.init_z = scanned ? nullptr : z0; a.final_S = S1; a.final_z = z1;
     a.N = N; a.nseg = p.nseg; a.chunks_per_seg = p.cps; a.eps = eps;
+    if (direct) {
+        const int ndirect = (int)(BH * ((N + kBlk - 1) / kBlk));
+        { ProfScope ps(LA_K_FWD, s); LA_TRY(la::launch_fwd_direct(D, M, (int)t, a, sa, ndirect, p.nseg > 1 ? nblocks : 0, s)); }
+        return p.nseg > 1 && !p.fold ? scan() : LA_OK;
+    }
     { ProfScope ps(LA_K_FWD, s); LA_TRY(la::launch_pass_fwd(false, p.fwd_block, D, M, (int)t, a, nblocks, s)); }
     return LA_OK;
 }

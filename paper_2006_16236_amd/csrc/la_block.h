@@ -819,6 +819,126 @@ __global__ __launch_bounds__((kWave * kFwdWaves)) __attribute__((amdgpu_waves_pe
     }
 }
 
+// ---- causal forward of a few short sequences -------------------------------------------------------
+// Up to kDirectTokens tokens, few enough of them that every 32 queries have a compute unit to themselves: nothing is
+// carried, a workgroup takes 32 queries and its waves one block of 32 keys each, up to the queries' own, by
+// definition (eq. 8-9): scores, their sums and their product with V; the partial results are added up in LDS.  Such a
+// call is bound by latency: launches, and in each the way to memory and back.  Cut into segments it takes two
+// launches that depend on each other, here one: the segment totals, which a backward may ask the workspace for, come
+// from workgroups of their own in the same launch (block ndirect on).
+// All operands come straight from memory in the order the products need, split by the wave that reads them; the
+// arithmetic is that of FwdOut (three-part scores, den in fp32, scores of bf16 tensors in two parts against V).
+constexpr int kDirectTokens = la_plan::kDirectTokens, kDirectWaves = kDirectTokens / kBlk;
+// features 8 piece .. + 7 of a row, in three parts
+template <int D, typename T>
+__device__ __forceinline__ Op<3> direct_tok(const Rows r, const int row, const int ts, const int piece) {
+    f32x4 lo, hi;
+    if constexpr (is_bf16<T>) {
+        const u32x4_t u = __builtin_bit_cast(u32x4_t, rows_load<0>(r, (row * ts + 8 * piece) * 2, f32x4{}));
+        lo = widen(u32x2_t{u[0], u[1]}), hi = widen(u32x2_t{u[2], u[3]});
+    } else {
+        const int at = (row * ts + (is_poly<T> ? 0 : 8 * piece)) * 4;
+        lo = rows_load<0>(r, at, f32x4{}), hi = rows_load<0>(r, at + 16, f32x4{});
+    }
+    const float by = is_poly<T> ? rows_load1(r, (row * ts + piece) * 4) : 1.0f;        // feature 8i + j = x_i x_j
+    constexpr int kMap = is_poly<T> ? kMapScale : is_feat<T> ? kMapId : kMapPhi;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) lo[k] = map_value<kMap>(lo[k], by), hi[k] = map_value<kMap>(hi[k], by);
+    return op_of<3>(lo, hi);
+}
+template <typename T> __device__ __forceinline__ float direct_v(const Rows r, const int at) {      // at: in elements
+    float v;
+    if constexpr (is_bf16<T>)
+        v = __builtin_bit_cast(float, (unsigned)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, 2 * at, 0, 0) << 16);
+    else v = rows_load1(r, 4 * at);
+    return map_value<kMapFinite>(v, 1.0f);
+}
+
+template <int D, int M, typename T, bool kStrided = false>
+__global__ __launch_bounds__((kWave * kDirectWaves)) void fwd_direct_kernel(const PassArgs a, const SegArgs sa, const int ndirect) {
+    constexpr int SD = D / 32, YT = M / 16, PV = kVParts<T>, PW = is_bf16<T> ? 2 : 3, kSegWaves = 4;
+    constexpr int kRow = M + 4, kPart = kBlk * kRow, kRed = kDirectWaves * (kPart + kBlk);
+    __shared__ __attribute__((aligned(16))) float lds[kRed > seg_lds(D, M, kSegWaves) ? kRed : seg_lds(D, M, kSegWaves)];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), c = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if ((int)blockIdx.x >= ndirect) {
+        if (wave < kSegWaves) segment_totals<D, M, T, kStrided, kSegWaves>(sa, blockIdx.x - ndirect, lds);
+        return;
+    }
+    const int nblk = (a.N + kBlk - 1) / kBlk, qb = blockIdx.x % nblk, bh = blockIdx.x / nblk;
+    const int tsd = tok_stride<kStrided>(a.tok_heads, qk_width<T>(D)), tsm = tok_stride<kStrided>(a.tok_heads, M);
+    const int q0 = qb * kBlk, nq = min(kBlk, a.N - q0);
+    float *const sden = lds + kDirectWaves * kPart;
+    const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+    if (wave <= qb) {
+        const int k0 = wave * kBlk, nk = min(kBlk, a.N - k0);
+        const size_t based = seq_base<kStrided>(a.N, a.heads, bh, qk_width<T>(D)), basem = seq_base<kStrided>(a.N, a.heads, bh, M);
+        const Rows rq = rows_of(static_cast<const T *>(a.Q) + based + (size_t)q0 * tsd, tsd, nq);
+        const Rows rk = rows_of(static_cast<const T *>(a.K) + based + (size_t)k0 * tsd, tsd, nk);
+        const Rows rv = rows_of(static_cast<const T *>(a.V) + basem + (size_t)k0 * tsm, tsm, nk);
+        Op<3> kt[2][SD], qt[2][SD];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int s = 0; s < SD; ++s) {
+                kt[i][s] = direct_tok<D, T>(rk, 16 * i + c, tsd, 4 * s + g);
+                qt[i][s] = direct_tok<D, T>(rq, 16 * i + c, tsd, 4 * s + g);
+            }
+        // V as the operand that a pair of score tiles meets: column 16 y + c of rows 4g .. + 3 and 16 + 4g .. + 3
+        Op<PV> vt[YT];
+#pragma unroll
+        for (int y = 0; y < YT; ++y) {
+            f32x4 lo, hi;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                lo[r] = direct_v<T>(rv, (4 * g + r) * tsm + 16 * y + c);
+                hi[r] = direct_v<T>(rv, (16 + 4 * g + r) * tsm + 16 * y + c);
+            }
+            vt[y] = op_of<PV>(lo, hi);
+        }
+        const bool own = wave == qb;         // the queries' own block: keys up to each query
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            f32x4 w0 = dot(kt[0], qt[i], zero4), w1 = dot(kt[1], qt[i], zero4);     // rows: keys, lane c: query 16 i + c
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {    // select, never multiply
+                w0[r] = !own || i != 0 || 4 * g + r <= c ? w0[r] : 0.f;
+                w1[r] = !own || (i != 0 && 4 * g + r <= c) ? w1[r] : 0.f;
+            }
+            const float p = sum_over_groups(((w0[0] + w0[1]) + (w0[2] + w0[3])) + ((w1[0] + w1[1]) + (w1[2] + w1[3])));
+            if (g == 0) sden[wave * kBlk + 16 * i + c] = p;
+            const Op<PW> wop = op_of<PW>(w0, w1);
+            Op<PW> wo[YT];
+            f32x4 o[YT];
+#pragma unroll
+            for (int y = 0; y < YT; ++y) wo[y] = wop, o[y] = zero4;
+            mma_n(vt, wo, o);
+#pragma unroll
+            for (int y = 0; y < YT; ++y)
+                *reinterpret_cast<f32x4 *>(lds + wave * kPart + (16 * i + c) * kRow + 16 * y + 4 * g) = o[y];
+        }
+    }
+    __syncthreads();
+    constexpr int kQuads = M / 4;            // of a row
+    if (tid >= kBlk * kQuads) return;
+    const int row = tid / kQuads, col = 4 * (tid % kQuads);
+    f32x4 o = zero4;
+    float den = 0.f;
+    for (int w = 0; w <= qb; ++w) {          // (all eight read at once, the others not taken: 0.2 to 0.4 us more)
+        o += *reinterpret_cast<const f32x4 *>(lds + w * kPart + row * kRow + col);
+        den += sden[w * kBlk + row];
+    }
+    if (row >= nq) return;
+    den += a.eps;
+    const float ri = __builtin_amdgcn_rcpf(den);
+    if (a.out != nullptr) {
+        T *p = static_cast<T *>(a.out) + seq_base<kStrided>(a.N, a.heads, bh, M) + (size_t)(q0 + row) * tsm + col;
+        if constexpr (is_bf16<T>) *reinterpret_cast<u32x2_t *>(p) = u32x2_t{round_pair(o[0] * ri, o[1] * ri), round_pair(o[2] * ri, o[3] * ri)};
+        else *reinterpret_cast<f32x4 *>(p) = o * ri;
+    }
+    if (a.den != nullptr && col == 0) a.den[(size_t)bh * a.N + q0 + row] = den;
+}
+
 // ---- causal dQ (eq. 13) ----------------------------------------------------------------------------
 // Out role (i, h): dQ of the 16 tokens of sub-block i, columns of half h.  The scores of a sub-block
 // are formed by both of its roles (12 or 24 of 54 to 66 products per block, against a barrier and an
@@ -1213,8 +1333,8 @@ struct RevOut : BlkLane {
                 out[t] = dot(rr, vt, *reinterpret_cast<const f32x4 *>(srho + col_of<kPair>(t, 4 * g)));
             }
             const Op<P> wop = op_of<P>(w0, w1);
-            int rowk = row, lk = lane;       // the addresses are formed again per block, not kept: 128 registers
-            asm volatile("" : "+v"(rowk), "+v"(lk));
+            int rowk = row, lk = lane;
+            if constexpr (kJ >= 0) asm volatile("" : "+v"(rowk), "+v"(lk));      // addresses formed per block, not kept: 128 registers
 #pragma unroll
             for (int t = 0; t < TD; t += 2) {
                 const Op<P> qf[2] = {read_feat<D, P, kPair>(tl.sq, kBlk * D, 0, t, lk),
@@ -1388,11 +1508,12 @@ __global__ __launch_bounds__((kWave * kBwdWaves<D, M, T>)) __attribute__((amdgpu
     char *const scratch = reinterpret_cast<char *>(kOwn ? tiles : tiles + Tiles::kElems);
     Tiles tl(a, tiles, bh, tid, wave);
     if constexpr (Tiles::kWaves == 8) {
-        if (wave < 2) {
+        constexpr bool kOwnCode = !is_bf16<T> && (D == 64 || M == 64);        // (fp32 32 x 32 step 64 x 784 36.5 -> 36.8 us with it)
+        if (kOwnCode && wave < 2) {
             RevOut<D, M, T, kStrided, 0> out(a, tl, bh, tid, wave, sr, srho, sdel, scratch);
             blk_loop(tl, blk0 + count - 1, -1, count, out);
         } else if (wave < 4) {
-            RevOut<D, M, T, kStrided, 1> out(a, tl, bh, tid, wave, sr, srho, sdel, scratch);
+            RevOut<D, M, T, kStrided, kOwnCode ? 1 : -1> out(a, tl, bh, tid, wave, sr, srho, sdel, scratch);
             blk_loop(tl, blk0 + count - 1, -1, count, out);
         } else {
             StateRole st(a, tl, bh, seg, tid, wave, sr, srho, sdel);

@@ -84,8 +84,8 @@ template <typename T> __device__ __forceinline__ void store_elem(T *p, float v);
 // the kernel that follows a storing one reads faster (the segment sums 0.096 instead of 0.116 ms),
 // the step 2.4 % faster, the non-causal step 4 %.  bf16 rows that leave 16 bytes per lane
 // carry the hint too (non-causal step of 64 x 16384 405 -> 392 us, causal step of 16 x 65536 565 -> 557, of 32 x 3072
-// 75.2 -> 71.4); two-byte bf16 stores stay plain: marked non-temporal they make the non-causal backward 20 % slower.  Loads are plain unless the caller
-// of the kernel asks otherwise (PassArgs::stream).
+// 75.2 -> 71.4); two-byte bf16 stores stay plain: marked non-temporal they make the non-causal backward 20 % slower.
+// Loads are plain unless the caller of the kernel asks otherwise (PassArgs::stream).
 #ifndef LA_NT_STORES
 #define LA_NT_STORES 1
 #endif

@@ -14,6 +14,9 @@ namespace la {
 // block: the workgroup kernels of la_block.h (causal passes); the plan that sized the segments says which
 hipError_t launch_pass_fwd(bool global, bool block, int D, int M, int dtype, const PassArgs &a, int nblocks,
                            hipStream_t s);
+// causal forward of a few short sequences: ndirect workgroups, and in the same launch the totals of nsegs segments
+hipError_t launch_fwd_direct(int D, int M, int dtype, const PassArgs &a, const SegArgs &sa, int ndirect, int nsegs,
+                             hipStream_t s);
 // dQ, 1/den, delta and (a.totals) the per-segment Q, dO sums; causal or against the global sums
 hipError_t launch_pass_dq(bool causal, bool block, int D, int M, int dtype, const PassArgs &a, int nblocks,
                           hipStream_t s);

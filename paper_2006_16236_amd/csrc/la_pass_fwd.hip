@@ -23,6 +23,15 @@ hipError_t launch_pass_fwd(bool global, bool block, int D, int M, int dtype, con
     return hipGetLastError();
 }
 
+hipError_t launch_fwd_direct(int D, int M, int dtype, const PassArgs &a, const SegArgs &sa, int ndirect, int nsegs,
+                             hipStream_t s) {
+    LA_DISPATCH(D, M, dtype, {
+        if (a.tok_heads > 1) fwd_direct_kernel<kD, kM, TT, true><<<ndirect + nsegs, kWave * kDirectWaves, 0, s>>>(a, sa, ndirect);
+        else fwd_direct_kernel<kD, kM, TT><<<ndirect + nsegs, kWave * kDirectWaves, 0, s>>>(a, sa, ndirect);
+    });
+    return hipGetLastError();
+}
+
 hipError_t launch_segment_state(bool block, int D, int M, int dtype, const SegArgs &a, int nblocks,
                                 hipStream_t s) {
     LA_DISPATCH(D, M, dtype, {

@@ -1831,22 +1831,26 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-template <int D, int M, typename T, bool kStrided = false, int kWaves = 1>
-__global__ __launch_bounds__(kWave * kWaves) void segment_state_kernel(const SegArgs a) {
+// LDS of a segment's workgroup: tiles private to each wave; several waves: afterwards the sums of each
+constexpr int seg_sums(int D, int M, int waves) { return waves == 1 ? 0 : D * M + D; }
+constexpr int seg_lds(int D, int M, int waves) {
+    return waves * (tile_floats(D) + tile_floats(M) > seg_sums(D, M, waves) ? tile_floats(D) + tile_floats(M) : seg_sums(D, M, waves));
+}
+// segment `block` of all, by the first kWaves waves of a workgroup
+template <int D, int M, typename T, bool kStrided, int kWaves>
+__device__ __forceinline__ void segment_totals(const SegArgs &a, const unsigned block, float *const lds) {
     constexpr int XT = D / 16, ZT = M / 16;
     // bf16 tensors: 16-bit operands (two parts), not plain bf16 products.  These sums also
     // serve the backward passes (as the states at the segment borders, and as the grand total
     // of the non-causal gradient), which need S and z built from the same feature values
     // to better than 8 bits: their results are differences of nearly equal terms.
     constexpr int kParts = is_bf16<T> ? 2 : 3;
-    // tiles private to each wave; several waves: afterwards the sums of each
-    constexpr int kTiles = tile_floats(D) + tile_floats(M), kSums = kWaves == 1 ? 0 : D * M + D;
-    __shared__ __attribute__((aligned(16))) float lds[kWaves * (kTiles > kSums ? kTiles : kSums)];
+    constexpr int kTiles = tile_floats(D) + tile_floats(M);
     const int lane = threadIdx.x & (kWave - 1), c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float *const lds_y = lds + wave * kTiles, *const lds_z = lds_y + tile_floats(D);
     const bool nt = a.stream != 0;        // non-temporal fetches
-    const int seg = blockIdx.x % a.nseg, bh = blockIdx.x / a.nseg;
+    const int seg = block % a.nseg, bh = block / a.nseg;
     if (seg == a.skip_seg) return;
     const int nchunks = (a.N + kChunk - 1) / kChunk;
     const int ch_begin = seg * a.chunks_per_seg;
@@ -1977,6 +1981,11 @@ __global__ __launch_bounds__(kWave * kWaves) void segment_state_kernel(const Seg
         const float e = sum_over_groups(ec[xt]);
         if (g == 0) st[D * M + 16 * xt + c] = e;
     }
+}
+template <int D, int M, typename T, bool kStrided = false, int kWaves = 1>
+__global__ __launch_bounds__(kWave * kWaves) void segment_state_kernel(const SegArgs a) {
+    __shared__ __attribute__((aligned(16))) float lds[seg_lds(D, M, kWaves)];
+    segment_totals<D, M, T, kStrided, kWaves>(a, blockIdx.x, lds);
 }
 
 }  // namespace la

@@ -12,6 +12,8 @@ namespace la_plan {
 
 constexpr int kChunk = 16;                                        // tokens per chunk (la_device.h)
 constexpr int kBlk = 32;                                          // tokens per block (la_block.h)
+constexpr int kDirectTokens = 256;                                // most tokens of fwd_direct_kernel (la_block.h)
+constexpr int kDirectGroups = 256;                                // most workgroups of it: one per CU
 constexpr int state_stride(int D, int M) { return D * M + D; }    // floats per state (la_passes.h)
 
 // ---- schedule ---------------------------------------------------------------------------------
@@ -25,6 +27,7 @@ struct Plan {
                     // segment totals before (after) its own segment itself
     bool fwd_block; // the forward (and its segment sums) by the workgroup kernels of la_block.h
     bool bwd_block; // the causal backward
+    bool fwd_direct; // the forward from no state by fwd_direct_kernel, the segment totals in the same launch
     int bwd_group;  // how many of the forward's segments a workgroup of the backward takes
     // Whether the call fetches its tiles with non-temporal loads.  A step sweeps Q, K, V (and dO) several
     // times, one kernel after the other.  Where those tensors fit the last-level cache (256 MB) the
@@ -64,7 +67,7 @@ inline Plan make_plan(const Tuning &tn, long BH, int N) {
     p.nseg = (p.nchunks + p.cps - 1) / p.cps;
     p.fold = p.nseg > 1 && p.nseg <= tn.fold_max;
     p.nt_loads = tn.stream == 1 ? 1 : 0;
-    p.fwd_block = p.bwd_block = false;
+    p.fwd_block = p.bwd_block = p.fwd_direct = false;
     p.bwd_group = 0;      // see backward_group
     return p;
 }
@@ -150,7 +153,7 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 // (The polynomial map is cut like fp32 tensors of 64 features.)
 // tok_heads: H of token-major tensors, else 0.  The workgroup kernels address the 32 tokens of a block with
 // 32-bit byte offsets, which token-major tensors of a few hundred thousand heads exceed; the wave kernels do not.
-inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype t, int tok_heads) {
+inline Plan causal_cut(const Tuning &tn, long BH, int N, int C, int M, la_dtype t, int tok_heads) {
     Plan wave = make_plan(tn, BH, N);
     wave.bwd_group = backward_group(tn, C, M);
     const int64_t block_bytes = (int64_t)kBlk * (tok_heads > 1 ? tok_heads : 1) * (C > M ? C : M) * (int64_t)esize(t);
@@ -227,6 +230,21 @@ inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype
     p.fwd_block = bf16 && (C == 64 || narrow) ? 2 * BH < waves : 4 * BH < 3 * waves;
     const bool one_round = 16 * BH >= 7 * waves && 2 * BH <= waves;
     p.bwd_block = bf16 || !(one || one_round || (C == 32 && 2 * BH > waves) || (M == 32 && 10 * BH > 7 * waves));
+    return p;
+}
+
+// ... and whether the forward of short sequences goes by definition (fwd_direct_kernel: one launch, 32 queries per
+// workgroup, up to eight blocks of 32 keys).  Its work grows with the square of the length, so it is for launches that
+// leave compute units idle: up to one workgroup on each, beyond that it loses (fp32 D = M = 64, segments / direct in us:
+// 64 x 96, 192 workgroups, 10.6/8.4; 32 x 256, 256 workgroups, 17.0/11.6; 128 x 96, 384, 11.7/12.1; 64 x 256, 512,
+// 13.9/19.0; bf16 32 x 256 15.7/10.3, 64 x 256 12.5/16.1).  One sequence of 256: fp32 D = M = 32 7.5/5.5, D = M = 64
+// 10.7/8.2, bf16 9.8/6.6; of 65: 6.3/3.9, 9.6/4.9, 8.2/4.5.  Up to 64 tokens of bf16 or of a 32-wide D, one segment in
+// one launch is as fast (3.8/3.9, bf16 4.4/4.5) and stays.  Calls that carry a state in or out go by segments.
+inline Plan causal_plan(const Tuning &tn, long BH, int N, int C, int M, la_dtype t, int tok_heads) {
+    Plan p = causal_cut(tn, BH, N, C, M, t, tok_heads);
+    const long groups = BH * ((N + kBlk - 1) / kBlk);
+    const bool short_one = N <= kBlk || (N <= 2 * kBlk && (esize(t) == 2 || C == 32));
+    p.fwd_direct = tn.block == -1 && p.fwd_block && !short_one && N <= kDirectTokens && groups <= kDirectGroups;
     return p;
 }
 
