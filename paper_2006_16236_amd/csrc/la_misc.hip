@@ -1,6 +1,7 @@
 // Small bandwidth-bound kernels: the scan over segment states and the recurrent
 // decode step (eq. 16-20).
 #include "la_launch.h"
+#include "la_plan.h"
 
 namespace la {
 
@@ -129,7 +130,7 @@ template <int LEVELS> __device__ __forceinline__ float tree_sum_lanes(float v) {
 // A step of a serving batch is one trip to memory and back, so everything it reads is on its way before anything
 // is computed or stored: with loads and stores in turn the compiler cannot move a load ahead of a store that might
 // alias it, and a workgroup makes up to eight trips one after the other (B*H = 512, D = M = 64, back to back 4.4 -> 3.9 us;
-// 32768: 208.6 -> 200.7).  kStream: S passes the caches by, see launch_recurrent_step.
+// 32768: 208.6 -> 200.7).  kStream: S passes the caches by, see la_plan::step_streams.
 template <int D, int M, typename T, bool kStream>
 __global__ __launch_bounds__(256) void recurrent_step_kernel(const T *q, const T *k, const T *v,
                                                              float *S, float *z, T *out,
@@ -498,11 +499,7 @@ hipError_t launch_recurrent_steps(const void *q, const void *k, const void *v, f
 hipError_t launch_recurrent_step(const void *q, const void *k, const void *v, float *S, float *z,
                                  void *out, int BH, int D, int M, float eps, int dtype,
                                  hipStream_t s) {
-    // What is left of the states in the last-level cache (256 MB) when a step has gone through them serves the next
-    // step; where they are so much larger that little of it does, non-temporal loads and stores are faster (one
-    // without the other is not).  Plain / non-temporal in us, D = M = 64, by MB of S: 134 42.9/42.5, 268 75.7/84.7,
-    // 282 84.0/89.3, 295 92.9/93.5, 308 101/98, 341 120/108, 537 201/173, 786 296/255.
-    const bool stream = (size_t)BH * D * M * sizeof(float) > ((size_t)288 << 20);
+    const bool stream = la_plan::step_streams(BH, D, M, (la_dtype)dtype);
     LA_DISPATCH(D, M, dtype, {
         if (stream) recurrent_step_kernel<kD, kM, TT, true><<<BH, 256, 0, s>>>((const TT *)q, (const TT *)k, (const TT *)v, S, z, (TT *)out, eps);
         else recurrent_step_kernel<kD, kM, TT, false><<<BH, 256, 0, s>>>((const TT *)q, (const TT *)k, (const TT *)v, S, z, (TT *)out, eps);

@@ -263,4 +263,19 @@ inline size_t global_bwd_bytes(const Tuning &tn, long BH, int N, int C, int M) {
     return 2 * states_bytes(BH, make_plan(tn, BH, N), C, M) + align256((size_t)BH * N * sizeof(float));
 }
 
+// Whether a decode step's states pass the caches by (non-temporal loads and stores; one without the other is not
+// faster).  What is left of them in the last-level cache (256 MB) when a step has gone through them serves the next
+// step; where they are so much larger that little of it does, they had better pass.  fp32 calls had better from the
+// size of the L2s (32 MB) on already: with plain ones they are slower there than with the loads and stores of the
+// sweep in turn, bf16 calls are not.  Plain / non-temporal in us, D = M = 64, one state again and again, by MB of S:
+//   fp32  23 6.7/6.6  31 10.1/9.6  34 11.7/10.8  67 24.4/21.6  134 45.3/42.6  201 67.3/63.8  229 76/73  268 81/86
+//         295 93/94  341 120/108  537 201/173    in turn  31 9.4  34 10.7  67 23.6  134 43.6  201 63.6  229 72  268 86
+//   bf16  34 9.4/10.8  67 21.5/21.3  134 41.0/42.0  201 60/63  268 81/84  295 91/93
+// Four states in turn, as of the layers of a model: fp32 33 13.4/12.2, 100 37/33, 200 74/64; bf16 11.6/12.1, 37/33, 73/64.
+// Other head sizes: fp32 64 x 32 34 12.9/11.6, 67 25.2/22.5; 32 x 32 34 15.4/14.6.
+inline bool step_streams(long BH, int D, int M, la_dtype t) {
+    const size_t mb = (size_t)BH * D * M * sizeof(float) >> 20;
+    return mb >= 288 || (esize(t) == 4 && mb >= 24 && mb < 240);
+}
+
 }  // namespace la_plan

@@ -49,10 +49,12 @@ def check(kind, B, H, D, M, lengths):
 
 @pytest.mark.parametrize("kind", ["f32", "bf16"])
 @pytest.mark.parametrize("D,M", [(64, 64), (32, 32), (64, 32)])
-def test_states_beyond_the_cache(kind, D, M):
-    """Above 288 MB of S the step passes the caches by: the same bits, sequence by sequence, as a call of few sequences."""
+@pytest.mark.parametrize("mb", [24, 288])
+def test_states_beyond_the_cache(kind, D, M, mb):
+    """Above 288 MB of S, fp32 from 24 MB on, the step passes the caches by: the same bits, sequence by sequence, as calls
+    of few sequences, which do not."""
     import paper_2006_16236_amd as la
-    BH = (288 << 20) // (D * M * 4) + 3
+    BH = (mb << 20) // (D * M * 4) + 3
     dt = torch.bfloat16 if kind == "bf16" else torch.float32
     g = torch.Generator(DEV).manual_seed(D + 2 * M)
     q, k = (torch.randn(BH, 1, D, device=DEV, generator=g).to(dt) for _ in range(2))
@@ -61,7 +63,7 @@ def test_states_beyond_the_cache(kind, D, M):
     z = torch.rand(BH, 1, D, device=DEV, generator=g)
     S1, z1, out, out1 = S.clone(), z.clone(), torch.empty_like(v), torch.empty_like(v)
     la.la_recurrent_step(q, k, v, S, z, out, 1e-6)
-    for part in (slice(0, BH // 2), slice(BH // 2, BH)):
+    for part in (slice(b, b + 1024) for b in range(0, BH, 1024)):
         la.la_recurrent_step(q[part], k[part], v[part], S1[part], z1[part], out1[part], 1e-6)
     torch.cuda.synchronize()
     assert torch.equal(out, out1) and torch.equal(S, S1) and torch.equal(z, z1)
