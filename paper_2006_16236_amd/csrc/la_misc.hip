@@ -232,7 +232,9 @@ __device__ __forceinline__ float add_row_pairs(float x0, float x1) {
     return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
-template <int D, int M, typename T>
+// kOne: one batch in all, and one buffer for it, half of the LDS: such a launch wants many workgroups in flight (eight steps
+// of 4096 sequences, 64 x 32 heads 23.7 -> 18.7 us, 64 x 64 29.4 -> 28.0; with four waves 22.9 and 30.3).
+template <int D, int M, typename T, bool kOne>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void recurrent_steps_kernel(const T *q, const T *k, const T *v,
                                                               float *S, float *z, T *out,
                                                               float eps, int steps, size_t BH) {
@@ -240,15 +242,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void r
     constexpr int W = qk_width<T>(D);          // elements per token of q and k
     constexpr int NF = kStepBatch * 2 * D / 256, NV = kStepBatch * M / 256;      // values a thread stages per batch
     typedef float fN __attribute__((ext_vector_type(NIT)));
-    __shared__ __attribute__((aligned(16))) float feat[2][kStepBatch][2][D];          // k, q; row (wave, rsub, it) order
-    __shared__ __attribute__((aligned(16))) float vals[2][kStepBatch][M];
+    constexpr int kBufs = kOne ? 1 : 2;
+    __shared__ __attribute__((aligned(16))) float feat[kBufs][kStepBatch][2][D];          // k, q; row (wave, rsub, it) order
+    __shared__ __attribute__((aligned(16))) float vals[kBufs][kStepBatch][M];
     constexpr bool kPairs = LPR == 16;         // the sums of neighbouring rows are added before they go to LDS
     constexpr int kSums = kPairs ? RPW / 2 : RPW;
-    __shared__ __attribute__((aligned(16))) float part[2][kStepBatch][4][kWave][kPairs ? 2 : 4];   // read-out partial sums
-    __shared__ __attribute__((aligned(16))) float dprod[2][kStepBatch][D];            // q z of a row; row order as in feat
+    __shared__ __attribute__((aligned(16))) float part[kBufs][kStepBatch][4][kWave][kPairs ? 2 : 4];   // read-out partial sums
+    __shared__ __attribute__((aligned(16))) float dprod[kBufs][kStepBatch][D];            // q z of a row; row order as in feat
 
     const int bh = blockIdx.x, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int batches = (steps + kStepBatch - 1) / kStepBatch;
+    const int batches = kOne ? 1 : (steps + kStepBatch - 1) / kStepBatch;
     if (wave < 4) {
         __builtin_amdgcn_s_setprio(2);            // every batch waits for these
         const int lane = threadIdx.x & 63, col4 = (lane % LPR) * 4, rsub = lane / LPR, r0 = wave * RPW + rsub;
@@ -262,7 +265,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void r
         for (int it = 0; it < NIT; ++it) s4[it] = *reinterpret_cast<const f32x4 *>(Sh + (size_t)(it * RPI + r0) * M + col4);
         __syncthreads();
         for (int b = 0; b < batches; ++b) {
-            const int n = min(kStepBatch, steps - b * kStepBatch), buf = b & 1;
+            const int n = min(kStepBatch, steps - b * kStepBatch), buf = b & (kBufs - 1);
             float dp8[kStepBatch];
             auto step = [&](const int t) {
                 const fN kd = *reinterpret_cast<const fN *>(&feat[buf][t][0][r0 * NIT]);
@@ -341,7 +344,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void r
     static_assert(M / NV == 32 && D % 32 == 0, "32 threads per step");
     const int t = tid / 32, m = NV * (tid % 32);
     auto outputs = [&](const int b) {
-        const int buf = b & 1;
+        const int buf = b & (kBufs - 1);
         const float *y = &dprod[buf][t][D / 32 * (tid % 32)];
         float dn = tree_sum_lanes<4>(D == 64 ? y[0] + y[D / 32 - 1] : y[0]);
         dn = dn + __shfl_xor(dn, 16) + eps;
@@ -381,7 +384,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void r
 
 // The same a step at a time, for launches of a few steps: the next token's q, k, v are fetched while the
 // current one is processed, one barrier per step.  What bounds such a launch is the state's way in and out, and
-// that wants many workgroups in flight: 2 KB of LDS instead of 77, and no fetch of eight steps for one.
+// that wants many workgroups in flight: 2 KB of LDS instead of 20 to 40, and no fetch of eight steps for one.
 template <int D, int M, typename T>
 __global__ __launch_bounds__(256) void recurrent_steps_few_kernel(const T *q, const T *k, const T *v,
                                                               float *S, float *z, T *out,
@@ -468,30 +471,19 @@ __global__ __launch_bounds__(256) void recurrent_steps_few_kernel(const T *q, co
     if (keeps) *zh = zr;
 }
 
-// Which of the two.  Few / batched steps in us on the device (B*H sequences, fp32 unless noted):
-//   T = 1   64 x 64  64: 2.5/2.8  1024: 5.4/7.1  2048: 10.5/11.5  4096: 22.6/21.5  8192: 42/37  bf16 8192: 33.8/36.9
-//           32 x 32  1024: 3.3/4.5  8192: 13.9/27.6   64 x 32  8192: 23.3/34.0   32 x 64  8192: 23.5/26.1
-//   T = 2   64 x 64  512: 4.5/4.2  1024: 6.4/7.4  2048: 10.8/11.9  4096: 24.6/22.2  bf16 8192: 34.7/37.4   32 x 32  512: 3.4/3.1  8192: 19.4/29.3
-//   T = 3   64 x 64  1024: 7.6/7.7  2048: 13.6/12.7  bf16 2048: 12.8/12.8  4096: 21.4/22.1   32 x 32  2048: 8.1/8.3  4096: 13.6/14.8
-//           64 x 32  2048: 10.1/9.9  4096: 18.0/21.1   32 x 64  4096: 17.2/16.8  8192: 31.0/27.8  bf16 4096: 15.1/17.1
-//   T = 4   64 x 64  2048: 15.7/12.8  bf16 8192: 39.5/37.9   32 x 32  8192: 31.8/32.0
-inline bool few_steps(int steps, int BH, int D, int M, bool bf16) {
-    if (D == 64 && M == 64 && !bf16 && BH >= 4096) return false;
-    return steps == 1 || (steps == 2 && BH >= 1024) || (steps == 3 && BH >= 4096 && (bf16 || M == 32));
-}
-
 hipError_t launch_recurrent_steps(const void *q, const void *k, const void *v, float *S, float *z,
                                   void *out, int steps, int BH, int D, int M, float eps, int dtype,
                                   hipStream_t s) {
     LA_DISPATCH(D, M, dtype, {
-        if (few_steps(steps, BH, D, M, is_bf16<TT>)) {
+        if (la_plan::steps_one_by_one(steps, BH, D, M, (la_dtype)dtype)) {
             recurrent_steps_few_kernel<kD, kM, TT><<<BH, 256, 0, s>>>((const TT *)q, (const TT *)k, (const TT *)v, S, z, (TT *)out,
                                                                       eps, steps, (size_t)BH);
             return hipGetLastError();
         }
-        recurrent_steps_kernel<kD, kM, TT><<<BH, 512, 0, s>>>((const TT *)q, (const TT *)k,
-                                                             (const TT *)v, S, z, (TT *)out, eps,
-                                                             steps, (size_t)BH);
+        if (steps <= kStepBatch) recurrent_steps_kernel<kD, kM, TT, true><<<BH, 512, 0, s>>>((const TT *)q, (const TT *)k, (const TT *)v, S, z, (TT *)out,
+                                                                                            eps, steps, (size_t)BH);
+        else recurrent_steps_kernel<kD, kM, TT, false><<<BH, 512, 0, s>>>((const TT *)q, (const TT *)k, (const TT *)v, S, z, (TT *)out, eps, steps,
+                                                                          (size_t)BH);
     });
     return hipGetLastError();
 }

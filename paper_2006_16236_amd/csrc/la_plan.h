@@ -278,4 +278,20 @@ inline bool step_streams(long BH, int D, int M, la_dtype t) {
     return mb >= 288 || (esize(t) == 4 && mb >= 24 && mb < 240);
 }
 
+// Which kernel takes the steps of a launch: one at a time, or a batch of up to eight (and more batches after it).
+// One at a time / in batches, us on the device (B*H sequences, fp32 unless noted):
+//   T = 1   64 x 64  512 4.1/4.2  1024 5.8/6.9  2048 11.0/11.5  4096 23.9/22.9  8192 43.5/42.2  16384 81/85 (polynomial 82/96)
+//                    bf16 4096 21.6/22.7  8192 41.0/41.7  16384 79/85
+//           32 x 32  1024 3.4/3.4  8192 14.7/17.7   64 x 32  8192 24.7/24.9  bf16 21.9/25.0   32 x 64  8192 24.4/22.9  bf16 21.5/22.7
+//   T = 2   64 x 64  512 4.7/4.4  1024 6.8/7.2  2048 11.9/13.0  3000 19.8/18.5  4096 25.1/23.7  bf16 2048 10.8/12.1  8192 41.9/42.5
+//           32 x 32  512 3.3/3.0  8192 19.9/18.6   32 x 64  8192 27.9/24.0  bf16 23.7/23.6
+//           64 x 32  2048 8.3/7.2  4096 15.8/15.7  8192 26.9/26.2  bf16 2048 8.4/7.4  4096 14.4/15.3  8192 24.8/25.9  polynomial 28.6/30.3
+//   T = 3   64 x 64  1024 8.0/7.5  4096 27.5/24.4  bf16 4096 24.4/23.7   32 x 32  4096 14.0/9.7   64 x 32  4096 18.7/16.2
+inline bool steps_one_by_one(int steps, long BH, int D, int M, la_dtype t) {
+    const bool widest = D == 64 && M == 64, fp32 = esize(t) == 4;
+    if (steps == 1) return !(widest && fp32 && BH >= 4096 && BH < 15360);     // (64 to 240 MB of S)
+    if (steps == 2 && widest) return BH >= 1024 && !(fp32 && BH >= 2560);
+    return steps == 2 && D == 64 && BH >= 4096;
+}
+
 }  // namespace la_plan

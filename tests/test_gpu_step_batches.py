@@ -22,7 +22,8 @@ def test_batches_equal_single_steps(kind, D, M):
 def test_few_steps_of_many_sequences(kind, D, M):
     if kind == "poly2" and D != 64:
         pytest.skip("the polynomial map has 64 features")
-    for BH, steps in ((1023, (2,)), (1024, (1, 2, 3)), (2047, (3,)), (2048, (2, 3, 4, 5)), (4096, (2, 3)), (4097, (2, 3, 4))):
+    for BH, steps in ((1023, (2,)), (1024, (1, 2, 3)), (2047, (3,)), (2048, (2, 3, 4, 5)), (2559, (2,)), (2560, (2,)), (4095, (1, 2)),
+                      (4096, (1, 2, 3, 8)), (4097, (2, 3, 4)), (15359, (1,)), (15360, (1,))):
         check(kind, BH, 1, D, M, steps)
 
 

@@ -9,7 +9,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2006_16236_amd", "csrc")
-FIELDS = ("nchunks", "nseg", "cps", "fold", "fwd_block", "bwd_block", "bwd_group", "writes", "states", "bwd", "step_streams")
+FIELDS = ("nchunks", "nseg", "cps", "fold", "fwd_block", "bwd_block", "bwd_group", "writes", "states", "bwd", "step_streams", "one_by_one")
 DEFAULT = dict(target=2048, min_chunks=2, fold=8, group=0, block=-1, heads=0)
 F32, BF16, POLY2 = 0, 1, 4
 
@@ -130,3 +130,20 @@ def test_which_decode_steps_pass_the_caches_by(plans):
         assert [streams(mb, F32, C, M) for mb in (1, 16, 23, 24, 32, 128, 239, 240, 256, 287, 288, 1024)] == [0, 0, 0, 1, 1, 1, 1, 0, 0, 0, 1, 1]
         assert [streams(mb, BF16, C, M) for mb in (1, 24, 128, 240, 287, 288, 1024)] == [0, 0, 0, 0, 0, 1, 1]
     assert streams(32, POLY2) == 1 and streams(16, POLY2) == 0
+
+
+def test_which_decode_steps_go_one_by_one(plans):
+    """One step, and two of many sequences, a token at a time but where the batched kernel is faster; a single step of
+    fp32 sequences with more than 240 MB of state had become up to 14 % slower in a batch."""
+    def one(T, BH, C, M, t=F32):
+        return plans([(BH, T, C, M, t, {})])[0]["one_by_one"]
+    assert [one(1, b, 64, 64) for b in (1, 4095, 4096, 15359, 15360, 1 << 20)] == [1, 1, 0, 0, 1, 1]
+    assert [one(1, b, 64, 64, POLY2) for b in (1, 4096, 16384)] == [1, 0, 1]
+    assert all(one(1, b, C, M, t) for b in (1, 4096, 16384) for C, M, t in ((64, 64, BF16), (32, 32, F32), (64, 32, F32), (32, 64, F32)))
+    assert [one(2, b, 64, 64) for b in (1023, 1024, 2559, 2560, 16384)] == [0, 1, 1, 0, 0]
+    assert [one(2, b, 64, 64, BF16) for b in (1023, 1024, 16384)] == [0, 1, 1]
+    for t in (F32, BF16, POLY2):
+        assert [one(2, b, 64, 32, t) for b in (4095, 4096, 16384)] == [0, 1, 1]
+    assert not any(one(2, b, C, M) for b in (1, 4096, 16384) for C, M in ((32, 32), (32, 64)))
+    assert not any(one(T, b, C, M, t) for T in (3, 4, 8, 9, 784) for b in (1, 1024, 16384)
+                   for C, M, t in ((64, 64, F32), (64, 64, BF16), (32, 32, F32), (64, 32, F32)))
