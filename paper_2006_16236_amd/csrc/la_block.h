@@ -292,7 +292,7 @@ struct BlkTiles {
     const T *Qs, *Ks, *Vs, *Gs;
     const float *scale;                     // of the rows of dO: den (kLeadQ, its reciprocal is taken) or 1/den
     int N, tid, half, tsd, tsm;
-    bool nt;
+    bool nt, nt_out;
     int offd, offm;                         // bytes
     int qd, qm;
     staged_t<T> fq[kQuads<D>], fk[kQuads<D>], fv[kQuads<M>], fg[kQuads<M>];
@@ -304,7 +304,7 @@ struct BlkTiles {
 
     __device__ __forceinline__ BlkTiles(const PassArgs &a, uint16_t *lds, int bh, int tid_, int wave)
         : N(a.N), tid(tid_), half(wave >= kWaves / 2), tsd(tok_stride<kStrided>(a.tok_heads, qk_width<T>(D))),
-          tsm(tok_stride<kStrided>(a.tok_heads, M)), nt(a.stream != 0) {
+          tsm(tok_stride<kStrided>(a.tok_heads, M)), nt(a.stream != 0), nt_out(a.nt_out != 0) {
         sq = lds, sk = sq + PQ * kBlk * D, sv = sk + PK * kBlk * D, sg = sv + PV * kBlk * M;
         if constexpr (kRaw) sf = reinterpret_cast<float *>(sg + PG * kBlk * M);
         Qs = static_cast<const T *>(a.Q) + seq_base<kStrided>(a.N, a.heads, bh, W);
@@ -461,9 +461,10 @@ struct OutRows {
         return (row / (512 / kBytes)) * stride + (row % (512 / kBytes)) * kBytes +
                ((piece ^ (row * kBytes / 256)) << 4);
     }
-    // `r`: the tokens of the block, `at0`: byte offset of the wave's first token and column, `ts`: token stride in elements
+    // `r`: the tokens of the block, `at0`: byte offset of the wave's first token and column, `ts`: token stride in elements,
+    // `nt`: PassArgs::nt_out
     template <int kStride>
-    static __device__ __forceinline__ void store(char *scratch, Rows r, int at0, int ts, const f32x4 (&out)[NT], int lane) {
+    static __device__ __forceinline__ void store(char *scratch, Rows r, int at0, int ts, const f32x4 (&out)[NT], int lane, bool nt) {
         const int c = lane & 15, g = lane >> 4;
         if constexpr (kDirect) {
             __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{round_pair(out[0][0], out[0][1]), round_pair(out[0][2], out[0][3])}, r,
@@ -485,8 +486,9 @@ struct OutRows {
 #pragma unroll
             for (int k = 0; k < 16 / kRows; ++k) {
                 const u32x4_t v = *reinterpret_cast<const u32x4_t *>(scratch + at<kStride>(row0 + kRows * k, piece));
-                __builtin_amdgcn_raw_buffer_store_b128(v, r, (row0 + kRows * k) * ts * (int)sizeof(T) + 16 * piece + at0, 0,
-                                                       LA_NT_STORES != 0 ? kAuxNt : 0);
+                const int to = (row0 + kRows * k) * ts * (int)sizeof(T) + 16 * piece + at0;
+                if (LA_NT_STORES != 0 && (!is_bf16<T> || nt)) __builtin_amdgcn_raw_buffer_store_b128(v, r, to, 0, kAuxNt);      // (uniform)
+                else __builtin_amdgcn_raw_buffer_store_b128(v, r, to, 0, 0);
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -682,7 +684,7 @@ struct FwdOut : BlkLane {
             for (int r = 0; r < 4; ++r) out[y][r] *= ri;
         if (outs != nullptr)             // (a forward that is run for its denominators only)
             OutTile::template store<kScratchInTiles<D, M> ? 2 * kBlk * D : 4 * 512>(
-                scratch, rows_of(outs + (size_t)t0 * tl.tsm, tl.tsm, nv), (16 * i * tl.tsm + h * (M / 2)) * (int)sizeof(T), tl.tsm, out, lane);
+                scratch, rows_of(outs + (size_t)t0 * tl.tsm, tl.tsm, nv), (16 * i * tl.tsm + h * (M / 2)) * (int)sizeof(T), tl.tsm, out, lane, tl.nt_out);
         if (den_out != nullptr && h == 0 && g == 0 && row < nv) den_out[t0 + row] = den;
     }
 };
@@ -1060,7 +1062,7 @@ struct DqOut : BlkLane {
             __syncthreads();
         } else {
             OutTile::template store<kScratchInTiles<D, M> ? 2 * kBlk * D : 4 * 512>(
-                scratch, rows_of(outs + (size_t)t0 * tl.tsd, tl.tsd, nv), (16 * i * tl.tsd + h * (D / 2)) * (int)sizeof(T), tl.tsd, out, lane);
+                scratch, rows_of(outs + (size_t)t0 * tl.tsd, tl.tsd, nv), (16 * i * tl.tsd + h * (D / 2)) * (int)sizeof(T), tl.tsd, out, lane, tl.nt_out);
         }
         if (h == 0 && g == 0 && row < nv) {
             delta_out[t0 + row] = d;
@@ -1357,7 +1359,7 @@ struct RevOut : BlkLane {
         if constexpr (is_poly<T>) {      // (four waves, as in the dQ pass)
             if (j() == 0)
                 RowsV::template store<kStride>(scratch, rows_of(outv + (size_t)t0 * tl.tsm, tl.tsm, nv), 16 * i * tl.tsm * (int)sizeof(T),
-                                               tl.tsm, reinterpret_cast<const f32x4 (&)[TM]>(out), lane);
+                                               tl.tsm, reinterpret_cast<const f32x4 (&)[TM]>(out), lane, tl.nt_out);
             __syncthreads();
             float *rows = reinterpret_cast<float *>(tl.sk);
             if (j() != 0) {
@@ -1370,10 +1372,10 @@ struct RevOut : BlkLane {
         } else if (TD == TM || j() == 0) {
             T *o = TD == TM && j() != 0 ? outk : outv;
             RowsV::template store<kStride>(scratch, rows_of(o + (size_t)t0 * tl.tsm, tl.tsm, nv), 16 * i * tl.tsm * (int)sizeof(T), tl.tsm,
-                                           reinterpret_cast<const f32x4 (&)[TM]>(out), lane);
+                                           reinterpret_cast<const f32x4 (&)[TM]>(out), lane, tl.nt_out);
         } else {
             RowsK::template store<kStride>(scratch, rows_of(outk + (size_t)t0 * tl.tsd, tl.tsd, nv), 16 * i * tl.tsd * (int)sizeof(T), tl.tsd,
-                                           reinterpret_cast<const f32x4 (&)[TD]>(out), lane);
+                                           reinterpret_cast<const f32x4 (&)[TD]>(out), lane, tl.nt_out);
         }
     }
 };

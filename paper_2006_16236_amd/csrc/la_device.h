@@ -78,13 +78,13 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {      // round to
     return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f));     // v_cvt_pk_bf16_f32
 }
 
-template <typename T> __device__ __forceinline__ void store_elem(T *p, float v);
 // The outputs are written once and not read again inside a step, so the fp32 stores are marked
 // non-temporal (the lines need not stay in the caches).  Measured on MI355X at B=2, H=8, N=65536:
 // the kernel that follows a storing one reads faster (the segment sums 0.096 instead of 0.116 ms),
-// the step 2.4 % faster, the non-causal step 4 %.  bf16 rows that leave 16 bytes per lane
-// carry the hint too (non-causal step of 64 x 16384 405 -> 392 us, causal step of 16 x 65536 565 -> 557, of 32 x 3072
-// 75.2 -> 71.4); two-byte bf16 stores stay plain: marked non-temporal they make the non-causal backward 20 % slower.
+// the step 2.4 % faster, the non-causal step 4 %.  bf16 rows that leave 16 bytes per lane and single elements of fp32
+// calls with the caller's features carry the hint from some size of the outputs on, PassArgs::nt_out: of smaller ones
+// it costs whoever reads them behind the call more than it gives.  Two-byte bf16 stores stay plain: marked
+// non-temporal they make the non-causal backward 20 % slower.
 // Loads are plain unless the caller of the kernel asks otherwise (PassArgs::stream).
 #ifndef LA_NT_STORES
 #define LA_NT_STORES 1
@@ -92,21 +92,10 @@ template <typename T> __device__ __forceinline__ void store_elem(T *p, float v);
 #ifndef LA_NT_LOADS
 #define LA_NT_LOADS 1
 #endif
-template <> __device__ __forceinline__ void store_elem<float>(float *p, float v) {
-    if constexpr (LA_NT_STORES != 0) __builtin_nontemporal_store(v, p);
-    else *p = v;
-}
-template <> __device__ __forceinline__ void store_elem<bf16_t>(bf16_t *p, float v) {
-    p->bits = f32_to_bf16_bits(v);
-}
-template <> __device__ __forceinline__ void store_elem<feat_f32>(feat_f32 *p, float v) {
-    store_elem(&p->v, v);
-}
-template <> __device__ __forceinline__ void store_elem<poly2_f32>(poly2_f32 *p, float v) {
-    store_elem(reinterpret_cast<float *>(p), v);
-}
-template <> __device__ __forceinline__ void store_elem<feat_bf16>(feat_bf16 *p, float v) {
-    p->bits = f32_to_bf16_bits(v);
+template <bool kNt = true, typename T> __device__ __forceinline__ void store_elem(T *p, float v) {
+    if constexpr (is_bf16<T>) p->bits = f32_to_bf16_bits(v);
+    else if constexpr (kNt && LA_NT_STORES != 0) __builtin_nontemporal_store(v, reinterpret_cast<float *>(p));
+    else *reinterpret_cast<float *>(p) = v;
 }
 
 // four consecutive floats of a state (written by the kernel before, read once per workgroup:

@@ -133,6 +133,8 @@ struct PassArgs {
     // and need not stay in the caches); 0, the host's default: plain loads, so that a later kernel
     // of the same step finds in the last-level cache what fits there.
     int stream;
+    // 1: the stores whose kind la_plan::nt_outputs decides by size are non-temporal (see store_elem)
+    int nt_out;
 };
 
 // element offset of token 0 of sequence bh in a tensor of row width F, and the distance
@@ -220,16 +222,19 @@ __device__ __forceinline__ void park_tile(float *tile, const ST (&st)[F / 16],
     }
 }
 
+// Before and after the non-temporal one of two stores that differ in nothing else: the compiler would make them one, plain
+__device__ __forceinline__ void keep_apart() { asm volatile("; non-temporal"); }
+
 // A 16 x F output tile from the MFMA layout (lane (c, g), out[zt][r]: token 4g + r, column
 // 16zt + c) to memory through one LDS tile private to the calling wave: written as it is, read
 // back so that a lane holds consecutive columns of one token (four fp32, or eight values that
 // are rounded to bf16 in pairs) and stored 16 bytes per lane.  A wave instruction then writes
 // whole rows (F = 64: four tokens of 256 bytes, or eight of 128 bytes for bf16) where
 // element-wise stores write 64-byte (bf16: 32-byte) pieces, one element per lane.
-// `tile_out` points at column 0 of the tile's first token, `tso` is the token stride in elements.
+// `tile_out` points at column 0 of the tile's first token, `tso` is the token stride in elements; `nt`: PassArgs::nt_out.
 template <int F, typename T>
 __device__ __forceinline__ void store_tile(float *lds_o, const f32x4 (&out)[F / 16], T *tile_out,
-                                           const int tso, const int nvalid, const int lane) {
+                                           const int tso, const int nvalid, const int lane, const bool nt) {
     const int c = lane & 15, g = lane >> 4;
 #pragma unroll
     for (int zt = 0; zt < F / 16; ++zt)
@@ -247,8 +252,13 @@ __device__ __forceinline__ void store_tile(float *lds_o, const f32x4 (&out)[F / 
                                     round_pair(hi[0], hi[1]), round_pair(hi[2], hi[3])};
             u32x4_t *p = reinterpret_cast<u32x4_t *>(tile_out + (size_t)row * tso + col);
             if (row < nvalid) {
-                if constexpr (LA_NT_STORES != 0) __builtin_nontemporal_store(packed, p);
-                else *p = packed;
+                if (LA_NT_STORES != 0 && F == 64 && nt) {       // (uniform; nt_outputs says never of narrower rows)
+                    keep_apart();
+                    __builtin_nontemporal_store(packed, p);
+                    keep_apart();
+                } else {
+                    *p = packed;
+                }
             }
         } else {
             static_assert(sizeof(T) == 4, "fp32 element types");
@@ -258,6 +268,34 @@ __device__ __forceinline__ void store_tile(float *lds_o, const f32x4 (&out)[F / 
                 else *p = lo;
             }
         }
+    }
+}
+
+// The same tile element by element, from the lane's own position `lane_out` (token 4g, column c)
+template <int FT, typename T>
+__device__ __forceinline__ void store_tile_elems(T *lane_out, const f32x4 (&out)[FT], const int tso, const int nvalid, const int g, const bool nt) {
+    auto whole = [&](auto nt_tag) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int zt = 0; zt < FT; ++zt) store_elem<decltype(nt_tag)::value>(lane_out + (r * tso + 16 * zt), out[zt][r]);
+    };
+    constexpr bool kBySize = std::is_same<T, feat_f32>::value;
+    if (nvalid == kChunk) {                  // (uniform branches)
+        if (kBySize && !nt) {
+            whole(std::false_type{});
+        } else {
+            if constexpr (kBySize) keep_apart();
+            whole(std::true_type{});
+            if constexpr (kBySize) keep_apart();
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (4 * g + r < nvalid) {
+#pragma unroll
+                for (int zt = 0; zt < FT; ++zt) store_elem<!kBySize>(lane_out + (r * tso + 16 * zt), out[zt][r]);
+            }
     }
 }
 
@@ -913,20 +951,9 @@ __device__ __forceinline__ void run_pass(const PassArgs &a, Stager &stg, const f
         } else if ((PASS == kFwd || PASS == kGlobal) && out_tensor == nullptr) {
             // a forward that is run for its denominators only (uniform branch)
         } else if (lds_o != nullptr) {      // uniform
-            store_tile<DZ>(lds_o, out, outs + (size_t)t0 * tso, tso, nvalid, lane);
-        } else if (nvalid == kChunk) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int zt = 0; zt < ZT; ++zt) store_elem(lane_out + (r * tso + 16 * zt), out[zt][r]);
+            store_tile<DZ>(lds_o, out, outs + (size_t)t0 * tso, tso, nvalid, lane, a.nt_out != 0);
         } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (4 * g + r < nvalid) {
-#pragma unroll
-                    for (int zt = 0; zt < ZT; ++zt)
-                        store_elem(lane_out + (r * tso + 16 * zt), out[zt][r]);
-                }
+            store_tile_elems<ZT>(lane_out, out, tso, nvalid, g, a.nt_out != 0);
         }
 
         // ---- carry: U += Y^T Z, and the ones-column vector --------------------------------
@@ -1440,8 +1467,9 @@ __global__ __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(2))) 
 // The input tiles are double-buffered in LDS: each wave parks its two tiles of the next chunk
 // while the other is still reading the current ones, so a chunk costs two barriers and the
 // feature map (32 exponentials per lane and chunk, wave 0) is off the critical path.
+// (narrow heads: four waves per SIMD, 128 registers, which the two kinds of stores of given features exceed by two without the bound)
 template <int D, int M, typename T, bool kStrided = false>
-__global__ __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(2))) void dq_causal_kernel(
+__global__ __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu((D == 32 && M == 32 ? 4 : 2)))) void dq_causal_kernel(
     const PassArgs a) {
     constexpr int DT = D / 16, MT = M / 16;
     // fp32 tensors: three-part operands where a product runs on the bf16 pipe, fp32 MFMAs for the
@@ -1626,18 +1654,8 @@ __global__ __launch_bounds__(2 * kWave) __attribute__((amdgpu_waves_per_eu(2))) 
                     store_elem(p, g0);
                     store_elem(p + 1, g1);
                 }
-            } else if (nvalid == kChunk) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int zt = 0; zt < DT; ++zt) store_elem(lane_out + (r * tso + 16 * zt), out[zt][r]);
             } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (4 * g + r < nvalid) {
-#pragma unroll
-                        for (int zt = 0; zt < DT; ++zt) store_elem(lane_out + (r * tso + 16 * zt), out[zt][r]);
-                    }
+                store_tile_elems<DT>(lane_out, out, tso, nvalid, g, a.nt_out != 0);
             }
             // lanes c < 4 of each group write 1/den and delta of token 4g + c
             const float dsel = c == 0 ? d4[0] : c == 1 ? d4[1] : c == 2 ? d4[2] : d4[3];

@@ -34,8 +34,8 @@ struct Plan {
     // later sweeps find them there if the loads are plain (measured: MNIST / CIFAR shapes 2 % and 9 %
     // faster than with non-temporal loads); where they do not, the two kinds are equally fast for fp32
     // tensors and plain loads 1.5 % faster for bf16 ones (N = 65536).  So plain loads are the default
-    // and LA_STREAM_LOADS=1 is there for measuring.  (The outputs are always stored non-temporally and
-    // the segment states always loaded plain.)
+    // and LA_STREAM_LOADS=1 is there for measuring.  (How the outputs are stored: nt_outputs; the segment states are always
+    // loaded plain.)
     int nt_loads;
 };
 
@@ -261,6 +261,27 @@ inline size_t causal_bwd_bytes(const Tuning &tn, long BH, int N, int C, int M) {
 // non-causal: the two grand totals; den if it is recomputed
 inline size_t global_bwd_bytes(const Tuning &tn, long BH, int N, int C, int M) {
     return 2 * states_bytes(BH, make_plan(tn, BH, N), C, M) + align256((size_t)BH * N * sizeof(float));
+}
+
+// Whether a call's outputs leave with non-temporal stores, where that goes by size: bf16 rows (16 bytes per lane), and
+// the element-wise stores of fp32 calls with the caller's features (all other fp32 stores always do, two-byte ones never).
+// The call's own next kernel reads faster, but what reads the outputs behind the call no longer finds them in the
+// last-level cache.  Plain / non-temporal in us, token-major, H = 8, D = M = 64: the forward and a projection of O
+// (F); the step with sums of O, dQ, dK, dV with tensors of their size (A); the step with the projection and the
+// weight and input gradients of dQ, dK, dV (G); by MB of O:
+//   bf16, causal      1 x 512 0.5 F 19.9/21.4   4 x 784 3 F 30.4/31.8 G 157/167   8 x 1024 8 F 37.4/38.8 G 263/299
+//                     4 x 3072 13 F 44.1/45.6 A 97.6/99.2 G 352/404   64 x 1024 67 F 123/128 A 369/366 G 1178/1184
+//                     128 x 1024 134 F 235/234 A 795/788 G 2123/2113   2 x 65536 134 F 293/284 A 820/810 G 2141/2130
+//   bf16, non-causal  4 x 3072 13 F 48.7/50.0 G 351/386   5 x 16384 84 F 184/189   95 x 1024 100 F 231/233 A 637/639 G 1798/1808
+//                     8 x 16384 134 F 250/247 A 678/669 G 2004/1996
+//   given features    non-causal 8 x 1024 17 G 387/398   4 x 3072 25 G 567/583   8 x 3072 50 A 250/247 G 992/993
+//                     causal 33 x 1000 68 A 411/403 G 1697/1682   3 x 16384 101 A 724/706 G 2250/2241
+// bf16 heads with a 32-wide D or M (rows of 64 bytes) gain nothing at any size: 32 x 32, non-causal, 84 MB A 460/467
+// G 1734/1750, 168 MB A 915/918 G 2939/2963.
+inline bool nt_outputs(long BH, int N, int C, int M, la_dtype t) {
+    const size_t mb = (size_t)BH * N * (C > M ? C : M) * esize(t) >> 20;
+    if (esize(t) == 2) return C == 64 && M == 64 && mb >= 128;
+    return t != LA_F32_FEATURES || mb >= 64;
 }
 
 // Whether a decode step's states pass the caches by (non-temporal loads and stores; one without the other is not
