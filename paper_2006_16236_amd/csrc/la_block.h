@@ -26,12 +26,16 @@
 //              and parked, the state is cut and published, the block after that is fetched
 // Two such workgroups share a compute unit (LDS: 74 KB each at D = M = 64, fp32; one alone takes 1.3
 // to 1.4 times as long), so that one parks while the other multiplies.  Eight waves with one role each in 128
-// registers; four waves with two roles each only for the polynomial map.  (The fp32 backward with a 64-wide D or M had
+// registers; four waves with two roles each only for the polynomial map.  The fp32 backward with a 64-wide D or M had
 // four while its state roles took all of their products at once and its two out roles shared their code, and with it
 // the registers of both: at 128 they went to scratch memory, whose loads wait for the fetch that is under way.
-// dQ + dV + dK, four -> eight waves, D = M = 64, N = 1024: B*H = 64 188 -> 161 us, 256 200 -> 189, 512 333 -> 323,
-// 1024 673 -> 652; 64 x 32 145 -> 117, 152 -> 137, 254 -> 237, 500 -> 468.)  A second block in flight per
-// thread changes nothing (bf16 0.606 -> 0.610 ms per step).
+// dQ + dV + dK of whole calls as the plan cuts them, four -> eight waves (B*H x N, us): D = M = 64 32 x 3072 77.1 -> 71.3,
+// 64 x 512 33.3 -> 30.0, 200 x 512 80.2 -> 73.4, 256 x 1024 175 -> 163, 512 x 512 164 -> 152, 700 x 1024 514 -> 486; 64 x 32
+// 32 x 3072 51.8 -> 48.2, 128 x 1024 67.3 -> 60.5, 512 x 1024 256 -> 230; 32 x 64 48.5 -> 45.0, 61.0 -> 57.4, 233 -> 214.
+// At D = M = 64 dQ is one register short (8 bytes of scratch per lane), dV + dK none; while they were four and two short,
+// workgroups of one to three blocks were slower than with four waves (32 x 1024 in pieces of two 34.9 us, 33.3 so, four waves
+// 33.7; 512 x 32 14.3, 13.9, 14.0; 768 x 64 36.1, 33.0, 34.3), and 256 x 1024 is 2 to 3 % slower so than it was then.
+// A second block in flight per thread changes nothing (bf16 0.606 -> 0.610 ms per step).
 #pragma once
 
 #include "la_passes.h"
@@ -951,6 +955,7 @@ struct DqOut : BlkLane {
     using Tiles = BlkTiles<kLeadQ, D, M, T, kStrided>;
     static constexpr int P = Tiles::P, PV = Tiles::PV, PG = Tiles::PG, NT = D / 32, SM = M / 32;
     static constexpr bool kPair = is_bf16<T> && NT == 2;
+    static constexpr bool kFresh = Tiles::kWaves == 8 && !is_bf16<T> && D == 64 && M == 64;
     using OutTile = OutRows<T, NT>;
     const Tiles &tl;
     const uint16_t *ss;
@@ -1021,9 +1026,11 @@ struct DqOut : BlkLane {
         }
         const Op<P> wop = op_of<P>(w0, w1);
         float p = 0.f;
+        int lk = lane;
+        if constexpr (kFresh) asm volatile("" : "+v"(lk));      // addresses formed per block, not kept: 128 registers
 #pragma unroll
         for (int y = 0; y < NT; ++y) {
-            const Op<P> kf[1] = {read_feat<D, P, kPair>(tl.sk, kBlk * D, 0, h * NT + y, lane)};
+            const Op<P> kf[1] = {read_feat<D, P, kPair>(tl.sk, kBlk * D, 0, h * NT + y, lk)};
             const Op<P> wo[1] = {wop};
             const Op<1> mo[1] = {mask};
             f32x4 o[1] = {out[y]};
@@ -1346,7 +1353,7 @@ struct RevOut : BlkLane {
                 mma_n(qf, wo, o);
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    const f32x4 f = tl.full_values(rowk, col_of<kPair>(t + u, 4 * g) >> 2);
+                    const f32x4 f = tl.full_values(rowk, col_of<kPair>(t + u, 4 * (lk >> 4)) >> 2);
 #pragma unroll
                     for (int r = 0; r < 4; ++r) out[t + u][r] = o[u][r] * feature_slope<T>(f[r]);
                 }
