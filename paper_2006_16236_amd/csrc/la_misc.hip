@@ -106,10 +106,22 @@ template <typename T> __device__ __forceinline__ float feature_of(const T *row, 
     else return feature<T>(to_f32(row[d]));
 }
 
-// a b, rounded by itself: the denominators of the three decode kernels are sums of these products over the rows in one order
-__device__ __forceinline__ float product(float a, float b) {
-#pragma clang fp contract(off)
-    return a * b;
+// The denominators of the three decode kernels: the products q z of the NIT rows that a lane sweeps, row after row, each
+// added unrounded; over the lanes and waves in the order of the columns' sums.  (Rounded products, added pairwise, lose where
+// they cancel: outputs of the polynomial map, 300 steps, 3.5e-6 -> 6.8e-6 against 64 bits.)
+template <int NIT, typename Q> __device__ __forceinline__ float rows_dot(const Q &q, const float (&z)[NIT]) {
+    float d = 0.f;
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) d = fmaf(q[it], z[it], d);
+    return d;
+}
+// the same from z as the lanes of a row keep it: lane `it` of each four (of each two: NIT = 2) has row it's
+template <int NIT> __device__ __forceinline__ float rows_dot_of_lanes(const float (&q)[NIT], const float zr) {
+    float z[4] = {dpp_move<0x00>(zr), NIT > 1 ? dpp_move<0x55>(zr) : 0.f, NIT > 2 ? dpp_move<0xaa>(zr) : 0.f, NIT > 2 ? dpp_move<0xff>(zr) : 0.f};
+    float zn[NIT];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) zn[it] = z[it];
+    return rows_dot<NIT>(q, zn);
 }
 // (x0 + x1) + (x2 + x3) ... over each 2^LEVELS neighbouring lanes (up to 16), result in all of them
 template <int LEVELS> __device__ __forceinline__ float tree_sum_lanes(float v) {
@@ -168,7 +180,7 @@ __global__ __launch_bounds__(256) void recurrent_step_kernel(const T *q, const T
         qd[it] = feature_of<T>(qh, it * RPI + r0);
     }
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    float kz = kd[0], qz = qd[0];
+    float kz = kd[0];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
 #pragma unroll
@@ -176,14 +188,14 @@ __global__ __launch_bounds__(256) void recurrent_step_kernel(const T *q, const T
             s4[it][e] = fmaf(kd[it], v4[e], s4[it][e]);          // eq. 18
             acc[e] = fmaf(qd[it], s4[it][e], acc[e]);
         }
-        if (own == it) kz = kd[it], qz = qd[it];
+        if (own == it) kz = kd[it];
         f32x4 *p = reinterpret_cast<f32x4 *>(Sh + it * RPI * M);
         if constexpr (kStream) __builtin_nontemporal_store(s4[it], p);
         else *p = s4[it];
     }
     zr += kz;                                                    // eq. 19
     if (keeps) *zh = zr;
-    float dpart = tree_sum_lanes<NIT == 4 ? 2 : NIT - 1>(product(qz, zr));
+    float dpart = rows_dot_of_lanes<NIT>(qd, zr);
 #pragma unroll
     for (int off = LPR; off < kWave; off <<= 1) {
 #pragma unroll
@@ -207,8 +219,8 @@ __global__ __launch_bounds__(256) void recurrent_step_kernel(const T *q, const T
 //
 // Steps are taken kStepBatch at a time by two groups of four waves.  The first runs the rank-1 updates and its lanes'
 // partial read-outs of a batch and leaves the partial sums in LDS, neighbouring rows added where a row takes 16 lanes
-// (D = M = 64: 36 vector instructions and five LDS accesses per step, no barrier inside a batch).  The second meanwhile
-// adds up and stores the batch before, stages k, q (each feature mapped once) and v of the one to come, and has the one
+// (D = M = 64: 41 vector instructions and four LDS accesses per step, no barrier inside a batch).  The second meanwhile
+// adds up and stores the batch before, with its denominators (q and z of each row), stages k, q (each feature mapped once) and v of the one to come, and has the one
 // after that in flight: chains of LDS reads, additions and divisions that leave a SIMD idle half of the time where
 // the first group has to walk them itself.  One barrier per batch.
 // B*H = 512, T = 784, D = M = 64: 742 us with the sums formed step by step, 185 with four waves that do everything, 158
@@ -248,7 +260,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void r
     constexpr bool kPairs = LPR == 16;         // the sums of neighbouring rows are added before they go to LDS
     constexpr int kSums = kPairs ? RPW / 2 : RPW;
     __shared__ __attribute__((aligned(16))) float part[kBufs][kStepBatch][4][kWave][kPairs ? 2 : 4];   // read-out partial sums
-    __shared__ __attribute__((aligned(16))) float dprod[kBufs][kStepBatch][D];            // q z of a row; row order as in feat
+    __shared__ __attribute__((aligned(16))) float zrow[kBufs][kStepBatch][D];             // z after a step; row order as in feat
 
     const int bh = blockIdx.x, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int batches = kOne ? 1 : (steps + kStepBatch - 1) / kStepBatch;
@@ -266,7 +278,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void r
         __syncthreads();
         for (int b = 0; b < batches; ++b) {
             const int n = min(kStepBatch, steps - b * kStepBatch), buf = b & (kBufs - 1);
-            float dp8[kStepBatch];
+            float z8[kStepBatch];
             auto step = [&](const int t) {
                 const fN kd = *reinterpret_cast<const fN *>(&feat[buf][t][0][r0 * NIT]);
                 const fN qd = *reinterpret_cast<const fN *>(&feat[buf][t][1][r0 * NIT]);
@@ -287,18 +299,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void r
                     *reinterpret_cast<f32x4 *>(&part[buf][t][wave][lane][0]) = acc;
                 }
                 zr += feat[buf][t][0][r0 * NIT + own];                       // eq. 19
-                return product(feat[buf][t][1][r0 * NIT + own], zr);
+                return zr;
             };
             if (n == kStepBatch) {
 #pragma unroll
-                for (int t = 0; t < kStepBatch; ++t) dp8[t] = step(t);
+                for (int t = 0; t < kStepBatch; ++t) z8[t] = step(t);
             } else {
 #pragma unroll
-                for (int t = 0; t < kStepBatch; ++t) dp8[t] = t < n ? step(t) : 0.f;
+                for (int t = 0; t < kStepBatch; ++t) z8[t] = t < n ? step(t) : 0.f;
             }
             if (keeps) {
 #pragma unroll
-                for (int t = 0; t < kStepBatch; ++t) dprod[buf][t][r0 * NIT + own] = dp8[t];
+                for (int t = 0; t < kStepBatch; ++t) zrow[buf][t][r0 * NIT + own] = z8[t];
             }
             __syncthreads();
         }
@@ -339,15 +351,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void r
 #pragma unroll
         for (int j = 0; j < NV; ++j) (&vals[buf][0][0])[tid + 256 * j] = xv[j];
     };
-    // NV adjacent columns of one step per thread, 32 threads per step; the denominator's D products are
-    // added up between those threads
-    static_assert(M / NV == 32 && D % 32 == 0, "32 threads per step");
-    const int t = tid / 32, m = NV * (tid % 32);
-    auto outputs = [&](const int b) {
+    // NV adjacent columns of one step per thread, 32 threads per step, which add up the step's denominator between them
+    static_assert(M / NV == 32 && (RPI == 16 || RPI == 32), "32 threads per step");
+    const int t = tid / 32, m = NV * (tid % 32), own_rows = NIT * (tid % RPI);
+    auto outputs = [&](const int b, const fN qn) {       // qn: q of the thread's rows in that batch
         const int buf = b & (kBufs - 1);
-        const float *y = &dprod[buf][t][D / 32 * (tid % 32)];
-        float dn = tree_sum_lanes<4>(D == 64 ? y[0] + y[D / 32 - 1] : y[0]);
-        dn = dn + __shfl_xor(dn, 16) + eps;
+        const fN zv = *reinterpret_cast<const fN *>(&zrow[buf][t][own_rows]);
+        float zn[NIT];
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) zn[it] = zv[it];
+        float dn = tree_sum_lanes<4>(rows_dot<NIT>(qn, zn));
+        if constexpr (RPI == 32) dn += __shfl_xor(dn, 16);
+        dn += eps;
         if (b * kStepBatch + t < steps) {
             float num[NV][4];
 #pragma unroll
@@ -371,15 +386,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void r
     stage(0);
     if (kStepBatch < steps) fetch(kStepBatch);
     __syncthreads();
+    fN qn;
     for (int b = 0; b < batches; ++b) {
-        if (b > 0) outputs(b - 1);
+        if (b > 0) outputs(b - 1, qn);
+        qn = *reinterpret_cast<const fN *>(&feat[b & (kBufs - 1)][t][1][own_rows]);     // (the next batch but one takes their place)
         if (b + 1 < batches) {
             stage((b + 1) & 1);
             if (b + 2 < batches) fetch((b + 2) * kStepBatch);
         }
         __syncthreads();
     }
-    outputs(batches - 1);
+    outputs(batches - 1, qn);
 }
 
 // The same a step at a time, for launches of a few steps: the next token's q, k, v are fetched while the
@@ -432,18 +449,19 @@ __global__ __launch_bounds__(256) void recurrent_steps_few_kernel(const T *q, co
         if (t + 1 < steps) fetch(t + 1, x_next, v_next);
 
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        float qd[NIT];
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const float kd = __shfl(f, it * RPW + rsub);
-            const float qd = __shfl(f, NR + it * RPW + rsub);
+            qd[it] = __shfl(f, NR + it * RPW + rsub);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 s4[it][e] = fmaf(kd, v4[e], s4[it][e]);
-                acc[e] = fmaf(qd, s4[it][e], acc[e]);
+                acc[e] = fmaf(qd[it], s4[it][e], acc[e]);
             }
         }
         zr += __shfl(f, own * RPW + rsub);
-        float dpart = tree_sum_lanes<NIT == 4 ? 2 : NIT - 1>(product(__shfl(f, NR + own * RPW + rsub), zr));
+        float dpart = rows_dot_of_lanes<NIT>(qd, zr);
 #pragma unroll
         for (int off = LPR; off < kWave; off <<= 1) {
 #pragma unroll

@@ -68,3 +68,28 @@ def test_states_beyond_the_cache(kind, D, M, mb):
         la.la_recurrent_step(q[part], k[part], v[part], S1[part], z1[part], out1[part], 1e-6)
     torch.cuda.synchronize()
     assert torch.equal(out, out1) and torch.equal(S, S1) and torch.equal(z, z1)
+
+
+@pytest.mark.parametrize("D,M", [(64, 64), (64, 32), (32, 64)])
+@pytest.mark.parametrize("BH,T", [(3, 1), (3, 2), (3, 8), (3, 17), (1100, 2), (4100, 2)])
+def test_products_of_the_denominator_are_not_rounded(D, M, BH, T):
+    """den = sum q z, the rows a lane sweeps one after the other as fused multiply-adds: 1 * -(1 + 2^-11) and then
+    (1 + 2^-12)^2 = 1 + 2^-11 + 2^-24 leave 2^-24, where the rounded products leave nothing."""
+    import paper_2006_16236_amd as la
+    RPI = 1024 // M                          # rows of S that a workgroup sweeps at a time
+    q, k = (torch.zeros(T, BH, 1, D, device=DEV) for _ in range(2))
+    v = torch.ones(T, BH, 1, M, device=DEV)
+    S, z = torch.zeros(BH, 1, D, M, device=DEV), torch.zeros(BH, 1, D, device=DEV)
+    row = torch.arange(BH, device=DEV) % RPI
+    i = torch.arange(BH, device=DEV)
+    q[:, i, 0, row], q[:, i, 0, row + RPI] = 1.0, 1 + 2.0 ** -12
+    z[i, 0, row], z[i, 0, row + RPI] = -(1 + 2.0 ** -11), 1 + 2.0 ** -12
+    S[i, 0, row] = 0.5
+    out = torch.zeros_like(v)
+    la.la_recurrent_steps(q, k, v, S, z, out, 0.0, features=True)
+    torch.cuda.synchronize()
+    assert (out == 2.0 ** 23).all()
+    out.zero_()
+    la.la_recurrent_step(q[0], k[0], v[0], S, z, out[0], 0.0, features=True)
+    torch.cuda.synchronize()
+    assert (out[0] == 2.0 ** 23).all()
