@@ -71,12 +71,14 @@ def to_host(t):
 
 @contextlib.contextmanager
 def schedule(target_waves=None, min_seg_chunks=None, fold_max_segs=None, bwd_seg_group=None,
-             stream_loads=None):
+             stream_loads=None, block_kernels=None):
     """Force the segment schedule (and the kind of loads) of the library through its environment
-    knobs."""
+    knobs.  block_kernels: None leaves LA_BLOCK_KERNELS as it is."""
     keys = {"LA_TARGET_WAVES": target_waves, "LA_MIN_SEG_CHUNKS": min_seg_chunks,
             "LA_FOLD_MAX_SEGS": fold_max_segs, "LA_BWD_SEG_GROUP": bwd_seg_group,
             "LA_STREAM_LOADS": stream_loads}
+    if block_kernels is not None:
+        keys["LA_BLOCK_KERNELS"] = block_kernels
     old = {k: os.environ.get(k) for k in keys}
     try:
         for k, v in keys.items():

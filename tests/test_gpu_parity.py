@@ -47,13 +47,14 @@ def run_bwd(la, Q, K, V, G, eps, bf16=False, reuse_fwd=True, reuse_states=True):
 EDGE_N = [1, 15, 16, 17, 63, 64, 65, 257, 784, 1000]
 
 
+# (short sequences: also with the workgroup kernels forced, segment by segment, where the default forward is in one launch)
 @pytest.mark.parametrize("sched", list(SCHEDULES))
-@pytest.mark.parametrize("N", EDGE_N)
-def test_causal_fwd_edge_lengths(la, oracle, N, sched):
+@pytest.mark.parametrize("N,blocks", [(N, None) for N in EDGE_N] + [(N, 1) for N in EDGE_N + [97, 255] if N <= 256])
+def test_causal_fwd_edge_lengths(la, oracle, N, blocks, sched):
     B, H, D, M = 2, 3, 64, 64
     Q, K, V = wl.random_case(100 + N, B, H, N, D, M)[:3]
     ref, dref = oracle.causal_fwd_prefix(Q, K, V, 1e-6, return_den=True)
-    with schedule(**SCHEDULES[sched]):
+    with schedule(**SCHEDULES[sched], block_kernels=blocks):
         O, den = run_fwd(la, Q, K, V, 1e-6)
     assert rel_err(O, ref) <= tol_for(N)
     assert rel_err(den, dref) <= tol_for(N)

@@ -9,7 +9,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2006_16236_amd", "csrc")
-FIELDS = ("nchunks", "nseg", "cps", "fold", "fwd_block", "bwd_block", "bwd_group", "writes", "states", "bwd", "step_streams", "one_by_one", "nt_outputs")
+FIELDS = ("nchunks", "nseg", "cps", "fold", "fwd_block", "bwd_block", "bwd_group", "writes", "states", "bwd", "step_streams", "one_by_one", "nt_outputs", "fwd_direct")
 DEFAULT = dict(target=2048, min_chunks=2, fold=8, group=0, block=-1, heads=0)
 F32, BF16, GIVEN, POLY2 = 0, 1, 2, 4
 
@@ -162,3 +162,25 @@ def test_which_outputs_leave_non_temporally(plans):
         assert [nt(mb, GIVEN, C, M) for mb in (1, 24, 63, 64, 256)] == [0, 0, 0, 1, 1]
         assert all(nt(mb, F32, C, M) for mb in (1, 64, 256))
     assert all(nt(mb, POLY2) for mb in (1, 64, 256))
+
+
+def test_which_forwards_go_by_definition(plans):
+    """fwd_direct_kernel: 33 to 256 tokens, from 65 on where one segment in one launch is as fast (bf16, a 32-wide D), up to 256
+    workgroups of 32 queries, in head-major and token-major calls; a forced choice of kernels turns it off."""
+    def direct(BH, N, C, M, t=F32, **kw):
+        return plans([(BH, N, C, M, t, kw)])[0]["fwd_direct"]
+    for M in (64, 32):
+        for t, C in ((F32, 64), (GIVEN, 64), (POLY2, 64)):
+            assert [direct(1, N, C, M, t) for N in (1, 32, 33, 64, 65, 255, 256, 257)] == [0, 0, 1, 1, 1, 1, 1, 0]
+        for t, C in ((BF16, 64), (3, 64), (F32, 32), (BF16, 32), (GIVEN, 32), (3, 32)):
+            assert [direct(1, N, C, M, t) for N in (1, 32, 33, 64, 65, 255, 256, 257)] == [0, 0, 0, 0, 1, 1, 1, 0]
+    for t in (F32, BF16, GIVEN, POLY2):
+        assert [direct(BH, 256, 64, 64, t) for BH in (1, 32, 33, 64)] == [1, 1, 0, 0]               # 8 workgroups each
+        assert [direct(BH, 65, 64, 64, t) for BH in (85, 86)] == [1, 0]                               # 3 each
+    for N in (33, 65, 256):
+        assert direct(8, N, 64, 64, heads=8) == 1 and direct(8, N, 64, 64, block=0) == 0 and direct(8, N, 64, 64, block=1) == 0
+    # the schedule's other knobs do not turn it off, and its totals are scanned where they do not fold
+    assert all(direct(1, 133, 64, 64, **kw) for kw in (dict(target=1 << 20, min_chunks=1), dict(target=1 << 20, min_chunks=3), dict(target=24, fold=64),
+                                                            dict(target=24, fold=1), dict(fold=1), dict(group=2)))
+    scanned = plans([(1, 133, 64, 64, F32, dict(fold=1))])[0]
+    assert scanned["fwd_direct"] and scanned["nseg"] > 1 and not scanned["fold"]
