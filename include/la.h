@@ -183,6 +183,8 @@ int la_causal_fwd_noalloc(const void *Q, const void *K, const void *V, void *O, 
  * eq. 16-17), S1, z1 receive the state after token N-1 (both NULL: not wanted).  A prompt can
  * be processed in parallel and continued token by token with la_recurrent_step, or a long
  * sequence processed in pieces.  S0/z0 must not alias S1/z1.  Workspace as la_causal_fwd.
+ * Short sequences (up to 256 tokens): la_causal_fwd adds in another order than a call with any
+ * of the four state pointers, so the two may differ in the last bits of O and den.
  */
 int la_causal_fwd_state(const void *Q, const void *K, const void *V, const float *S0,
                         const float *z0, void *O, float *den, float *S1, float *z1,

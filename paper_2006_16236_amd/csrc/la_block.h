@@ -831,7 +831,8 @@ __global__ __launch_bounds__((kWave * kFwdWaves)) __attribute__((amdgpu_waves_pe
 // definition (eq. 8-9): scores, their sums and their product with V; the partial results are added up in LDS.  Such a
 // call is bound by latency: launches, and in each the way to memory and back.  Cut into segments it takes two
 // launches that depend on each other, here one: the segment totals, which a backward may ask the workspace for, come
-// from workgroups of their own in the same launch (block ndirect on).
+// from workgroups of their own in the same launch (block ndirect on).  (One workgroup of either kind fills a compute unit:
+// D = M = 64, fp32, 185 registers and 70 KB of LDS; where the queries' own fill the machine, the totals come in a second round.)
 // All operands come straight from memory in the order the products need, split by the wave that reads them; the
 // arithmetic is that of FwdOut (three-part scores, den in fp32, scores of bf16 tensors in two parts against V).
 constexpr int kDirectTokens = la_plan::kDirectTokens, kDirectWaves = kDirectTokens / kBlk;
@@ -868,6 +869,7 @@ __global__ __launch_bounds__((kWave * kDirectWaves)) void fwd_direct_kernel(cons
     const int tid = threadIdx.x, lane = tid & (kWave - 1), c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if ((int)blockIdx.x >= ndirect) {
+        // (the other waves are done: a workgroup's barrier does not wait for waves that have ended)
         if (wave < kSegWaves) segment_totals<D, M, T, kStrided, kSegWaves>(sa, blockIdx.x - ndirect, lds);
         return;
     }
