@@ -221,7 +221,7 @@ int run_causal_fwd(const void *Q, const void *K, const void *V, void *O, float *
     const bool scanned = p.nseg > 1 && !p.fold;      // the scan has added the caller's state already
     la::PassArgs a{};
     a.stream = p.nt_loads;
-    a.nt_out = nt_outputs(BH, N, D, M, t);
+    a.nt_out = nt_outputs(BH, N, D, M, t, true);
     a.heads = heads; a.tok_heads = tok_heads;
     a.Q = Q; a.K = K; a.V = V; a.G = nullptr; a.rden = nullptr; a.delta = nullptr;
     a.out = O; a.den = den; a.state = p.nseg > 1 ? states : nullptr; a.fold = p.fold;
@@ -251,7 +251,7 @@ int run_global_fwd(const void *Q, const void *K, const void *V, void *O, float *
         { ProfScope ps(LA_K_SCAN, s); LA_TRY(la::launch_scan(states, (int)BH, p.nseg, la::state_stride(D, M), la::kScanTotal, s)); }
     la::PassArgs a{};
     a.stream = p.nt_loads;
-    a.nt_out = nt_outputs(BH, N, D, M, t);
+    a.nt_out = nt_outputs(BH, N, D, M, t, false);
     a.heads = heads; a.tok_heads = tok_heads;
     a.Q = Q; a.K = K; a.V = V; a.out = O; a.den = den; a.state = states; a.fold = p.fold;
     a.N = N; a.nseg = p.nseg; a.chunks_per_seg = p.cps; a.eps = eps;
@@ -501,7 +501,7 @@ static int causal_bwd_impl(const void *Q, const void *K, const void *V, const fl
     // are cut, the per-segment sums that the reverse direction starts from
     la::PassArgs a{};
     a.stream = p.nt_loads;
-    a.nt_out = nt_outputs(BH, N, C, M, t);
+    a.nt_out = nt_outputs(BH, N, C, M, t, true);
     a.heads = H; a.tok_heads = tok_heads;
     a.Q = Q; a.K = K; a.V = V; a.G = dO; a.rden = rden; a.delta = delta; a.den = nullptr;
     a.den_in = den; a.rden_out = rden; a.delta_out = delta; a.totals = pb.nseg > 1 ? stR : nullptr;
@@ -652,7 +652,7 @@ static int global_bwd_impl(const void *Q, const void *K, const void *V, const vo
     }
     la::PassArgs a{};
     a.stream = p.nt_loads;
-    a.nt_out = nt_outputs(BH, N, C, M, t);
+    a.nt_out = nt_outputs(BH, N, C, M, t, false);
     a.heads = H; a.tok_heads = tok_heads;
     a.Q = Q; a.K = K; a.V = V; a.G = dO; a.den_in = den; a.totals = stR;
     a.N = N; a.nseg = pb.nseg; a.chunks_per_seg = pb.cps; a.eps = eps;

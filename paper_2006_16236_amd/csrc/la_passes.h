@@ -252,7 +252,7 @@ __device__ __forceinline__ void store_tile(float *lds_o, const f32x4 (&out)[F / 
                                     round_pair(hi[0], hi[1]), round_pair(hi[2], hi[3])};
             u32x4_t *p = reinterpret_cast<u32x4_t *>(tile_out + (size_t)row * tso + col);
             if (row < nvalid) {
-                if (LA_NT_STORES != 0 && F == 64 && nt) {       // (uniform; nt_outputs says never of narrower rows)
+                if (LA_NT_STORES != 0 && F == 64 && nt) {       // (uniform; narrower rows gain nothing)
                     keep_apart();
                     __builtin_nontemporal_store(packed, p);
                     keep_apart();

@@ -269,21 +269,20 @@ inline size_t global_bwd_bytes(const Tuning &tn, long BH, int N, int C, int M) {
 // Whether a call's outputs leave with non-temporal stores, where that goes by size: bf16 rows (16 bytes per lane), and
 // the element-wise stores of fp32 calls with the caller's features (all other fp32 stores always do, two-byte ones never).
 // The call's own next kernel reads faster, but what reads the outputs behind the call no longer finds them in the
-// last-level cache.  Plain / non-temporal in us, token-major, H = 8, D = M = 64: the forward and a projection of O
-// (F); the step with sums of O, dQ, dK, dV with tensors of their size (A); the step with the projection and the
-// weight and input gradients of dQ, dK, dV (G); by MB of O:
-//   bf16, causal      1 x 512 0.5 F 19.9/21.4   4 x 784 3 F 30.4/31.8 G 157/167   8 x 1024 8 F 37.4/38.8 G 263/299
-//                     4 x 3072 13 F 44.1/45.6 A 97.6/99.2 G 352/404   64 x 1024 67 F 123/128 A 369/366 G 1178/1184
-//                     128 x 1024 134 F 235/234 A 795/788 G 2123/2113   2 x 65536 134 F 293/284 A 820/810 G 2141/2130
-//   bf16, non-causal  4 x 3072 13 F 48.7/50.0 G 351/386   5 x 16384 84 F 184/189   95 x 1024 100 F 231/233 A 637/639 G 1798/1808
-//                     8 x 16384 134 F 250/247 A 678/669 G 2004/1996
-//   given features    non-causal 8 x 1024 17 G 387/398   4 x 3072 25 G 567/583   8 x 3072 50 A 250/247 G 992/993
-//                     causal 33 x 1000 68 A 411/403 G 1697/1682   3 x 16384 101 A 724/706 G 2250/2241
-// bf16 heads with a 32-wide D or M (rows of 64 bytes) gain nothing at any size: 32 x 32, non-causal, 84 MB A 460/467
-// G 1734/1750, 168 MB A 915/918 G 2939/2963.
-inline bool nt_outputs(long BH, int N, int C, int M, la_dtype t) {
+// last-level cache.  The time with plain stores over that with non-temporal ones, token-major, H = 8, means over 1001, 3072 and 12000
+// tokens, by MB of the wider outputs: the step by itself / the forward and a projection of O / the step with sums of O, dQ, dK, dV
+// with other tensors / the step with the projection and the weight and input gradients of dQ, dK, dV:
+//   bf16 causal 64 x 64   13 1.04 .97 .98 .87   32 1.01 .97 1.01 .99   48 1.04 .98 1.01 .99   64 1.04 1.00 1.00 1.00 (8192 tokens 1.03 .97 .97 1.00)   80 1.04 1.02 1.00 1.00   96 1.02 1.01 .99 1.00
+//               64 x 32   32 1.01 .99 1.00 .98   48 1.02 .99 1.01 1.00   64 1.02 .99 1.01 1.00   96 1.02 .99 1.00 1.00   128 1.01 1.00 1.00 1.00
+//               32 x 64   32 1.00 .95 1.00 1.00   64 1.04 .99 1.01 1.00   96 1.05 1.01 1.00 1.00   128 1.01 1.00 1.00 1.00
+//   bf16 non-causal 64 x 64   13 1.03 .97 1.00 .91   64 1.02 1.00 .98 1.00   96 1.00 1.00 .98 1.00   128 1.02 1.01 1.00 1.00
+//               64 x 32   64 1.00 1.00 .98 1.00   96 1.00 .96 .98 1.00     32 x 32   64 1.00 .97 .97 .99   128 1.00 1.00 .99 .99
+//   given features (one call each)   non-causal 8 x 1024 17 1.00 1.00 .99 .97   8 x 3072 50 1.10 1.00 1.01 1.00
+//               causal 33 x 1000 68 1.04 1.00 1.02 1.01   3 x 16384 101 1.04 1.03 1.02 1.00
+// (bf16, 4 x 3072 tokens, 64 x 64, us: step 73.4/70.7, with projection and gradients 352/404.)
+inline bool nt_outputs(long BH, int N, int C, int M, la_dtype t, bool causal) {
     const size_t mb = (size_t)BH * N * (C > M ? C : M) * esize(t) >> 20;
-    if (esize(t) == 2) return C == 64 && M == 64 && mb >= 128;
+    if (esize(t) == 2) return C == 64 && (causal ? mb >= 80 : M == 64 && mb >= 128);
     return t != LA_F32_FEATURES || mb >= 64;
 }
 

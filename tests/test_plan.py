@@ -9,7 +9,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2006_16236_amd", "csrc")
-FIELDS = ("nchunks", "nseg", "cps", "fold", "fwd_block", "bwd_block", "bwd_group", "writes", "states", "bwd", "step_streams", "one_by_one", "nt_outputs", "fwd_direct")
+FIELDS = ("nchunks", "nseg", "cps", "fold", "fwd_block", "bwd_block", "bwd_group", "writes", "states", "bwd", "step_streams", "one_by_one", "nt_causal", "nt_global", "fwd_direct")
 DEFAULT = dict(target=2048, min_chunks=2, fold=8, group=0, block=-1, heads=0)
 F32, BF16, GIVEN, POLY2 = 0, 1, 2, 4
 
@@ -150,18 +150,22 @@ def test_which_decode_steps_go_one_by_one(plans):
 
 
 def test_which_outputs_leave_non_temporally(plans):
-    """bf16 outputs below 128 MB and the elements of given fp32 features below 64 MB stay in the caches for whoever reads
-    them next (projection and weight gradients of 4 x 3072 tokens, bf16: 352 -> 404 us behind non-temporal stores)."""
-    def nt(mb, t, C=64, M=64):
+    """Outputs of bf16 calls and the elements of given fp32 features stay in the caches for whoever reads them next, up to 64 to 128
+    MB (projection and weight gradients of 4 x 3072 tokens, bf16: 352 -> 404 us behind non-temporal stores)."""
+    def nt(mb, t, C=64, M=64, kind="nt_causal"):
         N = 1024
-        return plans([((mb << 20) // (N * max(C, M) * (2 if t in (BF16, 3) else 4)), N, C, M, t, {})])[0]["nt_outputs"]
+        return plans([((mb << 20) // (N * max(C, M) * (2 if t in (BF16, 3) else 4)), N, C, M, t, {})])[0][kind]
     for t in (BF16, 3):
-        assert [nt(mb, t) for mb in (1, 12, 64, 127, 128, 256)] == [0, 0, 0, 0, 1, 1]
-        assert not any(nt(mb, t, C, M) for mb in (1, 64, 128, 1024) for C, M in ((32, 32), (32, 64), (64, 32)))
-    for C, M in ((64, 64), (32, 32), (32, 64), (64, 32)):
-        assert [nt(mb, GIVEN, C, M) for mb in (1, 24, 63, 64, 256)] == [0, 0, 0, 1, 1]
-        assert all(nt(mb, F32, C, M) for mb in (1, 64, 256))
-    assert all(nt(mb, POLY2) for mb in (1, 64, 256))
+        for M in (64, 32):
+            assert [nt(mb, t, M=M) for mb in (1, 12, 64, 79, 80, 256)] == [0, 0, 0, 0, 1, 1]
+            assert not any(nt(mb, t, 32, M, kind) for mb in (1, 64, 128, 1024) for kind in ("nt_causal", "nt_global"))
+            assert not nt(1024, t, 64, 32, "nt_global")
+        assert [nt(mb, t, kind="nt_global") for mb in (1, 64, 127, 128, 256)] == [0, 0, 0, 1, 1]
+    for kind in ("nt_causal", "nt_global"):
+        for C, M in ((64, 64), (32, 32), (32, 64), (64, 32)):
+            assert [nt(mb, GIVEN, C, M, kind) for mb in (1, 24, 63, 64, 256)] == [0, 0, 0, 1, 1]
+            assert all(nt(mb, F32, C, M, kind) for mb in (1, 64, 256))
+        assert all(nt(mb, POLY2, kind=kind) for mb in (1, 64, 256))
 
 
 def test_which_forwards_go_by_definition(plans):
