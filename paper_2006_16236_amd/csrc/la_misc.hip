@@ -223,10 +223,9 @@ __global__ __launch_bounds__(256) void recurrent_step_kernel(const T *q, const T
 // adds up and stores the batch before, with its denominators (q and z of each row), stages k, q (each feature mapped once) and v of the one to come, and has the one
 // after that in flight: chains of LDS reads, additions and divisions that leave a SIMD idle half of the time where
 // the first group has to walk them itself.  One barrier per batch.
-// B*H = 512, T = 784, D = M = 64: 742 us with the sums formed step by step, 185 with four waves that do everything, 158
-// with eight, 152 with the pairs added, 149 with the first group ahead in the SIMDs' choice.  Bounded by LDS (half of the time
-// without stalls is its) and instruction issue: the features taken from a neighbouring lane by the instruction itself
-// (`v_fmac_f32_dpp`) instead of from LDS cost more than they save (187 -> 199 with four waves).
+// B*H = 512, T = 784, D = M = 64: 742 us with the sums formed step by step, 184 with four waves that do everything, 160
+// so.  Bounded by vector instructions: the counters have the SIMDs' vector pipes busy throughout, the LDS half of the time.  (The features
+// taken from a neighbouring lane by the instruction itself, `v_fmac_f32_dpp`, instead of from LDS: 187 -> 199 with four waves.)
 constexpr int kStepBatch = 8;
 // (x0 + x1) + (x2 + x3) ...: the order in which the single step's shuffles add
 template <int N> __device__ __forceinline__ float tree_sum(const float (&x)[N]) {

@@ -95,16 +95,19 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 // (512 workgroups, two per CU), in whole 32-token blocks: fewer, longer segments, hence less state to
 // write, scan and read.  The wave kernels (la_passes.h) have the shorter chain per token and win
 // where segments are long.  Measured on MI355X, step times wave / workgroup kernels in us (B*H x N):
-//   fp32, D = M = 64   16 x 65536  1028/1047   16 x 16384  284/271   16 x 8192  164/146   16 x 2048  81/58
-//   bf16, D = M = 64   16 x 65536   689/587    16 x 16384  203/160   16 x 8192  123/90    16 x 2048  65/45
-//   fp32, D = M = 32   16 x 65536   461/469    16 x 16384  127/122   16 x 8192   78/68    16 x 2048  35/32
-//   bf16, D = M = 32   16 x 65536   303/302    16 x 16384   93/86    16 x 8192   61/52    16 x 2048  35/29
-//   fp32, 64 x 32      16 x 65536   736/767    16 x 16384  191/193   16 x 8192  112/106   16 x 2048  57/44
-//   bf16, 64 x 32      16 x 65536   521/476    16 x 16384  151/128   16 x 8192   91/73    16 x 2048  50/37
-//   fp32, 32 x 64      16 x 65536   702/710    16 x 16384  182/179   16 x 8192  106/99    16 x 2048  53/41
-//   bf16, 32 x 64      16 x 65536   473/397    16 x 16384  138/107   16 x 8192   85/63    16 x 2048  45/35
+//   fp32, D = M = 64   16 x 65536  1048/1019   16 x 16384  286/251   16 x 8192  162/137   16 x 2048  81/55
+//   bf16, D = M = 64   16 x 65536   709/568    16 x 16384  193/150   16 x 8192  121/88    16 x 2048  66/44
+//   fp32, D = M = 32   16 x 65536   462/464    16 x 16384  123/115   16 x 8192   76/66    16 x 2048  36/32
+//   bf16, D = M = 32   16 x 65536   302/305    16 x 16384   91/84    16 x 8192   60/52    16 x 2048  34/28
+//   fp32, 64 x 32      16 x 65536   750/712    16 x 16384  185/176   16 x 8192  111/98    16 x 2048  57/40
+//   bf16, 64 x 32      16 x 65536   529/457    16 x 16384  147/122   16 x 8192   92/72    16 x 2048  51/37
+//   fp32, 32 x 64      16 x 65536   721/671    16 x 16384  175/161   16 x 8192  105/90    16 x 2048  52/38
+//   bf16, 32 x 64      16 x 65536   475/389    16 x 16384  133/101   16 x 8192   84/63    16 x 2048  45/35
+// (wave / workgroup as LA_BLOCK_KERNELS=0 / 1 forces them.)
 // so the line lies at 512 tokens per segment (fp32 with D = M = 64, bf16 with a 64-wide head dimension) or
-// 256 (fp32 with a 32-wide D or M, where the two are within 2 to 4 % at 512, and bf16 32 x 32).  The line of bf16
+// 256 (fp32 with a 32-wide D or M, where the two were within 2 to 4 % at 512, and bf16 32 x 32).  The fp32 lines were
+// drawn while the workgroup backward had four waves and the wave kernels were ahead at 16 x 65536 (1028/1047, 736/767, 702/710);
+// with eight they could lie higher for a 64-wide D or M.  The line of bf16
 // 32 x 32 heads could lie higher: at 512 tokens per segment they take 0.92 of the wave kernels' step, 100 x 2000
 // 83/71 us, and only the forward is slower (31/34 us at 16 x 16384); it was drawn when the backward took 0.97.
 // Above it bf16 tensors with a 64-wide head dimension keep the wave kernel in the forward only (16 x 65536,
@@ -128,12 +131,16 @@ inline size_t states_bytes(long BH, const Plan &p, int D, int M) {
 // four pieces 135), narrow heads of more than 1024 tokens from 512 (bf16 406 x 1711 whole took 1.08 of the
 // wave kernels' step when that line was drawn, 0.92 with the present backward, forward 1.25).  Whole sequences, each kernel by what fills the machine
 // (fp32 D = M = 64, forward / dQ / dV+dK in us):
-//   1024 x 1024  wave 334 / 285 / 317   workgroup 235 / 354 / 358
-//   2048 x 512   wave 208 / 348 / 402   workgroup 252 / 350 / 356
-//   2048 x 512, D = M = 32   wave 113 / 135 / 144   workgroup 110 / 162 / 158
+//   1024 x 1024  wave 337 / 292 / 330   workgroup 248 / 296 / 359
+//   2048 x 512   wave 213 / 341 / 414   workgroup 229 / 271 / 324
+//   2048 x 512, D = M = 32   wave 113 / 133 / 144   workgroup 105 / 132 / 154
+//   64 x 32   1024 x 1024  wave 227 / 229 / 227   workgroup 167 / 203 / 240     2048 x 512  152 / 279 / 252   167 / 210 / 234
+//   32 x 64   1024 x 1024  wave 201 / 208 / 228   workgroup 154 / 189 / 238     2048 x 512  152 / 216 / 255   158 / 184 / 235
+// (Forced.  The lines were drawn with the four-wave backward; wave kernels that they keep and that are behind now: backward 2048 x 512
+// 64 x 32 531/444, 32 x 64 471/419, 1024 x 1024 456/443 and 436/427, forward 2048 x 512, D = M = 32 113/105.)
 // Workgroup / wave kernels of whole sequences, geometric mean over drawn lengths:
 //   bf16 forward from 1024 on     D = M = 64  1.09 .. 1.31   64 x 32  1.15 .. 1.52   32 x 32  1.03 .. 1.22   32 x 64  0.88
-//   backward with M = 32, fp32, from 1434 on  1.04 .. 1.24
+//   backward with M = 32, fp32, from 1434 on  1.04 .. 1.24 (64 x 32 with four waves; with eight 0.82 .. 0.98, 300 to 1000 tokens)
 //   bf16 64 x 32, 513 .. 640 of more than 512 tokens (wave kernels in several pieces)  step 1.06, forward 1.08; with
 //   the present backward 550 x 700 has 0.87 and 0.94: the rule that keeps the wave kernels there could go
 // A block is 32 tokens: of one chunk, or three, half a block is padding, and from 256 or 512 sequences on that
@@ -272,7 +279,8 @@ inline size_t global_bwd_bytes(const Tuning &tn, long BH, int N, int C, int M) {
 // last-level cache.  The time with plain stores over that with non-temporal ones, token-major, H = 8, means over 1001, 3072 and 12000
 // tokens, by MB of the wider outputs: the step by itself / the forward and a projection of O / the step with sums of O, dQ, dK, dV
 // with other tensors / the step with the projection and the weight and input gradients of dQ, dK, dV:
-//   bf16 causal 64 x 64   13 1.04 .97 .98 .87   32 1.01 .97 1.01 .99   48 1.04 .98 1.01 .99   64 1.04 1.00 1.00 1.00 (8192 tokens 1.03 .97 .97 1.00)   80 1.04 1.02 1.00 1.00   96 1.02 1.01 .99 1.00
+//   bf16 causal 64 x 64   13 1.04 .97 .98 .87   32 1.01 .97 1.01 .99   48 1.04 .98 1.01 .99   64 1.04 1.00 1.00 1.00 (8192
+//               tokens 1.03 .97 .97 1.00)   80 1.04 1.02 1.00 1.00   96 1.02 1.01 .99 1.00   128 1.02 1.01 1.00 1.00
 //               64 x 32   32 1.01 .99 1.00 .98   48 1.02 .99 1.01 1.00   64 1.02 .99 1.01 1.00   96 1.02 .99 1.00 1.00   128 1.01 1.00 1.00 1.00
 //               32 x 64   32 1.00 .95 1.00 1.00   64 1.04 .99 1.01 1.00   96 1.05 1.01 1.00 1.00   128 1.01 1.00 1.00 1.00
 //   bf16 non-causal 64 x 64   13 1.03 .97 1.00 .91   64 1.02 1.00 .98 1.00   96 1.00 1.00 .98 1.00   128 1.02 1.01 1.00 1.00
